@@ -80,7 +80,7 @@ def _timed_ms(torch, fn, reps=10):
     return e0.elapsed_time(e1) / reps
 
 
-ATTN_SOURCES = ("tree_attn_mfma.hip", "tree_attn_mfma_smallm.hip", "tree_attn_generic.hip", "mfma_common.h")
+ATTN_SOURCES = ("tree_attn_mfma.hip", "tree_attn_mfma_smallm.hip", "attn_merge.hip", "attn_work.h", "mfma_common.h")
 
 
 def csrc_digest(names=None):

@@ -89,7 +89,8 @@ size_t s4c_tree_attn_workspace_size(const s4c_attn_shape* shape, int32_t max_cac
  *                   gets an all-zero output.
  *   workspace       >= s4c_tree_attn_workspace_size(shape, max_cache_len) bytes, 256-byte
  *                   aligned; contents need not be initialised; may be NULL if that size is 0.
- * Results are deterministic (fixed split count and merge order for a given shape). */
+ * Results are deterministic: how the keys are divided between workgroups, and the order in which parts are merged,
+ * follow from the shape, max_cache_len and cache_len[]. */
 s4c_status s4c_tree_attn(const s4c_attn_shape* shape, const void* q, const void* k_tree,
                          const void* v_tree, const void* k_cache, const void* v_cache,
                          const int32_t* cache_len, const int32_t* parent, int32_t max_cache_len,
@@ -298,7 +299,8 @@ s4c_status s4c_draft_linear(int32_t T, int32_t H, int32_t Hout, int32_t dtype, c
 /* Text for a status code (any integer: unknown codes get "unknown status").  Static, never NULL. */
 const char* s4c_strerror(int code);
 
-/* Number of KV splits s4c_tree_attn uses for this shape (1 = single pass); for reporting. */
+/* Number of parts s4c_tree_attn divides the keys of one (sequence, KV head) into when every sequence is max_cache_len
+ * long (1 = single pass); for reporting. */
 int32_t s4c_tree_attn_num_splits(const s4c_attn_shape* shape, int32_t max_cache_len);
 
 #ifdef __cplusplus

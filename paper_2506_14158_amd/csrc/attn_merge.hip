@@ -1,0 +1,88 @@
+// Combines the parts of the (sequence, KV head) units that the attention kernels' teams divided between them
+// (attn_work.h): out = sum_p 2^(m_p - m) O_p / sum_p 2^(m_p - m) l_p, parts in tile order => deterministic.
+//
+// A workgroup takes a chunk of query rows of one unit and leaves at once if the unit was not divided.  32 lanes per
+// row (D = 128: one float4 each, D = 64: float2), the loads of up to four parts in flight together: the kernel is a few
+// microseconds of latency, not of work.
+#include "attn_work.h"
+
+namespace s4c {
+
+namespace {
+
+constexpr int kRows = 8;            // rows per workgroup and pass
+constexpr int kBatch = 4;           // parts whose loads are in flight together
+
+template <typename T, int D>
+__global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a, int passes) {
+    constexpr int VW = D / 32;                                   // floats per lane
+    const int sub = threadIdx.x & 31;
+    const int unit = blockIdx.x, b = unit / a.Hkv, kvh = unit - b * a.Hkv;
+    const int g0 = a.ws_parts[2 * unit], g1 = a.ws_parts[2 * unit + 1];
+    if (g0 == g1) return;                                        // written by its one team already
+    for (int pass = 0; pass < passes; ++pass) {
+        const int r = (blockIdx.y * passes + pass) * kRows + (threadIdx.x >> 5);
+        if (r >= a.M) return;
+        float m = -INFINITY, l = 0.f, o[VW];
+#pragma unroll
+        for (int j = 0; j < VW; ++j) o[j] = 0.f;
+        for (int g = g0; g <= g1; g += kBatch) {
+            float ms[kBatch], ls[kBatch], v[kBatch][VW];
+#pragma unroll
+            for (int p = 0; p < kBatch; ++p) {
+                ms[p] = ls[p] = 0.f;
+                if (g + p <= g1) {
+                    const size_t prow = work::part_row(a, g + p, g + p == g0 ? 1 : 0) + r;
+                    ms[p] = a.ws_ml[prow * 2];
+                    ls[p] = a.ws_ml[prow * 2 + 1];
+#pragma unroll
+                    for (int j = 0; j < VW; ++j) v[p][j] = a.ws_o[prow * D + sub * VW + j];
+                }
+            }
+            float mb = m;
+#pragma unroll
+            for (int p = 0; p < kBatch; ++p) mb = fmaxf(mb, ls[p] > 0.f ? ms[p] : -INFINITY);
+            if (!(mb > -INFINITY)) continue;
+            const float w0 = fast_exp2(m - mb);
+            l *= w0;
+#pragma unroll
+            for (int j = 0; j < VW; ++j) o[j] *= w0;
+#pragma unroll
+            for (int p = 0; p < kBatch; ++p)
+                if (ls[p] > 0.f) {
+                    const float w = fast_exp2(ms[p] - mb);
+                    l = fmaf(ls[p], w, l);
+#pragma unroll
+                    for (int j = 0; j < VW; ++j) o[j] = fmaf(v[p][j], w, o[j]);
+                }
+            m = mb;
+        }
+        const float inv = (l > 0.f) ? 1.f / l : 0.f;
+        const int node = r / a.G, g = r - node * a.G;
+        T* dst = (T*)a.out + (((size_t)b * a.N + node) * a.Hq + (kvh * a.G + g)) * D + sub * VW;
+        T packed[VW];
+#pragma unroll
+        for (int j = 0; j < VW; ++j) packed[j] = from_f32<T>(o[j] * inv);
+        __builtin_memcpy(__builtin_assume_aligned(dst, sizeof(packed)), packed, sizeof(packed));
+    }
+}
+
+template <typename T>
+hipError_t launch(const AttnArgs& a, hipStream_t st) {
+    // one pass per workgroup, more where that would be over about 2048 workgroups (units that are not divided should
+    // cost little)
+    const long units = (long)a.B * a.Hkv, chunks = (a.M + kRows - 1) / kRows;
+    const int passes = (int)((units * chunks + 2047) / 2048);
+    const dim3 grid((unsigned)units, (unsigned)((chunks + passes - 1) / passes)), block(256);
+    if (a.D == 64) hipLaunchKernelGGL((attn_merge_kernel<T, 64>), grid, block, 0, st, a, passes);
+    else hipLaunchKernelGGL((attn_merge_kernel<T, 128>), grid, block, 0, st, a, passes);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_attn_merge(const AttnArgs& a, int dtype, hipStream_t st) {
+    return dtype == S4C_F32 ? launch<float>(a, st) : dtype == S4C_F16 ? launch<f16_t>(a, st) : launch<bf16_t>(a, st);
+}
+
+}  // namespace s4c

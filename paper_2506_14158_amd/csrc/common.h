@@ -59,13 +59,15 @@ struct AttnArgs {
     const int32_t* parent;
     void* out;
     int32_t* status;
-    float* ws_o;    // [B][Hkv][splits][M][D]  unnormalised partial outputs
-    float* ws_ml;   // [B][Hkv][splits][M][2]  (running max in log2 units, running sum)
+    float* ws_o;    // [teams][2][M][D]  unnormalised outputs of the parts of divided units (attn_work.h)
+    float* ws_ml;   // [teams][2][M][2]  (running max in log2 units, running sum)
+    int32_t* ws_parts;    // [B][Hkv][2]  first and last team of a unit
     int32_t B, Hq, Hkv, D, N, S_cap, G, M;
     int32_t max_cache_len;
-    int32_t splits;   // KV splits; 1 => kernels write `out` directly
-    int32_t chunk;    // prefix keys per split (multiple of the key tile)
-    int32_t mtiles;   // query-row tiles per (sequence, KV head); set by the launcher
+    int32_t teams;      // teams the work is divided between (attn_work.h)
+    int32_t whole;      // 1: a team per (sequence, KV head), nothing to merge
+    int32_t mtiles;     // query-row tiles per (sequence, KV head) = workgroups per team
+    int32_t tile_keys, tile_shift;   // keys per tile of the kernel that will run, and its log2
     float scale_log2; // softmax scale * log2(e)
     // paged cache (block_table != null): k_cache / v_cache are pools [num_pages][Hkv][page][D],
     // row j of sequence b is row j & (page-1) of page block_table[b][j >> page_shift]
@@ -74,12 +76,13 @@ struct AttnArgs {
 };
 
 // launchers (defined in the kernel translation units); return hipGetLastError()
-hipError_t launch_tree_attn_generic(const AttnArgs& a, int dtype, hipStream_t st);
-hipError_t launch_tree_attn_mfma(const AttnArgs& a, int dtype, hipStream_t st);      // dtype: S4C_BF16 or S4C_F16
-hipError_t launch_tree_attn_smallm(const AttnArgs& a, int dtype, hipStream_t st);   // M <= 64, called by the above
+hipError_t launch_tree_attn_large(const AttnArgs& a, int dtype, hipStream_t st);    // 16-bit data, more than 64 query rows
+hipError_t launch_tree_attn_small(const AttnArgs& a, int dtype, hipStream_t st);    // at most 64 query rows, or fp32 data
 hipError_t launch_attn_merge(const AttnArgs& a, int dtype, hipStream_t st);
-bool mfma_path_supported(const s4c_attn_shape& s);
-int mfma_rows_per_block(const s4c_attn_shape& s);
+// What one workgroup of the kernel for this shape takes: query rows, keys per tile, and how many fit on a CU.
+struct AttnTile { int rows, keys, per_cu; };
+AttnTile attn_tile_large(const s4c_attn_shape& s);
+AttnTile attn_tile_small(const s4c_attn_shape& s);
 
 struct AcceptArgs {
     const void* logits;

@@ -19,9 +19,6 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 typedef __attribute__((address_space(3))) unsigned char lds_u8;
 typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
 
-constexpr int kD = 128;
-constexpr int kRowB = kD * 2;               // bytes per K/V row
-
 enum TileMode { kPlain = 0, kTail = 1, kTree = 2 };
 
 // One wave-wide direct-to-LDS load: lane i's 16 bytes land at LDS byte address lds_base + 16 i

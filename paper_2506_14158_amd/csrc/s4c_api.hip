@@ -80,54 +80,54 @@ bool shape_ok(const s4c_attn_shape* s, s4c_status* why) {
 }
 
 struct AttnPlan {
-    bool mfma;
-    int splits;
-    int chunk;
-    size_t ws_o_bytes, ws_ml_bytes;
+    bool large;                // more than 64 rows of 16-bit data: the kernel whose waves split the rows
+    int teams, whole, mtiles, tile_keys, tile_shift;
+    int parts;                 // most parts a unit is divided into when no sequence is shorter than max_cache_len
+    size_t ws_o_bytes, ws_ml_bytes, ws_parts_bytes;
 };
 
-// Fixed function of (shape, max_cache_len): the same inputs always get the same split count
-// and therefore bit-identical results.
+// How the key tiles are divided between workgroups (attn_work.h): a fixed function of (shape, max_cache_len), so
+// that the workspace query and the launch agree.
 AttnPlan plan_attn(const s4c_attn_shape& s, int32_t max_cache_len) {
     AttnPlan p;
-    p.mfma = mfma_path_supported(s);
     const int M = s.N * (s.Hq / s.Hkv);
-    const int rows = p.mfma ? mfma_rows_per_block(s) : 32;
-    const long mtiles = (M + rows - 1) / rows;
-    const long units = (long)s.B * s.Hkv * mtiles;
-    // Balance unit: the device's CUs (256 on an MI355X) for the matrix-core kernels (HBM- or MFMA-bound: what counts is
-    // an equal share of work per CU), four workgroups per CU for the scalar kernel.  Split the prefix so that the launch fills
-    // whole rounds of the CUs without paying for more partial results than that needs:
-    // cost(s) = rounds * slots / workgroups * (1 + 4 % per extra split), chunks a multiple of 128 keys
-    // (32, its key tile, for the scalar kernel, whose launches are latency-bound).
-    const long slots = (long)device_cus() * (p.mfma ? 1 : 4);
-    const long gran = p.mfma ? 128 : 32;
-    // at least 256 keys per split for the matrix-core kernels: below that a split's fixed costs (prologue, partial
-    // results, its share of the merge) outweigh what the extra workgroups stream (1024 keys, 32 units: 4 splits
-    // measured 7 % faster than 8)
-    long max_splits = max_cache_len / (p.mfma ? 256 : 32);
-    if (max_splits > 16) max_splits = 16;
-    if (max_splits < 1) max_splits = 1;
-    long splits = 1;
-    double best = 1e30;
-    for (long sp = 1; sp <= max_splits; ++sp) {
-        const long wgs = units * sp, rounds = (wgs + slots - 1) / slots;
-        const double cost = (double)(rounds * slots) / (double)wgs * (1.0 + 0.04 * (double)(sp - 1));
-        if (cost < best - 1e-9) { best = cost; splits = sp; }
-    }
-    long chunk = (max_cache_len + splits - 1) / splits;
-    chunk = ((chunk + gran - 1) / gran) * gran;
-    if (chunk < gran) chunk = gran;
-    splits = (max_cache_len + chunk - 1) / chunk;
-    if (splits < 1) splits = 1;
-    p.splits = (int)splits;
-    p.chunk = (int)chunk;
-    if (p.splits == 1) {
-        p.ws_o_bytes = p.ws_ml_bytes = 0;
+    p.large = s.dtype != S4C_F32 && M > 64;
+    const AttnTile t = p.large ? attn_tile_large(s) : attn_tile_small(s);
+    p.mtiles = (M + t.rows - 1) / t.rows;
+    p.tile_keys = t.keys;
+    p.tile_shift = __builtin_ctz((unsigned)t.keys);
+    const long long slots = (long long)device_cus() * t.per_cu;
+    const long long units = (long long)s.B * s.Hkv;
+    const long long tiles = (max_cache_len + t.keys - 1) / t.keys + (s.N + t.keys - 1) / t.keys;   // of the longest unit
+    // Teams: one round of the chip, its workgroups all on one XCD (32 CUs); fewer when a share would get shorter than
+    // kMinKeys keys, below which a part's fixed costs (prologue, partial results, its share of the merge) outweigh what
+    // the extra workgroups stream; at most 32 parts per unit.
+    const long long kMinKeys = 256, per_xcd = slots / 8;
+    long long teams = per_xcd >= p.mtiles ? per_xcd / p.mtiles * 8 : 8;
+    const long long most = units * tiles * t.keys / kMinKeys;
+    if (teams > most) teams = most;
+    if (teams > units * 32) teams = units * 32;
+    // Not worth dividing (every unit already has a team, or gets no second one), or more tiles than the kernels' 32-bit
+    // tile numbers: a team per unit.
+    p.whole = teams <= units && (units * p.mtiles <= slots || units * tiles > 0x3FFFFFFFll);
+    if (units * tiles > 0x3FFFFFFFll) p.whole = 1;
+    if (p.whole) teams = units;
+    // Shares that end where units end have no second part to start and finish: taken when that leaves at most 7 % of the
+    // teams out.
+    else if (teams > units && teams % units <= teams * 7 / 100) teams -= teams % units;
+    if (teams < 1) teams = 1;
+    p.teams = (int)teams;
+    if (p.whole) {
+        p.parts = 1;
+        p.ws_o_bytes = p.ws_ml_bytes = p.ws_parts_bytes = 0;
     } else {
-        const size_t prow = (size_t)s.B * s.Hkv * p.splits * M;
+        const long long share = units * tiles / teams;                       // >= 1: kMinKeys is several tiles
+        p.parts = (int)((tiles + share - 1) / share + (tiles % share || teams % units ? 1 : 0));
+        if (units * tiles % teams == 0 && share % tiles == 0) p.parts = 1;   // shares are whole units
+        const size_t prow = (size_t)p.teams * 2 * M;
         p.ws_o_bytes = prow * s.D * sizeof(float);
         p.ws_ml_bytes = ((prow * 2 * sizeof(float) + 255) / 256) * 256;
+        p.ws_parts_bytes = (((size_t)units * 2 * sizeof(int32_t) + 255) / 256) * 256;
     }
     return p;
 }
@@ -154,13 +154,13 @@ size_t s4c_tree_attn_workspace_size(const s4c_attn_shape* shape, int32_t max_cac
     s4c_status why;
     if (!shape || !shape_ok(shape, &why) || max_cache_len < 0) return 0;
     const AttnPlan p = plan_attn(*shape, max_cache_len);
-    return p.ws_o_bytes + p.ws_ml_bytes;
+    return p.ws_o_bytes + p.ws_ml_bytes + p.ws_parts_bytes;
 }
 
 int32_t s4c_tree_attn_num_splits(const s4c_attn_shape* shape, int32_t max_cache_len) {
     s4c_status why;
     if (!shape || !shape_ok(shape, &why) || max_cache_len < 0) return 0;
-    return plan_attn(*shape, max_cache_len).splits;
+    return plan_attn(*shape, max_cache_len).parts;
 }
 
 #pragma GCC visibility pop
@@ -188,25 +188,27 @@ s4c_status tree_attn_impl(const s4c_attn_shape* shape, const void* q, const void
         !aligned16(out))
         return S4C_ERR_SHAPE;
     const AttnPlan p = plan_attn(*shape, max_cache_len);
-    const size_t need = p.ws_o_bytes + p.ws_ml_bytes;
+    const size_t need = p.ws_o_bytes + p.ws_ml_bytes + p.ws_parts_bytes;
     if (need > 0 && (!workspace || workspace_bytes < need || (((uintptr_t)workspace) & 255))) return S4C_ERR_WORKSPACE;
 
     AttnArgs a;
     a.q = q; a.k_tree = k_tree; a.v_tree = v_tree; a.k_cache = k_cache; a.v_cache = v_cache;
     a.cache_len = cache_len; a.parent = parent; a.out = out; a.status = status;
     a.ws_ml = (float*)workspace;
-    a.ws_o = (float*)((char*)workspace + p.ws_ml_bytes);
+    a.ws_parts = (int32_t*)((char*)workspace + p.ws_ml_bytes);
+    a.ws_o = (float*)((char*)workspace + p.ws_ml_bytes + p.ws_parts_bytes);
     a.B = shape->B; a.Hq = shape->Hq; a.Hkv = shape->Hkv; a.D = shape->D; a.N = shape->N;
     a.S_cap = shape->S_cap; a.G = shape->Hq / shape->Hkv; a.M = a.N * a.G;
-    a.max_cache_len = max_cache_len; a.splits = p.splits; a.chunk = p.chunk;
+    a.max_cache_len = max_cache_len; a.teams = p.teams; a.whole = p.whole; a.mtiles = p.mtiles;
+    a.tile_keys = p.tile_keys; a.tile_shift = p.tile_shift;
     a.scale_log2 = (scale > 0.f ? scale : 1.0f / sqrtf((float)shape->D)) * kLog2e;
     a.block_table = block_table; a.max_blocks = max_blocks; a.page_shift = page_shift; a.num_pages = num_pages;
 
     hipStream_t st = (hipStream_t)hip_stream;
-    // Splits are combined by a second kernel: the kernel boundary is what makes one workgroup's
+    // Parts are combined by a second kernel: the kernel boundary is what makes one workgroup's
     // partial results visible to another across the chip's separate L2s at no extra cost.
-    hipError_t e = p.mfma ? launch_tree_attn_mfma(a, shape->dtype, st) : launch_tree_attn_generic(a, shape->dtype, st);
-    if (e == hipSuccess && p.splits > 1) e = launch_attn_merge(a, shape->dtype, st);
+    hipError_t e = p.large ? launch_tree_attn_large(a, shape->dtype, st) : launch_tree_attn_small(a, shape->dtype, st);
+    if (e == hipSuccess && !p.whole) e = launch_attn_merge(a, shape->dtype, st);
     return e == hipSuccess ? S4C_OK : S4C_ERR_HIP;
 }
 }  // namespace

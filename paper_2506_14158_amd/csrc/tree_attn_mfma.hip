@@ -1,5 +1,5 @@
 // Tree-masked attention on the CDNA4 matrix cores (paper Sec. 3.2, Fig. 3): bf16 or fp16 in, fp32
-// accumulate, head size 128.
+// accumulate, more than 64 query rows per KV head (fewer: tree_attn_mfma_smallm.hip); head size 64 or 128.
 //
 // The N tree nodes times the G query heads that share one KV head form a dense tile of
 // M = N*G query rows, so both contractions run on v_mfma_f32_32x32x16_bf16 (_f16 for fp16 data).
@@ -18,12 +18,15 @@
 //   * A direct-to-LDS load writes 1 KB contiguous per wave, so rows cannot be padded; instead the
 //     16-byte chunks of a row are XOR-swizzled (K: chunk ^ (row & 15); V: chunk ^ ((row & 3) << 2)),
 //     applied on the global-address side of the load.  That makes the 16-byte row reads of K and
-//     the 4-row x 64-byte transposing reads of V bank-conflict free.
+//     the 4-row x 64-byte transposing reads of V bank-conflict free.  (Head size 64: two rows share
+//     256 bytes of banks, so K uses chunk ^ ((row >> 1) & 7) and V chunk ^ (((row >> 1) & 1) << 2).)
 //   * Full prefix tiles run a mask-free body.  The ragged last prefix tile and the tree rows
 //     (extra tiles whose scores are kept only where the key node is the query node or one of its
 //     ancestors; 128-bit masks built from parent[] in LDS) run a masked copy of the body.  Rows
 //     past the end of a ragged tile are clamped to its last valid row (in bounds, finite).
-//   * With KV splits > 1 the kernel writes unnormalised partials for the merge kernel.
+//   * The keys are divided between teams of workgroups (attn_work.h); parts of a divided unit are written
+//     unnormalised for the merge kernel.
+#include "attn_work.h"
 #include "mfma_common.h"
 
 namespace s4c {
@@ -34,16 +37,21 @@ using namespace mfma;
 
 constexpr int kBN = 64;                     // keys per tile
 constexpr float kLazyLog2 = 8.0f;           // full tiles rescale only when a row maximum grew by more than 2^8
-constexpr int kTileB = kBN * kRowB;         // bytes per K (or V) tile: 16 KB
-constexpr int kStageB = 2 * kTileB;         // K then V
-constexpr int lds_bytes_for(int ns) { return ns * kStageB + kMaxNodes * 16 + kMaxNodes * 4; }
+constexpr int lds_bytes_for(int ns, int d) { return ns * 2 * kBN * d * 2 + kMaxNodes * 16 + kMaxNodes * 4; }
 
-
-template <int WR, int NS, int WPE, bool PAGED, bool F16>
+template <int WR, int NS, int WPE, bool PAGED, bool F16, int kD>
 __global__ __launch_bounds__(WR * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 void tree_attn_mfma_kernel(AttnArgs a) {
     constexpr int NT = WR * 64;
     constexpr int BM = WR * 32;
+    constexpr int kRowB = kD * 2;                // bytes per K/V row
+    constexpr int kTileB = kBN * kRowB;          // bytes per K (or V) tile
+    constexpr int kStageB = 2 * kTileB;          // K then V
+    constexpr int kLPR = kRowB / 16;             // lanes (16-byte chunks) per row in a direct-to-LDS load
+    constexpr int kRPI = 64 / kLPR;              // rows per load instruction
+    constexpr int kKT = kD / 16, kDB = kD / 32;  // MFMA steps of the scores; 32-column blocks of the output
+    auto k_swz = [](int r) { return kD == 64 ? (r >> 1) & 7 : r & 15; };
+    auto v_swz = [](int r) { return kD == 64 ? ((r >> 1) & 1) << 2 : (r & 3) << 2; };
     constexpr int CH = (kBN * kD / 8) / NT;      // direct-to-LDS loads per thread per K (or V) tile
     static_assert(CH >= 1, "tile smaller than the workgroup");
     static_assert(NS >= 2 && 2 * CH * (NS - 2) < 64, "too many loads in flight for vmcnt");
@@ -57,55 +65,158 @@ void tree_attn_mfma_kernel(AttnArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int N = a.N, G = a.G, M = a.M;
 
-    // Workgroups are handed to the 8 XCDs round-robin by linear id.  The `team` workgroups of
-    // one (sequence, KV head) -- its query-row tiles and KV splits -- take consecutive slots of
-    // ONE XCD, so the row tiles that stream the same K/V rows share that XCD's L2.
-    const int team = a.mtiles * a.splits;
+    // Workgroups are handed to the 8 XCDs round-robin by linear id.  The workgroups of a team -- the row tiles of
+    // one unit, walking the same keys -- take consecutive slots of ONE XCD and share the K/V rows through its L2.
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int unit = (slot / team) * 8 + xcd;            // (sequence, KV head) index
-    if (unit >= a.B * a.Hkv) return;
-    const int member = slot % team;
-    const int mt = member / a.splits, sp = member % a.splits;
-    const int b = unit / a.Hkv, kvh = unit % a.Hkv;
+    const int team = work::team_id(a, xcd, slot / a.mtiles), mt = slot % a.mtiles;
 
-    // ---- validate the sequence; build ancestor-or-self masks
-    int bad_tree = 0;
-    if (tid < N) {
-        const int p = a.parent[(size_t)b * N + tid];
-        spar[tid] = p;
-        bad_tree = (p < -1 || p >= tid);
+    // ---- direct-to-LDS tile loads.  Load c of a wave (instruction ii = wave + WR c of the tile) covers rows
+    // kRPI ii .. : lane -> (row, physical chunk) and fetches the logical chunk that the swizzle maps there.  For full
+    // prefix tiles the per-lane byte offsets are loop invariants and the tile base advances in scalar registers.
+    uint32_t kvo_k[CH], kvo_v[CH];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        const int row = kRPI * (wave + WR * c) + lane / kLPR, pc = lane % kLPR;
+        kvo_k[c] = row * kRowB + ((pc ^ k_swz(row)) << 4);
+        kvo_v[c] = row * kRowB + ((pc ^ v_swz(row)) << 4);
     }
-    bad_tree = __syncthreads_or(bad_tree);
-    const int P = a.cache_len[b];
-    int bad_len = (P < 0 || P > a.max_cache_len || P > a.S_cap);
-    if constexpr (PAGED) {
-        // every page the prefix touches must be a page of the pool (each workgroup checks them all,
-        // so all workgroups of the sequence agree)
-        int bad_page = 0;
-        if (!bad_len)
+    // per-lane LDS byte offsets inside a stage
+    const int g32 = lane >> 5;                    // which half of the wave
+    const int i16 = lane & 15, dhalf = (lane >> 4) & 1;
+    uint32_t k_off[kKT], v_off[kDB];
+#pragma unroll
+    for (int tt = 0; tt < kKT; ++tt) k_off[tt] = (lane & 31) * kRowB + (((2 * tt + g32) ^ k_swz(lane & 31)) << 4);
+#pragma unroll
+    for (int db = 0; db < kDB; ++db) {
+        const int vrow = 4 * g32 + (i16 >> 2);
+        v_off[db] = kTileB + vrow * kRowB + (((4 * db + 2 * dhalf + ((i16 & 3) >> 1)) ^ v_swz(vrow)) << 4) + 8 * (i16 & 1);
+    }
+
+    const work::Lens lens(a);
+    work::Walk cw = work::walk_first(a, lens, team);      // what is multiplied
+    if (cw.b < 0) return;
+    work::Walk pw = cw;                                   // what is loaded
+    const int n_share = uniform(cw.left + cw.tile_end - cw.tile);
+    int issued = 0, done = 0;
+    const ptrdiff_t v_minus_k = (const unsigned char*)a.v_cache - (const unsigned char*)a.k_cache;
+    const ptrdiff_t vt_minus_kt = (const unsigned char*)a.v_tree - (const unsigned char*)a.k_tree;
+    const uint32_t tree_stride = (uint32_t)a.Hkv * kRowB;
+
+    // Loads the next tile of the share (tile `issued`, ring stage issued % NS).  Every address is in bounds whatever
+    // the inputs hold: prefix rows lie below the usable length, page ids are clamped to the pool (a sequence with a bad
+    // one is flagged and its result discarded).  Full prefix tiles take the short way: p_full of them are left in the
+    // segment, the next one at p_k (or, paged, at key p_key).
+    int p_full = 0, p_key = 0;
+    const unsigned char* p_k = nullptr;
+    auto page_addr = [&](int k0) __attribute__((always_inline)) {               // (a tile never straddles pages: pages are powers of two >= the tile)
+        int id = scalar_load_i32(uniform((const unsigned char*)(a.block_table + (size_t)pw.b * a.max_blocks)),
+                                 (uint32_t)uniform(k0 >> a.page_shift) * 4u);
+        id = (unsigned)id < (unsigned)a.num_pages ? id : 0;
+        return uniform((const unsigned char*)a.k_cache +
+                       ((((size_t)id * a.Hkv + pw.kvh) << a.page_shift) + (size_t)(k0 & ((1 << a.page_shift) - 1))) * kRowB);
+    };
+    auto begin_segment = [&]() __attribute__((always_inline)) {
+        p_full = uniform(max(0, min(work::usable(a, lens.at(a, pw.b)) / kBN, pw.tile_end) - pw.tile));
+        p_key = pw.tile * kBN;
+        if constexpr (!PAGED)
+            p_k = uniform((const unsigned char*)a.k_cache + (((size_t)pw.b * a.Hkv + pw.kvh) * (size_t)a.S_cap + p_key) * kRowB);
+    };
+    begin_segment();
+    auto stage_base = [&]() __attribute__((always_inline)) {
+        return __builtin_amdgcn_readfirstlane(lds0 + ((uint32_t)issued % NS) * kStageB + wave * 1024);
+    };
+    auto issue_full = [&]() __attribute__((always_inline)) {
+        const uint32_t sbase = stage_base();
+        const unsigned char* kg = PAGED ? page_addr(p_key) : uniform(p_k);
+        const unsigned char* vg = uniform(kg + v_minus_k);
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            dma16(kg, kvo_k[c], sbase + WR * c * 1024);
+            dma16(vg, kvo_v[c], sbase + WR * c * 1024 + kTileB);
+        }
+        if constexpr (PAGED) p_key += kBN; else p_k += kBN * kRowB;
+    };
+    auto end_tile = [&]() __attribute__((always_inline)) {
+        if (pw.tile == pw.tile_end) {
+            pw = work::walk_next(a, lens, pw);
+            if (pw.b >= 0) begin_segment();
+        }
+    };
+    auto issue_next = [&]() __attribute__((always_inline)) {
+        ++pw.tile;
+        if (p_full > 0) {
+            issue_full();
+            --p_full;
+        } else {
+            const int P = work::usable(a, lens.at(a, pw.b)), u_pref = (P + kBN - 1) / kBN;
+            const uint32_t sbase = stage_base();
+            const bool tree = pw.tile > u_pref;
+            const int k0 = (pw.tile - 1 - (tree ? u_pref : 0)) * kBN;
+            const unsigned char* kg;
+            if (tree) kg = uniform((const unsigned char*)a.k_tree + (((size_t)pw.b * N + k0) * a.Hkv + pw.kvh) * kRowB);
+            else kg = PAGED ? page_addr(k0) : uniform(p_k);
+            kg = uniform(kg);
+            const unsigned char* vg = uniform(kg + (tree ? vt_minus_kt : v_minus_k));
+            const int last = (tree ? N : P) - 1 - k0;                       // >= 0: last valid row of the tile
+            const uint32_t rstride = tree ? tree_stride : (uint32_t)kRowB;
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                const int row = kRPI * (wave + WR * c) + lane / kLPR, pc = lane % kLPR;
+                const uint32_t roff = (uint32_t)min(row, last) * rstride;
+                dma16(kg, roff + ((pc ^ k_swz(row)) << 4), sbase + WR * c * 1024);
+                dma16(vg, roff + ((pc ^ v_swz(row)) << 4), sbase + WR * c * 1024 + kTileB);
+            }
+        }
+        ++issued;
+        end_tile();
+    };
+    issue_next();
+
+    const bool wave_on = mt * BM + wave * 32 < M;         // some of this wave's rows exist
+    int b_known = -1, bad_seq = 0;
+    for (; cw.b >= 0; cw = work::walk_next(a, lens, cw)) {
+    const int b = cw.b, kvh = cw.kvh;
+    const int P = work::usable(a, lens.at(a, b));
+
+    // ---- another sequence: validate it; build its ancestor-or-self masks
+    if (b != b_known) {
+        b_known = b;
+        int bad_tree = 0;
+        if (tid < N) {
+            const int p = a.parent[(size_t)b * N + tid];
+            spar[tid] = p;
+            bad_tree = (p < -1 || p >= tid);
+        }
+        bad_tree = __syncthreads_or(bad_tree);
+        int bad_len = P != lens.at(a, b);
+        if constexpr (PAGED) {
+            // every page the prefix touches must be a page of the pool (each workgroup checks them all,
+            // so all workgroups of the sequence agree)
+            int bad_page = 0;
             for (int i = tid; i < ((P + (1 << a.page_shift) - 1) >> a.page_shift); i += NT) {
                 const int id = a.block_table[(size_t)b * a.max_blocks + i];
                 bad_page |= (id < 0 || id >= a.num_pages);
             }
-        bad_len |= __syncthreads_or(bad_page);
+            bad_len |= __syncthreads_or(bad_page);
+        }
+        if (a.status && tid == 0 && cw.tile == 0 && kvh == 0 && mt == 0)
+            a.status[b] = (bad_tree ? S4C_SEQ_BAD_TREE : 0) | (bad_len ? S4C_SEQ_BAD_LEN : 0);
+        // wave-uniform by construction; tell the compiler so that everything derived from it stays scalar
+        bad_seq = __builtin_amdgcn_readfirstlane((bad_tree || bad_len) ? 1 : 0);
+        for (int i = tid; i < N && !bad_tree; i += NT) {
+            uint32_t m[4] = {0, 0, 0, 0};
+            for (int j = i; j >= 0; j = spar[j]) m[j >> 5] |= 1u << (j & 31);
+            *(uint4*)(anc + i * 4) = make_uint4(m[0], m[1], m[2], m[3]);
+        }
+        __syncthreads();
     }
-    if (a.status && tid == 0 && member == 0 && kvh == 0)
-        a.status[b] = (bad_tree ? S4C_SEQ_BAD_TREE : 0) | (bad_len ? S4C_SEQ_BAD_LEN : 0);
-    // wave-uniform by construction; tell the compiler so that everything derived from it stays scalar
-    const bool bad = __builtin_amdgcn_readfirstlane((bad_tree || bad_len) ? 1 : 0) != 0;
-    for (int i = tid; i < N && !bad; i += NT) {
-        uint32_t m[4] = {0, 0, 0, 0};
-        for (int j = i; j >= 0; j = spar[j]) m[j >> 5] |= 1u << (j & 31);
-        anc[i * 4 + 0] = m[0]; anc[i * 4 + 1] = m[1]; anc[i * 4 + 2] = m[2]; anc[i * 4 + 3] = m[3];
-    }
-    __syncthreads();
+    const bool bad = bad_seq != 0;
 
     // ---- this lane's query row
-    const int g32 = lane >> 5;                    // which half of the wave
     const int rq = mt * BM + wave * 32 + (lane & 31);
     const bool rvalid = rq < M;
     const int node = rvalid ? rq / G : 0;
-    const int head = kvh * G + (rvalid ? rq % G : 0);
+    const int head = kvh * G + (rvalid ? rq - node * G : 0);
     uint32_t amask[4] = {0, 0, 0, 0};
     if (rvalid && !bad) {
 #pragma unroll
@@ -113,111 +224,29 @@ void tree_attn_mfma_kernel(AttnArgs a) {
     }
 
     // Q^T fragments: B operand of step t holds d = 16 t + 8 g32 + (0..7) of row rq
-    bf16x8 qf[8];
+    bf16x8 qf[kKT];
     {
         const bf16_t* qrow = (const bf16_t*)a.q + (((size_t)b * N + node) * a.Hq + head) * kD + g32 * 8;
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
+        for (int t = 0; t < kKT; ++t) {
             uint4 raw = make_uint4(0, 0, 0, 0);
             if (rvalid) raw = *(const uint4*)(qrow + 16 * t);
             qf[t] = __builtin_bit_cast(bf16x8, raw);
         }
     }
 
-    // ---- tiles of this workgroup: prefix range of the split, then (last split) the tree rows
-    int kb = sp * a.chunk, ke = min(P, (sp + 1) * a.chunk);
-    if (bad || ke < kb) { kb = 0; ke = 0; }
-    kb = uniform(kb);
-    ke = uniform(ke);
-    const int n_full = (ke - kb) / kBN;                          // mask-free prefix tiles
-    const int n_pref = (ke - kb + kBN - 1) / kBN;
-    const int n_tree = (!bad && sp == a.splits - 1) ? (N + kBN - 1) / kBN : 0;
-    const int n_tiles = n_pref + n_tree;
-
-    // cache rows kb + j of this (sequence, KV head): contiguous, or looked up page by page (a tile
-    // never straddles pages: pages are powers of two >= the tile)
-    const unsigned char* kc = (const unsigned char*)a.k_cache + (((size_t)b * a.Hkv + kvh) * (size_t)a.S_cap + kb) * kRowB;
-    const unsigned char* vc = (const unsigned char*)a.v_cache + (((size_t)b * a.Hkv + kvh) * (size_t)a.S_cap + kb) * kRowB;
-    const int32_t* bt_row = PAGED ? a.block_table + (size_t)b * a.max_blocks : nullptr;
-    auto cache_row = [&](const void* pool_or_base, const unsigned char* contiguous, int j) -> const unsigned char* {
-        if constexpr (PAGED) {
-            const int key = uniform(kb + j);
-            const int id = scalar_load_i32(uniform((const unsigned char*)bt_row), (uint32_t)(key >> a.page_shift) * 4u);
-            const size_t row = (((size_t)id * a.Hkv + kvh) << a.page_shift) + (size_t)(key & ((1 << a.page_shift) - 1));
-            return uniform((const unsigned char*)pool_or_base + row * kRowB);
-        } else {
-            return uniform(contiguous + (size_t)j * kRowB);
-        }
-    };
-    const unsigned char* kt = (const unsigned char*)a.k_tree + ((size_t)b * N * a.Hkv + kvh) * kRowB;
-    const unsigned char* vt = (const unsigned char*)a.v_tree + ((size_t)b * N * a.Hkv + kvh) * kRowB;
-    const uint32_t tree_stride = (uint32_t)a.Hkv * kRowB;
-
-    // ---- direct-to-LDS tile loads.  Load c of a wave (instruction ii = wave + WR c of the tile)
-    // covers rows 4 ii .. 4 ii + 3: lane -> (row 4 ii + lane/16, physical chunk lane%16) and fetches
-    // the logical chunk that the swizzle maps there.  For full prefix tiles the per-lane byte
-    // offsets are loop invariants and the tile base advances in scalar registers.
-    uint32_t kvo_k[CH], kvo_v[CH];
+    f32x16 o[kDB];
 #pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        const int row = 4 * (wave + WR * c) + (lane >> 4), pc = lane & 15;
-        kvo_k[c] = row * kRowB + ((pc ^ (row & 15)) << 4);
-        kvo_v[c] = row * kRowB + ((pc ^ ((row & 3) << 2)) << 4);
-    }
-    auto issue_tile = [&](int t) {
-        const uint32_t sbase = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(t % NS) * kStageB + wave * 1024);
-        if (t < n_full) {
-            const unsigned char* kg = cache_row(a.k_cache, kc, t * kBN);
-            const unsigned char* vg = PAGED ? kg + ((const unsigned char*)a.v_cache - (const unsigned char*)a.k_cache)
-                                            : cache_row(a.v_cache, vc, t * kBN);
-#pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                dma16(kg, kvo_k[c], sbase + WR * c * 1024);
-                dma16(vg, kvo_v[c], sbase + WR * c * 1024 + kTileB);
-            }
-        } else {
-            const bool tree = t >= n_pref;
-            const int k0 = tree ? (t - n_pref) * kBN : t * kBN;             // relative to kb for the prefix
-            const int klast = (tree ? N : ke - kb) - 1;
-            // rows are addressed relative to the tile's first row (or the last valid row, if the
-            // tile starts beyond it), which for the prefix fixes the page
-            const int kq = min(k0, klast);
-            const unsigned char* kg = tree ? uniform(kt + (size_t)kq * tree_stride) : cache_row(a.k_cache, kc, kq);
-            const unsigned char* vg = tree ? uniform(vt + (size_t)kq * tree_stride)
-                                           : (PAGED ? kg + ((const unsigned char*)a.v_cache - (const unsigned char*)a.k_cache)
-                                                    : cache_row(a.v_cache, vc, kq));
-            const uint32_t rstride = tree ? tree_stride : (uint32_t)kRowB;
-#pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                const int row = 4 * (wave + WR * c) + (lane >> 4), pc = lane & 15;
-                const uint32_t roff = (uint32_t)(min(k0 + row, klast) - kq) * rstride;
-                dma16(kg, roff + ((pc ^ (row & 15)) << 4), sbase + WR * c * 1024);
-                dma16(vg, roff + ((pc ^ ((row & 3) << 2)) << 4), sbase + WR * c * 1024 + kTileB);
-            }
-        }
-    };
-
-    // per-lane LDS byte offsets inside a stage
-    const int i16 = lane & 15, dhalf = (lane >> 4) & 1;
-    uint32_t k_off[8], v_off[4];
-#pragma unroll
-    for (int tt = 0; tt < 8; ++tt) k_off[tt] = (lane & 31) * kRowB + (((2 * tt + g32) ^ i16) << 4);
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-        v_off[db] = kTileB + (4 * g32 + (i16 >> 2)) * kRowB +
-                    ((((db ^ (i16 >> 2)) << 2) + 2 * dhalf + ((i16 & 3) >> 1)) << 4) + 8 * (i16 & 1);
-
-    f32x16 o[4];
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
+    for (int db = 0; db < kDB; ++db)
 #pragma unroll
         for (int j = 0; j < 16; ++j) o[db][j] = 0.f;
     float m_run = -INFINITY, l_run = 0.f;      // l_run: this lane's half of the keys only
 
     // ---- one tile: scores, (mask,) online softmax, accumulate
-    auto tile_body = [&](auto mode_tag, int t) {
+    // kTail: keys >= arg masked; kTree: tree tile `arg` of the unit, ancestor mask
+    auto tile_body = [&](auto mode_tag, int arg) __attribute__((always_inline)) {
         constexpr int MODE = decltype(mode_tag)::value;
-        const lds_u8* stage = (const lds_u8*)smem + (t % NS) * kStageB;     // LDS address space throughout
+        const lds_u8* stage = (const lds_u8*)smem + ((uint32_t)done % NS) * kStageB;     // LDS address space throughout
 
         // S^T = K Q^T for the two 32-key blocks.  The two accumulator chains are interleaved (a
         // dependent MFMA cannot start before its predecessor retires); the K fragments of the
@@ -232,30 +261,34 @@ void tree_attn_mfma_kernel(AttnArgs a) {
             }
 #pragma unroll
             for (int j = 0; j < 16; ++j) { s[0][j] = 0.f; s[1][j] = 0.f; }
+            if constexpr (kKT == 8) {
 #pragma unroll
-            for (int tt = 0; tt < 4; ++tt) {
-                s[0] = mma32<F16>(kf[0][tt], qf[tt], s[0]);
-                kf[0][tt] = *(const lds_bf16x8*)(stage + k_off[tt + 4]);
-                s[1] = mma32<F16>(kf[1][tt], qf[tt], s[1]);
-                kf[1][tt] = *(const lds_bf16x8*)(stage + 32 * kRowB + k_off[tt + 4]);
+                for (int tt = 0; tt < 4; ++tt) {
+                    s[0] = mma32<F16>(kf[0][tt], qf[tt], s[0]);
+                    kf[0][tt] = *(const lds_bf16x8*)(stage + k_off[tt + 4]);
+                    s[1] = mma32<F16>(kf[1][tt], qf[tt], s[1]);
+                    kf[1][tt] = *(const lds_bf16x8*)(stage + 32 * kRowB + k_off[tt + 4]);
+                }
             }
 #pragma unroll
             for (int tt = 0; tt < 4; ++tt) {
-                s[0] = mma32<F16>(kf[0][tt], qf[tt + 4], s[0]);
-                s[1] = mma32<F16>(kf[1][tt], qf[tt + 4], s[1]);
+                s[0] = mma32<F16>(kf[0][tt], qf[tt + kKT - 4], s[0]);
+                s[1] = mma32<F16>(kf[1][tt], qf[tt + kKT - 4], s[1]);
             }
             __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);      // 8 LDS reads
+            if constexpr (kKT == 8) {
 #pragma unroll
-            for (int tt = 0; tt < 8; ++tt) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // 1 MFMA
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // 1 LDS read
+                for (int tt = 0; tt < 8; ++tt) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // 1 MFMA
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // 1 LDS read
+                }
             }
             __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);      // 8 MFMAs
         }
 
         // key of register j of block kblk, relative to the tile: 32 kblk + 8 (j/4) + 4 g32 + (j%4)
         if constexpr (MODE == kTree) {
-            const int w0 = (t - n_pref) * 2;            // 32-node word of block 0
+            const int w0 = arg * 2;                     // 32-node word of block 0
 #pragma unroll
             for (int kblk = 0; kblk < 2; ++kblk) {
                 const int w = w0 + kblk;
@@ -265,12 +298,11 @@ void tree_attn_mfma_kernel(AttnArgs a) {
                     if (!((word >> ((j >> 2) * 8 + (j & 3))) & 1u)) s[kblk][j] = -INFINITY;
             }
         } else if constexpr (MODE == kTail) {
-            const int nvalid = (ke - kb) - t * kBN;
 #pragma unroll
             for (int kblk = 0; kblk < 2; ++kblk)
 #pragma unroll
                 for (int j = 0; j < 16; ++j)
-                    if (kblk * 32 + (j >> 2) * 8 + 4 * g32 + (j & 3) >= nvalid) s[kblk][j] = -INFINITY;
+                    if (kblk * 32 + (j >> 2) * 8 + 4 * g32 + (j & 3) >= arg) s[kblk][j] = -INFINITY;
         }
 
         // online softmax for this lane's row (log2 units)
@@ -292,7 +324,7 @@ void tree_attn_mfma_kernel(AttnArgs a) {
                 const float alpha = fast_exp2(m_run - m_new);          // first tile: exp2(-inf) = 0
                 l_run *= alpha;
 #pragma unroll
-                for (int db = 0; db < 4; ++db)
+                for (int db = 0; db < kDB; ++db)
 #pragma unroll
                     for (int j = 0; j < 16; ++j) o[db][j] *= alpha;
                 m_run = m_new;
@@ -322,7 +354,7 @@ void tree_attn_mfma_kernel(AttnArgs a) {
             l_run = l_run * alpha + psum;
             if (__any(m_new > m_run)) {
 #pragma unroll
-                for (int db = 0; db < 4; ++db)
+                for (int db = 0; db < kDB; ++db)
 #pragma unroll
                     for (int j = 0; j < 16; ++j) o[db][j] *= alpha;
             }
@@ -336,60 +368,78 @@ void tree_attn_mfma_kernel(AttnArgs a) {
 #pragma unroll
             for (int st = 0; st < 4; ++st)
                 pb[st] = round8<F16>(s[st >> 1], 8 * (st & 1));
-            auto vfrag = [&](const lds_u8* p) {     // 8 keys x 1 column of V^T: two transposing reads
+            auto vfrag = [&](const lds_u8* p) __attribute__((always_inline)) {     // 8 keys x 1 column of V^T: two transposing reads
                 const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
                 const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 8 * kRowB));
                 return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
             };
-            bf16x8 vf[2][4];
+            bf16x8 vf[2][kDB];
 #pragma unroll
-            for (int db = 0; db < 4; ++db) vf[0][db] = vfrag(stage + v_off[db]);
+            for (int db = 0; db < kDB; ++db) vf[0][db] = vfrag(stage + v_off[db]);
 #pragma unroll
             for (int st = 0; st < 4; ++st) {
                 if (st < 3) {
 #pragma unroll
-                    for (int db = 0; db < 4; ++db) vf[(st + 1) & 1][db] = vfrag(stage + (st + 1) * 16 * kRowB + v_off[db]);
+                    for (int db = 0; db < kDB; ++db) vf[(st + 1) & 1][db] = vfrag(stage + (st + 1) * 16 * kRowB + v_off[db]);
                 }
 #pragma unroll
-                for (int db = 0; db < 4; ++db)
+                for (int db = 0; db < kDB; ++db)
                     o[db] = mma32<F16>(vf[st & 1][db], pb[st], o[db]);
             }
         }
     };
 
-    // The compiler does not see the direct-to-LDS loads; settle every load it does know about
-    // (the Q fragments) here, so that it places no vmcnt wait of its own inside the tile loop.
-    wait_vmcnt<0>();
-    for (int t = 0; t < NS - 1 && t < n_tiles; ++t) issue_tile(t);
+    // The compiler does not see the direct-to-LDS loads; settle the Q fragments here, so that it places no
+    // vmcnt wait of its own inside the tile loop.
+#pragma unroll
+    for (int t = 0; t < kKT; ++t) asm volatile("" : "+v"(qf[t]));
+    while (issued < done + NS - 1 && issued < n_share) issue_next();       // (the first segment: the rest of the ring)
 
-    auto sync_and_prefetch = [&](int t) {
-        // tile t has landed once at most NS-2 younger tiles of this wave are outstanding
-        if (t + NS - 2 < n_tiles) wait_vmcnt<2 * CH * (NS - 2)>(); else wait_vmcnt<0>();
-        __syncthreads();          // every wave's part of tile t is in LDS; stage (t-1) % NS is free
-        if (t + NS - 1 < n_tiles) issue_tile(t + NS - 1);
+    auto sync = [&]() __attribute__((always_inline)) {
+        // tile `done` has landed once at most NS-2 younger tiles of this wave are outstanding
+        if (done + NS - 2 < n_share) wait_vmcnt<2 * CH * (NS - 2)>(); else wait_vmcnt<0>();
+        __syncthreads();          // every wave's part of the tile is in LDS; the stage before it is free
+        if (issued < n_share) issue_next();
     };
-    int t = 0;
-    for (; t < n_full; ++t) {
-        sync_and_prefetch(t);
-        tile_body(std::integral_constant<int, kPlain>{}, t);
+    const int u_pref = (P + kBN - 1) / kBN, t_end = uniform(cw.tile_end);
+    int t = uniform(cw.tile);
+    // While the loads run ahead inside this segment's full prefix tiles, nothing has to be decided per tile.
+    if (uniform(pw.b) == uniform(b) && uniform(pw.kvh) == uniform(kvh)) {
+        const int n = uniform(p_full);
+        for (int i = 0; i < n; ++i, ++done) {
+            wait_vmcnt<2 * CH * (NS - 2)>();
+            __syncthreads();
+            issue_full();
+            ++issued;
+            if (wave_on) tile_body(std::integral_constant<int, kPlain>{}, 0);
+        }
+        t += n;
+        pw.tile += n;
+        p_full = 0;
+        end_tile();
     }
-    for (; t < n_pref; ++t) {
-        sync_and_prefetch(t);
-        tile_body(std::integral_constant<int, kTail>{}, t);
+    for (const int e = min(P / kBN, t_end); t < e; ++t, ++done) {
+        sync();
+        if (wave_on) tile_body(std::integral_constant<int, kPlain>{}, 0);
     }
-    for (; t < n_tiles; ++t) {
-        sync_and_prefetch(t);
-        tile_body(std::integral_constant<int, kTree>{}, t);
+    for (const int e = min(u_pref, t_end); t < e; ++t, ++done) {
+        sync();
+        if (wave_on) tile_body(std::integral_constant<int, kTail>{}, P - t * kBN);
+    }
+    for (; t < t_end; ++t, ++done) {
+        sync();
+        if (wave_on) tile_body(std::integral_constant<int, kTree>{}, t - u_pref);
     }
 
+    if (!a.whole && mt == 0 && tid == 0) work::note_parts(a, team, cw);
     // ---- write this lane's row: d = 32 db + 8 (j/4) + 4 g32 + (j%4)
-    const float l_tot = l_run + __shfl_xor(l_run, 32);
-    if (a.splits == 1) {
-        if (!rvalid) return;
+    const float l_tot = bad ? 0.f : l_run + __shfl_xor(l_run, 32);       // a flagged sequence: zero output
+    if (work::walk_is_whole(cw)) {
+        if (rvalid) {
         const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
         bf16_t* orow = (bf16_t*)a.out + (((size_t)b * N + node) * a.Hq + head) * kD + 4 * g32;
 #pragma unroll
-        for (int db = 0; db < 4; ++db)
+        for (int db = 0; db < kDB; ++db)
 #pragma unroll
             for (int jq = 0; jq < 4; ++jq) {
                 uint2 pk;
@@ -397,12 +447,13 @@ void tree_attn_mfma_kernel(AttnArgs a) {
                 pk.y = round1<F16>(o[db][4 * jq + 2] * inv) | (round1<F16>(o[db][4 * jq + 3] * inv) << 16);
                 *(uint2*)(orow + 32 * db + 8 * jq) = pk;
             }
+        }
     } else {
         if (rvalid) {
-            const size_t prow = (((size_t)b * a.Hkv + kvh) * a.splits + sp) * M + rq;
+            const size_t prow = work::part_row(a, team, cw.tile == 0 ? 1 : 0) + rq;
             float* orow = a.ws_o + prow * kD + 4 * g32;
 #pragma unroll
-            for (int db = 0; db < 4; ++db)
+            for (int db = 0; db < kDB; ++db)
 #pragma unroll
                 for (int jq = 0; jq < 4; ++jq)
                     *(float4*)(orow + 32 * db + 8 * jq) =
@@ -413,42 +464,43 @@ void tree_attn_mfma_kernel(AttnArgs a) {
             }
         }
     }
+    }
 }
 
 int pick_wr(int M) { return M <= 128 ? 4 : 8; }
 
-template <int WR, int NS, int WPE, bool PAGED, bool F16>
+template <int WR, int NS, int WPE, bool PAGED, bool F16, int D>
 hipError_t launch(const AttnArgs& a, hipStream_t st) {
-    constexpr int kLds = lds_bytes_for(NS);
+    constexpr int kLds = lds_bytes_for(NS, D);
     static std::atomic<uint64_t> lds_set{0};
-    const hipError_t ea = ensure_dynamic_lds((const void*)tree_attn_mfma_kernel<WR, NS, WPE, PAGED, F16>, kLds, lds_set);
+    const hipError_t ea = ensure_dynamic_lds((const void*)tree_attn_mfma_kernel<WR, NS, WPE, PAGED, F16, D>, kLds, lds_set);
     if (ea != hipSuccess) return ea;
-    AttnArgs k = a;
-    k.mtiles = (a.M + WR * 32 - 1) / (WR * 32);
-    const long units8 = ((long)a.B * a.Hkv + 7) / 8 * 8;          // padded to whole XCD rounds
-    dim3 grid((unsigned)(units8 * k.mtiles * a.splits)), block(WR * 64);
-    hipLaunchKernelGGL((tree_attn_mfma_kernel<WR, NS, WPE, PAGED, F16>), grid, block, kLds, st, k);
+    const long teams8 = ((long)a.teams + 7) / 8 * 8;              // padded to whole XCD rounds
+    dim3 grid((unsigned)(teams8 * a.mtiles)), block(WR * 64);
+    hipLaunchKernelGGL((tree_attn_mfma_kernel<WR, NS, WPE, PAGED, F16, D>), grid, block, kLds, st, a);
     return hipGetLastError();
+}
+
+// four waves (up to 128 rows): one workgroup per CU and wave per SIMD; eight: two waves per SIMD
+template <bool PAGED, bool F16, int D>
+hipError_t launch_rows(const AttnArgs& a, hipStream_t st) {
+    return pick_wr(a.M) == 4 ? launch<4, 4, 1, PAGED, F16, D>(a, st) : launch<8, 4, 2, PAGED, F16, D>(a, st);
+}
+template <bool F16>
+hipError_t launch_by_shape(const AttnArgs& a, hipStream_t st) {
+    if (a.D == 64) return a.block_table ? launch_rows<true, F16, 64>(a, st) : launch_rows<false, F16, 64>(a, st);
+    return a.block_table ? launch_rows<true, F16, 128>(a, st) : launch_rows<false, F16, 128>(a, st);
 }
 
 }  // namespace
 
-bool mfma_path_supported(const s4c_attn_shape& s) { return (s.dtype == S4C_BF16 || s.dtype == S4C_F16) && s.D == kD; }
-
-// Few rows: the key-parallel kernel (one 64-row workgroup); otherwise 32 rows per wave.
-int mfma_rows_per_block(const s4c_attn_shape& s) {
-    const int M = s.N * (s.Hq / s.Hkv);
-    return M <= 64 ? 64 : 32 * pick_wr(M);
+// 32 rows per wave.  (Head size 64 leaves room for two four-wave workgroups on a CU.)
+AttnTile attn_tile_large(const s4c_attn_shape& s) {
+    const int wr = pick_wr(s.N * (s.Hq / s.Hkv));
+    return AttnTile{32 * wr, kBN, wr == 4 && 2 * lds_bytes_for(4, s.D) <= 160 * 1024 ? 2 : 1};
 }
 
-template <bool F16>
-static hipError_t launch_by_shape(const AttnArgs& a, hipStream_t st) {
-    if (a.block_table) return pick_wr(a.M) == 4 ? launch<4, 4, 1, true, F16>(a, st) : launch<8, 4, 2, true, F16>(a, st);
-    return pick_wr(a.M) == 4 ? launch<4, 4, 1, false, F16>(a, st) : launch<8, 4, 2, false, F16>(a, st);
-}
-
-hipError_t launch_tree_attn_mfma(const AttnArgs& a, int dtype, hipStream_t st) {
-    if (a.M <= 64) return launch_tree_attn_smallm(a, dtype, st);
+hipError_t launch_tree_attn_large(const AttnArgs& a, int dtype, hipStream_t st) {
     return dtype == S4C_F16 ? launch_by_shape<true>(a, st) : launch_by_shape<false>(a, st);
 }
 

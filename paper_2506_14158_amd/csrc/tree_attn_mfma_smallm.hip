@@ -1,17 +1,21 @@
-// Tree-masked attention on the matrix cores for few query rows per KV head (M = N*G <= 64):
-// the HBM-bound shape (paper Sec. 3.2; every drafted node attends to the whole prefix, so with
-// 64 rows each K/V byte only feeds 64 FLOP).
+// Tree-masked attention on the matrix cores for few query rows per KV head (M = N*G <= 64 rows), and for fp32 data
+// at any M (64 rows at a time): paper Sec. 3.2; every drafted node attends to the whole prefix, so with 64 rows a
+// K/V byte of 16-bit data only feeds 64 FLOP and the kernel is a stream over K and V.
 //
-// With so few rows one (sequence, KV head) cannot occupy a CU by splitting rows, so the waves
-// of a workgroup split the KEYS instead: wave w owns row block w & 1 (32 rows) and key group
-// w >> 1.  A round is one 32-key tile per key group; two rounds fit in LDS, so while one round
-// is consumed the next is in flight (direct-to-LDS loads, XOR-swizzled as in the large-M
-// kernel).  Every wave keeps its own online-softmax state over its key group; after the last
-// round the partial states of a row are merged through LDS (the ring is dead by then) and
-// written with coalesced stores -- no HBM round trip for the partials of the key groups.  The
-// tree rows form the last round(s) (tile i = nodes 32 i .. 32 i + 31), masked with the 128-bit
-// ancestor sets built from parent[].  Measured on 256 (sequence, KV head) units with a 64K
-// prefix: 6.25 TB/s of K/V, 96 % of what a plain streaming-read kernel reaches on the same box.
+// With so few rows one (sequence, KV head) cannot occupy a CU by splitting rows, so the waves of a workgroup split
+// the KEYS instead: wave w owns row block w % RBW (32 rows) and key group w / RBW.  A round is one 32-key tile per
+// key group; a ring of NR rounds lives in LDS (direct-to-LDS loads, XOR-swizzled), NR - 1 of them in flight while
+// one is consumed.  Every wave keeps its own online-softmax state over its key group; at the end of a segment (a run
+// of tiles of one unit, attn_work.h) the states of a row are merged through LDS, while the ring already fills for the
+// next segment, and written.  Tree rows are the unit's last tiles, masked with the 128-bit ancestor sets built
+// from parent[].
+//   16-bit data: v_mfma_f32_32x32x16, K read as 16-byte row pieces, V^T through the transposing LDS read.
+//   fp32 data:   v_mfma_f32_32x32x2_f32 (fp32 products and sums, 256 FLOP/clock/CU -- what the vector ALUs have, but
+//                fed by one LDS value per 32 products instead of two per product).  The reduction index of Q.K is
+//                permuted (lane half g takes elements 8 t + 4 g .. + 3) so that both operands are 16-byte reads, and
+//                P^T is used straight out of the score accumulator: register j of lane half g holds key
+//                8 (j/4) + 4 g + j%4, so step j multiplies V rows that far apart.
+#include "attn_work.h"
 #include "mfma_common.h"
 
 namespace s4c {
@@ -21,391 +25,524 @@ namespace {
 using namespace mfma;
 
 constexpr int kBN = 32;                      // keys per tile
-constexpr int kTileKB = kBN * kRowB;         // K (or V) bytes of a tile: 8 KB
-constexpr int kTileB = 2 * kTileKB;          // K then V: 16 KB
-constexpr int kMergeRowB = (kD + 4) * 4;     // padded fp32 row of a partial output: 528 B
+constexpr float kLazyLog2 = 8.0f;            // full tiles rescale only when a row maximum grew by more than 2^8
 constexpr int kAuxB = kMaxNodes * 16 + kMaxNodes * 4;
 
-// KG key groups (tiles per round) => 2 KG waves.  KG = 4: one workgroup per CU with a 128 KB ring;
-// KG = 2: 69 KB per workgroup, so two workgroups share a CU and one's set-up and merge overlap
-// the other's streaming.
-template <int KG>
+enum Elem { kB16 = 0, kH16 = 1, kF32 = 2 };  // bf16, fp16, fp32
+
+// KG key groups x RBW row blocks of 32 = waves; NR rounds in the ring.
+template <Elem E, int D_, int KG_, int RBW_, int NR_>
 struct Cfg {
-    static constexpr int kRoundB = KG * kTileB;
-    static constexpr int kRingB = 2 * kRoundB;
-    static constexpr int kWaves = 2 * KG;
+    static constexpr Elem kElem = E;
+    static constexpr int kD = D_, kKG = KG_, kRBW = RBW_, kNR = NR_;
+    static constexpr int kEs = E == kF32 ? 4 : 2;
+    static constexpr int kRowB = kD * kEs;               // bytes per K/V row
+    static constexpr int kTileKB = kBN * kRowB;          // K (or V) bytes of a tile
+    static constexpr int kTileB = 2 * kTileKB;           // K then V
+    static constexpr int kRoundB = kKG * kTileB;
+    static constexpr int kRingB = kNR * kRoundB;
+    static constexpr int kWaves = kKG * kRBW;
     static constexpr int kThreads = 64 * kWaves;
-    static constexpr int kMergeB = kWaves * 32 * kMergeRowB + kWaves * 32 * 2 * 4;
-    static constexpr int kLdsBytes = (kRingB + kAuxB > kMergeB) ? kRingB + kAuxB : kMergeB;
+    static constexpr int kCH = kTileKB / 1024 / kRBW;    // direct-to-LDS loads per wave for its share of K (or V)
+    // the key groups' states of a row meet in LDS one 32-column block at a time (a region of its own, so that the
+    // ring keeps filling for the next segment): padded rows of 36 floats, and each row's (maximum, sum)
+    static constexpr int kMergeRow = 36;
+    static constexpr int kMergeB = (kKG - 1) * kRBW * 32 * (kMergeRow + 2) * 4;
+    static constexpr int kLdsBytes = kRingB + kAuxB + kMergeB;
+    static constexpr int kPerCu = 2 * kLdsBytes <= 160 * 1024 ? 2 : 1;
+    static_assert(kLdsBytes <= 160 * 1024, "LDS of one CU");
+    static_assert(kCH >= 1 && 2 * kCH * (kNR - 1) < 64, "loads in flight are counted in vmcnt");
+    // 16-byte chunk swizzle of row r: K is read as one chunk of 16 (or 32) consecutive rows at a time, V as 4 rows x
+    // 64 bytes (16-bit) or two rows 4 apart x 128 bytes (fp32); both spread over all banks
+    static __device__ __forceinline__ int k_swz(int r) {
+        if constexpr (kRowB == 128) return (r >> 1) & 7;
+        else return r & 15;
+    }
+    static __device__ __forceinline__ int v_swz(int r) {
+        if constexpr (kElem == kF32) return ((r >> 2) & 1) << 3;
+        else if constexpr (kRowB == 128) return ((r >> 1) & 1) << 2;
+        else return (r & 3) << 2;
+    }
 };
 
-template <int kKG, bool PAGED, bool F16>
-__global__ __launch_bounds__(Cfg<kKG>::kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <class C, bool PAGED>
+__global__ __launch_bounds__(C::kThreads) __attribute__((amdgpu_waves_per_eu(C::kPerCu * C::kWaves / 4, 2)))
 void tree_attn_smallm_kernel(AttnArgs a) {
-    constexpr int kRoundB = Cfg<kKG>::kRoundB, kRingB = Cfg<kKG>::kRingB, kWaves = Cfg<kKG>::kWaves;
-    constexpr int kThreads = Cfg<kKG>::kThreads;
+    constexpr int kD = C::kD, kKG = C::kKG, kRBW = C::kRBW, kNR = C::kNR, kRowB = C::kRowB;
+    constexpr int kThreads = C::kThreads, kCH = C::kCH;
+    constexpr bool kIs32 = C::kElem == kF32, F16 = C::kElem == kH16;
+    constexpr int kDB = kD / 32;                              // 32-column blocks of the output
+    constexpr int kLPR = kRowB / 16;                          // lanes (16-byte chunks) per row in a direct-to-LDS load
+    constexpr int kRPI = 64 / kLPR;                           // rows per load instruction
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    uint32_t* anc = (uint32_t*)(smem + kRingB);              // [kMaxNodes][4]
-    int32_t* spar = (int32_t*)(anc + kMaxNodes * 4);         // [kMaxNodes]
+    uint32_t* anc = (uint32_t*)(smem + C::kRingB);            // [kMaxNodes][4]
+    int32_t* spar = (int32_t*)(anc + kMaxNodes * 4);          // [kMaxNodes]
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int rb = wave & 1, kg = wave >> 1;
+    const int rb = wave % kRBW, kg = wave / kRBW;
     const int N = a.N, G = a.G, M = a.M;
+    const int g32 = lane >> 5;
 
-    // the splits of one (sequence, KV head) take consecutive slots of one XCD
+    // the workgroups of a team (row tiles that walk the same keys) take consecutive slots of one XCD
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int unit = (slot / a.splits) * 8 + xcd;
-    if (unit >= a.B * a.Hkv) return;
-    const int sp = slot % a.splits;
-    const int b = unit / a.Hkv, kvh = unit % a.Hkv;
+    const int team = work::team_id(a, xcd, slot / a.mtiles), mt = slot % a.mtiles;
 
-    // ---- validate the sequence; build ancestor-or-self masks
-    int bad_tree = 0;
-    if (tid < N) {
-        const int p = a.parent[(size_t)b * N + tid];
-        spar[tid] = p;
-        bad_tree = (p < -1 || p >= tid);
+    // per-lane offsets: direct-to-LDS loads (instruction ii covers rows kRPI ii ..), fragment reads inside a tile
+    uint32_t kvo_k[kCH], kvo_v[kCH];
+#pragma unroll
+    for (int c = 0; c < kCH; ++c) {
+        const int row = kRPI * (rb * kCH + c) + lane / kLPR, pc = lane % kLPR;
+        kvo_k[c] = row * kRowB + ((pc ^ C::k_swz(row)) << 4);
+        kvo_v[c] = row * kRowB + ((pc ^ C::v_swz(row)) << 4);
     }
-    bad_tree = __syncthreads_or(bad_tree);
-    const int P = a.cache_len[b];
-    int bad_len = (P < 0 || P > a.max_cache_len || P > a.S_cap);
-    if constexpr (PAGED) {
-        // every page the prefix touches must be a page of the pool (each workgroup checks them all,
-        // so all workgroups of the sequence agree)
-        int bad_page = 0;
-        if (!bad_len)
-            for (int i = tid; i < ((P + (1 << a.page_shift) - 1) >> a.page_shift); i += kThreads) {
-                const int id = a.block_table[(size_t)b * a.max_blocks + i];
-                bad_page |= (id < 0 || id >= a.num_pages);
-            }
-        bad_len |= __syncthreads_or(bad_page);
-    }
-    if (a.status && tid == 0 && sp == 0 && kvh == 0)
-        a.status[b] = (bad_tree ? S4C_SEQ_BAD_TREE : 0) | (bad_len ? S4C_SEQ_BAD_LEN : 0);
-    const bool bad = __builtin_amdgcn_readfirstlane((bad_tree || bad_len) ? 1 : 0) != 0;
-    // ---- rounds of this workgroup: prefix range of the split, then (last split) the tree round
-    int kb = sp * a.chunk, ke = min(P, (sp + 1) * a.chunk);
-    if (bad || ke < kb) { kb = 0; ke = 0; }
-    kb = uniform(kb);
-    ke = uniform(ke);
-    const int len = ke - kb;
-    const int n_full = len / (kKG * kBN);                          // rounds with four full tiles
-    const int n_pref = (len + kKG * kBN - 1) / (kKG * kBN);
-    const int n_tree = (!bad && sp == a.splits - 1) ? (N + kKG * kBN - 1) / (kKG * kBN) : 0;
-    const int n_rounds = n_pref + n_tree;
-
-    const unsigned char* kc = (const unsigned char*)a.k_cache + (((size_t)b * a.Hkv + kvh) * (size_t)a.S_cap + kb) * kRowB;
-    const unsigned char* vc = (const unsigned char*)a.v_cache + (((size_t)b * a.Hkv + kvh) * (size_t)a.S_cap + kb) * kRowB;
-    const unsigned char* kt = (const unsigned char*)a.k_tree + ((size_t)b * N * a.Hkv + kvh) * kRowB;
-    const unsigned char* vt = (const unsigned char*)a.v_tree + ((size_t)b * N * a.Hkv + kvh) * kRowB;
-    const uint32_t tree_stride = (uint32_t)a.Hkv * kRowB;
-    // cache row kb + j of this (sequence, KV head): contiguous, or looked up page by page (a tile
-    // never straddles pages: pages are powers of two >= 64 rows)
-    const int32_t* bt_row = PAGED ? a.block_table + (size_t)b * a.max_blocks : nullptr;
-    auto cache_row = [&](const void* pool, const unsigned char* contiguous, int j) -> const unsigned char* {
-        if constexpr (PAGED) {
-            const int key = uniform(kb + j);
-            const int id = scalar_load_i32(uniform((const unsigned char*)bt_row), (uint32_t)(key >> a.page_shift) * 4u);
-            const size_t row = (((size_t)id * a.Hkv + kvh) << a.page_shift) + (size_t)(key & ((1 << a.page_shift) - 1));
-            return uniform((const unsigned char*)pool + row * kRowB);
+    const int i16 = lane & 15, dhalf = (lane >> 4) & 1;
+    constexpr int kKT = kIs32 ? kD / 8 : kD / 16;             // 16-byte K pieces per row and lane half
+    uint32_t k_off[kKT], v_off[kDB];
+#pragma unroll
+    for (int tt = 0; tt < kKT; ++tt) k_off[tt] = (lane & 31) * kRowB + (((2 * tt + g32) ^ C::k_swz(lane & 31)) << 4);
+#pragma unroll
+    for (int db = 0; db < kDB; ++db) {
+        if constexpr (kIs32) {
+            // element d = 32 db + lane % 32 of row 4 g32 (rows 8 q + 4 g32 + e follow at constant distances)
+            const int d = 32 * db + (lane & 31);
+            v_off[db] = C::kTileKB + 4 * g32 * kRowB + (((d >> 2) ^ (g32 << 3)) << 4) + 4 * (d & 3);
         } else {
-            return uniform(contiguous + (size_t)j * kRowB);
+            const int vrow = 4 * g32 + (i16 >> 2);
+            v_off[db] = C::kTileKB + vrow * kRowB + (((4 * db + 2 * dhalf + ((i16 & 3) >> 1)) ^ C::v_swz(vrow)) << 4) + 8 * (i16 & 1);
+        }
+    }
+    const ptrdiff_t v_minus_k = (const unsigned char*)a.v_cache - (const unsigned char*)a.k_cache;
+    const ptrdiff_t vt_minus_kt = (const unsigned char*)a.v_tree - (const unsigned char*)a.k_tree;
+    const uint32_t tree_stride = (uint32_t)a.Hkv * kRowB;
+
+    const work::Lens lens(a);
+    work::Walk cw = work::walk_first(a, lens, team);      // what is multiplied
+    if (cw.b < 0) return;
+    work::Walk pw = cw;                                   // what is loaded
+    int issued = 0, done = 0;                             // rounds
+
+    // Loads the next round: tile kg of the KG tiles from pw.tile on (a round does not reach past its segment; a group
+    // without a tile in a segment's last round fetches the segment's last tile again, so that every wave has the same
+    // number of loads in flight, and does not compute on it).  Every address is in bounds whatever the inputs hold:
+    // prefix rows lie below the usable length, page ids are clamped to the pool (a sequence with a bad one is
+    // flagged and its result discarded).  Rounds of full prefix tiles take the short way: p_full of them are left in
+    // the segment, this group's next tile at p_k (or, paged, at key p_key).
+    int p_full = 0, p_key = 0;
+    const unsigned char* p_k = nullptr;
+    auto page_addr = [&](int k0) __attribute__((always_inline)) {               // (a tile never straddles pages: pages are powers of two >= 64 rows)
+        int id = scalar_load_i32(uniform((const unsigned char*)(a.block_table + (size_t)pw.b * a.max_blocks)),
+                                 (uint32_t)uniform(k0 >> a.page_shift) * 4u);
+        id = (unsigned)id < (unsigned)a.num_pages ? id : 0;
+        return uniform((const unsigned char*)a.k_cache +
+                       ((((size_t)id * a.Hkv + pw.kvh) << a.page_shift) + (size_t)(k0 & ((1 << a.page_shift) - 1))) * kRowB);
+    };
+    auto cache_addr = [&](int k0) __attribute__((always_inline)) {
+        return uniform((const unsigned char*)a.k_cache + (((size_t)pw.b * a.Hkv + pw.kvh) * (size_t)a.S_cap + k0) * kRowB);
+    };
+    auto begin_segment = [&]() __attribute__((always_inline)) {
+        p_full = uniform(max(0, min(work::usable(a, lens.at(a, pw.b)) / kBN, pw.tile_end) - pw.tile) / kKG);
+        p_key = (pw.tile + kg) * kBN;
+        if constexpr (!PAGED) p_k = cache_addr(p_key);
+    };
+    begin_segment();
+    auto stage_base = [&]() __attribute__((always_inline)) {
+        return __builtin_amdgcn_readfirstlane(lds0 + ((uint32_t)issued % kNR) * C::kRoundB + kg * C::kTileB + rb * kCH * 1024);
+    };
+    auto issue_full = [&]() __attribute__((always_inline)) {
+        const uint32_t sbase = stage_base();
+        const unsigned char* kgp = PAGED ? page_addr(p_key) : uniform(p_k);
+        const unsigned char* vgp = uniform(kgp + v_minus_k);
+#pragma unroll
+        for (int c = 0; c < kCH; ++c) {
+            dma16(kgp, kvo_k[c], sbase + c * 1024);
+            dma16(vgp, kvo_v[c], sbase + c * 1024 + C::kTileKB);
+        }
+        if constexpr (PAGED) p_key += kKG * kBN; else p_k += kKG * kBN * kRowB;
+    };
+    auto end_round = [&]() __attribute__((always_inline)) {
+        if (pw.tile >= pw.tile_end) {
+            pw = work::walk_next(a, lens, pw);
+            if (pw.b >= 0) begin_segment();
         }
     };
-    const ptrdiff_t v_minus_k = (const unsigned char*)a.v_cache - (const unsigned char*)a.k_cache;
-
-    // ---- direct-to-LDS loads: the two waves of key group kg load tile kg of every round, four
-    // 1 KB instructions each for K and for V (instruction ii covers rows 4 ii .. 4 ii + 3).
-    uint32_t kvo_k[4], kvo_v[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const int row = 4 * (rb * 4 + c) + (lane >> 4), pc = lane & 15;
-        kvo_k[c] = row * kRowB + ((pc ^ (row & 15)) << 4);
-        kvo_v[c] = row * kRowB + ((pc ^ ((row & 3) << 2)) << 4);
-    }
-    auto issue_round = [&](int r) {
-        const uint32_t sbase = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(r & 1) * kRoundB + kg * kTileB + rb * 4096);
-        if (r < n_full) {
-            const unsigned char* kgp = cache_row(a.k_cache, kc, (r * kKG + kg) * kBN);
-            const unsigned char* vgp = PAGED ? kgp + v_minus_k : cache_row(a.v_cache, vc, (r * kKG + kg) * kBN);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                dma16(kgp, kvo_k[c], sbase + c * 1024);
-                dma16(vgp, kvo_v[c], sbase + c * 1024 + kTileKB);
-            }
+    auto issue_round = [&]() __attribute__((always_inline)) {
+        if (p_full > 0) {
+            issue_full();
+            --p_full;
         } else {
-            const bool tree = r >= n_pref;
-            const int k0 = (tree ? r - n_pref : r) * kKG * kBN + kg * kBN;     // first row of this tile
-            const int klast = max((tree ? N : len) - 1, 0);
-            // rows are addressed relative to the tile's first row (or to the last valid row, if the
-            // tile starts beyond it), which for the prefix fixes the page
-            const int kq = min(k0, klast);
-            const unsigned char* kgp = tree ? uniform(kt + (size_t)kq * tree_stride) : cache_row(a.k_cache, kc, kq);
-            const unsigned char* vgp = tree ? uniform(vt + (size_t)kq * tree_stride)
-                                            : (PAGED ? kgp + v_minus_k : cache_row(a.v_cache, vc, kq));
+            const int P = work::usable(a, lens.at(a, pw.b)), u_pref = (P + kBN - 1) / kBN;
+            const uint32_t sbase = stage_base();
+            const int t = uniform(min(pw.tile + kg, pw.tile_end - 1));
+            const bool tree = t >= u_pref;
+            const int k0 = (tree ? t - u_pref : t) * kBN;
+            const unsigned char* kgp;
+            if (tree) kgp = uniform((const unsigned char*)a.k_tree + (((size_t)pw.b * N + k0) * a.Hkv + pw.kvh) * kRowB);
+            else kgp = PAGED ? page_addr(k0) : cache_addr(k0);
+            kgp = uniform(kgp);
+            const unsigned char* vgp = uniform(kgp + (tree ? vt_minus_kt : v_minus_k));
+            const int last = (tree ? N : P) - 1 - k0;                      // >= 0: last valid row of the tile
             const uint32_t rstride = tree ? tree_stride : (uint32_t)kRowB;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int row = 4 * (rb * 4 + c) + (lane >> 4), pc = lane & 15;
-                const uint32_t roff = (uint32_t)(min(k0 + row, klast) - kq) * rstride;   // clamped: in bounds, masked later
-                dma16(kgp, roff + ((pc ^ (row & 15)) << 4), sbase + c * 1024);
-                dma16(vgp, roff + ((pc ^ ((row & 3) << 2)) << 4), sbase + c * 1024 + kTileKB);
+            for (int c = 0; c < kCH; ++c) {
+                const int row = kRPI * (rb * kCH + c) + lane / kLPR, pc = lane % kLPR;
+                const uint32_t roff = (uint32_t)min(row, last) * rstride;
+                dma16(kgp, roff + ((pc ^ C::k_swz(row)) << 4), sbase + c * 1024);
+                dma16(vgp, roff + ((pc ^ C::v_swz(row)) << 4), sbase + c * 1024 + C::kTileKB);
             }
         }
+        ++issued;
+        pw.tile += kKG;
+        end_round();
     };
-
-    // Round 0 starts streaming now; the Q fragments are requested right behind it and the
-    // ancestor masks are built while both are in flight.  (The direct-to-LDS loads are invisible
-    // to the compiler; loads it does know about may follow them, since completion is in order and
-    // its waits then only become stricter.)
-    if (n_rounds > 0) issue_round(0);
-
-    // ---- this lane's query row
-    const int g32 = lane >> 5;
-    const int rq = rb * 32 + (lane & 31);
-    const bool rvalid = rq < M;
-    const int node = rvalid ? rq / G : 0;
-    const int head = kvh * G + (rvalid ? rq % G : 0);
-    bf16x8 qf[8];
-    {
-        const bf16_t* qrow = (const bf16_t*)a.q + (((size_t)b * N + node) * a.Hq + head) * kD + g32 * 8;
+    // The first rounds start streaming now; what a segment needs besides K and V is requested behind them.  (The
+    // direct-to-LDS loads are invisible to the compiler; loads it does know about may follow them, since completion
+    // is in order and its waits then only become stricter.)
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            uint4 raw = make_uint4(0, 0, 0, 0);
-            if (rvalid) raw = *(const uint4*)(qrow + 16 * t);
-            qf[t] = __builtin_bit_cast(bf16x8, raw);
-        }
-    }
+    for (int r = 0; r < kNR - 1; ++r)
+        if (pw.b >= 0) issue_round();
 
-    for (int i = tid; i < N && !bad; i += kThreads) {
-        const int tid_ = i;
-        uint32_t m[4] = {0, 0, 0, 0};
-        for (int j = tid_; j >= 0; j = spar[j]) m[j >> 5] |= 1u << (j & 31);
-        anc[tid_ * 4 + 0] = m[0]; anc[tid_ * 4 + 1] = m[1]; anc[tid_ * 4 + 2] = m[2]; anc[tid_ * 4 + 3] = m[3];
-    }
-    __syncthreads();
+    int b_known = -1, bad_seq = 0;
+    for (; cw.b >= 0; cw = work::walk_next(a, lens, cw)) {
+        const int b = cw.b, kvh = cw.kvh;
+        const int P = work::usable(a, lens.at(a, b)), u_pref = (P + kBN - 1) / kBN;
+        const int t_end = uniform(cw.tile_end);
 
-    // ancestor words of this row, pre-shifted for this half of the wave; tree round i of key group kg
-    // covers nodes 32 (i KG + kg) ..
-    uint32_t amask[4] = {0, 0, 0, 0};
-    if (rvalid && !bad) {
-#pragma unroll
-        for (int w = 0; w < 4; ++w) amask[w] = anc[node * 4 + w] >> (4 * g32);
-    }
-
-    // per-lane LDS byte offsets inside a tile
-    const int i16 = lane & 15, dhalf = (lane >> 4) & 1;
-    uint32_t k_off[8], v_off[4];
-#pragma unroll
-    for (int tt = 0; tt < 8; ++tt) k_off[tt] = (lane & 31) * kRowB + (((2 * tt + g32) ^ i16) << 4);
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-        v_off[db] = kTileKB + (4 * g32 + (i16 >> 2)) * kRowB +
-                    ((((db ^ (i16 >> 2)) << 2) + 2 * dhalf + ((i16 & 3) >> 1)) << 4) + 8 * (i16 & 1);
-
-    f32x16 o[4];
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) o[db][j] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;
-
-    // one 32-key tile: S^T = K Q^T, (mask,) online softmax, O^T += V^T P^T
-    // MODE kPlain: all 32 keys valid; kTail: keys >= nvalid masked (nvalid may be <= 0); kTree: ancestor mask
-    auto tile = [&](auto mode_tag, int r, int nvalid) {
-        constexpr int MODE = decltype(mode_tag)::value;
-        const lds_u8* stage = (const lds_u8*)smem + (r & 1) * kRoundB + kg * kTileB;
-        f32x16 s;
+        // ---- this lane's query row
+        const int rq = (mt * kRBW + rb) * 32 + (lane & 31);
+        const bool rvalid = rq < M;
+        const int node = rvalid ? rq / G : 0;
+        const int head = kvh * G + (rvalid ? rq - node * G : 0);
+        uint4 qf[kKT];           // 16-bit: elements 16 t + 8 g32 .. + 7; fp32: elements 8 t + 4 g32 .. + 3
         {
-            bf16x8 kf[8];
+            const unsigned char* qrow = (const unsigned char*)a.q + ((((size_t)b * N + node) * a.Hq + head) * kD) * C::kEs + g32 * 16;
 #pragma unroll
-            for (int tt = 0; tt < 8; ++tt) kf[tt] = *(const lds_bf16x8*)(stage + k_off[tt]);
-            f32x16 s1;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) { s[j] = 0.f; s1[j] = 0.f; }
-#pragma unroll
-            for (int tt = 0; tt < 8; tt += 2) {        // two chains over the head dimension, summed below
-                s = mma32<F16>(kf[tt], qf[tt], s);
-                s1 = mma32<F16>(kf[tt + 1], qf[tt + 1], s1);
+            for (int t = 0; t < kKT; ++t) {
+                qf[t] = make_uint4(0, 0, 0, 0);
+                if (rvalid) qf[t] = *(const uint4*)(qrow + 32 * t);
             }
-#pragma unroll
-            for (int j = 0; j < 16; ++j) s[j] += s1[j];
         }
-        // register j is key 8 (j/4) + 4 g32 + (j%4) of the tile
-        if constexpr (MODE == kTree) {
-            const int w = (r - n_pref) * kKG + kg;             // 32-node word of this tile (< 4 since N <= 128)
-            const uint32_t tree_word = (w == 0 ? amask[0] : w == 1 ? amask[1] : w == 2 ? amask[2] : amask[3]);
-#pragma unroll
-            for (int j = 0; j < 16; ++j)
-                if (!((tree_word >> ((j >> 2) * 8 + (j & 3))) & 1u)) s[j] = -INFINITY;
-        } else if constexpr (MODE == kTail) {
-#pragma unroll
-            for (int j = 0; j < 16; ++j)
-                if ((j >> 2) * 8 + 4 * g32 + (j & 3) >= nvalid) s[j] = -INFINITY;
+        // ---- another sequence: validate it; build its ancestor-or-self masks
+        if (b != b_known) {
+            b_known = b;
+            int bad_tree = 0;
+            for (int i = tid; i < N; i += kThreads) {
+                const int p = a.parent[(size_t)b * N + i];
+                spar[i] = p;
+                bad_tree |= (p < -1 || p >= i);
+            }
+            bad_tree = __syncthreads_or(bad_tree);
+            int bad_len = P != lens.at(a, b);
+            if constexpr (PAGED) {
+                // every page the prefix touches must be a page of the pool (each workgroup checks them all, so all
+                // workgroups of the sequence agree)
+                int bad_page = 0;
+                for (int i = tid; i < ((P + (1 << a.page_shift) - 1) >> a.page_shift); i += kThreads) {
+                    const int id = a.block_table[(size_t)b * a.max_blocks + i];
+                    bad_page |= (id < 0 || id >= a.num_pages);
+                }
+                bad_len |= __syncthreads_or(bad_page);
+            }
+            if (a.status && tid == 0 && cw.tile == 0 && kvh == 0 && mt == 0)
+                a.status[b] = (bad_tree ? S4C_SEQ_BAD_TREE : 0) | (bad_len ? S4C_SEQ_BAD_LEN : 0);
+            bad_seq = __builtin_amdgcn_readfirstlane((bad_tree || bad_len) ? 1 : 0);
+            for (int i = tid; i < N && !bad_tree; i += kThreads) {
+                uint32_t m[4] = {0, 0, 0, 0};
+                for (int j = i; j >= 0; j = spar[j]) m[j >> 5] |= 1u << (j & 31);
+                *(uint4*)(anc + i * 4) = make_uint4(m[0], m[1], m[2], m[3]);
+            }
+            __syncthreads();
         }
-        float mx = s[0];
+        const bool bad = bad_seq != 0;
+        // ancestor words of this row, pre-shifted for this half of the wave
+        uint32_t amask[4] = {0, 0, 0, 0};
+        if (rvalid && !bad) {
 #pragma unroll
-        for (int j = 1; j < 16; j += 2) mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[j]), s[(j + 1) & 15]);
-        mx = max_across_halves(mx);
-        const float m_new = fmaxf(m_run, mx * a.scale_log2);
-        float m_safe = m_new;
-        if constexpr (MODE != kPlain) m_safe = (m_new == -INFINITY) ? 0.f : m_new;   // nothing visible yet
-        const float alpha = fast_exp2(m_run - m_safe);
-        float psum = 0.f;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const float p = fast_exp2(fmaf(s[j], a.scale_log2, -m_safe));
-            s[j] = p;
-            psum += p;
+            for (int q = 0; q < 4; ++q) amask[q] = anc[node * 4 + q] >> (4 * g32);
         }
-        l_run = l_run * alpha + psum;
-        if (__any(m_new > m_run)) {
-#pragma unroll
-            for (int db = 0; db < 4; ++db)
-#pragma unroll
-                for (int j = 0; j < 16; ++j) o[db][j] *= alpha;
-        }
-        m_run = m_new;
 
-        bf16x8 pb[2];
+        f32x16 o[kDB];
 #pragma unroll
-        for (int st = 0; st < 2; ++st)
-            pb[st] = round8<F16>(s, 8 * st);
-        auto vfrag = [&](const lds_u8* p) {
-            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
-            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 8 * kRowB));
-            return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+        for (int db = 0; db < kDB; ++db)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) o[db][j] = 0.f;
+        float m_run = -INFINITY, l_run = 0.f;
+
+        // one 32-key tile: S^T = K Q^T, (mask,) online softmax, O^T += V^T P^T
+        // masked: bit 8 (j/4) + j%4 of `visible` tells whether register j's key counts for this lane's row
+        auto tile = [&](auto masked_tag, uint32_t visible) __attribute__((always_inline)) {
+            constexpr bool MASKED = decltype(masked_tag)::value;
+            const lds_u8* stage = (const lds_u8*)smem + ((uint32_t)done % kNR) * C::kRoundB + kg * C::kTileB;
+            f32x16 s;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) s[j] = 0.f;
+            if constexpr (kIs32) {
+                typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+#pragma unroll
+                for (int t0 = 0; t0 < kKT; t0 += 8) {
+                    f32x4 kf[8];
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) kf[t] = *(const lds_f32x4*)(stage + k_off[t0 + t]);
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) {
+                        const f32x4 q4 = __builtin_bit_cast(f32x4, qf[t0 + t]);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[t][e], q4[e], s, 0, 0, 0);
+                    }
+                }
+            } else {
+                bf16x8 kf[kKT];
+#pragma unroll
+                for (int tt = 0; tt < kKT; ++tt) kf[tt] = *(const lds_bf16x8*)(stage + k_off[tt]);
+                f32x16 s1;
+#pragma unroll
+                for (int j = 0; j < 16; ++j) s1[j] = 0.f;
+#pragma unroll
+                for (int tt = 0; tt < kKT; tt += 2) {        // two chains over the head dimension, summed below
+                    s = mma32<F16>(kf[tt], __builtin_bit_cast(bf16x8, qf[tt]), s);
+                    s1 = mma32<F16>(kf[tt + 1], __builtin_bit_cast(bf16x8, qf[tt + 1]), s1);
+                }
+#pragma unroll
+                for (int j = 0; j < 16; ++j) s[j] += s1[j];
+            }
+            if constexpr (MASKED) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j)
+                    if (!((visible >> ((j >> 2) * 8 + (j & 3))) & 1u)) s[j] = -INFINITY;
+            }
+            float mx = s[0];
+#pragma unroll
+            for (int j = 1; j < 16; j += 2) mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[j]), s[(j + 1) & 15]);
+            mx = max_across_halves(mx) * a.scale_log2;
+            // The reference maximum moves only when some row of the wave outgrew it by more than 2^kLazyLog2 (always
+            // at its first visible key); until then exponentials are taken against the stale reference, which the
+            // final division does not notice, and the accumulator is not touched.
+            if (__any(mx > m_run + kLazyLog2)) {
+                const float m_new = fmaxf(m_run, mx);
+                float alpha = fast_exp2(m_run - m_new);                      // first tile: exp2(-inf) = 0
+                if constexpr (MASKED) alpha = (m_new == -INFINITY) ? 1.f : alpha;
+                l_run *= alpha;
+#pragma unroll
+                for (int db = 0; db < kDB; ++db)
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) o[db][j] *= alpha;
+                m_run = m_new;
+            }
+            float m_ref = m_run;
+            if constexpr (MASKED) m_ref = (m_run == -INFINITY) ? 0.f : m_run;     // nothing visible yet: all terms are 0
+            float psum = 0.f;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const float p = fast_exp2(fmaf(s[j], a.scale_log2, -m_ref));
+                s[j] = p;
+                psum += p;
+            }
+            l_run += psum;
+
+            if constexpr (kIs32) {
+                typedef __attribute__((address_space(3))) float lds_f32;
+#pragma unroll
+                for (int jq = 0; jq < 4; ++jq)
+#pragma unroll
+                    for (int db = 0; db < kDB; ++db) {
+                        float vf[4];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) vf[e] = *(const lds_f32*)(stage + v_off[db] + (8 * jq + e) * kRowB);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[e], s[4 * jq + e], o[db], 0, 0, 0);
+                    }
+            } else {
+                bf16x8 pb[2];
+#pragma unroll
+                for (int st = 0; st < 2; ++st) pb[st] = round8<F16>(s, 8 * st);
+                auto vfrag = [&](const lds_u8* p) __attribute__((always_inline)) {
+                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 8 * kRowB));
+                    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                };
+                bf16x8 vf[2][kDB];
+#pragma unroll
+                for (int st = 0; st < 2; ++st)
+#pragma unroll
+                    for (int db = 0; db < kDB; ++db) vf[st][db] = vfrag(stage + st * 16 * kRowB + v_off[db]);
+#pragma unroll
+                for (int st = 0; st < 2; ++st)
+#pragma unroll
+                    for (int db = 0; db < kDB; ++db) o[db] = mma32<F16>(vf[st][db], pb[st], o[db]);
+            }
         };
-        bf16x8 vf[2][4];
-#pragma unroll
-        for (int st = 0; st < 2; ++st)
-#pragma unroll
-            for (int db = 0; db < 4; ++db) vf[st][db] = vfrag(stage + st * 16 * kRowB + v_off[db]);
-#pragma unroll
-        for (int st = 0; st < 2; ++st)
-#pragma unroll
-            for (int db = 0; db < 4; ++db)
-                o[db] = mma32<F16>(vf[st][db], pb[st], o[db]);
-    };
 
-    // ---- round pipeline: round r+1 is in flight while round r is consumed
-    // Settle the compiler-visible loads (Q) here, so that it places no vmcnt wait of its own inside
-    // the round loop (which would also wait for the round just issued).
-    wait_vmcnt<0>();
+        // ---- round pipeline.  Settle the Q fragments here, so that the compiler places no vmcnt wait of its own
+        // inside the round loop (which would also wait for the rounds just issued).
 #pragma unroll
-    for (int t = 0; t < 8; ++t) asm volatile("" : "+v"(qf[t]));
-    auto sync_and_prefetch = [&](int r) {
-        wait_vmcnt<0>();           // this wave's share of round r has landed
-        __syncthreads();           // everybody's has; round r-1's half of the ring is free
-        if (r + 1 < n_rounds) issue_round(r + 1);
-    };
-    int r = 0;
-    for (; r < n_full; ++r) {
-        sync_and_prefetch(r);
-        tile(std::integral_constant<int, kPlain>{}, r, kBN);
-    }
-    for (; r < n_pref; ++r) {
-        sync_and_prefetch(r);
-        tile(std::integral_constant<int, kTail>{}, r, len - (r * kKG + kg) * kBN);
-    }
-    for (; r < n_rounds; ++r) {
-        sync_and_prefetch(r);
-        tile(std::integral_constant<int, kTree>{}, r, 0);
-    }
+        for (int t = 0; t < kKT; ++t) asm volatile("" : "+v"(qf[t].x), "+v"(qf[t].y), "+v"(qf[t].z), "+v"(qf[t].w));
+        auto sync_and_prefetch = [&]() __attribute__((always_inline)) {
+            // this wave's share of round `done` has landed once at most NR - 2 younger rounds are outstanding
+            if (kNR > 2 && issued - done == kNR - 1) wait_vmcnt<2 * kCH * (kNR - 2)>(); else wait_vmcnt<0>();
+            __syncthreads();           // everybody's has; the round before it is no longer read
+            if (pw.b >= 0) issue_round();
+        };
+        int t = uniform(cw.tile);
+        // While the loads run ahead inside this segment's full prefix tiles, nothing has to be decided per round.
+        if (uniform(pw.b) == uniform(b) && uniform(pw.kvh) == uniform(kvh)) {
+            const int n = uniform(p_full);
+            for (int i = 0; i < n; ++i, ++done) {
+                wait_vmcnt<2 * kCH * (kNR - 2)>();
+                __syncthreads();
+                issue_full();
+                ++issued;
+                tile(std::integral_constant<bool, false>{}, 0u);
+            }
+            t += n * kKG;
+            pw.tile += n * kKG;
+            p_full = 0;
+            end_round();
+        }
+        for (const int e = min(P / kBN, t_end) - kKG; t <= e; t += kKG, ++done) {
+            sync_and_prefetch();
+            tile(std::integral_constant<bool, false>{}, 0u);
+        }
+        for (; t < t_end; t += kKG, ++done) {
+            sync_and_prefetch();
+            const int my = t + kg;
+            if (my >= t_end) continue;
+            uint32_t visible;
+            if (my >= u_pref) {
+                const int word = my - u_pref;                            // 32-node word of this tile (< 4 since N <= 128)
+                visible = (word == 0 ? amask[0] : word == 1 ? amask[1] : word == 2 ? amask[2] : amask[3]);
+            } else {
+                const int nvalid = P - my * kBN;                         // the ragged last prefix tile: 1 .. 31 keys
+                visible = (nvalid >= kBN ? 0xFFFFFFFFu : (1u << nvalid) - 1u) >> (4 * g32);
+            }
+            tile(std::integral_constant<bool, true>{}, visible);
+        }
 
-    // ---- merge the four key groups of each row through LDS (the ring is no longer read)
-    const float l_tot = l_run + __shfl_xor(l_run, 32);
-    __syncthreads();
-    float* mo = (float*)smem;                                       // [waves][32 rows][kD + 4]
-    float* mml = (float*)(smem + kWaves * 32 * kMergeRowB);         // [waves][32 rows][2]
-    {
-        float* orow = mo + ((size_t)wave * 32 + (lane & 31)) * (kMergeRowB / 4) + 4 * g32;
+        // ---- merge the key groups of each row into key group 0, one 32-column block at a time
+        float l_tot = bad ? 0.f : l_run + __shfl_xor(l_run, 32);              // a flagged sequence: zero output
+        float* mo = (float*)(smem + C::kRingB + kAuxB);                       // [KG-1][RBW][32 rows][kMergeRow]
+        float* mml = mo + (kKG - 1) * kRBW * 32 * C::kMergeRow;               // [KG-1][RBW][32 rows][2]
+        const int mslot = ((kg - 1) * kRBW + rb) * 32 + (lane & 31);          // (kg > 0)
+        if (kg > 0 && g32 == 0) *(float2*)(mml + mslot * 2) = make_float2(m_run, l_tot);
+        float wg[kKG];                                                        // weights of the groups (kg == 0)
 #pragma unroll
-        for (int db = 0; db < 4; ++db)
+        for (int db = 0; db < kDB; ++db) {
+            if (kg > 0) {
 #pragma unroll
-            for (int jq = 0; jq < 4; ++jq)
-                *(float4*)(orow + 32 * db + 8 * jq) =
-                    make_float4(o[db][4 * jq], o[db][4 * jq + 1], o[db][4 * jq + 2], o[db][4 * jq + 3]);
-        if (g32 == 0) {
-            mml[(wave * 32 + lane) * 2] = m_run;
-            mml[(wave * 32 + lane) * 2 + 1] = l_tot;
+                for (int jq = 0; jq < 4; ++jq)
+                    *(float4*)(mo + mslot * C::kMergeRow + 8 * jq + 4 * g32) =
+                        make_float4(o[db][4 * jq], o[db][4 * jq + 1], o[db][4 * jq + 2], o[db][4 * jq + 3]);
+            }
+            __syncthreads();
+            if (kg == 0) {
+                if (db == 0) {
+                    float m_max = l_tot > 0.f ? m_run : -INFINITY, mg[kKG], lg[kKG];
+                    mg[0] = m_run;
+                    lg[0] = l_tot;
+#pragma unroll
+                    for (int g = 1; g < kKG; ++g) {
+                        const float2 ml = *(const float2*)(mml + (((g - 1) * kRBW + rb) * 32 + (lane & 31)) * 2);
+                        mg[g] = ml.x;
+                        lg[g] = ml.y;
+                        m_max = fmaxf(m_max, lg[g] > 0.f ? mg[g] : -INFINITY);
+                    }
+                    l_tot = 0.f;
+#pragma unroll
+                    for (int g = 0; g < kKG; ++g) {
+                        wg[g] = lg[g] > 0.f ? fast_exp2(mg[g] - m_max) : 0.f;     // 0: this key group saw nothing visible
+                        l_tot = fmaf(lg[g], wg[g], l_tot);
+                    }
+                    m_run = m_max;
+                }
+#pragma unroll
+                for (int j = 0; j < 16; ++j) o[db][j] *= wg[0];
+#pragma unroll
+                for (int g = 1; g < kKG; ++g)
+#pragma unroll
+                    for (int jq = 0; jq < 4; ++jq) {
+                        const float4 v = *(const float4*)(mo + (((g - 1) * kRBW + rb) * 32 + (lane & 31)) * C::kMergeRow + 8 * jq + 4 * g32);
+                        o[db][4 * jq] = fmaf(v.x, wg[g], o[db][4 * jq]);
+                        o[db][4 * jq + 1] = fmaf(v.y, wg[g], o[db][4 * jq + 1]);
+                        o[db][4 * jq + 2] = fmaf(v.z, wg[g], o[db][4 * jq + 2]);
+                        o[db][4 * jq + 3] = fmaf(v.w, wg[g], o[db][4 * jq + 3]);
+                    }
+            }
+            if (db + 1 < kDB) __syncthreads();
         }
-    }
-    __syncthreads();
-    // thread -> (row, 16 output columns): 8 threads cover a row with 32-byte pieces
-    constexpr int kTPR = kThreads / 64;          // threads per output row
-    constexpr int kCols = kD / kTPR;              // output columns per thread (16 or 32)
-    const int row = tid / kTPR, dcol = (tid % kTPR) * kCols;
-    if (row >= M && a.splits == 1) return;
-    const int orb = row >> 5, oq = row & 31;
-    float mg[kKG], lg[kKG], mmax = -INFINITY;
+        if (!a.whole && mt == 0 && tid == 0) work::note_parts(a, team, cw);
+        // ---- key group 0 writes the row: d = 32 db + 8 (j/4) + 4 g32 + (j%4)
+        if (kg == 0 && rvalid) {
+            if (work::walk_is_whole(cw)) {
+                const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
+                const size_t o0 = (((size_t)b * N + node) * a.Hq + head) * kD + 4 * g32;
 #pragma unroll
-    for (int g = 0; g < kKG; ++g) {
-        const int w = g * 2 + orb;
-        mg[g] = mml[(w * 32 + oq) * 2];
-        lg[g] = mml[(w * 32 + oq) * 2 + 1];
-        mmax = fmaxf(mmax, mg[g]);
-    }
-    float acc[kCols], l = 0.f;
+                for (int db = 0; db < kDB; ++db)
 #pragma unroll
-    for (int e = 0; e < kCols; ++e) acc[e] = 0.f;
+                    for (int jq = 0; jq < 4; ++jq) {
+                        const float v0 = o[db][4 * jq] * inv, v1 = o[db][4 * jq + 1] * inv, v2 = o[db][4 * jq + 2] * inv,
+                                    v3 = o[db][4 * jq + 3] * inv;
+                        if constexpr (kIs32) *(float4*)((float*)a.out + o0 + 32 * db + 8 * jq) = make_float4(v0, v1, v2, v3);
+                        else *(uint2*)((bf16_t*)a.out + o0 + 32 * db + 8 * jq) =
+                                 make_uint2(round1<F16>(v0) | (round1<F16>(v1) << 16), round1<F16>(v2) | (round1<F16>(v3) << 16));
+                    }
+            } else {
+                const size_t prow = work::part_row(a, team, cw.tile == 0 ? 1 : 0) + rq;
+                float* orow = a.ws_o + prow * kD + 4 * g32;
 #pragma unroll
-    for (int g = 0; g < kKG; ++g) {
-        if (lg[g] <= 0.f) continue;                 // this key group saw nothing visible
-        const float wgt = fast_exp2(mg[g] - mmax);
-        l += lg[g] * wgt;
-        const float* src = mo + ((size_t)(g * 2 + orb) * 32 + oq) * (kMergeRowB / 4) + dcol;
+                for (int db = 0; db < kDB; ++db)
 #pragma unroll
-        for (int e = 0; e < kCols; e += 4) {
-            const float4 v = *(const float4*)(src + e);
-            acc[e] = fmaf(v.x, wgt, acc[e]); acc[e + 1] = fmaf(v.y, wgt, acc[e + 1]);
-            acc[e + 2] = fmaf(v.z, wgt, acc[e + 2]); acc[e + 3] = fmaf(v.w, wgt, acc[e + 3]);
-        }
-    }
-    if (a.splits == 1) {
-        const int onode = row / G, ohead = kvh * G + row % G;
-        const float inv = (l > 0.f) ? 1.f / l : 0.f;
-        uint4* dst = (uint4*)((bf16_t*)a.out + (((size_t)b * N + onode) * a.Hq + ohead) * kD + dcol);
-#pragma unroll
-        for (int e = 0; e < kCols; e += 8) {
-            uint32_t pk[4];
-#pragma unroll
-            for (int h = 0; h < 4; ++h)
-                pk[h] = round1<F16>(acc[e + 2 * h] * inv) | (round1<F16>(acc[e + 2 * h + 1] * inv) << 16);
-            dst[e / 8] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
-        }
-    } else {
-        if (row < M) {
-            const size_t prow = (((size_t)b * a.Hkv + kvh) * a.splits + sp) * M + row;
-            float4* dst = (float4*)(a.ws_o + prow * kD + dcol);
-#pragma unroll
-            for (int e = 0; e < kCols / 4; ++e) dst[e] = make_float4(acc[4 * e], acc[4 * e + 1], acc[4 * e + 2], acc[4 * e + 3]);
-            if (tid % kTPR == 0) {
-                a.ws_ml[prow * 2] = mmax;
-                a.ws_ml[prow * 2 + 1] = l;
+                    for (int jq = 0; jq < 4; ++jq)
+                        *(float4*)(orow + 32 * db + 8 * jq) =
+                            make_float4(o[db][4 * jq], o[db][4 * jq + 1], o[db][4 * jq + 2], o[db][4 * jq + 3]);
+                if (g32 == 0) *(float2*)(a.ws_ml + prow * 2) = make_float2(m_run, l_tot);
             }
         }
     }
+}
+
+template <class C, bool PAGED>
+hipError_t launch(const AttnArgs& a, hipStream_t st) {
+    static std::atomic<uint64_t> lds_set{0};
+    const hipError_t ea = ensure_dynamic_lds((const void*)tree_attn_smallm_kernel<C, PAGED>, C::kLdsBytes, lds_set);
+    if (ea != hipSuccess) return ea;
+    const long teams8 = ((long)a.teams + 7) / 8 * 8;
+    dim3 grid((unsigned)(teams8 * a.mtiles)), block(C::kThreads);
+    hipLaunchKernelGGL((tree_attn_smallm_kernel<C, PAGED>), grid, block, C::kLdsBytes, st, a);
+    return hipGetLastError();
+}
+
+// The configuration for an element type, head size and row count, handed to `use` as a type.  Up to 32 rows: one
+// row block, four key groups, so that no wave works on rows that do not exist.
+template <Elem E, class Use>
+auto with_cfg(int D, int M, Use use) {
+    if constexpr (E == kF32) {
+        if (D == 64) return M <= 32 ? use(Cfg<E, 64, 4, 1, 2>{}) : use(Cfg<E, 64, 2, 2, 2>{});
+        return use(Cfg<E, 128, 2, 2, 2>{});          // (four key groups of 32 KB tiles would not fit twice)
+    } else {
+        if (D == 64) return M <= 32 ? use(Cfg<E, 64, 4, 1, 2>{}) : use(Cfg<E, 64, 2, 2, 4>{});
+        return M <= 32 ? use(Cfg<E, 128, 4, 1, 2>{}) : use(Cfg<E, 128, 2, 2, 2>{});
+    }
+}
+template <class Use>
+auto with_cfg(int dtype, int D, int M, Use use) {
+    if (dtype == S4C_F32) return with_cfg<kF32>(D, M, use);
+    return dtype == S4C_F16 ? with_cfg<kH16>(D, M, use) : with_cfg<kB16>(D, M, use);
 }
 
 }  // namespace
 
-template <int KG, bool PAGED, bool F16>
-static hipError_t launch_smallm(const AttnArgs& a, hipStream_t st) {
-    static std::atomic<uint64_t> lds_set{0};
-    const hipError_t ea = ensure_dynamic_lds((const void*)tree_attn_smallm_kernel<KG, PAGED, F16>, Cfg<KG>::kLdsBytes, lds_set);
-    if (ea != hipSuccess) return ea;
-    const long units8 = ((long)a.B * a.Hkv + 7) / 8 * 8;
-    dim3 grid((unsigned)(units8 * a.splits)), block(Cfg<KG>::kThreads);
-    hipLaunchKernelGGL((tree_attn_smallm_kernel<KG, PAGED, F16>), grid, block, Cfg<KG>::kLdsBytes, st, a);
-    return hipGetLastError();
+AttnTile attn_tile_small(const s4c_attn_shape& s) {
+    return with_cfg(s.dtype, s.D, s.N * (s.Hq / s.Hkv), [](auto c) {
+        typedef decltype(c) C;
+        return AttnTile{32 * C::kRBW, kBN, C::kPerCu};
+    });
 }
 
-hipError_t launch_tree_attn_smallm(const AttnArgs& a, int dtype, hipStream_t st) {
-    if (dtype == S4C_F16) return a.block_table ? launch_smallm<2, true, true>(a, st) : launch_smallm<2, false, true>(a, st);
-    return a.block_table ? launch_smallm<2, true, false>(a, st) : launch_smallm<2, false, false>(a, st);
+hipError_t launch_tree_attn_small(const AttnArgs& a, int dtype, hipStream_t st) {
+    return with_cfg(dtype, a.D, a.M, [&](auto c) {
+        typedef decltype(c) C;
+        return a.block_table ? launch<C, true>(a, st) : launch<C, false>(a, st);
+    });
 }
 
 }  // namespace s4c
