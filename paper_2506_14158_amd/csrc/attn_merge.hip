@@ -2,8 +2,8 @@
 // (attn_work.h): out = sum_p 2^(m_p - m) O_p / sum_p 2^(m_p - m) l_p, parts in tile order => deterministic.
 //
 // A workgroup takes a chunk of query rows of one unit and leaves at once if the unit was not divided.  32 lanes per
-// row (D = 128: one float4 each, D = 64: float2), the loads of up to four parts in flight together: the kernel is a few
-// microseconds of latency, not of work.
+// row (D = 128: one float4 each, D = 64: float2); every part's statistics and the first eight parts' outputs are in
+// flight together: the kernel is a few microseconds of latency, not of work.
 #include "attn_work.h"
 
 namespace s4c {
@@ -11,7 +11,7 @@ namespace s4c {
 namespace {
 
 constexpr int kRows = 8;            // rows per workgroup and pass
-constexpr int kBatch = 4;           // parts whose loads are in flight together
+constexpr int kBatch = 8;           // partial outputs in flight together
 
 template <typename T, int D>
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a, int passes) {
@@ -22,40 +22,48 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a, int passes)
     if (g0 == g1) return;                                        // written by its one team already
     for (int pass = 0; pass < passes; ++pass) {
         const int r = (blockIdx.y * passes + pass) * kRows + (threadIdx.x >> 5);
-        if (r >= a.M) return;
+        if (r >= a.M) return;                                    // (all 32 lanes of a row together)
         float m = -INFINITY, l = 0.f, o[VW];
 #pragma unroll
         for (int j = 0; j < VW; ++j) o[j] = 0.f;
-        for (int g = g0; g <= g1; g += kBatch) {
-            float ms[kBatch], ls[kBatch], v[kBatch][VW];
+        for (int gb = g0; gb <= g1; gb += 32) {                  // (more than 32 parts only if a sequence is much the longest)
+            const int n = min(32, g1 + 1 - gb);
+            auto part = [&](int p) { return work::part_row(a, gb + p, gb + p == g0 ? 1 : 0) + r; };
+            // lane p of the row holds part p's maximum and sum; the first outputs are requested with them
+            const float2 ml = sub < n ? *(const float2*)(a.ws_ml + part(sub) * 2) : make_float2(-INFINITY, 0.f);
+            float v[kBatch][VW];
+            auto fetch = [&](int p0) {
 #pragma unroll
-            for (int p = 0; p < kBatch; ++p) {
-                ms[p] = ls[p] = 0.f;
-                if (g + p <= g1) {
-                    const size_t prow = work::part_row(a, g + p, g + p == g0 ? 1 : 0) + r;
-                    ms[p] = a.ws_ml[prow * 2];
-                    ls[p] = a.ws_ml[prow * 2 + 1];
+                for (int p = 0; p < kBatch; ++p)
+                    if (p0 + p < n) {
 #pragma unroll
-                    for (int j = 0; j < VW; ++j) v[p][j] = a.ws_o[prow * D + sub * VW + j];
-                }
-            }
-            float mb = m;
+                        for (int j = 0; j < VW; ++j) v[p][j] = a.ws_o[part(p0 + p) * D + sub * VW + j];
+                    }
+            };
+            fetch(0);
+            float mb = ml.y > 0.f ? ml.x : -INFINITY;
 #pragma unroll
-            for (int p = 0; p < kBatch; ++p) mb = fmaxf(mb, ls[p] > 0.f ? ms[p] : -INFINITY);
-            if (!(mb > -INFINITY)) continue;
-            const float w0 = fast_exp2(m - mb);
-            l *= w0;
+            for (int off = 16; off >= 1; off >>= 1) mb = fmaxf(mb, __shfl_xor(mb, off, 32));
+            mb = fmaxf(mb, m);
+            const float w = ml.y > 0.f ? fast_exp2(ml.x - mb) : 0.f;         // 0: the part saw nothing visible
+            float lb = ml.y * w;
+#pragma unroll
+            for (int off = 16; off >= 1; off >>= 1) lb += __shfl_xor(lb, off, 32);
+            const float w0 = m > -INFINITY ? fast_exp2(m - mb) : 0.f;
+            l = fmaf(l, w0, lb);
+            m = mb;
 #pragma unroll
             for (int j = 0; j < VW; ++j) o[j] *= w0;
+            for (int p0 = 0; p0 < n; p0 += kBatch) {
+                if (p0 > 0) fetch(p0);
 #pragma unroll
-            for (int p = 0; p < kBatch; ++p)
-                if (ls[p] > 0.f) {
-                    const float w = fast_exp2(ms[p] - mb);
-                    l = fmaf(ls[p], w, l);
+                for (int p = 0; p < kBatch; ++p)
+                    if (p0 + p < n) {
+                        const float wp = __shfl(w, p0 + p, 32);
 #pragma unroll
-                    for (int j = 0; j < VW; ++j) o[j] = fmaf(v[p][j], w, o[j]);
-                }
-            m = mb;
+                        for (int j = 0; j < VW; ++j) o[j] = fmaf(v[p][j], wp, o[j]);
+                    }
+            }
         }
         const float inv = (l > 0.f) ? 1.f / l : 0.f;
         const int node = r / a.G, g = r - node * a.G;

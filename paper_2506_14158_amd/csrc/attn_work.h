@@ -3,12 +3,14 @@
 // The work of one (sequence, KV head) "unit" is a run of key tiles: its prefix tiles, then its tree tiles.  A
 // team is the workgroups that walk the same keys for the row tiles of one unit (a single workgroup when all query
 // rows fit one).  Two divisions:
-//   whole     team = unit.  Nothing to merge; for launches whose units all fit on the chip at once and are short.
-//   balanced  all units' tiles are laid end to end, sequence by sequence with their ACTUAL lengths, and the
-//             teams take equal consecutive shares (sizes differ by one tile).  A share may end inside a unit: that
-//             part goes to the workspace unnormalised and attn_merge_kernel combines a unit's parts in order.
-//             Equal shares are what keeps every CU busy to the end: with a fixed number of splits per unit, 104
-//             units of ragged length leave 48 of 256 CUs idle and the rest waiting for the longest sequence.
+//   split     every unit's tiles (of its ACTUAL length) are cut into `split` equal runs, a team each; a team walks
+//             one run.  split = 1: nothing to merge.  For launches whose teams all fit on the chip at once.
+//   balanced  (split = 0) all units' tiles are laid end to end, sequence by sequence with their actual lengths, and
+//             the teams take equal consecutive shares (sizes differ by one tile).  A share may end inside a unit.  Equal
+//             shares are what keeps every CU busy to the end: 104 units on 256 CUs leave 48 of them idle at two runs per
+//             unit, and with ragged lengths the rest wait for the longest sequence.
+// A part of a unit that several teams share goes to the workspace unnormalised; attn_merge_kernel combines a unit's
+// parts in order.
 // The shares are a function of the shape and of cache_len, so results are deterministic for given inputs.
 #pragma once
 #include "common.h"
@@ -113,10 +115,15 @@ struct Walk {
 __device__ __forceinline__ Walk walk_first(const AttnArgs& a, const Lens& lens, int team) {
     Walk w = {-1, 0, 0, 0, 0, 0};
     if (team >= a.teams) return w;
-    if (a.whole) {
-        w.b = team / a.Hkv;
-        w.kvh = team - w.b * a.Hkv;
-        w.tiles = w.tile_end = lens.tiles(a, w.b);
+    if (a.split > 0) {
+        const int unit = team / a.split, k = team - unit * a.split;
+        w.b = unit / a.Hkv;
+        w.kvh = unit - w.b * a.Hkv;
+        w.tiles = lens.tiles(a, w.b);
+        const int run = (w.tiles + a.split - 1) / a.split;
+        w.tile = k * run;
+        w.tile_end = min(w.tiles, w.tile + run);
+        if (w.tile >= w.tile_end) w.b = -1;
         return w;
     }
     const Order order(a, lens);
@@ -154,6 +161,47 @@ __device__ __forceinline__ bool walk_is_whole(const Walk& w) { return w.tile == 
 // workspace rows of a part: a team leaves at most one part that ends a unit or lies inside it (slot 0) and one
 // that begins a unit (slot 1)
 __device__ __forceinline__ size_t part_row(const AttnArgs& a, int team, int slot) { return ((size_t)team * 2 + slot) * a.M; }
+
+// ---- what a workgroup needs to know about a sequence besides its length
+// parent[b][tid], requested ahead of its use (workgroups have at least kMaxNodes threads)
+__device__ __forceinline__ int load_parent(const AttnArgs& a, int b) {
+    const int tid = threadIdx.x;
+    return tid < a.N ? a.parent[(size_t)b * a.N + tid] : -1;
+}
+// Checks the sequence (S4C_SEQ_BAD_TREE, S4C_SEQ_BAD_LEN; the same answer in all its workgroups) and leaves parent[] in
+// `spar`.  flags: one word per wavefront.  One barrier; the caller has one of its own before the next call.
+template <int NT, bool PAGED>
+__device__ __forceinline__ int check_sequence(const AttnArgs& a, const Lens& lens, int b, int parent, int32_t* spar, int32_t* flags) {
+    static_assert(NT >= kMaxNodes, "a thread per node");
+    const int tid = threadIdx.x, P = usable(a, lens.at(a, b));
+    int bad_page = 0;
+    if constexpr (PAGED) {
+        // every page the prefix touches must be a page of the pool
+        for (int i = tid; i < ((P + (1 << a.page_shift) - 1) >> a.page_shift); i += NT) {
+            const int id = a.block_table[(size_t)b * a.max_blocks + i];
+            bad_page |= (id < 0 || id >= a.num_pages);
+        }
+    }
+    if (tid < a.N) spar[tid] = parent;
+    const int mine = (__any(tid < a.N && (parent < -1 || parent >= tid)) ? S4C_SEQ_BAD_TREE : 0) |
+                     (__any(bad_page) || P != lens.at(a, b) ? S4C_SEQ_BAD_LEN : 0);
+    if ((tid & 63) == 0) flags[tid >> 6] = mine;
+    __syncthreads();
+    int all = 0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) all |= flags[w];
+    return __builtin_amdgcn_readfirstlane(all);
+}
+// 128-bit ancestor-or-self masks of a valid tree, from `spar`
+__device__ __forceinline__ void build_masks(const AttnArgs& a, const int32_t* spar, uint32_t* anc) {
+    const int tid = threadIdx.x;
+    if (tid < a.N) {
+        uint32_t m[4] = {0, 0, 0, 0};
+        for (int j = tid; j >= 0; j = spar[j]) m[j >> 5] |= 1u << (j & 31);
+        *(uint4*)(anc + tid * 4) = make_uint4(m[0], m[1], m[2], m[3]);
+    }
+    __syncthreads();
+}
 
 // Tells the merge kernel which teams share a unit: the team that begins it and the team that ends it say so.
 __device__ __forceinline__ void note_parts(const AttnArgs& a, int team, const Walk& w) {

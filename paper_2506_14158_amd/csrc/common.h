@@ -65,7 +65,7 @@ struct AttnArgs {
     int32_t B, Hq, Hkv, D, N, S_cap, G, M;
     int32_t max_cache_len;
     int32_t teams;      // teams the work is divided between (attn_work.h)
-    int32_t whole;      // 1: a team per (sequence, KV head), nothing to merge
+    int32_t split;      // teams per (sequence, KV head); 0: equal shares of all units' tiles laid end to end
     int32_t mtiles;     // query-row tiles per (sequence, KV head) = workgroups per team
     int32_t tile_keys, tile_shift;   // keys per tile of the kernel that will run, and its log2
     float scale_log2; // softmax scale * log2(e)

@@ -81,7 +81,7 @@ bool shape_ok(const s4c_attn_shape* s, s4c_status* why) {
 
 struct AttnPlan {
     bool large;                // more than 64 rows of 16-bit data: the kernel whose waves split the rows
-    int teams, whole, mtiles, tile_keys, tile_shift;
+    int teams, split, mtiles, tile_keys, tile_shift;
     int parts;                 // most parts a unit is divided into when no sequence is shorter than max_cache_len
     size_t ws_o_bytes, ws_ml_bytes, ws_parts_bytes;
 };
@@ -99,31 +99,31 @@ AttnPlan plan_attn(const s4c_attn_shape& s, int32_t max_cache_len) {
     const long long slots = (long long)device_cus() * t.per_cu;
     const long long units = (long long)s.B * s.Hkv;
     const long long tiles = (max_cache_len + t.keys - 1) / t.keys + (s.N + t.keys - 1) / t.keys;   // of the longest unit
-    // Teams: one round of the chip, its workgroups all on one XCD (32 CUs); fewer when a share would get shorter than
-    // kMinKeys keys, below which a part's fixed costs (prologue, partial results, its share of the merge) outweigh what
-    // the extra workgroups stream; at most 32 parts per unit.
-    const long long kMinKeys = 256, per_xcd = slots / 8;
+    // Teams: one round of the chip, a team's workgroups all on one XCD (an eighth of it); fewer when a share would get
+    // shorter than kMinKeys keys, below which a part's fixed costs (prologue, partial results, its share of the merge)
+    // outweigh what the extra workgroups stream; at most kMaxParts runs per unit.
+    const long long kMinKeys = 256, kMaxParts = 24, per_xcd = slots / 8;
     long long teams = per_xcd >= p.mtiles ? per_xcd / p.mtiles * 8 : 8;
     const long long most = units * tiles * t.keys / kMinKeys;
     if (teams > most) teams = most;
-    if (teams > units * 32) teams = units * 32;
-    // Not worth dividing (every unit already has a team, or gets no second one), or more tiles than the kernels' 32-bit
-    // tile numbers: a team per unit.
-    p.whole = teams <= units && (units * p.mtiles <= slots || units * tiles > 0x3FFFFFFFll);
-    if (units * tiles > 0x3FFFFFFFll) p.whole = 1;
-    if (p.whole) teams = units;
-    // Shares that end where units end have no second part to start and finish: taken when that leaves at most 7 % of the
-    // teams out.
-    else if (teams > units && teams % units <= teams * 7 / 100) teams -= teams % units;
-    if (teams < 1) teams = 1;
-    p.teams = (int)teams;
-    if (p.whole) {
+    if (teams > units * kMaxParts) teams = units * kMaxParts;
+    // A share that ends inside a unit has a second segment to start and finish, which costs as much as kSwitchKeys keys:
+    // whole numbers of runs per unit where the longer runs cost less than that, and where no unit would get a second.
+    const long long kSwitchKeys = 256;
+    long long split = 0;
+    if (units * tiles > 0x3FFFFFFFll) split = 1;                             // beyond the kernels' 32-bit tile numbers
+    else if (teams >= units) {
+        const long long q = teams / units;
+        if ((tiles + q - 1) / q * t.keys <= units * tiles * t.keys / teams + kSwitchKeys) split = q;
+    } else if (units * p.mtiles <= slots) split = 1;
+    p.split = (int)split;
+    p.teams = (int)(split > 0 ? units * split : teams < 1 ? 1 : teams);
+    if (split == 1) {
         p.parts = 1;
         p.ws_o_bytes = p.ws_ml_bytes = p.ws_parts_bytes = 0;
     } else {
-        const long long share = units * tiles / teams;                       // >= 1: kMinKeys is several tiles
-        p.parts = (int)((tiles + share - 1) / share + (tiles % share || teams % units ? 1 : 0));
-        if (units * tiles % teams == 0 && share % tiles == 0) p.parts = 1;   // shares are whole units
+        const long long share = units * tiles / p.teams;                     // >= 1: kMinKeys is several tiles
+        p.parts = (int)(split > 0 ? split : share % tiles == 0 && units * tiles % p.teams == 0 ? 1 : (tiles + share - 1) / share + 1);
         const size_t prow = (size_t)p.teams * 2 * M;
         p.ws_o_bytes = prow * s.D * sizeof(float);
         p.ws_ml_bytes = ((prow * 2 * sizeof(float) + 255) / 256) * 256;
@@ -199,7 +199,7 @@ s4c_status tree_attn_impl(const s4c_attn_shape* shape, const void* q, const void
     a.ws_o = (float*)((char*)workspace + p.ws_ml_bytes + p.ws_parts_bytes);
     a.B = shape->B; a.Hq = shape->Hq; a.Hkv = shape->Hkv; a.D = shape->D; a.N = shape->N;
     a.S_cap = shape->S_cap; a.G = shape->Hq / shape->Hkv; a.M = a.N * a.G;
-    a.max_cache_len = max_cache_len; a.teams = p.teams; a.whole = p.whole; a.mtiles = p.mtiles;
+    a.max_cache_len = max_cache_len; a.teams = p.teams; a.split = p.split; a.mtiles = p.mtiles;
     a.tile_keys = p.tile_keys; a.tile_shift = p.tile_shift;
     a.scale_log2 = (scale > 0.f ? scale : 1.0f / sqrtf((float)shape->D)) * kLog2e;
     a.block_table = block_table; a.max_blocks = max_blocks; a.page_shift = page_shift; a.num_pages = num_pages;
@@ -208,7 +208,7 @@ s4c_status tree_attn_impl(const s4c_attn_shape* shape, const void* q, const void
     // Parts are combined by a second kernel: the kernel boundary is what makes one workgroup's
     // partial results visible to another across the chip's separate L2s at no extra cost.
     hipError_t e = p.large ? launch_tree_attn_large(a, shape->dtype, st) : launch_tree_attn_small(a, shape->dtype, st);
-    if (e == hipSuccess && !p.whole) e = launch_attn_merge(a, shape->dtype, st);
+    if (e == hipSuccess && p.split != 1) e = launch_attn_merge(a, shape->dtype, st);
     return e == hipSuccess ? S4C_OK : S4C_ERR_HIP;
 }
 }  // namespace

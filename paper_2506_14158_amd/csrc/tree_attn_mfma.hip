@@ -37,7 +37,7 @@ using namespace mfma;
 
 constexpr int kBN = 64;                     // keys per tile
 constexpr float kLazyLog2 = 8.0f;           // full tiles rescale only when a row maximum grew by more than 2^8
-constexpr int lds_bytes_for(int ns, int d) { return ns * 2 * kBN * d * 2 + kMaxNodes * 16 + kMaxNodes * 4; }
+constexpr int lds_bytes_for(int ns, int d) { return ns * 2 * kBN * d * 2 + kMaxNodes * 16 + kMaxNodes * 4 + 64; }
 
 template <int WR, int NS, int WPE, bool PAGED, bool F16, int kD>
 __global__ __launch_bounds__(WR * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
@@ -59,6 +59,7 @@ void tree_attn_mfma_kernel(AttnArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     uint32_t* anc = (uint32_t*)(smem + NS * kStageB);        // [kMaxNodes][4]
     int32_t* spar = (int32_t*)(anc + kMaxNodes * 4);         // [kMaxNodes]
+    int32_t* flags = spar + kMaxNodes;                       // [WR]
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -173,65 +174,42 @@ void tree_attn_mfma_kernel(AttnArgs a) {
     issue_next();
 
     const bool wave_on = mt * BM + wave * 32 < M;         // some of this wave's rows exist
-    int b_known = -1, bad_seq = 0;
-    for (; cw.b >= 0; cw = work::walk_next(a, lens, cw)) {
-    const int b = cw.b, kvh = cw.kvh;
-    const int P = work::usable(a, lens.at(a, b));
-
-    // ---- another sequence: validate it; build its ancestor-or-self masks
-    if (b != b_known) {
-        b_known = b;
-        int bad_tree = 0;
-        if (tid < N) {
-            const int p = a.parent[(size_t)b * N + tid];
-            spar[tid] = p;
-            bad_tree = (p < -1 || p >= tid);
-        }
-        bad_tree = __syncthreads_or(bad_tree);
-        int bad_len = P != lens.at(a, b);
-        if constexpr (PAGED) {
-            // every page the prefix touches must be a page of the pool (each workgroup checks them all,
-            // so all workgroups of the sequence agree)
-            int bad_page = 0;
-            for (int i = tid; i < ((P + (1 << a.page_shift) - 1) >> a.page_shift); i += NT) {
-                const int id = a.block_table[(size_t)b * a.max_blocks + i];
-                bad_page |= (id < 0 || id >= a.num_pages);
-            }
-            bad_len |= __syncthreads_or(bad_page);
-        }
-        if (a.status && tid == 0 && cw.tile == 0 && kvh == 0 && mt == 0)
-            a.status[b] = (bad_tree ? S4C_SEQ_BAD_TREE : 0) | (bad_len ? S4C_SEQ_BAD_LEN : 0);
-        // wave-uniform by construction; tell the compiler so that everything derived from it stays scalar
-        bad_seq = __builtin_amdgcn_readfirstlane((bad_tree || bad_len) ? 1 : 0);
-        for (int i = tid; i < N && !bad_tree; i += NT) {
-            uint32_t m[4] = {0, 0, 0, 0};
-            for (int j = i; j >= 0; j = spar[j]) m[j >> 5] |= 1u << (j & 31);
-            *(uint4*)(anc + i * 4) = make_uint4(m[0], m[1], m[2], m[3]);
-        }
-        __syncthreads();
-    }
-    const bool bad = bad_seq != 0;
-
-    // ---- this lane's query row
+    // ---- this lane's query row.  Q^T fragments: B operand of step t holds d = 16 t + 8 g32 + (0..7) of the row.
+    // A segment's fragments and its sequence's parent[] are requested before the previous segment is written out.
     const int rq = mt * BM + wave * 32 + (lane & 31);
     const bool rvalid = rq < M;
-    const int node = rvalid ? rq / G : 0;
-    const int head = kvh * G + (rvalid ? rq - node * G : 0);
-    uint32_t amask[4] = {0, 0, 0, 0};
-    if (rvalid && !bad) {
-#pragma unroll
-        for (int w = 0; w < 4; ++w) amask[w] = anc[node * 4 + w];
-    }
-
-    // Q^T fragments: B operand of step t holds d = 16 t + 8 g32 + (0..7) of row rq
+    const int node = rvalid ? rq / G : 0, g = rvalid ? rq - node * G : 0;
     bf16x8 qf[kKT];
-    {
-        const bf16_t* qrow = (const bf16_t*)a.q + (((size_t)b * N + node) * a.Hq + head) * kD + g32 * 8;
+    auto load_q = [&](int b, int kvh) __attribute__((always_inline)) {
+        const bf16_t* qrow = (const bf16_t*)a.q + (((size_t)b * N + node) * a.Hq + kvh * G + g) * kD + g32 * 8;
 #pragma unroll
         for (int t = 0; t < kKT; ++t) {
             uint4 raw = make_uint4(0, 0, 0, 0);
             if (rvalid) raw = *(const uint4*)(qrow + 16 * t);
             qf[t] = __builtin_bit_cast(bf16x8, raw);
+        }
+    };
+    int parent = work::load_parent(a, cw.b);
+    load_q(cw.b, cw.kvh);
+
+    int b_known = -1, flagged = 0;
+    bool masks = false;                                   // anc[] holds b_known's masks
+    while (cw.b >= 0) {
+    const int b = cw.b, kvh = cw.kvh;
+    const int P = work::usable(a, lens.at(a, b)), u_pref = (P + kBN - 1) / kBN, t_end = uniform(cw.tile_end);
+    if (b != b_known) {
+        b_known = b;
+        masks = false;
+        flagged = work::check_sequence<NT, PAGED>(a, lens, b, parent, spar, flags);
+        if (a.status && tid == 0 && cw.tile == 0 && kvh == 0 && mt == 0) a.status[b] = flagged;
+    }
+    uint32_t amask[4] = {0, 0, 0, 0};
+    if (t_end > u_pref && !flagged) {
+        if (!masks) work::build_masks(a, spar, anc);
+        masks = true;
+        if (rvalid) {
+            const uint4 m = *(const uint4*)(anc + node * 4);
+            amask[0] = m.x; amask[1] = m.y; amask[2] = m.z; amask[3] = m.w;
         }
     }
 
@@ -401,7 +379,6 @@ void tree_attn_mfma_kernel(AttnArgs a) {
         __syncthreads();          // every wave's part of the tile is in LDS; the stage before it is free
         if (issued < n_share) issue_next();
     };
-    const int u_pref = (P + kBN - 1) / kBN, t_end = uniform(cw.tile_end);
     int t = uniform(cw.tile);
     // While the loads run ahead inside this segment's full prefix tiles, nothing has to be decided per tile.
     if (uniform(pw.b) == uniform(b) && uniform(pw.kvh) == uniform(kvh)) {
@@ -431,13 +408,18 @@ void tree_attn_mfma_kernel(AttnArgs a) {
         if (wave_on) tile_body(std::integral_constant<int, kTree>{}, t - u_pref);
     }
 
-    if (!a.whole && mt == 0 && tid == 0) work::note_parts(a, team, cw);
+    const work::Walk nw = work::walk_next(a, lens, cw);
+    if (nw.b >= 0) {
+        if (nw.b != b) parent = work::load_parent(a, nw.b);
+        load_q(nw.b, nw.kvh);
+    }
+    if (a.split != 1 && mt == 0 && tid == 0) work::note_parts(a, team, cw);
     // ---- write this lane's row: d = 32 db + 8 (j/4) + 4 g32 + (j%4)
-    const float l_tot = bad ? 0.f : l_run + __shfl_xor(l_run, 32);       // a flagged sequence: zero output
+    const float l_tot = flagged ? 0.f : l_run + __shfl_xor(l_run, 32);       // a flagged sequence: zero output
     if (work::walk_is_whole(cw)) {
         if (rvalid) {
         const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
-        bf16_t* orow = (bf16_t*)a.out + (((size_t)b * N + node) * a.Hq + head) * kD + 4 * g32;
+        bf16_t* orow = (bf16_t*)a.out + (((size_t)b * N + node) * a.Hq + kvh * G + g) * kD + 4 * g32;
 #pragma unroll
         for (int db = 0; db < kDB; ++db)
 #pragma unroll
@@ -464,6 +446,7 @@ void tree_attn_mfma_kernel(AttnArgs a) {
             }
         }
     }
+    cw = nw;
     }
 }
 

@@ -26,7 +26,7 @@ using namespace mfma;
 
 constexpr int kBN = 32;                      // keys per tile
 constexpr float kLazyLog2 = 8.0f;            // full tiles rescale only when a row maximum grew by more than 2^8
-constexpr int kAuxB = kMaxNodes * 16 + kMaxNodes * 4;
+constexpr int kAuxB = kMaxNodes * 16 + kMaxNodes * 4 + 64;
 
 enum Elem { kB16 = 0, kH16 = 1, kF32 = 2 };  // bf16, fp16, fp32
 
@@ -77,6 +77,7 @@ void tree_attn_smallm_kernel(AttnArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     uint32_t* anc = (uint32_t*)(smem + C::kRingB);            // [kMaxNodes][4]
     int32_t* spar = (int32_t*)(anc + kMaxNodes * 4);          // [kMaxNodes]
+    int32_t* flags = spar + kMaxNodes;                        // [waves]
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -203,63 +204,44 @@ void tree_attn_smallm_kernel(AttnArgs a) {
     for (int r = 0; r < kNR - 1; ++r)
         if (pw.b >= 0) issue_round();
 
-    int b_known = -1, bad_seq = 0;
-    for (; cw.b >= 0; cw = work::walk_next(a, lens, cw)) {
+    // ---- this lane's query row.  A segment's Q fragments and its sequence's parent[] are requested before the previous
+    // segment is written out.
+    const int rq = (mt * kRBW + rb) * 32 + (lane & 31);
+    const bool rvalid = rq < M;
+    const int node = rvalid ? rq / G : 0, gh = rvalid ? rq - node * G : 0;
+    uint4 qf[kKT];           // 16-bit: elements 16 t + 8 g32 .. + 7; fp32: elements 8 t + 4 g32 .. + 3
+    auto load_q = [&](int b, int kvh) __attribute__((always_inline)) {
+        const unsigned char* qrow = (const unsigned char*)a.q + ((((size_t)b * N + node) * a.Hq + kvh * G + gh) * kD) * C::kEs + g32 * 16;
+#pragma unroll
+        for (int t = 0; t < kKT; ++t) {
+            qf[t] = make_uint4(0, 0, 0, 0);
+            if (rvalid) qf[t] = *(const uint4*)(qrow + 32 * t);
+        }
+    };
+    int parent = work::load_parent(a, cw.b);
+    load_q(cw.b, cw.kvh);
+
+    int b_known = -1, flagged = 0;
+    bool masks = false;                                       // anc[] holds b_known's masks
+    while (cw.b >= 0) {
         const int b = cw.b, kvh = cw.kvh;
         const int P = work::usable(a, lens.at(a, b)), u_pref = (P + kBN - 1) / kBN;
         const int t_end = uniform(cw.tile_end);
-
-        // ---- this lane's query row
-        const int rq = (mt * kRBW + rb) * 32 + (lane & 31);
-        const bool rvalid = rq < M;
-        const int node = rvalid ? rq / G : 0;
-        const int head = kvh * G + (rvalid ? rq - node * G : 0);
-        uint4 qf[kKT];           // 16-bit: elements 16 t + 8 g32 .. + 7; fp32: elements 8 t + 4 g32 .. + 3
-        {
-            const unsigned char* qrow = (const unsigned char*)a.q + ((((size_t)b * N + node) * a.Hq + head) * kD) * C::kEs + g32 * 16;
-#pragma unroll
-            for (int t = 0; t < kKT; ++t) {
-                qf[t] = make_uint4(0, 0, 0, 0);
-                if (rvalid) qf[t] = *(const uint4*)(qrow + 32 * t);
-            }
-        }
-        // ---- another sequence: validate it; build its ancestor-or-self masks
         if (b != b_known) {
             b_known = b;
-            int bad_tree = 0;
-            for (int i = tid; i < N; i += kThreads) {
-                const int p = a.parent[(size_t)b * N + i];
-                spar[i] = p;
-                bad_tree |= (p < -1 || p >= i);
-            }
-            bad_tree = __syncthreads_or(bad_tree);
-            int bad_len = P != lens.at(a, b);
-            if constexpr (PAGED) {
-                // every page the prefix touches must be a page of the pool (each workgroup checks them all, so all
-                // workgroups of the sequence agree)
-                int bad_page = 0;
-                for (int i = tid; i < ((P + (1 << a.page_shift) - 1) >> a.page_shift); i += kThreads) {
-                    const int id = a.block_table[(size_t)b * a.max_blocks + i];
-                    bad_page |= (id < 0 || id >= a.num_pages);
-                }
-                bad_len |= __syncthreads_or(bad_page);
-            }
-            if (a.status && tid == 0 && cw.tile == 0 && kvh == 0 && mt == 0)
-                a.status[b] = (bad_tree ? S4C_SEQ_BAD_TREE : 0) | (bad_len ? S4C_SEQ_BAD_LEN : 0);
-            bad_seq = __builtin_amdgcn_readfirstlane((bad_tree || bad_len) ? 1 : 0);
-            for (int i = tid; i < N && !bad_tree; i += kThreads) {
-                uint32_t m[4] = {0, 0, 0, 0};
-                for (int j = i; j >= 0; j = spar[j]) m[j >> 5] |= 1u << (j & 31);
-                *(uint4*)(anc + i * 4) = make_uint4(m[0], m[1], m[2], m[3]);
-            }
-            __syncthreads();
+            masks = false;
+            flagged = work::check_sequence<kThreads, PAGED>(a, lens, b, parent, spar, flags);
+            if (a.status && tid == 0 && cw.tile == 0 && kvh == 0 && mt == 0) a.status[b] = flagged;
         }
-        const bool bad = bad_seq != 0;
         // ancestor words of this row, pre-shifted for this half of the wave
         uint32_t amask[4] = {0, 0, 0, 0};
-        if (rvalid && !bad) {
+        if (t_end > u_pref && !flagged) {
+            if (!masks) work::build_masks(a, spar, anc);
+            masks = true;
+            if (rvalid) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) amask[q] = anc[node * 4 + q] >> (4 * g32);
+                for (int q = 0; q < 4; ++q) amask[q] = anc[node * 4 + q] >> (4 * g32);
+            }
         }
 
         f32x16 o[kDB];
@@ -418,8 +400,13 @@ void tree_attn_smallm_kernel(AttnArgs a) {
             tile(std::integral_constant<bool, true>{}, visible);
         }
 
+        const work::Walk nw = work::walk_next(a, lens, cw);
+        if (nw.b >= 0) {
+            if (nw.b != b) parent = work::load_parent(a, nw.b);
+            load_q(nw.b, nw.kvh);
+        }
         // ---- merge the key groups of each row into key group 0, one 32-column block at a time
-        float l_tot = bad ? 0.f : l_run + __shfl_xor(l_run, 32);              // a flagged sequence: zero output
+        float l_tot = flagged ? 0.f : l_run + __shfl_xor(l_run, 32);              // a flagged sequence: zero output
         float* mo = (float*)(smem + C::kRingB + kAuxB);                       // [KG-1][RBW][32 rows][kMergeRow]
         float* mml = mo + (kKG - 1) * kRBW * 32 * C::kMergeRow;               // [KG-1][RBW][32 rows][2]
         const int mslot = ((kg - 1) * kRBW + rb) * 32 + (lane & 31);          // (kg > 0)
@@ -469,12 +456,12 @@ void tree_attn_smallm_kernel(AttnArgs a) {
             }
             if (db + 1 < kDB) __syncthreads();
         }
-        if (!a.whole && mt == 0 && tid == 0) work::note_parts(a, team, cw);
+        if (a.split != 1 && mt == 0 && tid == 0) work::note_parts(a, team, cw);
         // ---- key group 0 writes the row: d = 32 db + 8 (j/4) + 4 g32 + (j%4)
         if (kg == 0 && rvalid) {
             if (work::walk_is_whole(cw)) {
                 const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
-                const size_t o0 = (((size_t)b * N + node) * a.Hq + head) * kD + 4 * g32;
+                const size_t o0 = (((size_t)b * N + node) * a.Hq + kvh * G + gh) * kD + 4 * g32;
 #pragma unroll
                 for (int db = 0; db < kDB; ++db)
 #pragma unroll
@@ -497,6 +484,7 @@ void tree_attn_smallm_kernel(AttnArgs a) {
                 if (g32 == 0) *(float2*)(a.ws_ml + prow * 2) = make_float2(m_run, l_tot);
             }
         }
+        cw = nw;
     }
 }
 
