@@ -1,4 +1,7 @@
-"""Thin ctypes binding of libs4c.so: same names as the C ABI, argument marshalling only.
+"""Thin binding of libs4c.so: same names as the C ABI, argument marshalling only.
+
+The entry points that launch work go through the native module _s4c_py (csrc/py_binding.cpp), which makes the same
+checks as the code here and reports what it does not take; the code here then finds out why and raises.
 
 Every step of the tree-verification path runs in the HIP kernels behind these calls; PyTorch
 supplies device memory and the stream.  There is no CPU fallback: a missing library raises.
@@ -95,6 +98,19 @@ def lib() -> C.CDLL:
     return _lib
 
 
+_nat = None
+
+
+def _native():
+    """The native marshalling module (built in-tree next to libs4c.so)."""
+    global _nat
+    if _nat is None:
+        lib()
+        from . import _s4c_py
+        _nat = _s4c_py
+    return _nat
+
+
 def s4c_strerror(code: int) -> str:
     return lib().s4c_strerror(code).decode()
 
@@ -102,6 +118,14 @@ def s4c_strerror(code: int) -> str:
 def _check(code: int):
     if code != 0:
         raise S4CError(code, s4c_strerror(code))
+
+
+def _taken(code: int) -> bool:
+    """Whether the native module took the call (0 or a library error); False: it left the checks to the caller."""
+    if code > 0:
+        return False
+    _check(code)
+    return True
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
@@ -147,6 +171,8 @@ def s4c_tree_attn(q, k_tree, v_tree, k_cache, v_cache, cache_len, parent, max_ca
                   out: torch.Tensor, scale: float = 0.0, status: Optional[torch.Tensor] = None,
                   workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Tree-masked attention of all N nodes; writes and returns ``out`` ([B][N][Hq][D])."""
+    if _taken((_nat or _native()).tree_attn(q, k_tree, v_tree, k_cache, v_cache, cache_len, parent, max_cache_len, out, scale, status, workspace)):
+        return out
     shape = attn_shape(q, k_tree, k_cache)
     for t in (k_tree, v_tree, k_cache, v_cache, out):
         if t.dtype != q.dtype:
@@ -166,6 +192,9 @@ def s4c_tree_attn_paged(q, k_tree, v_tree, k_pool, v_pool, block_table, cache_le
                         out: torch.Tensor, scale: float = 0.0, status: Optional[torch.Tensor] = None,
                         workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Tree-masked attention over a paged cache: pools [num_pages][Hkv][page_size][D], block_table [B][max_blocks]."""
+    if _taken((_nat or _native()).tree_attn_paged(q, k_tree, v_tree, k_pool, v_pool, block_table, cache_len, parent, max_cache_len, out, scale,
+                                                status, workspace)):
+        return out
     B, N, Hq, D = q.shape
     num_pages, Hkv, page_size, _ = k_pool.shape
     max_blocks = int(block_table.shape[1])
@@ -189,6 +218,8 @@ def s4c_tree_attn_paged(q, k_tree, v_tree, k_pool, v_pool, block_table, cache_le
 
 def s4c_kv_compact_paged(k_tree, v_tree, k_pool, v_pool, block_table, cache_len, path, accept_len,
                          dst_index: Optional[torch.Tensor] = None, status: Optional[torch.Tensor] = None) -> None:
+    if _taken((_nat or _native()).kv_compact_paged(k_tree, v_tree, k_pool, v_pool, block_table, cache_len, path, accept_len, dst_index, status)):
+        return
     B, N, Hkv, D = k_tree.shape
     num_pages, _, page_size, _ = k_pool.shape
     max_blocks = int(block_table.shape[1])
@@ -227,6 +258,9 @@ def _accept_checks(logits, parent, tokens, max_path, path, accept_len, accepted_
 def s4c_accept_path(logits, parent, tokens, mode: int, max_path: int, path, accept_len, accepted_tokens,
                     bonus_token, workspace, p_draft=None, uniforms=None, temperature: float = 1.0,
                     status: Optional[torch.Tensor] = None) -> None:
+    if _taken((_nat or _native()).accept_path(logits, parent, tokens, mode, max_path, path, accept_len, accepted_tokens, bonus_token, p_draft,
+                                            uniforms, temperature, status, workspace)):
+        return
     B, N, V = _accept_checks(logits, parent, tokens, max_path, path, accept_len, accepted_tokens, bonus_token, p_draft, uniforms)
     ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     _check(lib().s4c_accept_path(B, N, V, _dtype_code(logits), int(mode), float(temperature), _ptr(logits),
@@ -242,6 +276,9 @@ def s4c_accept_path_static(logits, parent, tokens, mode: int, max_path: int, pat
                            bonus_token, p_draft=None, uniforms=None, temperature: float = 1.0,
                            status: Optional[torch.Tensor] = None) -> None:
     """s4c_accept_path without a workspace argument: the library's fixed per-GPU scratch is used."""
+    if _taken((_nat or _native()).accept_path_static(logits, parent, tokens, mode, max_path, path, accept_len, accepted_tokens, bonus_token,
+                                                   p_draft, uniforms, temperature, status)):
+        return
     B, N, V = _accept_checks(logits, parent, tokens, max_path, path, accept_len, accepted_tokens, bonus_token, p_draft, uniforms)
     _check(lib().s4c_accept_path_static(B, N, V, _dtype_code(logits), int(mode), float(temperature), _ptr(logits),
                                         _ptr(parent), _ptr(tokens), _ptr(p_draft), _ptr(uniforms), int(max_path),
@@ -256,6 +293,9 @@ def s4c_accept_resample_workspace_size(B: int, N: int, V: int, max_path: int) ->
 def s4c_accept_resample(logits, draft_probs, parent, tokens, uniforms, u_resample, max_path: int, path,
                         accept_len, accepted_tokens, bonus_token, workspace=None, temperature: float = 1.0,
                         status: Optional[torch.Tensor] = None) -> None:
+    if _taken((_nat or _native()).accept_resample(logits, draft_probs, parent, tokens, uniforms, u_resample, max_path, path, accept_len,
+                                                accepted_tokens, bonus_token, workspace, temperature, status)):
+        return
     B, N, V = logits.shape
     for t in (parent, tokens):
         if t.dtype != torch.int32 or tuple(t.shape) != (B, N):
@@ -281,6 +321,8 @@ def s4c_accept_resample(logits, draft_probs, parent, tokens, uniforms, u_resampl
 
 def s4c_kv_compact(k_tree, v_tree, k_cache, v_cache, cache_len, path, accept_len,
                    dst_index: Optional[torch.Tensor] = None, status: Optional[torch.Tensor] = None) -> None:
+    if _taken((_nat or _native()).kv_compact(k_tree, v_tree, k_cache, v_cache, cache_len, path, accept_len, dst_index, status)):
+        return
     B, N, Hkv, D = k_tree.shape
     S_cap = k_cache.shape[2]
     if tuple(k_cache.shape) != (B, Hkv, S_cap, D) or v_tree.shape != k_tree.shape or v_cache.shape != k_cache.shape:
@@ -297,6 +339,9 @@ def s4c_commit_path(k_tree, v_tree, k_cache, v_cache, cache_len, path, accept_le
                     dst_index: Optional[torch.Tensor] = None, status: Optional[torch.Tensor] = None) -> None:
     """k_tree/v_tree [layers][B][N][Hkv][D], caches [layers][B][Hkv][S_cap][D]; features [B][N][F] -> features_out
     [B][max_path][F] (same dtype)."""
+    if _taken((_nat or _native()).commit_path(k_tree, v_tree, k_cache, v_cache, cache_len, path, accept_len, features, features_out, dst_index,
+                                            status)):
+        return
     Ly, B, N, Hkv, D = k_tree.shape
     S_cap = k_cache.shape[3]
     if tuple(k_cache.shape) != (Ly, B, Hkv, S_cap, D) or v_tree.shape != k_tree.shape or v_cache.shape != k_cache.shape:
@@ -323,6 +368,9 @@ def s4c_commit_path_paged(k_tree, v_tree, k_pool, v_pool, block_table, cache_len
                           status: Optional[torch.Tensor] = None) -> None:
     """k_tree/v_tree [layers][B][N][Hkv][D], pools [layers][num_pages][Hkv][page][D], block_table [B][max_blocks]
     (one table for every layer); features as in s4c_commit_path."""
+    if _taken((_nat or _native()).commit_path_paged(k_tree, v_tree, k_pool, v_pool, block_table, cache_len, path, accept_len, features,
+                                                  features_out, dst_index, status)):
+        return
     Ly, B, N, Hkv, D = k_tree.shape
     _, num_pages, _, page, _ = k_pool.shape
     if tuple(k_pool.shape) != (Ly, num_pages, Hkv, page, D) or v_tree.shape != k_tree.shape or v_pool.shape != k_pool.shape:
@@ -354,6 +402,9 @@ def s4c_build_tree_workspace_size(B: int, N: int, V: int) -> int:
 def s4c_build_tree(draft_logits, nchild, root_token, kmax: int, parent, tokens, p_draft, workspace,
                    temperature: float = 1.0, level: Optional[torch.Tensor] = None,
                    status: Optional[torch.Tensor] = None) -> None:
+    if _taken((_nat or _native()).build_tree(draft_logits, nchild, root_token, kmax, parent, tokens, p_draft, workspace, temperature, level,
+                                           status)):
+        return
     B, N, V = draft_logits.shape
     for t in (nchild, parent, tokens) + ((level,) if level is not None else ()):
         if t.dtype != torch.int32 or tuple(t.shape) != (B, N):
@@ -375,6 +426,8 @@ def s4c_draft_linear_workspace_size(T: int, H: int, Hout: int) -> int:
 def s4c_draft_linear(e, f, W, out, bias=None, workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """out[t] = W @ concat(e[t], f[t]) + bias (bf16 or fp16, fp32 accumulate); returns ``out``.  Up to 512 tokens
     the call needs ``workspace`` (s4c_draft_linear_workspace_size bytes)."""
+    if _taken((_nat or _native()).draft_linear(e, f, W, out, bias, workspace)):
+        return out
     T, H = e.shape
     Hout = W.shape[0]
     if tuple(f.shape) != (T, H) or tuple(W.shape) != (Hout, 2 * H) or tuple(out.shape) != (T, Hout):

@@ -59,6 +59,29 @@ def build_probe_lib() -> str:
     return PROBE_LIB
 
 
+PY_SRC = os.path.join(CSRC, "py_binding.cpp")
+PY_LIB = os.path.join(PKG, "_s4c_py.so")
+
+
+def build_py_binding() -> str:
+    """The native half of binding.py: marshals torch tensors into libs4c's C ABI (host code, g++)."""
+    import sysconfig
+
+    import torch
+    tdir = os.path.dirname(os.path.abspath(torch.__file__))
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I" + sysconfig.get_paths()["include"], "-I" + os.path.join(tdir, "include"),
+           "-I" + os.path.join(tdir, "include", "torch", "csrc", "api", "include"), "-I" + os.path.join(rocm, "include"),
+           "-I" + os.path.join(ROOT, "include"), PY_SRC, "-o", PY_LIB, "-L" + PKG, "-ls4c",
+           "-L" + os.path.join(tdir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on %s:\n%s" % (PY_SRC, r.stderr[-8000:]))
+    return PY_LIB
+
+
 C_CLIENT_SRC = os.path.join(ROOT, "tests", "c_client", "verify_step.c")
 C_CLIENT_BIN = os.path.join(ROOT, "tests", "c_client", "verify_step")
 
@@ -78,5 +101,6 @@ def build_c_client() -> str:
 
 if __name__ == "__main__":
     print(build_lib(verbose=True))
+    print(build_py_binding())
     print(build_probe_lib())
     print(build_c_client())
