@@ -296,6 +296,32 @@ s4c_status s4c_draft_linear(int32_t T, int32_t H, int32_t Hout, int32_t dtype, c
                             const void* W, const void* bias, void* out, void* workspace, size_t workspace_bytes,
                             void* hip_stream);
 
+/* One verification step in one call: s4c_tree_attn, then s4c_accept_path, then s4c_kv_compact, same results, arguments
+ * and device status words as the three calls with these arguments.  The attention merge, the acceptance and
+ * the compaction share one launch where the logits have the shape's dtype.  S4C_SEQ_TIMEOUT may also appear in
+ * compact_status, if the workgroups that copy a sequence's rows did not hear of its path within 2 s.
+ *   attn_workspace    as s4c_tree_attn (s4c_tree_attn_workspace_size)
+ *   accept_workspace  >= s4c_verify_step_workspace_size(&shape, V) bytes, 256-byte aligned, otherwise as
+ *                     s4c_accept_path's */
+typedef struct {
+    s4c_attn_shape shape;
+    int32_t V, logits_dtype, mode, max_path, max_cache_len;
+    float scale, temperature;
+    const void *q, *k_tree, *v_tree;
+    void *k_cache, *v_cache;
+    int32_t* cache_len;
+    const int32_t *parent, *tokens;
+    const void* logits;
+    const float *p_draft, *uniforms;
+    void* out;
+    int32_t *path, *accept_len, *accepted_tokens, *bonus_token, *dst_index;
+    int32_t *attn_status, *accept_status, *compact_status;
+    void *attn_workspace, *accept_workspace;
+    size_t attn_workspace_bytes, accept_workspace_bytes;
+} s4c_step;
+size_t s4c_verify_step_workspace_size(const s4c_attn_shape* shape, int32_t V);
+s4c_status s4c_verify_step(const s4c_step* step, void* hip_stream);
+
 /* Text for a status code (any integer: unknown codes get "unknown status").  Static, never NULL. */
 const char* s4c_strerror(int code);
 

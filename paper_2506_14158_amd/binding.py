@@ -24,7 +24,8 @@ S4C_SEQ_BAD_TREE, S4C_SEQ_BAD_LEN, S4C_SEQ_TIMEOUT = 1, 2, 4
 EXPORTS = ("s4c_tree_attn_workspace_size", "s4c_tree_attn", "s4c_accept_path_workspace_size",
            "s4c_accept_path", "s4c_kv_compact", "s4c_strerror", "s4c_tree_attn_num_splits",
            "s4c_accept_resample", "s4c_accept_resample_workspace_size", "s4c_commit_path", "s4c_build_tree", "s4c_build_tree_workspace_size",
-           "s4c_draft_linear", "s4c_draft_linear_workspace_size", "s4c_tree_attn_paged", "s4c_kv_compact_paged", "s4c_commit_path_paged", "s4c_accept_path_static")
+           "s4c_draft_linear", "s4c_draft_linear_workspace_size", "s4c_tree_attn_paged", "s4c_kv_compact_paged", "s4c_commit_path_paged", "s4c_accept_path_static",
+           "s4c_verify_step", "s4c_verify_step_workspace_size")
 
 
 class S4CError(RuntimeError):
@@ -92,6 +93,8 @@ def lib() -> C.CDLL:
         L.s4c_accept_path_static.restype = C.c_int
         L.s4c_accept_path_static.argtypes = [C.c_int32] * 5 + [C.c_float] + [C.c_void_p] * 5 + [C.c_int32] + [
             C.c_void_p] * 6
+        L.s4c_verify_step_workspace_size.restype = C.c_size_t
+        L.s4c_verify_step_workspace_size.argtypes = [C.POINTER(AttnShape), C.c_int32]
         L.s4c_strerror.restype = C.c_char_p
         L.s4c_strerror.argtypes = [C.c_int]
         _lib = L
@@ -417,6 +420,22 @@ def s4c_build_tree(draft_logits, nchild, root_token, kmax: int, parent, tokens, 
     _check(lib().s4c_build_tree(B, N, V, _dtype_code(draft_logits), float(temperature), _ptr(draft_logits),
                                 _ptr(nchild), _ptr(root_token), int(kmax), _ptr(parent), _ptr(tokens), _ptr(p_draft),
                                 _ptr(level), _ptr(status), _ptr(workspace), ws_bytes, _stream()))
+
+
+def s4c_verify_step_workspace_size(shape: AttnShape, V: int) -> int:
+    return int(lib().s4c_verify_step_workspace_size(C.byref(shape), V))
+
+
+def s4c_verify_step(q, k_tree, v_tree, k_cache, v_cache, cache_len, parent, logits, tokens, mode: int, p_draft, uniforms,
+                    temperature: float, scale: float, out, attn_status, attn_workspace, path, accept_len, accepted_tokens,
+                    bonus_token, accept_status, accept_workspace, dst_index, compact_status, max_cache_len: int,
+                    max_path: int) -> bool:
+    """Attention, acceptance and compaction of one step in one call.  False if the arguments are not what the three
+    calls take together: nothing was launched, and making them one by one tells which and why."""
+    return _taken((_nat or _native()).verify_step(
+        q, k_tree, v_tree, k_cache, v_cache, cache_len, parent, logits, tokens, mode, p_draft, uniforms, temperature, scale, out,
+        attn_status, attn_workspace, path, accept_len, accepted_tokens, bonus_token, accept_status, accept_workspace, dst_index,
+        compact_status, max_cache_len, max_path))
 
 
 def s4c_draft_linear_workspace_size(T: int, H: int, Hout: int) -> int:

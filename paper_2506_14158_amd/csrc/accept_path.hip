@@ -1,4 +1,5 @@
-// Path acceptance (paper Sec. 3.2: per-node test, then the longest accepted path) in ONE launch.
+// Path acceptance (paper Sec. 3.2: per-node test, then the longest accepted path) in ONE launch; and the same launch
+// extended to the rest of a verification step (last section of this comment).
 //
 // Scan (the HBM-bound part).  A workgroup owns a segment of consecutive 8192-logit chunks of one
 // logits row and reads it exactly once with 16-byte loads, the next chunk in flight while the
@@ -26,6 +27,14 @@
 // out (which needs a GPU that stops scheduling the sequence's other workgroups) the sequence is
 // flagged S4C_SEQ_TIMEOUT and gets the empty result.  Workgroups are dispatched in grid order, so
 // by the time a collector starts every other workgroup of its sequence has been given a compute unit.
+//
+// step_kernel: the workgroups of the attention merge first (it only needs the attention kernel to have ended), then the
+// acceptance scan with its collectors, then workgroups that append the accepted path's K/V rows to the cache: a few per
+// sequence, a group of KV heads each, which wait for a message from the collector (the path, the cache length it
+// has read and advanced).  At batch 1 the three launches this replaces were 2 us of work each behind 2 us of launch, and a
+// sequence's rows, copied by one workgroup, waited for one address translation after another (each KV head's
+// rows lie in pages of their own): 13b, batch 4: 12.5 + 5.6 + 10.4 us in three launches.
+#include "attn_merge.h"
 #include "row_chunk.h"
 
 namespace s4c {
@@ -65,9 +74,93 @@ __device__ __forceinline__ bool await4(const rec_t* p, int nsegs, int words, uin
     }
 }
 
+// ---- what step_kernel adds
+struct StepArgs {
+    CompactArgs compact;
+    rec_t* messages;            // [B][copiers][kMessage]
+    int32_t merge_wgs, merge_chunks, merge_passes, attn_D;
+    int32_t scan_wgs;
+    int32_t copiers, heads;     // workgroups per sequence that append rows, KV heads of each
+};
+constexpr int kMessage = 2 + kMaxNodes;          // records: cache length (or -1), accepted length, path nodes
+constexpr int kMostCopiers = 8;
+constexpr long long kCopyTicks = 200000000;      // 2 s of the 100 MHz wall clock
+
+// The collector's half of the compaction, as s4c_kv_compact: checks that the rows fit, writes dst_index and status,
+// advances cache_len, and tells the sequence's copiers, each in a message of its own (it clears the message when
+// it has read it, so that a captured graph can replay the call).  Path of L + 1 nodes in `node`; all threads.
+__device__ __forceinline__ void announce_path(const StepArgs& x, const AcceptArgs& a, int b, int base, int L, const int32_t* node) {
+    const CompactArgs& c = x.compact;
+    const int i = threadIdx.x;
+    const bool bad = base < 0 || (long long)base + L + 1 > c.S_cap;
+    if (i < kMessage) {
+        const int32_t word = i == 0 ? (bad ? -1 : base) : i == 1 ? L : i - 2 <= L ? node[i - 2] : -1;
+        for (int w = 0; w < x.copiers; ++w) publish(x.messages + ((size_t)b * x.copiers + w) * kMessage + i, a.nonce, (uint32_t)word);
+    }
+    if (c.dst_index)
+        for (int k = i; k < c.max_path; k += kThreads) c.dst_index[(size_t)b * c.max_path + k] = (!bad && k <= L) ? base + k : -1;
+    if (i == 0) {
+        if (c.status) c.status[b] = bad ? S4C_SEQ_BAD_LEN : 0;
+        if (!bad) c.cache_len[b] = base + L + 1;
+    }
+}
+
+// A copier: waits for its message, appends the path's rows of its KV heads.
+__device__ __forceinline__ void copy_rows(const StepArgs& x, const AcceptArgs& a, int b, int w) {
+    const CompactArgs& c = x.compact;
+    __shared__ int32_t s_msg[kMessage];
+    const int tid = threadIdx.x;
+    int late = 0;
+    if (tid < kMessage) {
+        rec_t* m = x.messages + ((size_t)b * x.copiers + w) * kMessage + tid;
+        const long long deadline = (long long)wall_clock64() + kCopyTicks;
+        rec_t v;
+        for (;;) {
+            v = __hip_atomic_load(m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((uint32_t)(v >> 32) == a.nonce) break;
+            if ((long long)wall_clock64() - deadline >= 0) { late = 1; break; }
+            __builtin_amdgcn_s_sleep(4);
+        }
+        s_msg[tid] = (int32_t)(uint32_t)v;
+        if (!late) publish(m, ~a.nonce, 0u);
+    }
+    late = __syncthreads_or(late);
+    if (late) {
+        if (tid == 0 && c.status) atomicOr(&c.status[b], S4C_SEQ_TIMEOUT);
+        return;
+    }
+    const int base = s_msg[0], L = s_msg[1];
+    if (base < 0) return;
+    const int h0 = w * x.heads, nh = min(c.Hkv, h0 + x.heads) - h0;
+    const int vpr = c.row_bytes / 16, total = (L + 1) * nh * vpr;
+    constexpr int kInFlight = 4;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    for (int e0 = tid; e0 < total; e0 += kThreads * kInFlight) {
+        u32x4 kv[kInFlight], vv[kInFlight];
+        size_t dst[kInFlight];
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) {
+            const int e = e0 + u * kThreads;
+            if (e < total) {
+                const int q = e / vpr, v = e - q * vpr, k = q / nh, h = h0 + q - k * nh;
+                const size_t src = (((size_t)b * c.N + s_msg[2 + k]) * c.Hkv + h) * c.row_bytes + (size_t)v * 16;
+                dst[u] = (((size_t)b * c.Hkv + h) * c.S_cap + (size_t)(base + k)) * c.row_bytes + (size_t)v * 16;
+                kv[u] = *(const u32x4*)((const char*)c.k_tree + src);
+                vv[u] = *(const u32x4*)((const char*)c.v_tree + src);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u)
+            if (e0 + u * kThreads < total) {
+                *(u32x4*)((char*)c.k_cache + dst[u]) = kv[u];
+                *(u32x4*)((char*)c.v_cache + dst[u]) = vv[u];
+            }
+    }
+}
+
 // The path step for sequence b, run by all kThreads threads of one workgroup (thread i = node i).
-template <typename T>
-__device__ void path_step(const AcceptArgs& a, int b) {
+template <typename T, bool STEP>
+__device__ __forceinline__ void path_step(const AcceptArgs& a, const StepArgs& x, int b) {
     const long long deadline = (long long)wall_clock64() + a.wait_ticks;
     const int i = threadIdx.x;
     const int N = a.N;
@@ -78,6 +171,8 @@ __device__ void path_step(const AcceptArgs& a, int b) {
     __shared__ int32_t s_tok[kMaxNodes];
     __shared__ int32_t s_kids[kMaxNodes];
     __shared__ float s_m[kMaxNodes], s_S[kMaxNodes];
+    __shared__ int32_t s_node[kMaxNodes], s_len;     // the result, for announce_path
+    const int base = STEP ? x.compact.cache_len[b] : 0;
 
     // ---- everything node i needs that does not depend on another load is requested up front (the
     // step is a chain of dependent memory latencies, not of work)
@@ -150,6 +245,11 @@ __device__ void path_step(const AcceptArgs& a, int b) {
             a.accept_len[b] = 0;
             a.bonus_token[b] = -1;
             if (a.status) a.status[b] = S4C_SEQ_TIMEOUT;
+            s_node[0] = s_len = 0;
+        }
+        if constexpr (STEP) {
+            __syncthreads();
+            announce_path(x, a, b, base, s_len, s_node);
         }
         return;
     }
@@ -191,6 +291,11 @@ __device__ void path_step(const AcceptArgs& a, int b) {
             a.accept_len[b] = 0;
             a.bonus_token[b] = -1;
             if (a.status) a.status[b] = S4C_SEQ_BAD_TREE;
+            s_node[0] = s_len = 0;
+        }
+        if constexpr (STEP) {
+            __syncthreads();
+            announce_path(x, a, b, base, s_len, s_node);
         }
         return;
     }
@@ -204,23 +309,30 @@ __device__ void path_step(const AcceptArgs& a, int b) {
         for (int k = L; k >= 1; --k) {
             pth[k] = node;
             atk[k - 1] = s_tok[node];
+            if constexpr (STEP) s_node[k] = node;
             node = spar[node];
         }
+        if constexpr (STEP) { s_node[0] = 0; s_len = L; }
         a.accept_len[b] = L;
         a.bonus_token[b] = (a.mode == S4C_GREEDY) ? s_g[i] : -1;
         if (a.status) a.status[b] = 0;
     }
+    if constexpr (STEP) {
+        __syncthreads();
+        announce_path(x, a, b, base, s_len, s_node);
+    }
 }
 
-template <typename T>
-__global__ __launch_bounds__(kThreads) void accept_kernel(AcceptArgs a) {
+// one workgroup of the scan; the sequence's last one goes on to the path step
+template <typename T, bool STEP>
+__device__ __forceinline__ void scan_segment(const AcceptArgs& a, const StepArgs& x, int wg) {
     constexpr int VN = Vec16<T>::n;
     constexpr int NV = kPerThread / VN;               // 16-byte loads per thread and chunk
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // workgroup -> (rank k among the sequence's scanned rows, sequence b, segment sg); k slowest
-    const int sg = blockIdx.x % a.nseg;
-    const int b = (blockIdx.x / a.nseg) % a.B;
-    const int k = blockIdx.x / (a.nseg * a.B);
+    const int sg = wg % a.nseg;
+    const int b = (wg / a.nseg) % a.B;
+    const int k = wg / (a.nseg * a.B);
     const int V = a.V, N = a.N;
     const bool stochastic = a.mode == S4C_STOCHASTIC;
 
@@ -378,7 +490,30 @@ __global__ __launch_bounds__(kThreads) void accept_kernel(AcceptArgs a) {
         }
     }
     // ---- the sequence's last workgroup in grid order collects and runs the path step
-    if (k == N - 1 && sg == a.nseg - 1) path_step<T>(a, b);
+    if (k == N - 1 && sg == a.nseg - 1) path_step<T, STEP>(a, x, b);
+}
+
+template <typename T>
+__global__ __launch_bounds__(kThreads) void accept_kernel(AcceptArgs a) {
+    scan_segment<T, false>(a, StepArgs{}, blockIdx.x);
+}
+
+template <typename T>
+__global__ __launch_bounds__(kThreads) void step_kernel(AttnArgs attn, AcceptArgs a, StepArgs x) {
+    int wg = blockIdx.x;
+    if (wg < x.merge_wgs) {
+        const int unit = wg / x.merge_chunks, chunk = wg - unit * x.merge_chunks;
+        if (x.attn_D == 64) merge::merge_rows<T, 64>(attn, unit, chunk, x.merge_passes);
+        else merge::merge_rows<T, 128>(attn, unit, chunk, x.merge_passes);
+        return;
+    }
+    wg -= x.merge_wgs;
+    if (wg < x.scan_wgs) {
+        scan_segment<T, true>(a, x, wg);
+        return;
+    }
+    wg -= x.scan_wgs;
+    copy_rows(x, a, wg / x.copiers, wg % x.copiers);
 }
 
 }  // namespace
@@ -406,6 +541,35 @@ hipError_t launch_accept(const AcceptArgs& a, hipStream_t st) {
     if (a.dtype == S4C_F32) hipLaunchKernelGGL(accept_kernel<float>, grid, block, 0, st, a);
     else if (a.dtype == S4C_F16) hipLaunchKernelGGL(accept_kernel<f16_t>, grid, block, 0, st, a);
     else hipLaunchKernelGGL(accept_kernel<bf16_t>, grid, block, 0, st, a);
+    return hipGetLastError();
+}
+
+// up to kMostCopiers per sequence, whole KV heads each
+size_t step_message_bytes(int B, int Hkv) {
+    return (size_t)B * (Hkv < kMostCopiers ? Hkv : kMostCopiers) * kMessage * sizeof(rec_t);
+}
+
+hipError_t launch_step(const AttnArgs& attn, bool merged, const AcceptArgs& a, const CompactArgs& compact, unsigned long long* messages,
+                       hipStream_t st) {
+    StepArgs x;
+    x.compact = compact;
+    x.messages = messages;
+    x.merge_wgs = 0;
+    x.merge_chunks = x.merge_passes = 1;
+    x.attn_D = attn.D;
+    if (merged) {
+        const merge::Grid g = merge::grid_of(attn);
+        x.merge_wgs = g.units * g.chunks;
+        x.merge_chunks = g.chunks;
+        x.merge_passes = g.passes;
+    }
+    x.scan_wgs = a.nseg * a.B * a.N;
+    x.heads = (compact.Hkv + kMostCopiers - 1) / kMostCopiers;
+    x.copiers = (compact.Hkv + x.heads - 1) / x.heads;
+    const dim3 grid((unsigned)(x.merge_wgs + x.scan_wgs + a.B * x.copiers)), block(kThreads);
+    if (a.dtype == S4C_F32) hipLaunchKernelGGL(step_kernel<float>, grid, block, 0, st, attn, a, x);
+    else if (a.dtype == S4C_F16) hipLaunchKernelGGL(step_kernel<f16_t>, grid, block, 0, st, attn, a, x);
+    else hipLaunchKernelGGL(step_kernel<bf16_t>, grid, block, 0, st, attn, a, x);
     return hipGetLastError();
 }
 

@@ -103,6 +103,13 @@ struct AcceptArgs {
     float inv_temp_log2;   // log2(e) / T
 };
 hipError_t launch_accept(const AcceptArgs& a, hipStream_t st);
+struct AttnArgs;
+struct CompactArgs;
+// The rest of a verification step after the attention kernel in one launch: the merge of divided attention (if
+// `merge`), acceptance, and the accepted path's rows appended to the cache.  All three of one element type.
+hipError_t launch_step(const AttnArgs& attn, bool merge, const AcceptArgs& accept, const CompactArgs& compact,
+                       unsigned long long* messages, hipStream_t st);
+size_t step_message_bytes(int B, int Hkv);
 int accept_chunk_elems();
 void accept_plan(int B, int N, int V, int* chunks, int* seg, int* nseg);
 

@@ -372,10 +372,50 @@ PyObject* draft_linear(PyObject*, PyObject* const* v, Py_ssize_t n) {
     });
 }
 
+// (q, k_tree, v_tree, k_cache, v_cache, cache_len, parent, logits, tokens, mode, p_draft, uniforms, temperature, scale,
+//  out, attn_status, attn_workspace, path, accept_len, accepted_tokens, bonus_token, accept_status, accept_workspace,
+//  dst_index, compact_status, max_cache_len, max_path)
+PyObject* verify_step(PyObject*, PyObject* const* v, Py_ssize_t n) {
+    Args a(v, n, 27);
+    const AttnTensors t = attn_tensors(a, 0, 1, 3, 14);
+    const Tensor *len = a.tensor(5, I32), *par = a.tensor(6, I32), *lg = a.tensor(7), *tok = a.tensor(8, I32), *pd = a.maybe(10, F32),
+                 *u = a.maybe(11, F32), *ast = a.maybe(15), *aws = a.maybe(16), *path = a.tensor(17, I32), *alen = a.tensor(18, I32),
+                 *acc = a.tensor(19, I32), *bonus = a.tensor(20, I32), *cst = a.maybe(21), *cws = a.maybe(22), *dst = a.maybe(23),
+                 *kst = a.maybe(24);
+    s4c_step p{};
+    p.mode = (int32_t)a.integer(9);
+    p.temperature = a.real(12);
+    p.scale = a.real(13);
+    p.max_cache_len = (int32_t)a.integer(25);
+    p.max_path = (int32_t)a.integer(26);
+    p.logits_dtype = dtype(a, lg);
+    if (!a.ok || lg->dim() != 3) return answer(kNotMine);
+    p.shape = t.s;
+    p.shape.S_cap = (int32_t)t.kc->size(2);
+    p.V = (int32_t)lg->size(2);
+    a.shape(t.kc, {t.s.B, t.s.Hkv, p.shape.S_cap, t.s.D});
+    a.shape(lg, {t.s.B, t.s.N, p.V});
+    a.shape(par, {t.s.B, t.s.N});
+    a.shape(tok, {t.s.B, t.s.N});
+    if (pd) a.shape(pd, {t.s.B, t.s.N});
+    if (u) a.shape(u, {t.s.B, t.s.N});
+    a.shape(path, {t.s.B, p.max_path});
+    a.shape(acc, {t.s.B, p.max_path});
+    if (!a.ok) return answer(kNotMine);
+    p.q = ptr(t.q); p.k_tree = ptr(t.kt); p.v_tree = ptr(t.vt); p.k_cache = ptr(t.kc); p.v_cache = ptr(t.vc);
+    p.cache_len = (int32_t*)ptr(len); p.parent = (int32_t*)ptr(par); p.tokens = (int32_t*)ptr(tok); p.logits = ptr(lg);
+    p.p_draft = (float*)ptr(pd); p.uniforms = (float*)ptr(u); p.out = ptr(t.out); p.path = (int32_t*)ptr(path);
+    p.accept_len = (int32_t*)ptr(alen); p.accepted_tokens = (int32_t*)ptr(acc); p.bonus_token = (int32_t*)ptr(bonus);
+    p.dst_index = (int32_t*)ptr(dst); p.attn_status = (int32_t*)ptr(ast); p.accept_status = (int32_t*)ptr(cst);
+    p.compact_status = (int32_t*)ptr(kst); p.attn_workspace = ptr(aws); p.accept_workspace = ptr(cws);
+    p.attn_workspace_bytes = bytes(aws); p.accept_workspace_bytes = bytes(cws);
+    return launch([&] { return s4c_verify_step(&p, stream()); });
+}
+
 #define S4C_PY(name) {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {S4C_PY(tree_attn), S4C_PY(tree_attn_paged), S4C_PY(accept_path), S4C_PY(accept_path_static),
                          S4C_PY(accept_resample), S4C_PY(kv_compact), S4C_PY(kv_compact_paged), S4C_PY(commit_path),
-                         S4C_PY(commit_path_paged), S4C_PY(build_tree), S4C_PY(draft_linear), {nullptr, nullptr, 0, nullptr}};
+                         S4C_PY(commit_path_paged), S4C_PY(build_tree), S4C_PY(draft_linear), S4C_PY(verify_step), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_s4c_py", "libs4c's entry points on torch tensors", -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

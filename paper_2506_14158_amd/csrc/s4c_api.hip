@@ -174,11 +174,12 @@ int page_shift_of(int32_t page_size) {
     return -1;
 }
 
-s4c_status tree_attn_impl(const s4c_attn_shape* shape, const void* q, const void* k_tree, const void* v_tree,
-                          const void* k_cache, const void* v_cache, const int32_t* block_table, int32_t max_blocks,
-                          int32_t page_shift, int32_t num_pages, const int32_t* cache_len, const int32_t* parent,
-                          int32_t max_cache_len, float scale, void* out, int32_t* status, void* workspace,
-                          size_t workspace_bytes, void* hip_stream) {
+// everything of an attention call but the launches
+s4c_status tree_attn_prepare(const s4c_attn_shape* shape, const void* q, const void* k_tree, const void* v_tree,
+                             const void* k_cache, const void* v_cache, const int32_t* block_table, int32_t max_blocks,
+                             int32_t page_shift, int32_t num_pages, const int32_t* cache_len, const int32_t* parent,
+                             int32_t max_cache_len, float scale, void* out, int32_t* status, void* workspace,
+                             size_t workspace_bytes, AttnPlan* plan, AttnArgs* args) {
     if (!shape || !q || !k_tree || !v_tree || !cache_len || !parent || !out) return S4C_ERR_NULL;
     s4c_status why;
     if (!shape_ok(shape, &why)) return why;
@@ -191,7 +192,7 @@ s4c_status tree_attn_impl(const s4c_attn_shape* shape, const void* q, const void
     const size_t need = p.ws_o_bytes + p.ws_ml_bytes + p.ws_parts_bytes;
     if (need > 0 && (!workspace || workspace_bytes < need || (((uintptr_t)workspace) & 255))) return S4C_ERR_WORKSPACE;
 
-    AttnArgs a;
+    AttnArgs& a = *args;
     a.q = q; a.k_tree = k_tree; a.v_tree = v_tree; a.k_cache = k_cache; a.v_cache = v_cache;
     a.cache_len = cache_len; a.parent = parent; a.out = out; a.status = status;
     a.ws_ml = (float*)workspace;
@@ -203,11 +204,28 @@ s4c_status tree_attn_impl(const s4c_attn_shape* shape, const void* q, const void
     a.tile_keys = p.tile_keys; a.tile_shift = p.tile_shift;
     a.scale_log2 = (scale > 0.f ? scale : 1.0f / sqrtf((float)shape->D)) * kLog2e;
     a.block_table = block_table; a.max_blocks = max_blocks; a.page_shift = page_shift; a.num_pages = num_pages;
+    *plan = p;
+    return S4C_OK;
+}
 
+hipError_t launch_tree_attn(const AttnPlan& p, const AttnArgs& a, int dtype, hipStream_t st) {
+    return p.large ? launch_tree_attn_large(a, dtype, st) : launch_tree_attn_small(a, dtype, st);
+}
+
+s4c_status tree_attn_impl(const s4c_attn_shape* shape, const void* q, const void* k_tree, const void* v_tree,
+                          const void* k_cache, const void* v_cache, const int32_t* block_table, int32_t max_blocks,
+                          int32_t page_shift, int32_t num_pages, const int32_t* cache_len, const int32_t* parent,
+                          int32_t max_cache_len, float scale, void* out, int32_t* status, void* workspace,
+                          size_t workspace_bytes, void* hip_stream) {
+    AttnPlan p;
+    AttnArgs a;
+    const s4c_status ok = tree_attn_prepare(shape, q, k_tree, v_tree, k_cache, v_cache, block_table, max_blocks, page_shift, num_pages,
+                                            cache_len, parent, max_cache_len, scale, out, status, workspace, workspace_bytes, &p, &a);
+    if (ok != S4C_OK) return ok;
     hipStream_t st = (hipStream_t)hip_stream;
     // Parts are combined by a second kernel: the kernel boundary is what makes one workgroup's
     // partial results visible to another across the chip's separate L2s at no extra cost.
-    hipError_t e = p.large ? launch_tree_attn_large(a, shape->dtype, st) : launch_tree_attn_small(a, shape->dtype, st);
+    hipError_t e = launch_tree_attn(p, a, shape->dtype, st);
     if (e == hipSuccess && p.split != 1) e = launch_attn_merge(a, shape->dtype, st);
     return e == hipSuccess ? S4C_OK : S4C_ERR_HIP;
 }
@@ -272,11 +290,10 @@ s4c_status accept_args_ok(int32_t B, int32_t N, int32_t V, int32_t logits_dtype,
 }
 
 // `workspace` holds at least s4c_accept_path_workspace_size(B, N, V) bytes, 256-byte aligned
-s4c_status accept_launch(int32_t B, int32_t N, int32_t V, int32_t logits_dtype, int32_t mode, float temperature,
-                         const void* logits, const int32_t* parent, const int32_t* tokens, const float* p_draft,
-                         const float* uniforms, int32_t max_path, int32_t* path, int32_t* accept_len,
-                         int32_t* accepted_tokens, int32_t* bonus_token, int32_t* status, void* workspace,
-                         void* hip_stream) {
+AcceptArgs accept_prepare(int32_t B, int32_t N, int32_t V, int32_t logits_dtype, int32_t mode, float temperature,
+                          const void* logits, const int32_t* parent, const int32_t* tokens, const float* p_draft,
+                          const float* uniforms, int32_t max_path, int32_t* path, int32_t* accept_len,
+                          int32_t* accepted_tokens, int32_t* bonus_token, int32_t* status, void* workspace) {
     AcceptArgs a;
     a.logits = logits; a.parent = parent; a.tokens = tokens; a.p_draft = p_draft; a.uniforms = uniforms;
     a.path = path; a.accept_len = accept_len; a.accepted_tokens = accepted_tokens;
@@ -297,7 +314,33 @@ s4c_status accept_launch(int32_t B, int32_t N, int32_t V, int32_t logits_dtype, 
     accept_plan(B, N, V, &a.chunks, &a.seg, &a.nseg);
     a.max_path = max_path; a.mode = mode; a.dtype = logits_dtype;
     a.inv_temp_log2 = kLog2e / (mode == S4C_STOCHASTIC ? temperature : 1.0f);
+    return a;
+}
+
+s4c_status accept_launch(const AcceptArgs& a, void* hip_stream) {
     return launch_accept(a, (hipStream_t)hip_stream) == hipSuccess ? S4C_OK : S4C_ERR_HIP;
+}
+}  // namespace
+
+namespace {
+s4c_status compact_prepare(const s4c_attn_shape* shape, const void* k_tree, const void* v_tree, void* k_cache, void* v_cache,
+                           int32_t* cache_len, const int32_t* path, const int32_t* accept_len, int32_t max_path,
+                           int32_t* dst_index, int32_t* status, CompactArgs* args) {
+    if (!shape || !k_tree || !v_tree || !k_cache || !v_cache || !cache_len || !path || !accept_len)
+        return S4C_ERR_NULL;
+    s4c_attn_shape s = *shape;
+    if (s.Hq <= 0) s.Hq = s.Hkv;          // Hq is not used by this call
+    if (s.Hkv > 0 && s.Hq % s.Hkv != 0) s.Hq = s.Hkv;
+    s4c_status why;
+    if (!shape_ok(&s, &why)) return why;
+    if (max_path <= 0 || s.S_cap <= 0) return S4C_ERR_SHAPE;
+    CompactArgs& a = *args;
+    a.k_tree = k_tree; a.v_tree = v_tree; a.k_cache = k_cache; a.v_cache = v_cache;
+    a.cache_len = cache_len; a.path = path; a.accept_len = accept_len; a.dst_index = dst_index;
+    a.status = status; a.B = s.B; a.Hkv = s.Hkv; a.N = s.N; a.S_cap = s.S_cap; a.max_path = max_path;
+    a.row_bytes = s.D * (s.dtype == S4C_F32 ? 4 : 2);
+    a.block_table = nullptr; a.max_blocks = a.page_shift = a.num_pages = 0;
+    return S4C_OK;
 }
 }  // namespace
 
@@ -315,8 +358,8 @@ s4c_status s4c_accept_path(int32_t B, int32_t N, int32_t V, int32_t logits_dtype
     if (ok != S4C_OK) return ok;
     const size_t need = s4c_accept_path_workspace_size(B, N, V);
     if (!workspace || workspace_bytes < need || (((uintptr_t)workspace) & 255)) return S4C_ERR_WORKSPACE;
-    return accept_launch(B, N, V, logits_dtype, mode, temperature, logits, parent, tokens, p_draft, uniforms, max_path, path,
-                         accept_len, accepted_tokens, bonus_token, status, workspace, hip_stream);
+    return accept_launch(accept_prepare(B, N, V, logits_dtype, mode, temperature, logits, parent, tokens, p_draft, uniforms, max_path, path,
+                                        accept_len, accepted_tokens, bonus_token, status, workspace), hip_stream);
 }
 
 s4c_status s4c_accept_path_static(int32_t B, int32_t N, int32_t V, int32_t logits_dtype, int32_t mode,
@@ -331,8 +374,8 @@ s4c_status s4c_accept_path_static(int32_t B, int32_t N, int32_t V, int32_t logit
     if (s4c_accept_path_workspace_size(B, N, V) > (size_t)S4C_STATIC_SCRATCH_BYTES) return S4C_ERR_STATIC_SCRATCH;
     void* ws = nullptr;
     if (static_scratch(&ws) != hipSuccess) return S4C_ERR_HIP;
-    return accept_launch(B, N, V, logits_dtype, mode, temperature, logits, parent, tokens, p_draft, uniforms, max_path, path,
-                         accept_len, accepted_tokens, bonus_token, status, ws, hip_stream);
+    return accept_launch(accept_prepare(B, N, V, logits_dtype, mode, temperature, logits, parent, tokens, p_draft, uniforms, max_path, path,
+                                        accept_len, accepted_tokens, bonus_token, status, ws), hip_stream);
 }
 
 size_t s4c_accept_resample_workspace_size(int32_t B, int32_t N, int32_t V, int32_t max_path) {
@@ -377,21 +420,9 @@ s4c_status s4c_kv_compact(const s4c_attn_shape* shape, const void* k_tree, const
                           void* k_cache, void* v_cache, int32_t* cache_len, const int32_t* path,
                           const int32_t* accept_len, int32_t max_path, int32_t* dst_index,
                           int32_t* status, void* hip_stream) {
-    if (!shape || !k_tree || !v_tree || !k_cache || !v_cache || !cache_len || !path || !accept_len)
-        return S4C_ERR_NULL;
-    s4c_attn_shape s = *shape;
-    if (s.Hq <= 0) s.Hq = s.Hkv;          // Hq is not used by this call
-    if (s.Hkv > 0 && s.Hq % s.Hkv != 0) s.Hq = s.Hkv;
-    s4c_status why;
-    if (!shape_ok(&s, &why)) return why;
-    if (max_path <= 0 || s.S_cap <= 0) return S4C_ERR_SHAPE;
-
     CompactArgs a;
-    a.k_tree = k_tree; a.v_tree = v_tree; a.k_cache = k_cache; a.v_cache = v_cache;
-    a.cache_len = cache_len; a.path = path; a.accept_len = accept_len; a.dst_index = dst_index;
-    a.status = status; a.B = s.B; a.Hkv = s.Hkv; a.N = s.N; a.S_cap = s.S_cap; a.max_path = max_path;
-    a.row_bytes = s.D * (s.dtype == S4C_F32 ? 4 : 2);
-    a.block_table = nullptr; a.max_blocks = a.page_shift = a.num_pages = 0;
+    const s4c_status ok = compact_prepare(shape, k_tree, v_tree, k_cache, v_cache, cache_len, path, accept_len, max_path, dst_index, status, &a);
+    if (ok != S4C_OK) return ok;
     return launch_compact(a, (hipStream_t)hip_stream) == hipSuccess ? S4C_OK : S4C_ERR_HIP;
 }
 
@@ -593,6 +624,48 @@ s4c_status s4c_draft_linear(int32_t T, int32_t H, int32_t Hout, int32_t dtype, c
         return S4C_OK;
     }
     return launch_draft_linear(a, (hipStream_t)hip_stream) == hipSuccess ? S4C_OK : S4C_ERR_HIP;
+}
+
+size_t s4c_verify_step_workspace_size(const s4c_attn_shape* shape, int32_t V) {
+    s4c_status why;
+    if (!shape || !shape_ok(shape, &why) || V <= 0) return 0;
+    return s4c_accept_path_workspace_size(shape->B, shape->N, V) + (step_message_bytes(shape->B, shape->Hkv) + 255) / 256 * 256;
+}
+
+s4c_status s4c_verify_step(const s4c_step* p, void* hip_stream) {
+    if (!p) return S4C_ERR_NULL;
+    hipStream_t st = (hipStream_t)hip_stream;
+    AttnPlan plan;
+    AttnArgs attn;
+    CompactArgs compact;
+    s4c_status ok = tree_attn_prepare(&p->shape, p->q, p->k_tree, p->v_tree, p->k_cache, p->v_cache, nullptr, 0, 0, 0, p->cache_len, p->parent,
+                                      p->max_cache_len, p->scale, p->out, p->attn_status, p->attn_workspace, p->attn_workspace_bytes,
+                                      &plan, &attn);
+    if (ok != S4C_OK) return ok;
+    const int32_t B = p->shape.B, N = p->shape.N, V = p->V;
+    ok = accept_args_ok(B, N, V, p->logits_dtype, p->mode, p->temperature, p->logits, p->parent, p->tokens, p->p_draft, p->uniforms,
+                        p->max_path, p->path, p->accept_len, p->accepted_tokens, p->bonus_token);
+    if (ok != S4C_OK) return ok;
+    if (!p->accept_workspace || p->accept_workspace_bytes < s4c_verify_step_workspace_size(&p->shape, V) ||
+        (((uintptr_t)p->accept_workspace) & 255))
+        return S4C_ERR_WORKSPACE;
+    ok = compact_prepare(&p->shape, p->k_tree, p->v_tree, p->k_cache, p->v_cache, p->cache_len, p->path, p->accept_len, p->max_path,
+                         p->dst_index, p->compact_status, &compact);
+    if (ok != S4C_OK) return ok;
+    const AcceptArgs accept = accept_prepare(B, N, V, p->logits_dtype, p->mode, p->temperature, p->logits, p->parent, p->tokens, p->p_draft,
+                                             p->uniforms, p->max_path, p->path, p->accept_len, p->accepted_tokens, p->bonus_token,
+                                             p->accept_status, p->accept_workspace);
+    hipError_t e = launch_tree_attn(plan, attn, p->shape.dtype, st);
+    if (p->logits_dtype == p->shape.dtype) {
+        if (e == hipSuccess)
+            e = launch_step(attn, plan.split != 1, accept, compact,
+                            (unsigned long long*)((char*)p->accept_workspace + s4c_accept_path_workspace_size(B, N, V)), st);
+    } else {
+        if (e == hipSuccess && plan.split != 1) e = launch_attn_merge(attn, p->shape.dtype, st);
+        if (e == hipSuccess) e = launch_accept(accept, st);
+        if (e == hipSuccess) e = launch_compact(compact, st);
+    }
+    return e == hipSuccess ? S4C_OK : S4C_ERR_HIP;
 }
 
 #pragma GCC visibility pop

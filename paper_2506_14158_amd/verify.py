@@ -29,7 +29,9 @@ class TreeVerifier:
         self.dst_index = torch.empty(B, max_path, **i32)
         self.compact_status = torch.zeros(B, **i32)
         self.attn_ws = _b.alloc_workspace(_b.s4c_tree_attn_workspace_size(self.shape, max_cache_len), device)
-        self.accept_ws = _b.alloc_workspace(_b.s4c_accept_path_workspace_size(B, N, V), device)
+        # (also holds what the workgroups of a whole step tell each other)
+        self.accept_ws = _b.alloc_workspace(max(_b.s4c_accept_path_workspace_size(B, N, V),
+                                                _b.s4c_verify_step_workspace_size(self.shape, V)), device)
         # sequential acceptance: the exchange slots of the workgroup teams (a few hundred KB at most), allocated
         # here so that no call allocates later (a step may be under graph capture)
         self.resample_ws = _b.alloc_workspace(max(256, _b.s4c_accept_resample_workspace_size(B, N, V, max_path)), device)
@@ -61,6 +63,11 @@ class TreeVerifier:
 
     def step(self, q, k_tree, v_tree, k_cache, v_cache, cache_len, parent, logits, tokens, mode: int,
              p_draft=None, uniforms=None, temperature: float = 1.0, scale: float = 0.0):
+        if _b.s4c_verify_step(q, k_tree, v_tree, k_cache, v_cache, cache_len, parent, logits, tokens, mode, p_draft, uniforms,
+                              temperature, scale, self.out, self.attn_status, self.attn_ws, self.path, self.accept_len,
+                              self.accepted_tokens, self.bonus_token, self.accept_status, self.accept_ws, self.dst_index,
+                              self.compact_status, self.max_cache_len, self.max_path):
+            return
         self.tree_attn(q, k_tree, v_tree, k_cache, v_cache, cache_len, parent, scale)
         self.accept_path(logits, parent, tokens, mode, p_draft, uniforms, temperature)
         self.kv_compact(k_tree, v_tree, k_cache, v_cache, cache_len)
