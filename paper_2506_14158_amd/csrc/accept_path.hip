@@ -28,8 +28,8 @@
 // flagged S4C_SEQ_TIMEOUT and gets the empty result.  Workgroups are dispatched in grid order, so
 // by the time a collector starts every other workgroup of its sequence has been given a compute unit.
 //
-// step_kernel: the workgroups of the attention merge first (it only needs the attention kernel to have ended), then the
-// acceptance scan with its collectors, then workgroups that append the accepted path's K/V rows to the cache: a few per
+// step_kernel: the acceptance scan with its collectors, then the workgroups of the attention merge (it only needs the
+// attention kernel to have ended; the other chain is the longer one), then workgroups that append the accepted path's K/V rows to the cache: a few per
 // sequence, a group of KV heads each, which wait for a message from the collector (the path, the cache length it
 // has read and advanced).  At batch 1 the three launches this replaces were 2 us of work each behind 2 us of launch, and a
 // sequence's rows, copied by one workgroup, waited for one address translation after another (each KV head's
@@ -501,6 +501,11 @@ __global__ __launch_bounds__(kThreads) void accept_kernel(AcceptArgs a) {
 template <typename T>
 __global__ __launch_bounds__(kThreads) void step_kernel(AttnArgs attn, AcceptArgs a, StepArgs x) {
     int wg = blockIdx.x;
+    if (wg < x.scan_wgs) {
+        scan_segment<T, true>(a, x, wg);
+        return;
+    }
+    wg -= x.scan_wgs;
     if (wg < x.merge_wgs) {
         const int unit = wg / x.merge_chunks, chunk = wg - unit * x.merge_chunks;
         if (x.attn_D == 64) merge::merge_rows<T, 64>(attn, unit, chunk, x.merge_passes);
@@ -508,11 +513,6 @@ __global__ __launch_bounds__(kThreads) void step_kernel(AttnArgs attn, AcceptArg
         return;
     }
     wg -= x.merge_wgs;
-    if (wg < x.scan_wgs) {
-        scan_segment<T, true>(a, x, wg);
-        return;
-    }
-    wg -= x.scan_wgs;
     copy_rows(x, a, wg / x.copiers, wg % x.copiers);
 }
 

@@ -19,7 +19,8 @@ __device__ __forceinline__ void merge_rows(const AttnArgs& a, int unit, int chun
     constexpr int VW = D / 32;                                   // floats per lane
     const int sub = threadIdx.x & 31;
     const int b = unit / a.Hkv, kvh = unit - b * a.Hkv;
-    const int g0 = a.ws_parts[2 * unit], g1 = a.ws_parts[2 * unit + 1];
+    // split: the unit's teams, whether they had tiles or not; balanced: as the teams noted
+    const int g0 = a.split > 0 ? unit * a.split : a.ws_parts[2 * unit], g1 = a.split > 0 ? g0 + a.split - 1 : a.ws_parts[2 * unit + 1];
     if (g0 == g1) return;                                        // written by its one team already
     for (int pass = 0; pass < passes; ++pass) {
         const int r = (chunk * passes + pass) * kRows + (threadIdx.x >> 5);
@@ -62,7 +63,7 @@ __device__ __forceinline__ void merge_rows(const AttnArgs& a, int unit, int chun
                     if (p0 + p < n) {
                         const float wp = __shfl(w, p0 + p, 32);
 #pragma unroll
-                        for (int j = 0; j < VW; ++j) o[j] = fmaf(v[p][j], wp, o[j]);
+                        for (int j = 0; j < VW; ++j) o[j] = wp > 0.f ? fmaf(v[p][j], wp, o[j]) : o[j];   // (0: v may never have been written)
                     }
             }
         }

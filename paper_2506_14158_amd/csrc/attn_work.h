@@ -123,7 +123,7 @@ __device__ __forceinline__ Walk walk_first(const AttnArgs& a, const Lens& lens, 
         const int run = (w.tiles + a.split - 1) / a.split;
         w.tile = k * run;
         w.tile_end = min(w.tiles, w.tile + run);
-        if (w.tile >= w.tile_end) w.b = -1;
+        if (w.tile >= w.tile_end) w.b = -1;         // (an empty run: see note_empty)
         return w;
     }
     const Order order(a, lens);
@@ -162,37 +162,26 @@ __device__ __forceinline__ bool walk_is_whole(const Walk& w) { return w.tile == 
 // that begins a unit (slot 1)
 __device__ __forceinline__ size_t part_row(const AttnArgs& a, int team, int slot) { return ((size_t)team * 2 + slot) * a.M; }
 
-// ---- what a workgroup needs to know about a sequence besides its length
-// parent[b][tid], requested ahead of its use (workgroups have at least kMaxNodes threads)
-__device__ __forceinline__ int load_parent(const AttnArgs& a, int b) {
-    const int tid = threadIdx.x;
-    return tid < a.N ? a.parent[(size_t)b * a.N + tid] : -1;
-}
-// Checks the sequence (S4C_SEQ_BAD_TREE, S4C_SEQ_BAD_LEN; the same answer in all its workgroups) and leaves parent[] in
-// `spar`.  flags: one word per wavefront.  One barrier; the caller has one of its own before the next call.
-template <int NT, bool PAGED>
-__device__ __forceinline__ int check_sequence(const AttnArgs& a, const Lens& lens, int b, int parent, int32_t* spar, int32_t* flags) {
-    static_assert(NT >= kMaxNodes, "a thread per node");
-    const int tid = threadIdx.x, P = usable(a, lens.at(a, b));
-    int bad_page = 0;
-    if constexpr (PAGED) {
-        // every page the prefix touches must be a page of the pool
-        for (int i = tid; i < ((P + (1 << a.page_shift) - 1) >> a.page_shift); i += NT) {
-            const int id = a.block_table[(size_t)b * a.max_blocks + i];
-            bad_page |= (id < 0 || id >= a.num_pages);
-        }
-    }
-    if (tid < a.N) spar[tid] = parent;
-    const int mine = (__any(tid < a.N && (parent < -1 || parent >= tid)) ? S4C_SEQ_BAD_TREE : 0) |
-                     (__any(bad_page) || P != lens.at(a, b) ? S4C_SEQ_BAD_LEN : 0);
-    if ((tid & 63) == 0) flags[tid >> 6] = mine;
-    __syncthreads();
-    int all = 0;
+// ---- what a workgroup needs to know about a sequence besides its length (each wavefront finds out by itself: no barrier)
+// parent[] (in LDS) is not a tree
+__device__ __forceinline__ bool tree_is_bad(const AttnArgs& a, const int32_t* spar) {
+    const int lane = threadIdx.x & 63;
+    bool bad = false;
 #pragma unroll
-    for (int w = 0; w < NT / 64; ++w) all |= flags[w];
-    return __builtin_amdgcn_readfirstlane(all);
+    for (int i = lane; i < kMaxNodes; i += 64)
+        if (i < a.N) bad = bad || spar[i] < -1 || spar[i] >= i;
+    return __any(bad) != 0;
 }
-// 128-bit ancestor-or-self masks of a valid tree, from `spar`
+// a page that the prefix of length P touches is not a page of the pool
+__device__ __forceinline__ bool pages_are_bad(const AttnArgs& a, int b, int P) {
+    bool bad = false;
+    for (int i = threadIdx.x & 63; i < ((P + (1 << a.page_shift) - 1) >> a.page_shift); i += 64) {
+        const int id = a.block_table[(size_t)b * a.max_blocks + i];
+        bad = bad || id < 0 || id >= a.num_pages;
+    }
+    return __any(bad) != 0;
+}
+// 128-bit ancestor-or-self masks of a valid tree, from `spar`; the caller's barrier makes them visible
 __device__ __forceinline__ void build_masks(const AttnArgs& a, const int32_t* spar, uint32_t* anc) {
     const int tid = threadIdx.x;
     if (tid < a.N) {
@@ -200,10 +189,23 @@ __device__ __forceinline__ void build_masks(const AttnArgs& a, const int32_t* sp
         for (int j = tid; j >= 0; j = spar[j]) m[j >> 5] |= 1u << (j & 31);
         *(uint4*)(anc + tid * 4) = make_uint4(m[0], m[1], m[2], m[3]);
     }
-    __syncthreads();
+}
+// node of query row r (r / G without an integer division per row)
+__device__ __forceinline__ int node_of_row(int r, int G, float inv_G) {
+    int q = (int)((float)r * inv_G);
+    const int rem = r - q * G;
+    return rem < 0 ? q - 1 : rem >= G ? q + 1 : q;
 }
 
-// Tells the merge kernel which teams share a unit: the team that begins it and the team that ends it say so.
+// A team without tiles in a split launch leaves empty parts (sum 0), so that the merge kernel need not know how many
+// teams had some.
+__device__ __forceinline__ void note_empty(const AttnArgs& a, int team, int mt, int rows) {
+    if (a.split > 1 && team < a.teams)
+        for (int r = mt * rows + (int)threadIdx.x; r < min(a.M, (mt + 1) * rows); r += blockDim.x)
+            *(float2*)(a.ws_ml + (part_row(a, team, team % a.split == 0 ? 1 : 0) + r) * 2) = make_float2(-INFINITY, 0.f);
+}
+
+// Tells the merge kernel which teams share a unit (balanced launches): the team that begins it and the team that ends it.
 __device__ __forceinline__ void note_parts(const AttnArgs& a, int team, const Walk& w) {
     const size_t unit = (size_t)w.b * a.Hkv + w.kvh;
     if (w.tile == 0) a.ws_parts[2 * unit] = team;

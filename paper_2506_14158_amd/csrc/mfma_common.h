@@ -34,6 +34,11 @@ __device__ __forceinline__ void dma16(const void* sbase, uint32_t voff, uint32_t
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_base) : "memory");
 }
 
+// Lane i's 4 bytes land at lds_base + 4 i.
+__device__ __forceinline__ void dma4(const void* g, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(g), "s"(lds_base) : "memory");
+}
+
 // Values that are wave-uniform by construction but that the compiler cannot prove uniform.
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 __device__ __forceinline__ const unsigned char* uniform(const unsigned char* p) {

@@ -37,7 +37,7 @@ using namespace mfma;
 
 constexpr int kBN = 64;                     // keys per tile
 constexpr float kLazyLog2 = 8.0f;           // full tiles rescale only when a row maximum grew by more than 2^8
-constexpr int lds_bytes_for(int ns, int d) { return ns * 2 * kBN * d * 2 + kMaxNodes * 16 + kMaxNodes * 4 + 64; }
+constexpr int lds_bytes_for(int ns, int d) { return ns * 2 * kBN * d * 2 + kMaxNodes * 16 + kMaxNodes * 4; }
 
 template <int WR, int NS, int WPE, bool PAGED, bool F16, int kD>
 __global__ __launch_bounds__(WR * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
@@ -59,7 +59,6 @@ void tree_attn_mfma_kernel(AttnArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     uint32_t* anc = (uint32_t*)(smem + NS * kStageB);        // [kMaxNodes][4]
     int32_t* spar = (int32_t*)(anc + kMaxNodes * 4);         // [kMaxNodes]
-    int32_t* flags = spar + kMaxNodes;                       // [WR]
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -95,7 +94,10 @@ void tree_attn_mfma_kernel(AttnArgs a) {
 
     const work::Lens lens(a);
     work::Walk cw = work::walk_first(a, lens, team);      // what is multiplied
-    if (cw.b < 0) return;
+    if (cw.b < 0) {
+        work::note_empty(a, team, mt, BM);
+        return;
+    }
     work::Walk pw = cw;                                   // what is loaded
     const int n_share = uniform(cw.left + cw.tile_end - cw.tile);
     int issued = 0, done = 0;
@@ -171,15 +173,45 @@ void tree_attn_mfma_kernel(AttnArgs a) {
         ++issued;
         end_tile();
     };
-    issue_next();
 
-    const bool wave_on = mt * BM + wave * 32 < M;         // some of this wave's rows exist
+    // ---- The first segment's start is a chain of memory latencies, so everything it needs is requested at once:
+    // parent[], this wave's 32 Q rows (into the ring's last two stages, swizzled like K rows), and the tiles of the
+    // other stages.  All of it goes straight to LDS, so that waiting for Q does not mean waiting for the tiles behind it
+    // (the compiler knows nothing of these loads; a wait of its own for a register load counts them in).
+    const uint32_t q_stage = (NS - 2) * kStageB + wave * (32 * kRowB);
+    const int rq0 = mt * BM + wave * 32;
+    bool len_bad = work::usable(a, lens.at(a, cw.b)) != lens.at(a, cw.b);
+    if constexpr (PAGED) len_bad = len_bad || work::pages_are_bad(a, cw.b, work::usable(a, lens.at(a, cw.b)));
+    if (wave < 2 && wave * 64 + lane < N)
+        dma4(a.parent + (size_t)cw.b * N + wave * 64 + lane,
+             __builtin_amdgcn_readfirstlane(lds0 + NS * kStageB + kMaxNodes * 16 + wave * 256));
+    {
+        const float inv_G = 1.0f / (float)G;
+        const unsigned char* qb = (const unsigned char*)a.q + ((size_t)cw.b * N * a.Hq + cw.kvh * G) * kRowB;
+#pragma unroll
+        for (int c = 0; c < 32 / kRPI; ++c) {
+            const int row = kRPI * c + lane / kLPR, pc = lane % kLPR;
+            const int r = min(rq0 + row, M - 1), nd = work::node_of_row(r, G, inv_G);        // past the last row: any row
+            dma16(qb + ((size_t)nd * a.Hq + (r - nd * G)) * kRowB + ((pc ^ k_swz(row)) << 4),
+                  __builtin_amdgcn_readfirstlane(lds0 + q_stage + c * 1024));
+        }
+    }
+    for (int t = 0; t < NS - 2 && t < n_share; ++t) issue_next();
+    if (issued == NS - 2) wait_vmcnt<2 * CH * (NS - 2)>(); else wait_vmcnt<0>();
+
     // ---- this lane's query row.  Q^T fragments: B operand of step t holds d = 16 t + 8 g32 + (0..7) of the row.
-    // A segment's fragments and its sequence's parent[] are requested before the previous segment is written out.
-    const int rq = mt * BM + wave * 32 + (lane & 31);
+    // A later segment's fragments (and parent[]) are loaded before the previous one is written out.
+    const bool wave_on = rq0 < M;                         // some of this wave's rows exist
+    const int rq = rq0 + (lane & 31);
     const bool rvalid = rq < M;
     const int node = rvalid ? rq / G : 0, g = rvalid ? rq - node * G : 0;
     bf16x8 qf[kKT];
+#pragma unroll
+    for (int t = 0; t < kKT; ++t) {
+        uint4 raw = *(const uint4*)(smem + q_stage + k_off[t]);
+        if (!rvalid) raw = make_uint4(0, 0, 0, 0);
+        qf[t] = __builtin_bit_cast(bf16x8, raw);
+    }
     auto load_q = [&](int b, int kvh) __attribute__((always_inline)) {
         const bf16_t* qrow = (const bf16_t*)a.q + (((size_t)b * N + node) * a.Hq + kvh * G + g) * kD + g32 * 8;
 #pragma unroll
@@ -189,10 +221,12 @@ void tree_attn_mfma_kernel(AttnArgs a) {
             qf[t] = __builtin_bit_cast(bf16x8, raw);
         }
     };
-    int parent = work::load_parent(a, cw.b);
-    load_q(cw.b, cw.kvh);
+#pragma unroll
+    for (int t = 0; t < kKT; ++t) asm volatile("" : "+v"(qf[t]));          // in registers before the barrier
+    __syncthreads();                                      // Q and parent[] are here, their stages free
+    while (issued < NS - 1 && issued < n_share) issue_next();
 
-    int b_known = -1, flagged = 0;
+    int parent = -1, b_known = cw.b;
     bool masks = false;                                   // anc[] holds b_known's masks
     while (cw.b >= 0) {
     const int b = cw.b, kvh = cw.kvh;
@@ -200,13 +234,20 @@ void tree_attn_mfma_kernel(AttnArgs a) {
     if (b != b_known) {
         b_known = b;
         masks = false;
-        flagged = work::check_sequence<NT, PAGED>(a, lens, b, parent, spar, flags);
-        if (a.status && tid == 0 && cw.tile == 0 && kvh == 0 && mt == 0) a.status[b] = flagged;
+        len_bad = P != lens.at(a, b);
+        if constexpr (PAGED) len_bad = len_bad || work::pages_are_bad(a, b, P);
+        __syncthreads();                                  // the previous sequence's parent[] is no longer read
+        if (tid < N) spar[tid] = parent;
+        __syncthreads();
     }
     uint32_t amask[4] = {0, 0, 0, 0};
-    if (t_end > u_pref && !flagged) {
-        if (!masks) work::build_masks(a, spar, anc);
-        masks = true;
+    if (t_end > u_pref) {
+        if (!masks) {
+            if (!work::tree_is_bad(a, spar)) work::build_masks(a, spar, anc);
+            else if (tid < N) *(uint4*)(anc + tid * 4) = make_uint4(0, 0, 0, 0);
+            __syncthreads();
+            masks = true;
+        }
         if (rvalid) {
             const uint4 m = *(const uint4*)(anc + node * 4);
             amask[0] = m.x; amask[1] = m.y; amask[2] = m.z; amask[3] = m.w;
@@ -371,7 +412,6 @@ void tree_attn_mfma_kernel(AttnArgs a) {
     // vmcnt wait of its own inside the tile loop.
 #pragma unroll
     for (int t = 0; t < kKT; ++t) asm volatile("" : "+v"(qf[t]));
-    while (issued < done + NS - 1 && issued < n_share) issue_next();       // (the first segment: the rest of the ring)
 
     auto sync = [&]() __attribute__((always_inline)) {
         // tile `done` has landed once at most NS-2 younger tiles of this wave are outstanding
@@ -410,11 +450,13 @@ void tree_attn_mfma_kernel(AttnArgs a) {
 
     const work::Walk nw = work::walk_next(a, lens, cw);
     if (nw.b >= 0) {
-        if (nw.b != b) parent = work::load_parent(a, nw.b);
+        if (nw.b != b && tid < N) parent = a.parent[(size_t)nw.b * N + tid];
         load_q(nw.b, nw.kvh);
     }
-    if (a.split != 1 && mt == 0 && tid == 0) work::note_parts(a, team, cw);
+    if (a.split == 0 && mt == 0 && tid == 0) work::note_parts(a, team, cw);
     // ---- write this lane's row: d = 32 db + 8 (j/4) + 4 g32 + (j%4)
+    const int flagged = (work::tree_is_bad(a, spar) ? S4C_SEQ_BAD_TREE : 0) | (len_bad ? S4C_SEQ_BAD_LEN : 0);
+    if (a.status && tid == 0 && cw.tile == 0 && kvh == 0 && mt == 0) a.status[b] = flagged;
     const float l_tot = flagged ? 0.f : l_run + __shfl_xor(l_run, 32);       // a flagged sequence: zero output
     if (work::walk_is_whole(cw)) {
         if (rvalid) {

@@ -26,7 +26,7 @@ using namespace mfma;
 
 constexpr int kBN = 32;                      // keys per tile
 constexpr float kLazyLog2 = 8.0f;            // full tiles rescale only when a row maximum grew by more than 2^8
-constexpr int kAuxB = kMaxNodes * 16 + kMaxNodes * 4 + 64;
+constexpr int kAuxB = kMaxNodes * 16 + kMaxNodes * 4;
 
 enum Elem { kB16 = 0, kH16 = 1, kF32 = 2 };  // bf16, fp16, fp32
 
@@ -77,7 +77,6 @@ void tree_attn_smallm_kernel(AttnArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     uint32_t* anc = (uint32_t*)(smem + C::kRingB);            // [kMaxNodes][4]
     int32_t* spar = (int32_t*)(anc + kMaxNodes * 4);          // [kMaxNodes]
-    int32_t* flags = spar + kMaxNodes;                        // [waves]
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -120,7 +119,10 @@ void tree_attn_smallm_kernel(AttnArgs a) {
 
     const work::Lens lens(a);
     work::Walk cw = work::walk_first(a, lens, team);      // what is multiplied
-    if (cw.b < 0) return;
+    if (cw.b < 0) {
+        work::note_empty(a, team, mt, 32 * kRBW);
+        return;
+    }
     work::Walk pw = cw;                                   // what is loaded
     int issued = 0, done = 0;                             // rounds
 
@@ -197,19 +199,44 @@ void tree_attn_smallm_kernel(AttnArgs a) {
         pw.tile += kKG;
         end_round();
     };
-    // The first rounds start streaming now; what a segment needs besides K and V is requested behind them.  (The
-    // direct-to-LDS loads are invisible to the compiler; loads it does know about may follow them, since completion
-    // is in order and its waits then only become stricter.)
+    // ---- The first segment's start is a chain of memory latencies, so everything it needs is requested at once:
+    // parent[], this wave's 32 Q rows (into the ring's last round, swizzled like K rows), and the first NR - 1
+    // rounds.  All of it goes straight to LDS, so that waiting for Q does not mean waiting for the rounds behind it
+    // (the compiler knows nothing of these loads; a wait of its own for a register load counts them in).
+    const uint32_t q_stage = (uint32_t)(kNR - 1) * C::kRoundB + wave * C::kTileKB;
+    const int rq0 = (mt * kRBW + rb) * 32;
+    bool len_bad = work::usable(a, lens.at(a, cw.b)) != lens.at(a, cw.b);
+    if constexpr (PAGED) len_bad = len_bad || work::pages_are_bad(a, cw.b, work::usable(a, lens.at(a, cw.b)));
+    if (wave < 2 && wave * 64 + lane < N)
+        dma4(a.parent + (size_t)cw.b * N + wave * 64 + lane,
+             __builtin_amdgcn_readfirstlane(lds0 + C::kRingB + kMaxNodes * 16 + wave * 256));
+    {
+        const float inv_G = 1.0f / (float)G;
+        const unsigned char* qb = (const unsigned char*)a.q + ((size_t)cw.b * N * a.Hq + cw.kvh * G) * kRowB;
+#pragma unroll
+        for (int c = 0; c < C::kTileKB / 1024; ++c) {
+            const int row = kRPI * c + lane / kLPR, pc = lane % kLPR;
+            const int r = min(rq0 + row, M - 1), nd = work::node_of_row(r, G, inv_G);        // past the last row: any row
+            dma16(qb + ((size_t)nd * a.Hq + (r - nd * G)) * kRowB + ((pc ^ C::k_swz(row)) << 4),
+                  __builtin_amdgcn_readfirstlane(lds0 + q_stage + c * 1024));
+        }
+    }
 #pragma unroll
     for (int r = 0; r < kNR - 1; ++r)
         if (pw.b >= 0) issue_round();
+    if (issued == kNR - 1) wait_vmcnt<2 * kCH * (kNR - 1)>(); else wait_vmcnt<0>();
 
-    // ---- this lane's query row.  A segment's Q fragments and its sequence's parent[] are requested before the previous
-    // segment is written out.
-    const int rq = (mt * kRBW + rb) * 32 + (lane & 31);
+    // ---- this lane's query row; a later segment's Q fragments (and parent[]) are loaded before the previous one is
+    // written out
+    const int rq = rq0 + (lane & 31);
     const bool rvalid = rq < M;
     const int node = rvalid ? rq / G : 0, gh = rvalid ? rq - node * G : 0;
     uint4 qf[kKT];           // 16-bit: elements 16 t + 8 g32 .. + 7; fp32: elements 8 t + 4 g32 .. + 3
+#pragma unroll
+    for (int t = 0; t < kKT; ++t) {
+        qf[t] = *(const uint4*)(smem + q_stage + k_off[t]);
+        if (!rvalid) qf[t] = make_uint4(0, 0, 0, 0);
+    }
     auto load_q = [&](int b, int kvh) __attribute__((always_inline)) {
         const unsigned char* qrow = (const unsigned char*)a.q + ((((size_t)b * N + node) * a.Hq + kvh * G + gh) * kD) * C::kEs + g32 * 16;
 #pragma unroll
@@ -218,10 +245,7 @@ void tree_attn_smallm_kernel(AttnArgs a) {
             if (rvalid) qf[t] = *(const uint4*)(qrow + 32 * t);
         }
     };
-    int parent = work::load_parent(a, cw.b);
-    load_q(cw.b, cw.kvh);
-
-    int b_known = -1, flagged = 0;
+    int parent = -1, b_known = cw.b;
     bool masks = false;                                       // anc[] holds b_known's masks
     while (cw.b >= 0) {
         const int b = cw.b, kvh = cw.kvh;
@@ -230,14 +254,22 @@ void tree_attn_smallm_kernel(AttnArgs a) {
         if (b != b_known) {
             b_known = b;
             masks = false;
-            flagged = work::check_sequence<kThreads, PAGED>(a, lens, b, parent, spar, flags);
-            if (a.status && tid == 0 && cw.tile == 0 && kvh == 0 && mt == 0) a.status[b] = flagged;
+            len_bad = P != lens.at(a, b);
+            if constexpr (PAGED) len_bad = len_bad || work::pages_are_bad(a, b, P);
+            __syncthreads();                                  // the previous sequence's parent[] is no longer read
+            if (tid < N) spar[tid] = parent;
+            __syncthreads();
         }
         // ancestor words of this row, pre-shifted for this half of the wave
         uint32_t amask[4] = {0, 0, 0, 0};
-        if (t_end > u_pref && !flagged) {
-            if (!masks) work::build_masks(a, spar, anc);
-            masks = true;
+        if (t_end > u_pref) {
+            if (!masks) {
+                __syncthreads();                              // (the first segment: parent[] has landed)
+                if (!work::tree_is_bad(a, spar)) work::build_masks(a, spar, anc);
+                else if (tid < N) *(uint4*)(anc + tid * 4) = make_uint4(0, 0, 0, 0);
+                __syncthreads();
+                masks = true;
+            }
             if (rvalid) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) amask[q] = anc[node * 4 + q] >> (4 * g32);
@@ -366,21 +398,6 @@ void tree_attn_smallm_kernel(AttnArgs a) {
             if (pw.b >= 0) issue_round();
         };
         int t = uniform(cw.tile);
-        // While the loads run ahead inside this segment's full prefix tiles, nothing has to be decided per round.
-        if (uniform(pw.b) == uniform(b) && uniform(pw.kvh) == uniform(kvh)) {
-            const int n = uniform(p_full);
-            for (int i = 0; i < n; ++i, ++done) {
-                wait_vmcnt<2 * kCH * (kNR - 2)>();
-                __syncthreads();
-                issue_full();
-                ++issued;
-                tile(std::integral_constant<bool, false>{}, 0u);
-            }
-            t += n * kKG;
-            pw.tile += n * kKG;
-            p_full = 0;
-            end_round();
-        }
         for (const int e = min(P / kBN, t_end) - kKG; t <= e; t += kKG, ++done) {
             sync_and_prefetch();
             tile(std::integral_constant<bool, false>{}, 0u);
@@ -402,10 +419,12 @@ void tree_attn_smallm_kernel(AttnArgs a) {
 
         const work::Walk nw = work::walk_next(a, lens, cw);
         if (nw.b >= 0) {
-            if (nw.b != b) parent = work::load_parent(a, nw.b);
+            if (nw.b != b && tid < N) parent = a.parent[(size_t)nw.b * N + tid];
             load_q(nw.b, nw.kvh);
         }
         // ---- merge the key groups of each row into key group 0, one 32-column block at a time
+        const int flagged = (work::tree_is_bad(a, spar) ? S4C_SEQ_BAD_TREE : 0) | (len_bad ? S4C_SEQ_BAD_LEN : 0);
+        if (a.status && tid == 0 && cw.tile == 0 && kvh == 0 && mt == 0) a.status[b] = flagged;
         float l_tot = flagged ? 0.f : l_run + __shfl_xor(l_run, 32);              // a flagged sequence: zero output
         float* mo = (float*)(smem + C::kRingB + kAuxB);                       // [KG-1][RBW][32 rows][kMergeRow]
         float* mml = mo + (kKG - 1) * kRBW * 32 * C::kMergeRow;               // [KG-1][RBW][32 rows][2]
@@ -456,7 +475,7 @@ void tree_attn_smallm_kernel(AttnArgs a) {
             }
             if (db + 1 < kDB) __syncthreads();
         }
-        if (a.split != 1 && mt == 0 && tid == 0) work::note_parts(a, team, cw);
+        if (a.split == 0 && mt == 0 && tid == 0) work::note_parts(a, team, cw);
         // ---- key group 0 writes the row: d = 32 db + 8 (j/4) + 4 g32 + (j%4)
         if (kg == 0 && rvalid) {
             if (work::walk_is_whole(cw)) {
