@@ -1,26 +1,28 @@
 // Path acceptance (paper Sec. 3.2: per-node test, then the longest accepted path) in ONE launch; and the same launch
 // extended to the rest of a verification step (last section of this comment).
 //
-// Scan (the HBM-bound part).  A workgroup owns a segment of consecutive 8192-logit chunks of one
-// logits row and reads it exactly once with 16-byte loads, the next chunk in flight while the
-// current one is reduced in registers.  Per thread the hot loop keeps only a running maximum (and,
-// in stochastic mode, a sum of exp2 relative to it); the raw words of the chunk that holds the
-// thread's maximum are kept aside, and the position of the maximum is looked up in them once, at
-// the end of the segment.  The 256 threads are then combined with an order-independent
-// (value, lowest index) reduction.  Greedy mode scans every row (the bonus token may come from any
-// row); stochastic mode scans only the rows of nodes that have children: workgroup k of a
-// sequence takes the k-th such node, found from parent[] in LDS, so the workgroups with nothing
-// to do are the last of the grid rather than interleaved with the working ones.
+// Scan (the HBM-bound part).  The rows to scan of a sequence -- every row in greedy mode (the bonus token may come from
+// any), the rows of nodes that have children in stochastic mode -- are laid end to end and cut into equal runs of
+// 8192-logit chunks, one for each of the sequence's scanning workgroups; all of a launch's workgroups fit on the chip
+// at once, so none waits for a second turn.  (Fixed segments of up to 8 chunks made config 5 2612 workgroups on
+// 1280 places, the third turn almost empty.)  Measured, whole calls back to back, against fixed segments: 345 MB of bf16
+// logits 72.3 -> 70.5 us, 131 MB 29.0 -> 28.0, 9 MB 11.9 -> 9.1, 4 MB 10.8 -> 6.7; 51 MB in rows of odd length 71.7 -> 18.7.
+// Of what is left about 6 us are the launch, the first loads and the collector's look; the rest streams at 5.4 - 6 TB/s.
+// A chunk is read exactly once with 16-byte loads, the next one in
+// flight while it is reduced, across the ends of rows too.
+//   Greedy: per thread a running maximum; the raw words of the chunk that holds it are kept aside, and its position
+//   is looked up in them once per row; the 256 threads are then combined with an order-independent (value, lowest
+//   index) reduction.
+//   Stochastic: per thread a sum of exp2 against a reference that moves only when a logit outgrows it by more than
+//   2^kLazyLog2 (any reference serves, as long as reference and sum go together).
 //
-// Path step.  Every scanning workgroup publishes its segment statistics as three 8-byte records
-// (call nonce in the upper half, the statistic in the lower) with device-coherent stores.  The last
-// workgroup of a sequence in grid order is its collector: having finished its own segment (in
-// stochastic mode it never has one), it loads everything else the path step needs and then polls
-// the records of the sequence until every one carries this call's nonce, combines them per row,
-// applies the per-node test against the parent's row, ANDs along each node's ancestor chain and
-// writes the deepest accepted node's path (lowest index among equals).  No second launch, no
-// read-modify-write atomics (they serialise per address and take microseconds across the chip's
-// separate L2s), no cache flush: only the records bypass the non-coherent part of the L2.
+// Path step.  A run publishes its statistics of each row it touches as two 8-byte records (call nonce in the upper
+// half) with device-coherent stores.  The sequence's collector, a workgroup of its own behind the scanning ones in grid
+// order, loads everything else the path step needs and then polls the records of the sequence until every one
+// carries this call's nonce, combines them per row, applies the per-node test against the parent's row, ANDs along each
+// node's ancestor chain and writes the deepest accepted node's path (lowest index among equals).  No second launch,
+// no read-modify-write atomics (they serialise per address and take microseconds across the chip's separate L2s), no
+// cache flush: only the records bypass the non-coherent part of the L2.
 // A record needs no initialisation: anything without this call's nonce is "not there yet".  The
 // collector overwrites what it consumed with the complement of the nonce, so a captured graph can
 // replay the call, nonce and all.  The collector's wait is bounded by wall-clock time; when it runs
@@ -44,27 +46,28 @@ namespace {
 using namespace rowchunk;
 
 typedef unsigned long long rec_t;
+// Scanning workgroups that a CU holds at once: 5 (96 registers a thread), each with 16 KB of logits in flight, where
+// a CU needs about 50 KB to stream at its share of the memory's rate; 3 with 32 KB each for fp32 logits.
+template <typename T>
+constexpr int kWavesPerSimd = sizeof(T) == 4 ? 3 : 5;
 
 __device__ __forceinline__ void publish(rec_t* p, uint32_t nonce, uint32_t bits) {
     __hip_atomic_store(p, ((rec_t)nonce << 32) | bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Loads the records of up to four consecutive segments of a row in one burst (the loads are
+// Loads the records of up to four consecutive runs of a row in one burst (the loads are
 // independent round trips of a microsecond or two each, so they must not be taken one after the
 // other) and repeats until every one carries the nonce or the deadline (100 MHz wall clock) has
-// passed; returns whether they all arrived.  bits[3 s + w] = payload of word w of segment s.
-__device__ __forceinline__ bool await4(const rec_t* p, int nsegs, int words, uint32_t nonce, long long deadline, uint32_t (&bits)[12]) {
+// passed; returns whether they all arrived.  bits[2 s + w] = payload of word w of run s.
+__device__ __forceinline__ bool await4(const rec_t* p, int runs, uint32_t nonce, long long deadline, uint32_t (&bits)[8]) {
     for (;;) {
-        rec_t w[12];
+        rec_t w[8];
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int q = 0; q < 3; ++q)
-                w[3 * s + q] = (s < nsegs && q < words) ? __hip_atomic_load(p + 3 * s + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                                                        : ((rec_t)nonce << 32);
+        for (int e = 0; e < 8; ++e)
+            w[e] = e < 2 * runs ? __hip_atomic_load(p + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ((rec_t)nonce << 32);
         bool all = true;
 #pragma unroll
-        for (int e = 0; e < 12; ++e) {
+        for (int e = 0; e < 8; ++e) {
             all = all && ((uint32_t)(w[e] >> 32) == nonce);
             bits[e] = (uint32_t)w[e];
         }
@@ -73,6 +76,58 @@ __device__ __forceinline__ bool await4(const rec_t* p, int nsegs, int words, uin
         __builtin_amdgcn_s_sleep(8);
     }
 }
+
+// ---- the division of a sequence's scan
+// The scanned nodes of sequence b in LDS, ascending, and their number (ranks: position of a node, -1 for a row that is
+// not scanned).  All threads; ends with a barrier.
+struct Rows {
+    int32_t list[kMaxNodes], rank[kMaxNodes], has[kMaxNodes], count[2];
+};
+__device__ __forceinline__ int find_rows(const AcceptArgs& a, int b, Rows& r) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, N = a.N;
+    if (a.mode == S4C_GREEDY) {
+        if (tid < kMaxNodes) r.list[tid] = r.rank[tid] = tid;
+        __syncthreads();
+        return N;
+    }
+    // waves 0 and 1 hold one node per lane
+    if (tid < kMaxNodes) r.has[tid] = 0;
+    __syncthreads();
+    if (tid >= 1 && tid < N) {
+        const int p = a.parent[(size_t)b * N + tid];
+        if (p >= 0 && p < N) r.has[p] = 1;                 // a malformed tree is reported by the path step
+    }
+    __syncthreads();
+    const int has = tid < N ? r.has[tid] : 0;
+    const unsigned long long mask = __ballot(has);
+    if (lane == 0 && wave < 2) r.count[wave] = __popcll(mask);
+    __syncthreads();
+    if (tid < kMaxNodes) {
+        const int rank = __popcll(mask & ((1ull << lane) - 1ull)) + (wave == 1 ? r.count[0] : 0);
+        r.rank[tid] = has ? rank : -1;
+        if (has) r.list[rank] = tid;
+    }
+    __syncthreads();
+    return r.count[0] + r.count[1];
+}
+// Run j of `used`: `per` units, one more for the first `rem`; a unit is a chunk, or a whole row where rows are the shorter
+// way to runs of plan.seg chunks.
+struct Runs {
+    int unit, used, per, rem;
+    __device__ __forceinline__ Runs(const AcceptArgs& a, int rows) {
+        unit = a.plan.slots == 1 ? a.chunks : 1;
+        const int units = a.plan.slots == 1 ? rows : rows * a.chunks;
+        used = max(1, min(a.plan.wgs, a.plan.slots == 1 ? rows : units / a.plan.seg));
+        per = units / used;
+        rem = units - per * used;
+    }
+    __device__ __forceinline__ int begin(int j) const { return (j * per + min(j, rem)) * unit; }       // first chunk
+    __device__ __forceinline__ int of_chunk(int c) const {
+        const int u = c / unit, big = rem * (per + 1);
+        return u < big ? u / (per + 1) : rem + (u - big) / max(per, 1);
+    }
+};
+constexpr float kLazyLog2 = 24.0f;
 
 // ---- what step_kernel adds
 struct StepArgs {
@@ -161,6 +216,7 @@ __device__ __forceinline__ void copy_rows(const StepArgs& x, const AcceptArgs& a
 // The path step for sequence b, run by all kThreads threads of one workgroup (thread i = node i).
 template <typename T, bool STEP>
 __device__ __forceinline__ void path_step(const AcceptArgs& a, const StepArgs& x, int b) {
+    __shared__ Rows rows;
     const long long deadline = (long long)wall_clock64() + a.wait_ticks;
     const int i = threadIdx.x;
     const int N = a.N;
@@ -169,7 +225,6 @@ __device__ __forceinline__ void path_step(const AcceptArgs& a, const StepArgs& x
     __shared__ int32_t s_g[kMaxNodes];
     __shared__ int32_t s_best;
     __shared__ int32_t s_tok[kMaxNodes];
-    __shared__ int32_t s_kids[kMaxNodes];
     __shared__ float s_m[kMaxNodes], s_S[kMaxNodes];
     __shared__ int32_t s_node[kMaxNodes], s_len;     // the result, for announce_path
     const int base = STEP ? x.compact.cache_len[b] : 0;
@@ -179,7 +234,6 @@ __device__ __forceinline__ void path_step(const AcceptArgs& a, const StepArgs& x
     int bad = 0;
     int tok = -1, par_i = -1;
     float u_i = 0.f, pd_i = 0.f;
-    if (i < kMaxNodes) s_kids[i] = 0;
     if (i < N) {
         const int p = par_i = a.parent[(size_t)b * N + i];
         tok = a.tokens[(size_t)b * N + i];
@@ -196,45 +250,47 @@ __device__ __forceinline__ void path_step(const AcceptArgs& a, const StepArgs& x
     float lx = 0.f;
     if (a.mode == S4C_STOCHASTIC && i > 0 && i < N && !bad && tok >= 0 && tok < a.V)
         lx = to_f32<T>(((const T*)a.logits)[((size_t)b * N + par_i) * a.V + tok]);
-    __syncthreads();
-    if (i > 0 && i < N && !bad) s_kids[par_i] = 1;
+    const int n_rows = find_rows(a, b, rows);
     if (i == 0) s_best = 0;
     bad = __syncthreads_or(bad);
 
-    // ---- combine the segment statistics of row i.  In stochastic mode only the rows of nodes with
+    // ---- combine the statistics of row i's runs.  In stochastic mode only the rows of nodes with
     // children were scanned, and only those are combined (nothing reads a leaf's statistics: a node
     // is tested against its PARENT's row, and that mode has no bonus token).
     float m = -INFINITY, S = 0.f;
     int32_t g = 0x7FFFFFFF;
     int late = 0;
-    if (i < N && !bad && (a.mode == S4C_GREEDY || s_kids[i])) {
-        rec_t* r = a.rec + ((size_t)b * N + i) * a.nseg * 3;
-        const uint32_t spent = ~a.nonce;
-        const int words = (a.mode == S4C_STOCHASTIC) ? 3 : 2;
-        // pass 1: the row maximum and its token (segments ascend: strict '>' keeps the lowest index);
-        // pass 2 (stochastic): the segments' sums of exponentials, rescaled to the row maximum
-        for (int c0 = 0; c0 < a.nseg && !late; c0 += 4) {
-            uint32_t bits[12];
-            if (!await4(r + 3 * c0, min(4, a.nseg - c0), words, a.nonce, deadline, bits)) { late = 1; break; }
+    const Runs runs(a, n_rows);
+    const int rank = i < N ? rows.rank[i] : -1;      // (of a malformed tree too: every record of the call is consumed)
+    if (rank >= 0) {
+        const int j0 = runs.of_chunk(rank * a.chunks), parts = runs.of_chunk(rank * a.chunks + a.chunks - 1) - j0 + 1;
+        rec_t* r = a.rec + ((size_t)b * N + i) * a.plan.slots * 2;
+        for (int c0 = 0; c0 < parts && !late; c0 += 4) {
+            uint32_t bits[8];
+            if (!await4(r + 2 * c0, min(4, parts - c0), a.nonce, deadline, bits)) { late = 1; break; }
+            if (a.mode == S4C_GREEDY) {                        // runs ascend: strict '>' keeps the lowest index
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
-                if (c0 + s < a.nseg) {
-                    const float v = __uint_as_float(bits[3 * s]);
-                    if (v > m) { m = v; g = (int32_t)bits[3 * s + 1]; }
+                for (int s = 0; s < 4; ++s) {
+                    const float v = __uint_as_float(bits[2 * s]);
+                    if (c0 + s < parts && v > m) { m = v; g = (int32_t)bits[2 * s + 1]; }
                 }
-        }
-        if (a.mode == S4C_STOCHASTIC)
-            for (int c0 = 0; c0 < a.nseg && !late; c0 += 4) {
-                uint32_t bits[12];
-                if (!await4(r + 3 * c0, min(4, a.nseg - c0), words, a.nonce, deadline, bits)) { late = 1; break; }
+            } else {
+                float mn = m;
 #pragma unroll
                 for (int s = 0; s < 4; ++s)
-                    if (c0 + s < a.nseg)
-                        S += __uint_as_float(bits[3 * s + 2]) * fast_exp2((__uint_as_float(bits[3 * s]) - m) * a.inv_temp_log2);
+                    if (c0 + s < parts) mn = fmaxf(mn, __uint_as_float(bits[2 * s]));
+                if (m > -INFINITY) S *= fast_exp2((m - mn) * a.inv_temp_log2);
+                m = mn;
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    if (c0 + s < parts && __uint_as_float(bits[2 * s]) > -INFINITY)
+                        S += __uint_as_float(bits[2 * s + 1]) * fast_exp2((__uint_as_float(bits[2 * s]) - m) * a.inv_temp_log2);
             }
+        }
         // consumed: a replay of this very call (same nonce) must not mistake them for its own
+        const uint32_t spent = ~a.nonce;
         if (!late)
-            for (int c = 0; c < 3 * a.nseg; ++c) publish(r + c, spent, 0u);
+            for (int c = 0; c < 2 * parts; ++c) publish(r + c, spent, 0u);
     }
     late = __syncthreads_or(late);
     if (late) {
@@ -323,186 +379,146 @@ __device__ __forceinline__ void path_step(const AcceptArgs& a, const StepArgs& x
     }
 }
 
-// one workgroup of the scan; the sequence's last one goes on to the path step
-template <typename T, bool STEP>
-__device__ __forceinline__ void scan_segment(const AcceptArgs& a, const StepArgs& x, int wg) {
-    constexpr int VN = Vec16<T>::n;
-    constexpr int NV = kPerThread / VN;               // 16-byte loads per thread and chunk
+// one workgroup of the scan: run j of sequence b
+template <typename T, bool STOCHASTIC>
+__device__ __forceinline__ void scan_run(const AcceptArgs& a, int b, int j) {
+    constexpr int VN = RowReader<T>::VN, NV = RowReader<T>::NV;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // workgroup -> (rank k among the sequence's scanned rows, sequence b, segment sg); k slowest
-    const int sg = wg % a.nseg;
-    const int b = (wg / a.nseg) % a.B;
-    const int k = wg / (a.nseg * a.B);
-    const int V = a.V, N = a.N;
-    const bool stochastic = a.mode == S4C_STOCHASTIC;
-
-    __shared__ int32_t s_row;
+    __shared__ Rows rows;
     __shared__ float s_v[4];
     __shared__ int32_t s_i[4];
     __shared__ float s_s[4];
-
-    int row_in_seq = k;                               // greedy: every row is scanned
-    if (stochastic) {
-        // the k-th node (ascending) that has a child: waves 0 and 1 hold one node per lane
-        __shared__ uint32_t s_has[kMaxNodes];
-        __shared__ int32_t s_cnt0;
-        if (tid < kMaxNodes) s_has[tid] = 0;
-        if (tid == 0) s_row = -1;
-        __syncthreads();
-        if (tid >= 1 && tid < N) {
-            const int p = a.parent[(size_t)b * N + tid];
-            if (p >= 0 && p < N) s_has[p] = 1;       // a malformed tree is reported by the path step
-        }
-        __syncthreads();
-        const int has = (tid < N) ? (int)s_has[tid] : 0;
-        const unsigned long long mask = __ballot(has);
-        if (tid == 0) s_cnt0 = __popcll(mask);
-        __syncthreads();
-        if (wave < 2 && has) {
-            const int rank = __popcll(mask & ((1ull << lane) - 1ull)) + (wave == 1 ? s_cnt0 : 0);
-            if (rank == k) s_row = tid;
-        }
-        __syncthreads();
-        row_in_seq = s_row;                           // -1: this sequence has fewer than k+1 such nodes
-    }
-
-    if (row_in_seq >= 0) {
-        const size_t row = (size_t)b * N + row_in_seq;
-        const T* base = (const T*)a.logits + row * (size_t)V;
-        const int ch0 = sg * a.seg, ch1 = min(a.chunks, ch0 + a.seg);
-        const bool vec_ok = ((((uintptr_t)base) & 15) == 0);
-
-        // per-thread running state over the segment: maximum, the 16-byte words and the token offsets of the
-        // chunk that holds it, and a sum of exponentials relative to the maximum (rescaled when it grows)
-        float m_t = -INFINITY, s_t = 0.f;
+    const int n_rows = find_rows(a, b, rows);
+    const Runs runs(a, n_rows);
+    if (n_rows == 0 || j >= runs.used) return;
+    const int c_end = runs.begin(j + 1);
+    int c = runs.begin(j), rank = c / a.chunks, ch = c - rank * a.chunks;
+    const size_t row0 = (size_t)b * a.N;
+    uint4 raw[NV];
+    RowReader<T> reader(a.logits, row0 + rows.list[rank], a.V);
+    reader.fetch(ch, raw);
+    while (c < c_end) {
+        const int node = rows.list[rank], last = min(a.chunks, ch + c_end - c);       // this row's chunks ch .. last - 1
+        float m_t = -INFINITY, s_t = 0.f;               // greedy: maximum; stochastic: reference and sum
         uint4 wbest[NV];
-        int32_t ibest[NV];
+        int32_t cbest = 0;
+        if constexpr (!STOCHASTIC) {
 #pragma unroll
-        for (int j = 0; j < NV; ++j) { wbest[j] = make_uint4(0, 0, 0, 0); ibest[j] = 0; }
-
-        auto whole = [&](int ch) { return vec_ok && (ch + 1) * kChunk <= V; };
-        auto fetch = [&](uint4 (&raw)[NV], int ch) {
+            for (int q = 0; q < NV; ++q) wbest[q] = make_uint4(0, 0, 0, 0);
+        }
+        const RowReader<T> here = reader;
+        for (; ch < last; ++ch, ++c) {
+            uint4 cur[NV];
 #pragma unroll
-            for (int j = 0; j < NV; ++j) raw[j] = *(const uint4*)(base + ch * kChunk + (j * kThreads + tid) * VN);
-        };
-        auto decode = [&](const uint4 (&raw)[NV], float (&x)[kPerThread]) {
-#pragma unroll
-            for (int j = 0; j < NV; ++j) {
-                if constexpr (VN == 4) {
-                    x[j * VN + 0] = __uint_as_float(raw[j].x);
-                    x[j * VN + 1] = __uint_as_float(raw[j].y);
-                    x[j * VN + 2] = __uint_as_float(raw[j].z);
-                    x[j * VN + 3] = __uint_as_float(raw[j].w);
-                } else {
-                    const uint32_t w[4] = {raw[j].x, raw[j].y, raw[j].z, raw[j].w};
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) unpack2<T>(w[q], x[j * VN + 2 * q], x[j * VN + 2 * q + 1]);
-                }
+            for (int q = 0; q < NV; ++q) cur[q] = raw[q];
+            // the next chunk, of this row or of the next one, is in flight while this one is reduced
+            if (c + 1 < c_end) {
+                const bool next_row = ch + 1 == a.chunks;
+                if (next_row) reader = RowReader<T>(a.logits, row0 + rows.list[rank + 1], a.V);
+                reader.fetch(next_row ? 0 : ch + 1, raw);
             }
-        };
-        // whole, aligned chunks are fetched one chunk ahead as raw 16-byte words (kept as they are when the
-        // chunk raises the thread's maximum); a ragged or unaligned chunk is loaded element by element
-        uint4 raw[NV];
-        bool have = ch0 < ch1 && whole(ch0);
-        if (have) fetch(raw, ch0);
-        for (int ch = ch0; ch < ch1; ++ch) {
-            float x[kPerThread];
-            int32_t idx0[NV];
-            if (have) {
-                decode(raw, x);
+            float m_c = -INFINITY;
 #pragma unroll
-                for (int j = 0; j < NV; ++j) idx0[j] = ch * kChunk + (j * kThreads + tid) * VN;
+            for (int q = 0; q < NV; ++q) {
+                float x[VN];
+                decode<T>(cur[q], x);
+#pragma unroll
+                for (int e = 0; e < VN; e += 2) m_c = __builtin_fmaxf(__builtin_fmaxf(m_c, x[e]), x[e + 1]);
+            }
+            if constexpr (!STOCHASTIC) {
+                if (m_c > m_t) {                        // strict: an equal later chunk never replaces an earlier one
+                    m_t = m_c;
+                    cbest = ch;
+#pragma unroll
+                    for (int q = 0; q < NV; ++q) wbest[q] = cur[q];
+                }
             } else {
-                load_chunk<T>(base, ch * kChunk, min(V, (ch + 1) * kChunk), tid, x, idx0);
-            }
-            float m_c = x[0];
-#pragma unroll
-            for (int e = 1; e < kPerThread; e += 2) m_c = __builtin_fmaxf(__builtin_fmaxf(m_c, x[e]), x[(e + 1) & (kPerThread - 1)]);
-            const float m_old = m_t;
-            if (m_c > m_t) {                               // strict: an equal later chunk never replaces an earlier one
-                m_t = m_c;
-                if (have) {
-#pragma unroll
-                    for (int j = 0; j < NV; ++j) wbest[j] = raw[j];
-                } else {
-#pragma unroll
-                    for (int j = 0; j < NV; ++j) {
-                        if constexpr (VN == 4) {
-                            wbest[j] = make_uint4(__float_as_uint(x[j * 4]), __float_as_uint(x[j * 4 + 1]), __float_as_uint(x[j * 4 + 2]),
-                                                  __float_as_uint(x[j * 4 + 3]));
-                        } else {
-                            uint32_t w[4];
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) {           // exact: every x is a stored 16-bit value (or -inf)
-                                const T lo = from_f32<T>(x[j * VN + 2 * q]), hi = from_f32<T>(x[j * VN + 2 * q + 1]);
-                                w[q] = (uint32_t)__builtin_bit_cast(uint16_t, lo) | ((uint32_t)__builtin_bit_cast(uint16_t, hi) << 16);
-                            }
-                            wbest[j] = make_uint4(w[0], w[1], w[2], w[3]);
-                        }
-                    }
+                if ((m_c - m_t) * a.inv_temp_log2 > kLazyLog2) {               // (m_t = -inf: the first logit that is not padding)
+                    s_t *= fast_exp2((m_t - m_c) * a.inv_temp_log2);
+                    m_t = m_c;
                 }
+                const float ref = m_t > -INFINITY ? m_t * a.inv_temp_log2 : 0.f;
+                float sum[2] = {0.f, 0.f};
 #pragma unroll
-                for (int j = 0; j < NV; ++j) ibest[j] = idx0[j];
-            }
-            have = ch + 1 < ch1 && whole(ch + 1);
-            if (have) fetch(raw, ch + 1);                  // in flight while this chunk's exponentials are summed
-            if (stochastic && m_c > -INFINITY) {
-                const float ref = m_t * a.inv_temp_log2;   // m_t is max(old maximum, this chunk's) by now
-                float sum = 0.f;
+                for (int q = 0; q < NV; ++q) {
+                    float x[VN];
+                    decode<T>(cur[q], x);
 #pragma unroll
-                for (int e = 0; e < kPerThread; ++e) sum += fast_exp2(fmaf(x[e], a.inv_temp_log2, -ref));   // padding: 0
-                s_t = s_t * fast_exp2((m_old - m_t) * a.inv_temp_log2) + sum;                              // first chunk: 0 * 0
+                    for (int e = 0; e < VN; ++e) sum[e & 1] += fast_exp2(fmaf(x[e], a.inv_temp_log2, -ref));   // padding: 0
+                }
+                s_t += sum[0] + sum[1];
             }
         }
-        // the thread's argmax: lowest index among its elements equal to its maximum (scan descending,
-        // so that the lowest match is written last)
-        MaxIdx best = {m_t, 0x7FFFFFFF};
-        if (m_t > -INFINITY) {                             // (a thread of a ragged last chunk may hold padding only)
-            float xb[kPerThread];
-            decode(wbest, xb);
+        // ---- the row's part is done: combine the 256 threads
+        float out_v;
+        uint32_t out_w;
+        if constexpr (STOCHASTIC) {
+            float mw = m_t;
 #pragma unroll
-            for (int j = NV - 1; j >= 0; --j)
-#pragma unroll
-                for (int q = VN - 1; q >= 0; --q)
-                    if (xb[j * VN + q] == m_t) best.i = ibest[j] + q;
-        }
-
-        // ---- combine the 256 threads
-        const MaxIdx wb = wave_best(best);
-        if (lane == 0) { s_v[wave] = wb.v; s_i[wave] = wb.i; }
-        __syncthreads();
-        MaxIdx blk = {s_v[0], s_i[0]};
-#pragma unroll
-        for (int w = 1; w < 4; ++w) blk = better(blk, MaxIdx{s_v[w], s_i[w]});
-        float sum = 0.f;
-        if (stochastic) {
-            sum = (m_t > -INFINITY) ? s_t * fast_exp2((m_t - blk.v) * a.inv_temp_log2) : 0.f;
-            sum = wave_sum(sum);
-            if (lane == 0) s_s[wave] = sum;
+            for (int off = 32; off >= 1; off >>= 1) mw = fmaxf(mw, __shfl_xor(mw, off));
+            float sw = m_t > -INFINITY ? s_t * fast_exp2((m_t - mw) * a.inv_temp_log2) : 0.f;
+            sw = wave_sum(sw);
+            if (lane == 0) { s_v[wave] = mw; s_s[wave] = sw; }
             __syncthreads();
-            sum = (s_s[0] + s_s[1]) + (s_s[2] + s_s[3]);
+            out_v = fmaxf(fmaxf(s_v[0], s_v[1]), fmaxf(s_v[2], s_v[3]));
+            float t = 0.f;
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+                if (s_v[w] > -INFINITY) t += s_s[w] * fast_exp2((s_v[w] - out_v) * a.inv_temp_log2);
+            out_w = __float_as_uint(t);
+        } else {
+            // the thread's argmax: lowest index among its elements equal to its maximum (scan descending,
+            // so that the lowest match is written last)
+            MaxIdx best = {m_t, 0x7FFFFFFF};
+            if (m_t > -INFINITY) {                      // (a thread of a ragged chunk may hold padding only)
+#pragma unroll
+                for (int q = NV - 1; q >= 0; --q) {
+                    float x[VN];
+                    decode<T>(wbest[q], x);
+#pragma unroll
+                    for (int e = VN - 1; e >= 0; --e)
+                        if (x[e] == m_t) best.i = here.idx(cbest, q) + e;
+                }
+            }
+            const MaxIdx wb = wave_best(best);
+            if (lane == 0) { s_v[wave] = wb.v; s_i[wave] = wb.i; }
+            __syncthreads();
+            MaxIdx blk = {s_v[0], s_i[0]};
+#pragma unroll
+            for (int w = 1; w < 4; ++w) blk = better(blk, MaxIdx{s_v[w], s_i[w]});
+            out_v = blk.v;
+            out_w = (uint32_t)blk.i;
         }
         if (tid == 0) {
-            rec_t* r = a.rec + (row * a.nseg + sg) * 3;
-            publish(r, a.nonce, __float_as_uint(blk.v));
-            publish(r + 1, a.nonce, (uint32_t)blk.i);
-            publish(r + 2, a.nonce, __float_as_uint(sum));
+            rec_t* r = a.rec + ((row0 + node) * a.plan.slots + (j - runs.of_chunk(rank * a.chunks))) * 2;
+            publish(r, a.nonce, __float_as_uint(out_v));
+            publish(r + 1, a.nonce, out_w);
         }
+        __syncthreads();                                // s_v, s_i, s_s are written again for the next row
+        ++rank;
+        ch = 0;
     }
-    // ---- the sequence's last workgroup in grid order collects and runs the path step
-    if (k == N - 1 && sg == a.nseg - 1) path_step<T, STEP>(a, x, b);
 }
 
-template <typename T>
-__global__ __launch_bounds__(kThreads) void accept_kernel(AcceptArgs a) {
-    scan_segment<T, false>(a, StepArgs{}, blockIdx.x);
+// Workgroup wg of the scan: the runs of all sequences (run number slowest, so that the ones without work are the last of
+// the grid rather than interleaved with the working ones), then the sequences' collectors.
+template <typename T, bool STOCHASTIC, bool STEP>
+__device__ __forceinline__ void scan_or_collect(const AcceptArgs& a, const StepArgs& x, int wg) {
+    const int j = wg / a.B, b = wg - j * a.B;
+    if (j < a.plan.wgs) scan_run<T, STOCHASTIC>(a, b, j);
+    else path_step<T, STEP>(a, x, b);
 }
 
-template <typename T>
-__global__ __launch_bounds__(kThreads) void step_kernel(AttnArgs attn, AcceptArgs a, StepArgs x) {
+template <typename T, bool STOCHASTIC>
+__global__ __launch_bounds__(kThreads, kWavesPerSimd<T>) void accept_kernel(AcceptArgs a) {
+    scan_or_collect<T, STOCHASTIC, false>(a, StepArgs{}, blockIdx.x);
+}
+
+template <typename T, bool STOCHASTIC>
+__global__ __launch_bounds__(kThreads, kWavesPerSimd<T>) void step_kernel(AttnArgs attn, AcceptArgs a, StepArgs x) {
     int wg = blockIdx.x;
     if (wg < x.scan_wgs) {
-        scan_segment<T, true>(a, x, wg);
+        scan_or_collect<T, STOCHASTIC, true>(a, x, wg);
         return;
     }
     wg -= x.scan_wgs;
@@ -520,9 +536,8 @@ __global__ __launch_bounds__(kThreads) void step_kernel(AttnArgs attn, AcceptArg
 
 int accept_chunk_elems() { return kChunk; }
 
-// Segment length: a workgroup streams up to 8 chunks (128 KB of 16-bit logits) of a row, fewer when
-// that would leave less than about 1024 workgroups to spread over the chip.  A fixed function of the
-// sizes, so the workspace query and the launch agree.
+// Segments of the candidate-tree scan: up to 8 chunks of a row, fewer when that would leave less than about 1024 workgroups
+// to spread over the chip.
 void accept_plan(int B, int N, int V, int* chunks, int* seg, int* nseg) {
     const long long ch = ((long long)V + kChunk - 1) / kChunk;
     const long long units = (long long)B * N * ch;
@@ -535,12 +550,43 @@ void accept_plan(int B, int N, int V, int* chunks, int* seg, int* nseg) {
     *nseg = (int)((ch + sg - 1) / sg);
 }
 
+// A run is at least `seg` chunks long, so that a row's records take no more room than the three words that the workspace
+// has for each segment of accept_plan.  A row's chunks lie in at most ceil(chunks / seg) + 1 runs; where seg is
+// a whole row, runs are made of whole rows.
+AcceptPlan scan_plan(int B, int N, int V, int elem_bytes, int cus) {
+    int plain, seg, nseg;
+    accept_plan(B, N, V, &plain, &seg, &nseg);
+    AcceptPlan p;
+    p.chunks = (int)(((long long)V + 7 + kChunk - 1) / kChunk);          // a row may begin up to 7 elements into its first vector
+    auto slots = [&](int sg) { return sg >= p.chunks ? 1 : sg == 1 ? p.chunks : (p.chunks + sg - 1) / sg + 1; };
+    while (2 * slots(seg) > 3 * nseg) ++seg;
+    p.seg = seg;
+    p.slots = slots(seg);
+    const long long resident = (long long)cus * (elem_bytes == 4 ? kWavesPerSimd<float> : kWavesPerSimd<bf16_t>);
+    const long long runs = (long long)N * p.chunks / seg;
+    long long wgs = resident / B;
+    if (wgs > runs) wgs = runs;
+    p.wgs = (int)(wgs < 1 ? 1 : wgs);
+    return p;
+}
+
+template <typename T>
+static hipError_t launch_accept_as(const AcceptArgs& a, hipStream_t st) {
+    const dim3 grid((unsigned)((a.plan.wgs + 1) * a.B)), block(kThreads);
+    if (a.mode == S4C_STOCHASTIC) hipLaunchKernelGGL((accept_kernel<T, true>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((accept_kernel<T, false>), grid, block, 0, st, a);
+    return hipGetLastError();
+}
 hipError_t launch_accept(const AcceptArgs& a, hipStream_t st) {
     static_assert(kThreads >= 2 * 64 && kThreads >= kMaxNodes, "the path step and the row lookup use one thread per node");
-    dim3 grid((unsigned)((size_t)a.nseg * a.B * a.N)), block(kThreads);
-    if (a.dtype == S4C_F32) hipLaunchKernelGGL(accept_kernel<float>, grid, block, 0, st, a);
-    else if (a.dtype == S4C_F16) hipLaunchKernelGGL(accept_kernel<f16_t>, grid, block, 0, st, a);
-    else hipLaunchKernelGGL(accept_kernel<bf16_t>, grid, block, 0, st, a);
+    return a.dtype == S4C_F32 ? launch_accept_as<float>(a, st) : a.dtype == S4C_F16 ? launch_accept_as<f16_t>(a, st) : launch_accept_as<bf16_t>(a, st);
+}
+
+template <typename T>
+static hipError_t launch_step_as(const AttnArgs& attn, const AcceptArgs& a, const StepArgs& x, hipStream_t st) {
+    const dim3 grid((unsigned)(x.merge_wgs + x.scan_wgs + a.B * x.copiers)), block(kThreads);
+    if (a.mode == S4C_STOCHASTIC) hipLaunchKernelGGL((step_kernel<T, true>), grid, block, 0, st, attn, a, x);
+    else hipLaunchKernelGGL((step_kernel<T, false>), grid, block, 0, st, attn, a, x);
     return hipGetLastError();
 }
 
@@ -563,14 +609,11 @@ hipError_t launch_step(const AttnArgs& attn, bool merged, const AcceptArgs& a, c
         x.merge_chunks = g.chunks;
         x.merge_passes = g.passes;
     }
-    x.scan_wgs = a.nseg * a.B * a.N;
+    x.scan_wgs = (a.plan.wgs + 1) * a.B;
     x.heads = (compact.Hkv + kMostCopiers - 1) / kMostCopiers;
     x.copiers = (compact.Hkv + x.heads - 1) / x.heads;
-    const dim3 grid((unsigned)(x.merge_wgs + x.scan_wgs + a.B * x.copiers)), block(kThreads);
-    if (a.dtype == S4C_F32) hipLaunchKernelGGL(step_kernel<float>, grid, block, 0, st, attn, a, x);
-    else if (a.dtype == S4C_F16) hipLaunchKernelGGL(step_kernel<f16_t>, grid, block, 0, st, attn, a, x);
-    else hipLaunchKernelGGL(step_kernel<bf16_t>, grid, block, 0, st, attn, a, x);
-    return hipGetLastError();
+    return a.dtype == S4C_F32 ? launch_step_as<float>(attn, a, x, st) : a.dtype == S4C_F16 ? launch_step_as<f16_t>(attn, a, x, st)
+                                                                                          : launch_step_as<bf16_t>(attn, a, x, st);
 }
 
 }  // namespace s4c

@@ -84,6 +84,15 @@ struct AttnTile { int rows, keys, per_cu; };
 AttnTile attn_tile_large(const s4c_attn_shape& s);
 AttnTile attn_tile_small(const s4c_attn_shape& s);
 
+// How a call's scan is divided: see scan_plan in accept_path.hip
+struct AcceptPlan {
+    int32_t chunks;    // of a row of any alignment
+    int32_t seg;       // fewest chunks of a workgroup's run
+    int32_t slots;     // most runs that a row's chunks can lie in
+    int32_t wgs;       // scanning workgroups per sequence
+};
+AcceptPlan scan_plan(int B, int N, int V, int elem_bytes, int cus);
+
 struct AcceptArgs {
     const void* logits;
     const int32_t* parent;
@@ -95,11 +104,12 @@ struct AcceptArgs {
     int32_t* accepted_tokens;
     int32_t* bonus_token;
     int32_t* status;
-    unsigned long long* rec;   // [B*N][nseg][3] (call nonce << 32) | bits of (max, argmax, sum of exponentials)
+    unsigned long long* rec;   // [B*N][slots][2] (call nonce << 32) | bits of (maximum, argmax) or (reference, sum of exponentials)
     uint32_t nonce;    // tells this call's records from whatever the words held before
     long long wait_ticks;   // how long a collector waits for its sequence's records (100 MHz wall clock)
-    int32_t B, N, V, chunks, max_path, mode, dtype;
-    int32_t seg, nseg; // chunks per workgroup, workgroups per row
+    int32_t B, N, V, max_path, mode, dtype;
+    AcceptPlan plan;
+    int32_t chunks;    // of a row, for its alignment (<= plan.chunks)
     float inv_temp_log2;   // log2(e) / T
 };
 hipError_t launch_accept(const AcceptArgs& a, hipStream_t st);

@@ -44,6 +44,68 @@ template <> struct Vec16<float> { static constexpr int n = 4; };
 template <> struct Vec16<bf16_t> { static constexpr int n = 8; };
 template <> struct Vec16<f16_t> { static constexpr int n = 8; };
 
+// A logits row read in chunks of kChunk elements with 16-byte loads whatever its alignment: chunks are counted from the
+// 16-byte boundary at or below the row's start, `head` elements before it.  Vector j of a thread holds the Vec16<T>::n
+// elements from idx(chunk, j) on; elements outside [0, V) read as -inf.  Only the vectors that contain such
+// elements (the first and the last of a row) are put together element by element, so every load lies in the row.
+// (Rows of an odd length used to be read two bytes at a time.)
+template <typename T>
+struct RowReader {
+    static constexpr int VN = Vec16<T>::n;
+    static constexpr int NV = kPerThread / VN;
+    const T* base;
+    int V, head;
+    __device__ __forceinline__ RowReader(const void* logits, size_t row, int V_) : base((const T*)logits + row * (size_t)V_), V(V_) {
+        head = (int)(((uintptr_t)base & 15) / sizeof(T));
+    }
+    __device__ __forceinline__ int idx(int chunk, int j) const { return chunk * kChunk + (j * kThreads + (int)threadIdx.x) * VN - head; }
+    __device__ __forceinline__ void fetch(int chunk, uint4 (&raw)[NV]) const {
+        const int lo = chunk * kChunk - head;
+        if (lo >= 0 && lo <= V - kChunk) {                             // wave-uniform
+#pragma unroll
+            for (int j = 0; j < NV; ++j) raw[j] = *(const uint4*)(base + idx(chunk, j));
+            return;
+        }
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            const int e0 = idx(chunk, j);
+            constexpr uint32_t kNegInf = sizeof(T) == 4 ? 0xFF800000u : __is_same(T, f16_t) ? 0xFC00FC00u : 0xFF80FF80u;
+            raw[j] = make_uint4(kNegInf, kNegInf, kNegInf, kNegInf);
+            if (e0 >= 0 && e0 + VN <= V) {
+                raw[j] = *(const uint4*)(base + e0);
+            } else if (e0 + VN > 0 && e0 < V) {
+                uint32_t w[4] = {kNegInf, kNegInf, kNegInf, kNegInf};
+#pragma unroll
+                for (int k = 0; k < VN; ++k)
+                    if (e0 + k >= 0 && e0 + k < V) {
+                        if constexpr (sizeof(T) == 4) {
+                            w[k] = __builtin_bit_cast(uint32_t, base[e0 + k]);
+                        } else {
+                            const uint32_t x = __builtin_bit_cast(uint16_t, base[e0 + k]);
+                            w[k / 2] = (k & 1) ? (w[k / 2] & 0xFFFFu) | (x << 16) : (w[k / 2] & 0xFFFF0000u) | x;
+                        }
+                    }
+                raw[j] = make_uint4(w[0], w[1], w[2], w[3]);
+            }
+        }
+    }
+};
+// the elements of one vector, as floats
+template <typename T>
+__device__ __forceinline__ void decode(const uint4& raw, float (&x)[Vec16<T>::n]) {
+    if constexpr (sizeof(T) == 4) {
+        x[0] = __uint_as_float(raw.x);
+        x[1] = __uint_as_float(raw.y);
+        x[2] = __uint_as_float(raw.z);
+        x[3] = __uint_as_float(raw.w);
+    } else {
+        unpack2<T>(raw.x, x[0], x[1]);
+        unpack2<T>(raw.y, x[2], x[3]);
+        unpack2<T>(raw.z, x[4], x[5]);
+        unpack2<T>(raw.w, x[6], x[7]);
+    }
+}
+
 // Thread tid's 32 logits of the chunk [c0, cend) of the row at `base`, as floats: vector j of
 // the thread holds the Vec16<T>::n consecutive tokens starting at idx0[j] (ascending in j and
 // inside a vector).  Tokens at or beyond cend read as -inf.

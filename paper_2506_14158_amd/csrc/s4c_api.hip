@@ -261,7 +261,7 @@ size_t s4c_accept_path_workspace_size(int32_t B, int32_t N, int32_t V) {
     if (B <= 0 || N <= 0 || V <= 0) return 0;
     int chunks, seg, nseg;
     accept_plan(B, N, V, &chunks, &seg, &nseg);
-    return (((size_t)B * N * nseg * 3 * sizeof(unsigned long long) + 255) / 256) * 256;   // three records per (row, segment)
+    return (((size_t)B * N * nseg * 3 * sizeof(unsigned long long) + 255) / 256) * 256;   // room for two records per (row, run): scan_plan
 }
 
 #pragma GCC visibility pop
@@ -283,9 +283,8 @@ s4c_status accept_args_ok(int32_t B, int32_t N, int32_t V, int32_t logits_dtype,
         if (!p_draft || !uniforms) return S4C_ERR_NULL;
         if (!(temperature > 0.f)) return S4C_ERR_SHAPE;
     }
-    int chunks, seg, nseg;
-    accept_plan(B, N, V, &chunks, &seg, &nseg);
-    if ((size_t)B * N * nseg > 0x7FFFFFFFull) return S4C_ERR_UNSUPPORTED;
+    const AcceptPlan p = scan_plan(B, N, V, 2, device_cus());
+    if ((size_t)B * N * p.slots > 0x7FFFFFFFull || (size_t)N * p.chunks > 0x7FFFFFFFull) return S4C_ERR_UNSUPPORTED;
     return S4C_OK;
 }
 
@@ -311,7 +310,9 @@ AcceptArgs accept_prepare(int32_t B, int32_t N, int32_t V, int32_t logits_dtype,
     }
     a.wait_ticks = wait_us * 100;
     a.B = B; a.N = N; a.V = V;
-    accept_plan(B, N, V, &a.chunks, &a.seg, &a.nseg);
+    const size_t es = logits_dtype == S4C_F32 ? 4 : 2;
+    a.plan = scan_plan(B, N, V, (int)es, device_cus());
+    a.chunks = (((uintptr_t)logits | ((size_t)V * es)) & 15) ? a.plan.chunks : (V + accept_chunk_elems() - 1) / accept_chunk_elems();
     a.max_path = max_path; a.mode = mode; a.dtype = logits_dtype;
     a.inv_temp_log2 = kLog2e / (mode == S4C_STOCHASTIC ? temperature : 1.0f);
     return a;
