@@ -8,11 +8,11 @@
 // list's last entry; ties to the lowest token id) and writes the list out at the end, next to the
 // maximum and the sum of exponentials of its part: no barrier, no workgroup-level step, no
 // cross-lane step per chunk unless the list changes.
-// Kernel 2 (topk_row): one wavefront per row merges the parts' candidates into the row's top
-// nchild tokens and turns their logits into probabilities.
-// Kernel 3 (layout): one workgroup per sequence numbers the nodes level by level from the child
-// counts (prefix sum), checks that the counts describe a tree of exactly N nodes, and scatters
-// parent / token / probability / level of every node.
+// Kernel 2 (topk_row): one wavefront per row finds from the sequence's child counts which numbers its children have
+// (level by level: a prefix sum), whether the counts describe a tree of exactly N nodes, merges the parts' candidates into the
+// row's top nchild tokens, turns their logits into probabilities, and writes its children.  The numbering needs 128
+// words that are requested with everything else, so doing it once per row costs less than a launch of its own did.
+// HBM bounds kernel 1; kernel 2 is a chain of two memory latencies.
 #include "row_chunk.h"
 
 namespace s4c {
@@ -22,7 +22,7 @@ namespace {
 using namespace rowchunk;
 constexpr int kK = 8;                 // most children per node
 
-template <typename T>
+template <typename T, bool ALIGNED>
 __global__ __launch_bounds__(kThreads) void topk_chunk_kernel(BuildArgs a) {
     constexpr int VN = Vec16<T>::n;
     constexpr int NV = kPerThread / VN;
@@ -36,7 +36,7 @@ __global__ __launch_bounds__(kThreads) void topk_chunk_kernel(BuildArgs a) {
     const int k = blockIdx.x / (a.nseg * a.B);
     __shared__ int32_t s_row, s_cnt0;
     const int my_nc = (tid < N) ? a.nchild[(size_t)b * N + tid] : 0;
-    const int has = my_nc > 0 && my_nc <= a.kmax;       // (an invalid count is flagged by the layout kernel)
+    const int has = my_nc > 0 && my_nc <= a.kmax;       // (an invalid count is flagged by the row kernel)
     const unsigned long long mask = __ballot(has);
     if (tid == 0) { s_cnt0 = __popcll(mask); s_row = -1; }
     __syncthreads();
@@ -49,18 +49,22 @@ __global__ __launch_bounds__(kThreads) void topk_chunk_kernel(BuildArgs a) {
     const int row = b * N + s_row;
     const int nc = a.nchild[row];
     const int V = a.V;
+    const RowReader<T> reader(a.logits, row, V);
     const T* base = (const T*)a.logits + (size_t)row * V;
     const int ch0 = sg * a.seg, ch1 = min(a.chunks, ch0 + a.seg);
-    const bool vec_ok = ((((uintptr_t)base) & 15) == 0);
 
-    // whole, aligned chunks are fetched one chunk ahead as raw 16-byte words
+    // chunks are fetched one ahead as raw 16-byte words (ALIGNED: whole chunks; a row's last one is read in place)
     uint4 raw[NV];
-    auto whole = [&](int c) { return vec_ok && (c + 1) * kChunk <= V; };
+    auto ahead = [&](int c) { return c < ch1 && (!ALIGNED || (c + 1) * kChunk <= V); };
     auto fetch = [&](int c) {
+        if constexpr (ALIGNED) {
 #pragma unroll
-        for (int j = 0; j < NV; ++j) raw[j] = *(const uint4*)(base + c * kChunk + (j * kThreads + tid) * VN);
+            for (int j = 0; j < NV; ++j) raw[j] = *(const uint4*)(base + c * kChunk + (j * kThreads + tid) * VN);
+        } else {
+            reader.fetch(c, raw);
+        }
     };
-    bool have = ch0 < ch1 && whole(ch0);
+    bool have = ahead(ch0);
     if (have) fetch(ch0);
     float m_e = -INFINITY, s_e = 0.f;                  // this thread's running maximum and sum of exponentials
     float lv[kK];                                      // the wavefront's list (uniform across lanes)
@@ -70,25 +74,19 @@ __global__ __launch_bounds__(kThreads) void topk_chunk_kernel(BuildArgs a) {
   for (int ch = ch0; ch < ch1; ++ch) {
     float x[kPerThread];
     int32_t idx0[NV];
-    if (have) {
+    if (!ALIGNED || have) {
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
-            idx0[j] = ch * kChunk + (j * kThreads + tid) * VN;
-            if constexpr (VN == 4) {
-                x[j * VN + 0] = __uint_as_float(raw[j].x);
-                x[j * VN + 1] = __uint_as_float(raw[j].y);
-                x[j * VN + 2] = __uint_as_float(raw[j].z);
-                x[j * VN + 3] = __uint_as_float(raw[j].w);
-            } else {
-                const uint32_t w[4] = {raw[j].x, raw[j].y, raw[j].z, raw[j].w};
+            idx0[j] = ALIGNED ? ch * kChunk + (j * kThreads + tid) * VN : reader.idx(ch, j);
+            float v[VN];
+            decode<T>(raw[j], v);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) unpack2<T>(w[q], x[j * VN + 2 * q], x[j * VN + 2 * q + 1]);
-            }
+            for (int q = 0; q < VN; ++q) x[j * VN + q] = v[q];
         }
     } else {
         load_chunk<T>(base, ch * kChunk, min(V, (ch + 1) * kChunk), tid, x, idx0);
     }
-    have = ch + 1 < ch1 && whole(ch + 1);
+    have = ahead(ch + 1);
     if (have) fetch(ch + 1);                           // in flight while this chunk is searched
 
     // this thread's share of the sum of exponentials, relative to its own running maximum (rescaled when that
@@ -173,13 +171,16 @@ __global__ __launch_bounds__(kThreads) void topk_chunk_kernel(BuildArgs a) {
 }
 
 __global__ __launch_bounds__(64) void topk_row_kernel(BuildArgs a) {
-    const int row = blockIdx.x, lane = threadIdx.x;
+    const int row = blockIdx.x, lane = threadIdx.x, N = a.N;
+    const int b = row / N, i = row - b * N;
     const int parts = a.nseg * 4;                            // a wavefront's quarter of a segment of chunks each
     const size_t o = (size_t)row * parts;
-    // the child count, this lane's part statistics and (few parts) its whole list are requested together: the
+    // the sequence's child counts, this lane's part statistics and (few parts) its whole list are requested together: the
     // kernel is a chain of memory latencies, not of work
     const bool few = parts <= 64, mine = lane < parts;
-    const int nc = a.nchild[row];
+    const int32_t* counts = a.nchild + (size_t)b * N;
+    const int c0 = lane < N ? counts[lane] : 0, c1 = lane + 64 < N ? counts[lane + 64] : 0;
+    const int32_t root = i == 0 ? a.root_token[b] : -1;
     const float pm0 = (few && mine) ? a.ws_max[o + lane] : -INFINITY;
     const float ps0 = (few && mine) ? a.ws_sum[o + lane] : 0.f;
     float v[kK];
@@ -189,7 +190,31 @@ __global__ __launch_bounds__(64) void topk_row_kernel(BuildArgs a) {
         v[e] = (few && mine) ? a.ws_topv[(o + lane) * kK + e] : -INFINITY;      // (slots beyond nc hold leftovers: masked below)
         t[e] = (few && mine) ? a.ws_topi[(o + lane) * kK + e] : -1;
     }
-    if (nc <= 0 || nc > a.kmax) return;
+    // ---- numbering: lane l holds the counts of nodes l and l + 64 and their inclusive sums (s0, s1)
+    const bool ok0 = c0 >= 0 && c0 <= a.kmax, ok1 = c1 >= 0 && c1 <= a.kmax;
+    int s0 = ok0 ? c0 : 0, s1 = ok1 ? c1 : 0;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int y0 = __shfl_up(s0, off), y1 = __shfl_up(s1, off);
+        if (lane >= off) { s0 += y0; s1 += y1; }
+    }
+    s1 += __builtin_amdgcn_readlane(s0, 63);
+    auto handed = [&](int n) { return n < 64 ? __builtin_amdgcn_readlane(s0, n) : __builtin_amdgcn_readlane(s1, n - 64); };  // by nodes 0 .. n
+    // an invalid count, a node that would be a parent before it exists, or not exactly N nodes
+    const bool early = (lane >= 1 && lane < N && s0 - c0 < lane) || (lane + 64 < N && s1 - c1 < lane + 64);
+    const bool bad = __any(!ok0 || !ok1 || early) || handed(N - 1) != N - 1;
+    if (lane == 0 && (i == 0 || bad)) {                      // the root, or any node of what is no tree
+        a.parent[row] = -1;
+        a.tokens[row] = root;
+        a.p_draft[row] = 0.f;
+        if (a.level) a.level[row] = 0;
+        if (i == 0 && a.status) a.status[b] = bad ? S4C_SEQ_BAD_TREE : 0;
+    }
+    if (bad) return;
+    const int first = 1 + (i > 0 ? handed(i - 1) : 0), nc = 1 + handed(i) - first;
+    if (nc == 0) return;
+    int lev = 1;                                             // the children's level: levels end where the previous one's children do
+    for (int end = 1; end <= i; end = 1 + handed(end - 1)) ++lev;     // (grows every time: node `end` has a parent before it)
     // row maximum and sum of exponentials from the parts' statistics
     float m = pm0;
     if (!few)
@@ -211,8 +236,11 @@ __global__ __launch_bounds__(64) void topk_row_kernel(BuildArgs a) {
     auto emit = [&](int r, MaxIdx best) {
         if (lane == 0) {
             const bool found = best.i != 0x7FFFFFFF;
-            a.row_tok[(size_t)row * kK + r] = found ? best.i : -1;
-            a.row_p[(size_t)row * kK + r] = found ? fast_exp2((best.v - m) * a.inv_temp_log2) / S : 0.f;
+            const size_t c = (size_t)b * N + first + r;
+            a.parent[c] = i;
+            a.tokens[c] = found ? best.i : -1;
+            a.p_draft[c] = found ? fast_exp2((best.v - m) * a.inv_temp_log2) / S : 0.f;
+            if (a.level) a.level[c] = lev;
         }
     };
     if (few) {
@@ -255,72 +283,30 @@ __global__ __launch_bounds__(64) void topk_row_kernel(BuildArgs a) {
     }
 }
 
-__global__ __launch_bounds__(kMaxNodes) void tree_layout_kernel(BuildArgs a) {
-    const int b = blockIdx.x, i = threadIdx.x, N = a.N;
-    __shared__ int32_t s_scan[kMaxNodes];
-    __shared__ int32_t s_par[kMaxNodes];
-    const int nc = (i < N) ? a.nchild[(size_t)b * N + i] : 0;
-    int bad = (i < N) && (nc < 0 || nc > a.kmax);
-    s_scan[i] = bad ? 0 : nc;
-    __syncthreads();
-    // inclusive prefix sum of the child counts (Hillis-Steele over 128 entries)
-    for (int off = 1; off < kMaxNodes; off <<= 1) {
-        const int v = (i >= off) ? s_scan[i - off] : 0;
-        __syncthreads();
-        s_scan[i] += v;
-        __syncthreads();
-    }
-    const int excl = s_scan[i] - ((i < N && !bad) ? nc : 0);     // children handed out before node i
-    if (i >= 1 && i < N && excl < i) bad = 1;                     // node i would be a parent before it exists
-    if (i == N - 1 && s_scan[i] != N - 1) bad = 1;                // the counts must describe exactly N nodes
-    bad = __syncthreads_or(bad);
-
-    int32_t* par = a.parent + (size_t)b * N;
-    int32_t* tok = a.tokens + (size_t)b * N;
-    float* pd = a.p_draft + (size_t)b * N;
-    if (i < N) s_par[i] = -1;
-    __syncthreads();
-    if (!bad && i < N) {
-        for (int r = 0; r < nc; ++r) s_par[1 + excl + r] = i;
-    }
-    __syncthreads();
-    if (i < N) {
-        int32_t t = -1;
-        float p = 0.f;
-        int lev = 0;
-        if (i == 0) {
-            t = a.root_token[b];
-        } else if (!bad) {
-            const int pi = s_par[i];
-            const int rank = i - (1 + (s_scan[pi] - a.nchild[(size_t)b * N + pi]));
-            t = a.row_tok[((size_t)b * N + pi) * kK + rank];
-            p = a.row_p[((size_t)b * N + pi) * kK + rank];
-            for (int j = i; j > 0; j = s_par[j]) ++lev;
-        }
-        par[i] = bad ? -1 : s_par[i];
-        tok[i] = t;
-        pd[i] = p;
-        if (a.level) a.level[(size_t)b * N + i] = lev;
-    }
-    if (i == 0 && a.status) a.status[b] = bad ? S4C_SEQ_BAD_TREE : 0;
-}
-
 }  // namespace
 
 int build_tree_max_children() { return kK; }
 int build_tree_chunk_elems() { return kChunk; }
 
+// Rows on 16-byte boundaries are read in plain chunks, others through RowReader.  Read through RowReader too, 335 MB of
+// aligned bf16 rows take 88 us instead of 82; rows of odd length read two bytes at a time, as the plain chunks would be,
+// 71.4 us instead of 43.6 (103 MB).
+template <typename T>
+static void launch_topk(const BuildArgs& a, hipStream_t st) {
+    const dim3 grid((unsigned)((size_t)a.B * a.N * a.nseg));
+    if (a.V % Vec16<T>::n == 0 && (((uintptr_t)a.logits) & 15) == 0)
+        hipLaunchKernelGGL((topk_chunk_kernel<T, true>), grid, dim3(kThreads), 0, st, a);
+    else
+        hipLaunchKernelGGL((topk_chunk_kernel<T, false>), grid, dim3(kThreads), 0, st, a);
+}
+
 hipError_t launch_build_tree(const BuildArgs& a, hipStream_t st) {
-    const dim3 grid1((unsigned)((size_t)a.B * a.N * a.nseg));
-    if (a.dtype == S4C_F32) hipLaunchKernelGGL(topk_chunk_kernel<float>, grid1, dim3(kThreads), 0, st, a);
-    else if (a.dtype == S4C_F16) hipLaunchKernelGGL(topk_chunk_kernel<f16_t>, grid1, dim3(kThreads), 0, st, a);
-    else hipLaunchKernelGGL(topk_chunk_kernel<bf16_t>, grid1, dim3(kThreads), 0, st, a);
+    if (a.dtype == S4C_F32) launch_topk<float>(a, st);
+    else if (a.dtype == S4C_F16) launch_topk<f16_t>(a, st);
+    else launch_topk<bf16_t>(a, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(topk_row_kernel, dim3((unsigned)(a.B * a.N)), dim3(64), 0, st, a);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(tree_layout_kernel, dim3(a.B), dim3(kMaxNodes), 0, st, a);
     return hipGetLastError();
 }
 

@@ -121,7 +121,7 @@ hipError_t launch_step(const AttnArgs& attn, bool merge, const AcceptArgs& accep
                        unsigned long long* messages, hipStream_t st);
 size_t step_message_bytes(int B, int Hkv);
 int accept_chunk_elems();
-void accept_plan(int B, int N, int V, int* chunks, int* seg, int* nseg);
+void accept_plan(int B, int N, int V, int head, int* chunks, int* seg, int* nseg);
 
 struct ResampleArgs {
     const void* logits;
@@ -179,8 +179,6 @@ struct BuildArgs {
     float* ws_sum;             // [B*N][chunks]
     float* ws_topv;            // [B*N][chunks][8]
     int32_t* ws_topi;          // [B*N][chunks][8]
-    int32_t* row_tok;          // [B*N][8]
-    float* row_p;              // [B*N][8]
     int32_t B, N, V, chunks, kmax, dtype;
     int32_t seg, nseg;         // chunks per workgroup of the scan, workgroups per row
     float inv_temp_log2;

@@ -53,17 +53,24 @@ template <typename T>
 struct RowReader {
     static constexpr int VN = Vec16<T>::n;
     static constexpr int NV = kPerThread / VN;
-    const T* base;
+    // (named as global memory: where the compiler lost track of that, the loads became flat ones, which wait for LDS too)
+    typedef const __attribute__((address_space(1))) T* Ptr;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    Ptr base;
     int V, head;
-    __device__ __forceinline__ RowReader(const void* logits, size_t row, int V_) : base((const T*)logits + row * (size_t)V_), V(V_) {
+    __device__ __forceinline__ RowReader(const void* logits, size_t row, int V_) : base((Ptr)((const T*)logits + row * (size_t)V_)), V(V_) {
         head = (int)(((uintptr_t)base & 15) / sizeof(T));
     }
     __device__ __forceinline__ int idx(int chunk, int j) const { return chunk * kChunk + (j * kThreads + (int)threadIdx.x) * VN - head; }
+    __device__ __forceinline__ uint4 vec(int e) const {
+        const u32x4 w = *(const __attribute__((address_space(1))) u32x4*)(base + e);
+        return make_uint4(w[0], w[1], w[2], w[3]);
+    }
     __device__ __forceinline__ void fetch(int chunk, uint4 (&raw)[NV]) const {
         const int lo = chunk * kChunk - head;
         if (lo >= 0 && lo <= V - kChunk) {                             // wave-uniform
 #pragma unroll
-            for (int j = 0; j < NV; ++j) raw[j] = *(const uint4*)(base + idx(chunk, j));
+            for (int j = 0; j < NV; ++j) raw[j] = vec(idx(chunk, j));
             return;
         }
 #pragma unroll
@@ -72,7 +79,7 @@ struct RowReader {
             constexpr uint32_t kNegInf = sizeof(T) == 4 ? 0xFF800000u : __is_same(T, f16_t) ? 0xFC00FC00u : 0xFF80FF80u;
             raw[j] = make_uint4(kNegInf, kNegInf, kNegInf, kNegInf);
             if (e0 >= 0 && e0 + VN <= V) {
-                raw[j] = *(const uint4*)(base + e0);
+                raw[j] = vec(e0);
             } else if (e0 + VN > 0 && e0 < V) {
                 uint32_t w[4] = {kNegInf, kNegInf, kNegInf, kNegInf};
 #pragma unroll
@@ -106,58 +113,22 @@ __device__ __forceinline__ void decode(const uint4& raw, float (&x)[Vec16<T>::n]
     }
 }
 
-// Thread tid's 32 logits of the chunk [c0, cend) of the row at `base`, as floats: vector j of
-// the thread holds the Vec16<T>::n consecutive tokens starting at idx0[j] (ascending in j and
+// Thread tid's 32 logits of the chunk [c0, cend) of the row at `base`, which begins and ends on a 16-byte boundary, as
+// floats: vector j of the thread holds the Vec16<T>::n consecutive tokens starting at idx0[j] (ascending in j and
 // inside a vector).  Tokens at or beyond cend read as -inf.
 template <typename T>
 __device__ __forceinline__ void load_chunk(const T* base, int c0, int cend, int tid, float (&x)[kPerThread],
                                            int32_t (&idx0)[kPerThread / Vec16<T>::n]) {
     constexpr int VN = Vec16<T>::n;
-    constexpr int NV = kPerThread / VN;
-    const bool vec_ok = ((((uintptr_t)base) & 15) == 0);
-    if (vec_ok) {
 #pragma unroll
-        for (int j = 0; j < NV; ++j) {
-            const int e0 = c0 + (j * kThreads + tid) * VN;
-            idx0[j] = e0;
-            if (e0 + VN <= cend) {
-                const uint4 raw = *(const uint4*)(base + e0);
-                if constexpr (VN == 4) {
-                    x[j * VN + 0] = __uint_as_float(raw.x);
-                    x[j * VN + 1] = __uint_as_float(raw.y);
-                    x[j * VN + 2] = __uint_as_float(raw.z);
-                    x[j * VN + 3] = __uint_as_float(raw.w);
-                } else {
-                    const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+    for (int j = 0; j < kPerThread / VN; ++j) {
+        const int e0 = c0 + (j * kThreads + tid) * VN;
+        idx0[j] = e0;
+        float v[VN];
+        if (e0 + VN <= cend) decode<T>(*(const uint4*)(base + e0), v);
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) unpack2<T>(w[k], x[j * VN + 2 * k], x[j * VN + 2 * k + 1]);
-                }
-            } else {
-#pragma unroll
-                for (int k = 0; k < VN; ++k) x[j * VN + k] = (e0 + k < cend) ? to_f32<T>(base[e0 + k]) : -INFINITY;
-            }
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < NV; ++j) {
-            const int e0 = c0 + (j * kThreads + tid) * VN;
-            idx0[j] = e0;
-#pragma unroll
-            for (int k = 0; k < VN; ++k) x[j * VN + k] = (e0 + k < cend) ? to_f32<T>(base[e0 + k]) : -INFINITY;
-        }
+        for (int q = 0; q < VN; ++q) x[j * VN + q] = e0 + VN <= cend ? v[q] : -INFINITY;
     }
-}
-
-// this thread's largest logit (lowest token id among equals: the scan ascends, '>' is strict)
-template <int VN>
-__device__ __forceinline__ MaxIdx thread_best(const float (&x)[kPerThread], const int32_t (&idx0)[kPerThread / VN]) {
-    MaxIdx best = {-INFINITY, 0x7FFFFFFF};
-#pragma unroll
-    for (int j = 0; j < kPerThread / VN; ++j)
-#pragma unroll
-        for (int k = 0; k < VN; ++k)
-            if (x[j * VN + k] > best.v) { best.v = x[j * VN + k]; best.i = idx0[j] + k; }
-    return best;
 }
 
 }  // namespace rowchunk

@@ -260,7 +260,7 @@ s4c_status s4c_tree_attn_paged(const s4c_attn_shape* shape, const void* q, const
 size_t s4c_accept_path_workspace_size(int32_t B, int32_t N, int32_t V) {
     if (B <= 0 || N <= 0 || V <= 0) return 0;
     int chunks, seg, nseg;
-    accept_plan(B, N, V, &chunks, &seg, &nseg);
+    accept_plan(B, N, V, 0, &chunks, &seg, &nseg);
     return (((size_t)B * N * nseg * 3 * sizeof(unsigned long long) + 255) / 256) * 256;   // room for two records per (row, run): scan_plan
 }
 
@@ -457,10 +457,10 @@ s4c_status s4c_kv_compact_paged(const s4c_attn_shape* shape, const void* k_tree,
 }  // extern "C"
 
 namespace {
-struct BuildLayout { size_t chunks, off_sum, off_topv, off_topi, off_tok, off_p, total; };
+struct BuildLayout { size_t chunks, off_sum, off_topv, off_topi, total; };
 BuildLayout build_layout(int32_t B, int32_t N, int32_t V) {
     BuildLayout l;
-    l.chunks = ((size_t)V + build_tree_chunk_elems() - 1) / build_tree_chunk_elems();
+    l.chunks = ((size_t)V + 7 + build_tree_chunk_elems() - 1) / build_tree_chunk_elems();   // a row may begin up to 7 elements into its first vector
     const size_t rows = (size_t)B * N, K = (size_t)build_tree_max_children();
     auto up = [](size_t x) { return (x + 255) / 256 * 256; };
     size_t o = 0;
@@ -468,9 +468,7 @@ BuildLayout build_layout(int32_t B, int32_t N, int32_t V) {
     o += up(rows * parts * 4); l.off_sum = o;
     o += up(rows * parts * 4); l.off_topv = o;
     o += up(rows * parts * K * 4); l.off_topi = o;
-    o += up(rows * parts * K * 4); l.off_tok = o;
-    o += up(rows * K * 4); l.off_p = o;
-    o += up(rows * K * 4); l.total = o;
+    o += up(rows * parts * K * 4); l.total = o;
     return l;
 }
 }  // namespace
@@ -492,18 +490,20 @@ s4c_status s4c_build_tree(int32_t B, int32_t N, int32_t V, int32_t logits_dtype,
     if (N > kMaxNodes || kmax > build_tree_max_children() || !dtype_ok(logits_dtype))
         return S4C_ERR_UNSUPPORTED;
     const BuildLayout l = build_layout(B, N, V);
-    if ((size_t)B * N * l.chunks * 4 * (size_t)build_tree_max_children() > 0x7FFFFFFFull) return S4C_ERR_UNSUPPORTED;
+    const size_t row_chunks = ((size_t)V + build_tree_chunk_elems() - 1) / build_tree_chunk_elems();
+    if ((size_t)B * N * row_chunks * 4 * (size_t)build_tree_max_children() > 0x7FFFFFFFull) return S4C_ERR_UNSUPPORTED;
     if (!workspace || workspace_bytes < l.total || (((uintptr_t)workspace) & 255)) return S4C_ERR_WORKSPACE;
     BuildArgs a;
     a.logits = draft_logits; a.nchild = nchild; a.root_token = root_token; a.parent = parent; a.tokens = tokens;
     a.p_draft = p_draft; a.level = level; a.status = status;
     char* w = (char*)workspace;
     a.ws_max = (float*)w; a.ws_sum = (float*)(w + l.off_sum); a.ws_topv = (float*)(w + l.off_topv);
-    a.ws_topi = (int32_t*)(w + l.off_topi); a.row_tok = (int32_t*)(w + l.off_tok); a.row_p = (float*)(w + l.off_p);
-    a.B = B; a.N = N; a.V = V; a.chunks = (int32_t)l.chunks; a.kmax = kmax; a.dtype = logits_dtype;
-    {   // segments as in the acceptance scan (same chunk size, same sizes of launch)
-        int chunks_ = 0;
-        accept_plan(B, N, V, &chunks_, &a.seg, &a.nseg);
+    a.ws_topi = (int32_t*)(w + l.off_topi);
+    a.B = B; a.N = N; a.V = V; a.kmax = kmax; a.dtype = logits_dtype;
+    {   // rows that begin inside a 16-byte vector may reach into one chunk more (row_chunk.h)
+        const int vec = logits_dtype == S4C_F32 ? 4 : 8;
+        const int head = V % vec == 0 && aligned16(draft_logits) ? 0 : vec - 1;
+        accept_plan(B, N, V, head, &a.chunks, &a.seg, &a.nseg);
     }
     a.inv_temp_log2 = kLog2e / temperature;
     return launch_build_tree(a, (hipStream_t)hip_stream) == hipSuccess ? S4C_OK : S4C_ERR_HIP;

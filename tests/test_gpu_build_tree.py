@@ -114,3 +114,31 @@ def test_rejects_bad_arguments():
         B.s4c_build_tree(t, i(1, 2), i(1), 9, i(1, 2), i(1, 2), torch.zeros(1, 2, device="cuda"), ws)
     with pytest.raises(B.S4CError):      # workspace too small
         B.s4c_build_tree(t, i(1, 2), i(1), 2, i(1, 2), i(1, 2), torch.zeros(1, 2, device="cuda"), ws[:16])
+
+
+@pytest.mark.parametrize("size", [(2, 5, 1, 0), (3, 9, 7, 3), (2, 17, 8191, 1), (3, 65, 8192, 5), (1, 128, 8193, 0),
+                                  (2, 33, 16377, 7), (18, 60, 16385, 2), (2, 64, 128256, 1)], ids=str)
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+def test_rows_at_any_alignment(size, dtype):
+    """(B, N, V, elements that the logits start behind a 16-byte boundary): rows that begin anywhere in a 16-byte vector,
+    vocabularies around a chunk, the first and last token of a row among the children, ties, nodes in both words of
+    a lane's counts."""
+    Bn, N, V, off = size
+    rng = np.random.default_rng([Bn, N, V])
+    par = np.stack([synth.random_tree_parent(N, min(N, 6), (8,) * 6, rng) for _ in range(Bn)])
+    lg = np.round(2 * rng.standard_normal((Bn, N, V), dtype=np.float32), 1)
+    lg[:, ::2, -1] = lg[:, ::3, 0] = 12.0
+    host = {"bf16": synth.f32_to_bf16_bits, "f16": lambda a: a.astype(np.float16), "f32": lambda a: a}[dtype](lg)
+    nchild, root = counts_of(par), np.arange(Bn) + 3
+    r = O.build_tree(host, nchild, root, 8, 0.7)
+    t = np_to_torch(host, "cpu")
+    dev = torch.empty(t.numel() + off, dtype=t.dtype, device="cuda")[off:].view(t.shape)
+    dev.copy_(t)
+    i32 = lambda *s: torch.full(s, -7, dtype=torch.int32, device="cuda")
+    g = dict(parent=i32(Bn, N), tokens=i32(Bn, N), level=i32(Bn, N), status=i32(Bn), p_draft=torch.full((Bn, N), -7.0, device="cuda"))
+    ws = B.alloc_workspace(B.s4c_build_tree_workspace_size(Bn, N, V))
+    B.s4c_build_tree(dev, torch.from_numpy(nchild).cuda(), torch.from_numpy(root.astype(np.int32)).cuda(), 8, g["parent"],
+                     g["tokens"], g["p_draft"], ws, 0.7, g["level"], g["status"])
+    torch.cuda.synchronize()
+    same({k: v.cpu().numpy() for k, v in g.items()}, r)
+    assert np.array_equal(r["parent"], par)
