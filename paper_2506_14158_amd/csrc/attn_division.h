@@ -1,0 +1,188 @@
+// How a launch of the attention kernels divides its work: the arithmetic alone, which also compiles for the host
+// (tests/host/attn_division.cpp plays every workgroup of a launch through it).
+//
+// The work of one (sequence, KV head) "unit" is a run of key tiles: its prefix tiles, then its tree tiles.  A
+// team is the workgroups that walk the same keys for the row tiles of one unit (a single workgroup when all query
+// rows fit one).  Two divisions:
+//   split     every unit's tiles (of its ACTUAL length) are cut into `split` equal runs, a team each; a team walks
+//             one run.  split = 1: nothing to merge.  For launches whose teams all fit on the chip at once.
+//   balanced  (split = 0) all units' tiles are laid end to end, sequence by sequence with their actual lengths, and
+//             the teams take equal consecutive shares (sizes differ by one tile).  A share may end inside a unit.  Equal
+//             shares are what keeps every CU busy to the end: 104 units on 256 CUs leave 48 of them idle at two runs per
+//             unit, and with ragged lengths the rest wait for the longest sequence.
+// A part of a unit that several teams share goes to the workspace unnormalised; attn_merge_kernel combines a unit's
+// parts in order.
+// The shares are a function of the shape and of cache_len, so results are deterministic for given inputs.
+//
+// `A` is AttnArgs, or what a host program has with the same members; `L` tells the sequences' lengths, L::Order their
+// end-to-end order (attn_work.h has the kernels').
+#pragma once
+#include <stddef.h>
+#include <stdint.h>
+
+#if defined(__HIPCC__)
+#define S4C_WORK __device__ __forceinline__
+#define S4C_UNIFORM(x) __builtin_amdgcn_readfirstlane(x)
+#else
+#define S4C_WORK inline
+#define S4C_UNIFORM(x) (x)
+#endif
+
+namespace s4c {
+
+// What one workgroup of the kernel for a shape takes: query rows, keys per tile, and how many fit on a CU.
+struct AttnTile { int rows, keys, per_cu; };
+
+struct AttnDivision {
+    int teams, split, mtiles;
+    int parts;                 // most parts a unit is divided into when no sequence is shorter than max_cache_len
+};
+
+// How the key tiles of a shape are divided between workgroups: a fixed function of its sizes and max_cache_len, so that
+// the workspace query and the launch agree.  M: query rows of a unit; cus: compute units of the device.
+inline AttnDivision plan_division(int B, int Hkv, int N, int M, int max_cache_len, AttnTile t, int cus) {
+    AttnDivision p;
+    p.mtiles = (M + t.rows - 1) / t.rows;
+    const long long slots = (long long)cus * t.per_cu;
+    const long long units = (long long)B * Hkv;
+    const long long tiles = (max_cache_len + t.keys - 1) / t.keys + (N + t.keys - 1) / t.keys;   // of the longest unit
+    // Teams: one round of the chip, a team's workgroups all on one XCD (an eighth of it); fewer when a share would get
+    // shorter than kMinKeys keys, below which a part's fixed costs (prologue, partial results, its share of the merge)
+    // outweigh what the extra workgroups stream; at most kMaxParts runs per unit.
+    const long long kMinKeys = 256, kMaxParts = 24, per_xcd = slots / 8;
+    long long teams = per_xcd >= p.mtiles ? per_xcd / p.mtiles * 8 : 8;
+    const long long most = units * tiles * t.keys / kMinKeys;
+    if (teams > most) teams = most;
+    if (teams > units * kMaxParts) teams = units * kMaxParts;
+    // A share that ends inside a unit has a second segment to start and finish, which costs as much as kSwitchKeys keys:
+    // whole numbers of runs per unit where the longer runs cost less than that, and where no unit would get a second.
+    const long long kSwitchKeys = 256;
+    long long split = 0;
+    if (units * tiles > 0x3FFFFFFFll) split = 1;                             // beyond the kernels' 32-bit tile numbers
+    else if (teams >= units) {
+        const long long q = teams / units;
+        if ((tiles + q - 1) / q * t.keys <= units * tiles * t.keys / teams + kSwitchKeys) split = q;
+    } else if (units * p.mtiles <= slots) split = 1;
+    p.split = (int)split;
+    p.teams = (int)(split > 0 ? units * split : teams < 1 ? 1 : teams);
+    if (split == 1) {
+        p.parts = 1;
+    } else {
+        const long long share = units * tiles / p.teams;                     // >= 1: kMinKeys is several tiles
+        p.parts = (int)(split > 0 ? split : share % tiles == 0 && units * tiles % p.teams == 0 ? 1 : (tiles + share - 1) / share + 1);
+    }
+    return p;
+}
+
+namespace work {
+
+// prefix length used for the division: an out-of-range cache_len (the sequence is flagged) counts as empty
+template <class A>
+S4C_WORK int usable(const A& a, int P) { return (P < 0 || P > a.max_cache_len || P > a.S_cap) ? 0 : P; }
+template <class A>
+S4C_WORK int tiles_of(const A& a, int P) {
+    return ((P + a.tile_keys - 1) >> a.tile_shift) + ((a.N + a.tile_keys - 1) >> a.tile_shift);
+}
+
+// The team that runs on slot k of an XCD: neighbours in the end-to-end order share an XCD, so an XCD's workgroups
+// walk one eighth of the cache and not pieces of all of it.
+template <class A>
+S4C_WORK int team_id(const A& a, int xcd, int k) { return xcd * ((a.teams + 7) >> 3) + k; }
+
+// Team g's share begins at tile floor(g total / teams): equal shares, and whole units where the numbers divide.
+struct Shares {
+    int total, teams, per, rem;
+    S4C_WORK Shares(int total_, int teams_) : total(total_), teams(teams_), per(total_ / teams_), rem(total_ % teams_) {}
+    S4C_WORK int begin(int g) const { return g * per + (int)((unsigned)g * (unsigned)rem / (unsigned)teams); }   // teams < 2^16
+};
+
+// One team's walk over its share: a segment is a run of tiles [tile, tile_end) of one unit.  The kernels keep two: one
+// runs ahead and issues loads, one follows and multiplies, so that the loads never pause where a segment ends.
+struct Walk {
+    int b, kvh;            // unit of the current segment; b < 0: no segment
+    int tiles;             // tiles of that unit
+    int tile, tile_end;    // the segment
+    int left;              // tiles of the share after this segment
+};
+
+template <class A, class L>
+S4C_WORK Walk walk_first(const A& a, const L& lens, int team) {
+    Walk w = {-1, 0, 0, 0, 0, 0};
+    if (team >= a.teams) return w;
+    if (a.split > 0) {
+        const int unit = team / a.split, k = team - unit * a.split;
+        w.b = unit / a.Hkv;
+        w.kvh = unit - w.b * a.Hkv;
+        w.tiles = lens.tiles(a, w.b);
+        const int run = (w.tiles + a.split - 1) / a.split;
+        w.tile = k * run;
+        w.tile_end = w.tiles < w.tile + run ? w.tiles : w.tile + run;
+        if (w.tile >= w.tile_end) w.b = -1;         // (an empty run: see leaves_empty)
+        return w;
+    }
+    const typename L::Order order(a, lens);
+    const Shares s(order.total, a.teams);
+    const int x = S4C_UNIFORM(s.begin(team)), n = S4C_UNIFORM(s.begin(team + 1)) - x;
+    if (n <= 0) return w;
+    w.b = order.seq_of(a, lens, x);
+    w.tiles = lens.tiles(a, w.b);
+    const int first = order.begin(a, lens, w.b);
+    w.kvh = S4C_UNIFORM((x - first) / w.tiles);
+    w.tile = (x - first) - w.kvh * w.tiles;
+    w.tile_end = w.tiles < w.tile + n ? w.tiles : w.tile + n;
+    w.left = n - (w.tile_end - w.tile);
+    return w;
+}
+
+// (by value: a walk stays in scalar registers)
+template <class A, class L>
+S4C_WORK Walk walk_next(const A& a, const L& lens, const Walk w) {
+    Walk n = w;
+    n.b = -1;
+    if (w.left > 0) {
+        const bool next_seq = w.kvh + 1 == a.Hkv;
+        n.b = next_seq ? w.b + 1 : w.b;
+        n.kvh = next_seq ? 0 : w.kvh + 1;
+        n.tiles = lens.tiles(a, n.b);
+        n.tile = 0;
+        n.tile_end = n.tiles < w.left ? n.tiles : w.left;
+        n.left = w.left - n.tile_end;
+    }
+    return n;
+}
+
+// a walk's unit is covered by this segment alone (evaluate before the walk's `tile` moves)
+S4C_WORK bool walk_is_whole(const Walk& w) { return w.tile == 0 && w.tile_end == w.tiles; }
+// Workspace slot of a part: a team leaves at most one part that ends a unit or lies inside it (slot 0) and one
+// that begins a unit (slot 1).
+S4C_WORK int part_slot(const Walk& w) { return w.tile == 0 ? 1 : 0; }
+template <class A>
+S4C_WORK size_t part_row(const A& a, int team, int slot) { return ((size_t)team * 2 + slot) * a.M; }
+
+// A team without tiles in a split launch leaves empty parts (sum 0), so that the merge kernel need not know how many
+// teams had some.
+template <class A>
+S4C_WORK bool leaves_empty(const A& a, int team) { return a.split > 1 && team < a.teams; }
+template <class A>
+S4C_WORK int empty_slot(const A& a, int team) { return team % a.split == 0 ? 1 : 0; }
+
+// Tells the merge kernel which teams share a unit (balanced launches): the team that begins it and the team that ends it.
+template <class A>
+S4C_WORK void note_parts(const A& a, int team, const Walk& w) {
+    const size_t unit = (size_t)w.b * a.Hkv + w.kvh;
+    if (w.tile == 0) a.ws_parts[2 * unit] = team;
+    if (w.tile_end == w.tiles) a.ws_parts[2 * unit + 1] = team;
+}
+
+// The teams whose parts make up a unit: slot 1 of the first one, slot 0 of the others; one team alone has written the
+// unit's output itself.  Split: the unit's teams, whether they had tiles or not; balanced: as the teams noted.
+struct Parts {
+    int first, last;
+    template <class A>
+    S4C_WORK Parts(const A& a, int unit)
+        : first(a.split > 0 ? unit * a.split : a.ws_parts[2 * unit]), last(a.split > 0 ? first + a.split - 1 : a.ws_parts[2 * unit + 1]) {}
+    S4C_WORK int slot(int team) const { return team == first ? 1 : 0; }
+};
+
+}  // namespace work
+}  // namespace s4c

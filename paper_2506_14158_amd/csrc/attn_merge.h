@@ -1,5 +1,5 @@
 // Combines the parts of the (sequence, KV head) units that the attention kernels' teams divided between them
-// (attn_work.h): out = sum_p 2^(m_p - m) O_p / sum_p 2^(m_p - m) l_p, parts in tile order => deterministic.
+// (attn_division.h): out = sum_p 2^(m_p - m) O_p / sum_p 2^(m_p - m) l_p, parts in tile order => deterministic.
 //
 // A workgroup takes a chunk of query rows of one unit and leaves at once if the unit was not divided.  32 lanes per
 // row (D = 128: one float4 each, D = 64: float2); every part's statistics and the first eight parts' outputs are in
@@ -19,8 +19,8 @@ __device__ __forceinline__ void merge_rows(const AttnArgs& a, int unit, int chun
     constexpr int VW = D / 32;                                   // floats per lane
     const int sub = threadIdx.x & 31;
     const int b = unit / a.Hkv, kvh = unit - b * a.Hkv;
-    // split: the unit's teams, whether they had tiles or not; balanced: as the teams noted
-    const int g0 = a.split > 0 ? unit * a.split : a.ws_parts[2 * unit], g1 = a.split > 0 ? g0 + a.split - 1 : a.ws_parts[2 * unit + 1];
+    const work::Parts parts(a, unit);
+    const int g0 = parts.first, g1 = parts.last;
     if (g0 == g1) return;                                        // written by its one team already
     for (int pass = 0; pass < passes; ++pass) {
         const int r = (chunk * passes + pass) * kRows + (threadIdx.x >> 5);
@@ -30,7 +30,7 @@ __device__ __forceinline__ void merge_rows(const AttnArgs& a, int unit, int chun
         for (int j = 0; j < VW; ++j) o[j] = 0.f;
         for (int gb = g0; gb <= g1; gb += 32) {                  // (more than 32 parts only if a sequence is much the longest)
             const int n = min(32, g1 + 1 - gb);
-            auto part = [&](int p) { return work::part_row(a, gb + p, gb + p == g0 ? 1 : 0) + r; };
+            auto part = [&](int p) { return work::part_row(a, gb + p, parts.slot(gb + p)) + r; };
             // lane p of the row holds part p's maximum and sum; the first outputs are requested with them
             const float2 ml = sub < n ? *(const float2*)(a.ws_ml + part(sub) * 2) : make_float2(-INFINITY, 0.f);
             float v[kBatch][VW];

@@ -1,37 +1,17 @@
-// How a launch of the attention kernels divides its work (device side of plan_attn in s4c_api.hip).
-//
-// The work of one (sequence, KV head) "unit" is a run of key tiles: its prefix tiles, then its tree tiles.  A
-// team is the workgroups that walk the same keys for the row tiles of one unit (a single workgroup when all query
-// rows fit one).  Two divisions:
-//   split     every unit's tiles (of its ACTUAL length) are cut into `split` equal runs, a team each; a team walks
-//             one run.  split = 1: nothing to merge.  For launches whose teams all fit on the chip at once.
-//   balanced  (split = 0) all units' tiles are laid end to end, sequence by sequence with their actual lengths, and
-//             the teams take equal consecutive shares (sizes differ by one tile).  A share may end inside a unit.  Equal
-//             shares are what keeps every CU busy to the end: 104 units on 256 CUs leave 48 of them idle at two runs per
-//             unit, and with ragged lengths the rest wait for the longest sequence.
-// A part of a unit that several teams share goes to the workspace unnormalised; attn_merge_kernel combines a unit's
-// parts in order.
-// The shares are a function of the shape and of cache_len, so results are deterministic for given inputs.
+// What the attention kernels need to know about a launch's work: the division (attn_division.h) over the batch's actual
+// lengths, and the state of a sequence.
 #pragma once
 #include "common.h"
 
 namespace s4c {
 namespace work {
 
-// prefix length used for the division: an out-of-range cache_len (the sequence is flagged) counts as empty
-__device__ __forceinline__ int usable(const AttnArgs& a, int P) { return (P < 0 || P > a.max_cache_len || P > a.S_cap) ? 0 : P; }
-__device__ __forceinline__ int tiles_of(const AttnArgs& a, int P) {
-    return ((P + a.tile_keys - 1) >> a.tile_shift) + ((a.N + a.tile_keys - 1) >> a.tile_shift);
-}
-
-// The team that runs on slot k of an XCD: neighbours in the end-to-end order share an XCD, so an XCD's workgroups
-// walk one eighth of the cache and not pieces of all of it.
-__device__ __forceinline__ int team_id(const AttnArgs& a, int xcd, int k) { return xcd * ((a.teams + 7) >> 3) + k; }
-
 // Every function below is called by whole wavefronts and returns wave-uniform values.
 
 // cache_len of the batch, read once: lane l holds sequence l's (batches beyond 64 are read as they are needed)
+struct Order;
 struct Lens {
+    typedef work::Order Order;
     int mine;
     __device__ __forceinline__ explicit Lens(const AttnArgs& a) {
         const int lane = threadIdx.x & 63;
@@ -96,72 +76,6 @@ struct Order {
     }
 };
 
-// Team g's share begins at tile floor(g total / teams): equal shares, and whole units where the numbers divide.
-struct Shares {
-    int total, teams, per, rem;
-    __device__ __forceinline__ Shares(int total_, int teams_) : total(total_), teams(teams_), per(total_ / teams_), rem(total_ % teams_) {}
-    __device__ __forceinline__ int begin(int g) const { return g * per + (int)((unsigned)g * (unsigned)rem / (unsigned)teams); }   // teams < 2^16
-};
-
-// One team's walk over its share: a segment is a run of tiles [tile, tile_end) of one unit.  The kernels keep two: one
-// runs ahead and issues loads, one follows and multiplies, so that the loads never pause where a segment ends.
-struct Walk {
-    int b, kvh;            // unit of the current segment; b < 0: no segment
-    int tiles;             // tiles of that unit
-    int tile, tile_end;    // the segment
-    int left;              // tiles of the share after this segment
-};
-
-__device__ __forceinline__ Walk walk_first(const AttnArgs& a, const Lens& lens, int team) {
-    Walk w = {-1, 0, 0, 0, 0, 0};
-    if (team >= a.teams) return w;
-    if (a.split > 0) {
-        const int unit = team / a.split, k = team - unit * a.split;
-        w.b = unit / a.Hkv;
-        w.kvh = unit - w.b * a.Hkv;
-        w.tiles = lens.tiles(a, w.b);
-        const int run = (w.tiles + a.split - 1) / a.split;
-        w.tile = k * run;
-        w.tile_end = min(w.tiles, w.tile + run);
-        if (w.tile >= w.tile_end) w.b = -1;         // (an empty run: see note_empty)
-        return w;
-    }
-    const Order order(a, lens);
-    const Shares s(order.total, a.teams);
-    const int x = __builtin_amdgcn_readfirstlane(s.begin(team)), n = __builtin_amdgcn_readfirstlane(s.begin(team + 1)) - x;
-    if (n <= 0) return w;
-    w.b = order.seq_of(a, lens, x);
-    w.tiles = lens.tiles(a, w.b);
-    const int first = order.begin(a, lens, w.b);
-    w.kvh = __builtin_amdgcn_readfirstlane((x - first) / w.tiles);
-    w.tile = (x - first) - w.kvh * w.tiles;
-    w.tile_end = min(w.tiles, w.tile + n);
-    w.left = n - (w.tile_end - w.tile);
-    return w;
-}
-
-// (by value: a walk stays in scalar registers)
-__device__ __forceinline__ Walk walk_next(const AttnArgs& a, const Lens& lens, const Walk w) {
-    Walk n = w;
-    n.b = -1;
-    if (w.left > 0) {
-        const bool next_seq = w.kvh + 1 == a.Hkv;
-        n.b = next_seq ? w.b + 1 : w.b;
-        n.kvh = next_seq ? 0 : w.kvh + 1;
-        n.tiles = lens.tiles(a, n.b);
-        n.tile = 0;
-        n.tile_end = min(n.tiles, w.left);
-        n.left = w.left - n.tile_end;
-    }
-    return n;
-}
-
-// a walk's unit is covered by this segment alone (evaluate before the walk's `tile` moves)
-__device__ __forceinline__ bool walk_is_whole(const Walk& w) { return w.tile == 0 && w.tile_end == w.tiles; }
-// workspace rows of a part: a team leaves at most one part that ends a unit or lies inside it (slot 0) and one
-// that begins a unit (slot 1)
-__device__ __forceinline__ size_t part_row(const AttnArgs& a, int team, int slot) { return ((size_t)team * 2 + slot) * a.M; }
-
 // ---- what a workgroup needs to know about a sequence besides its length (each wavefront finds out by itself: no barrier)
 // parent[] (in LDS) is not a tree
 __device__ __forceinline__ bool tree_is_bad(const AttnArgs& a, const int32_t* spar) {
@@ -197,19 +111,11 @@ __device__ __forceinline__ int node_of_row(int r, int G, float inv_G) {
     return rem < 0 ? q - 1 : rem >= G ? q + 1 : q;
 }
 
-// A team without tiles in a split launch leaves empty parts (sum 0), so that the merge kernel need not know how many
-// teams had some.
+// the empty parts of a team without tiles, for the rows of row tile mt
 __device__ __forceinline__ void note_empty(const AttnArgs& a, int team, int mt, int rows) {
-    if (a.split > 1 && team < a.teams)
+    if (leaves_empty(a, team))
         for (int r = mt * rows + (int)threadIdx.x; r < min(a.M, (mt + 1) * rows); r += blockDim.x)
-            *(float2*)(a.ws_ml + (part_row(a, team, team % a.split == 0 ? 1 : 0) + r) * 2) = make_float2(-INFINITY, 0.f);
-}
-
-// Tells the merge kernel which teams share a unit (balanced launches): the team that begins it and the team that ends it.
-__device__ __forceinline__ void note_parts(const AttnArgs& a, int team, const Walk& w) {
-    const size_t unit = (size_t)w.b * a.Hkv + w.kvh;
-    if (w.tile == 0) a.ws_parts[2 * unit] = team;
-    if (w.tile_end == w.tiles) a.ws_parts[2 * unit + 1] = team;
+            *(float2*)(a.ws_ml + (part_row(a, team, empty_slot(a, team)) + r) * 2) = make_float2(-INFINITY, 0.f);
 }
 
 }  // namespace work

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "attn_division.h"
 #include "s4c.h"
 
 namespace s4c {
@@ -59,12 +60,12 @@ struct AttnArgs {
     const int32_t* parent;
     void* out;
     int32_t* status;
-    float* ws_o;    // [teams][2][M][D]  unnormalised outputs of the parts of divided units (attn_work.h)
+    float* ws_o;    // [teams][2][M][D]  unnormalised outputs of the parts of divided units (attn_division.h)
     float* ws_ml;   // [teams][2][M][2]  (running max in log2 units, running sum)
     int32_t* ws_parts;    // [B][Hkv][2]  first and last team of a unit
     int32_t B, Hq, Hkv, D, N, S_cap, G, M;
     int32_t max_cache_len;
-    int32_t teams;      // teams the work is divided between (attn_work.h)
+    int32_t teams;      // teams the work is divided between (attn_division.h)
     int32_t split;      // teams per (sequence, KV head); 0: equal shares of all units' tiles laid end to end
     int32_t mtiles;     // query-row tiles per (sequence, KV head) = workgroups per team
     int32_t tile_keys, tile_shift;   // keys per tile of the kernel that will run, and its log2
@@ -79,8 +80,6 @@ struct AttnArgs {
 hipError_t launch_tree_attn_large(const AttnArgs& a, int dtype, hipStream_t st);    // 16-bit data, more than 64 query rows
 hipError_t launch_tree_attn_small(const AttnArgs& a, int dtype, hipStream_t st);    // at most 64 query rows, or fp32 data
 hipError_t launch_attn_merge(const AttnArgs& a, int dtype, hipStream_t st);
-// What one workgroup of the kernel for this shape takes: query rows, keys per tile, and how many fit on a CU.
-struct AttnTile { int rows, keys, per_cu; };
 AttnTile attn_tile_large(const s4c_attn_shape& s);
 AttnTile attn_tile_small(const s4c_attn_shape& s);
 

@@ -81,53 +81,25 @@ bool shape_ok(const s4c_attn_shape* s, s4c_status* why) {
 
 struct AttnPlan {
     bool large;                // more than 64 rows of 16-bit data: the kernel whose waves split the rows
-    int teams, split, mtiles, tile_keys, tile_shift;
-    int parts;                 // most parts a unit is divided into when no sequence is shorter than max_cache_len
+    AttnTile tile;
+    AttnDivision division;
     size_t ws_o_bytes, ws_ml_bytes, ws_parts_bytes;
 };
 
-// How the key tiles are divided between workgroups (attn_work.h): a fixed function of (shape, max_cache_len), so
-// that the workspace query and the launch agree.
+// a fixed function of (shape, max_cache_len), so that the workspace query and the launch agree
 AttnPlan plan_attn(const s4c_attn_shape& s, int32_t max_cache_len) {
     AttnPlan p;
     const int M = s.N * (s.Hq / s.Hkv);
     p.large = s.dtype != S4C_F32 && M > 64;
-    const AttnTile t = p.large ? attn_tile_large(s) : attn_tile_small(s);
-    p.mtiles = (M + t.rows - 1) / t.rows;
-    p.tile_keys = t.keys;
-    p.tile_shift = __builtin_ctz((unsigned)t.keys);
-    const long long slots = (long long)device_cus() * t.per_cu;
-    const long long units = (long long)s.B * s.Hkv;
-    const long long tiles = (max_cache_len + t.keys - 1) / t.keys + (s.N + t.keys - 1) / t.keys;   // of the longest unit
-    // Teams: one round of the chip, a team's workgroups all on one XCD (an eighth of it); fewer when a share would get
-    // shorter than kMinKeys keys, below which a part's fixed costs (prologue, partial results, its share of the merge)
-    // outweigh what the extra workgroups stream; at most kMaxParts runs per unit.
-    const long long kMinKeys = 256, kMaxParts = 24, per_xcd = slots / 8;
-    long long teams = per_xcd >= p.mtiles ? per_xcd / p.mtiles * 8 : 8;
-    const long long most = units * tiles * t.keys / kMinKeys;
-    if (teams > most) teams = most;
-    if (teams > units * kMaxParts) teams = units * kMaxParts;
-    // A share that ends inside a unit has a second segment to start and finish, which costs as much as kSwitchKeys keys:
-    // whole numbers of runs per unit where the longer runs cost less than that, and where no unit would get a second.
-    const long long kSwitchKeys = 256;
-    long long split = 0;
-    if (units * tiles > 0x3FFFFFFFll) split = 1;                             // beyond the kernels' 32-bit tile numbers
-    else if (teams >= units) {
-        const long long q = teams / units;
-        if ((tiles + q - 1) / q * t.keys <= units * tiles * t.keys / teams + kSwitchKeys) split = q;
-    } else if (units * p.mtiles <= slots) split = 1;
-    p.split = (int)split;
-    p.teams = (int)(split > 0 ? units * split : teams < 1 ? 1 : teams);
-    if (split == 1) {
-        p.parts = 1;
+    p.tile = p.large ? attn_tile_large(s) : attn_tile_small(s);
+    p.division = plan_division(s.B, s.Hkv, s.N, M, max_cache_len, p.tile, device_cus());
+    if (p.division.split == 1) {
         p.ws_o_bytes = p.ws_ml_bytes = p.ws_parts_bytes = 0;
     } else {
-        const long long share = units * tiles / p.teams;                     // >= 1: kMinKeys is several tiles
-        p.parts = (int)(split > 0 ? split : share % tiles == 0 && units * tiles % p.teams == 0 ? 1 : (tiles + share - 1) / share + 1);
-        const size_t prow = (size_t)p.teams * 2 * M;
+        const size_t prow = (size_t)p.division.teams * 2 * M;
         p.ws_o_bytes = prow * s.D * sizeof(float);
         p.ws_ml_bytes = ((prow * 2 * sizeof(float) + 255) / 256) * 256;
-        p.ws_parts_bytes = (((size_t)units * 2 * sizeof(int32_t) + 255) / 256) * 256;
+        p.ws_parts_bytes = (((size_t)s.B * s.Hkv * 2 * sizeof(int32_t) + 255) / 256) * 256;
     }
     return p;
 }
@@ -160,7 +132,7 @@ size_t s4c_tree_attn_workspace_size(const s4c_attn_shape* shape, int32_t max_cac
 int32_t s4c_tree_attn_num_splits(const s4c_attn_shape* shape, int32_t max_cache_len) {
     s4c_status why;
     if (!shape || !shape_ok(shape, &why) || max_cache_len < 0) return 0;
-    return plan_attn(*shape, max_cache_len).parts;
+    return plan_attn(*shape, max_cache_len).division.parts;
 }
 
 #pragma GCC visibility pop
@@ -200,8 +172,8 @@ s4c_status tree_attn_prepare(const s4c_attn_shape* shape, const void* q, const v
     a.ws_o = (float*)((char*)workspace + p.ws_ml_bytes + p.ws_parts_bytes);
     a.B = shape->B; a.Hq = shape->Hq; a.Hkv = shape->Hkv; a.D = shape->D; a.N = shape->N;
     a.S_cap = shape->S_cap; a.G = shape->Hq / shape->Hkv; a.M = a.N * a.G;
-    a.max_cache_len = max_cache_len; a.teams = p.teams; a.split = p.split; a.mtiles = p.mtiles;
-    a.tile_keys = p.tile_keys; a.tile_shift = p.tile_shift;
+    a.max_cache_len = max_cache_len; a.teams = p.division.teams; a.split = p.division.split; a.mtiles = p.division.mtiles;
+    a.tile_keys = p.tile.keys; a.tile_shift = __builtin_ctz((unsigned)p.tile.keys);
     a.scale_log2 = (scale > 0.f ? scale : 1.0f / sqrtf((float)shape->D)) * kLog2e;
     a.block_table = block_table; a.max_blocks = max_blocks; a.page_shift = page_shift; a.num_pages = num_pages;
     *plan = p;
@@ -226,7 +198,7 @@ s4c_status tree_attn_impl(const s4c_attn_shape* shape, const void* q, const void
     // Parts are combined by a second kernel: the kernel boundary is what makes one workgroup's
     // partial results visible to another across the chip's separate L2s at no extra cost.
     hipError_t e = launch_tree_attn(p, a, shape->dtype, st);
-    if (e == hipSuccess && p.split != 1) e = launch_attn_merge(a, shape->dtype, st);
+    if (e == hipSuccess && p.division.split != 1) e = launch_attn_merge(a, shape->dtype, st);
     return e == hipSuccess ? S4C_OK : S4C_ERR_HIP;
 }
 }  // namespace
@@ -659,10 +631,10 @@ s4c_status s4c_verify_step(const s4c_step* p, void* hip_stream) {
     hipError_t e = launch_tree_attn(plan, attn, p->shape.dtype, st);
     if (p->logits_dtype == p->shape.dtype) {
         if (e == hipSuccess)
-            e = launch_step(attn, plan.split != 1, accept, compact,
+            e = launch_step(attn, plan.division.split != 1, accept, compact,
                             (unsigned long long*)((char*)p->accept_workspace + s4c_accept_path_workspace_size(B, N, V)), st);
     } else {
-        if (e == hipSuccess && plan.split != 1) e = launch_attn_merge(attn, p->shape.dtype, st);
+        if (e == hipSuccess && plan.division.split != 1) e = launch_attn_merge(attn, p->shape.dtype, st);
         if (e == hipSuccess) e = launch_accept(accept, st);
         if (e == hipSuccess) e = launch_compact(compact, st);
     }

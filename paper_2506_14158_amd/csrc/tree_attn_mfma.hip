@@ -24,7 +24,7 @@
 //     (extra tiles whose scores are kept only where the key node is the query node or one of its
 //     ancestors; 128-bit masks built from parent[] in LDS) run a masked copy of the body.  Rows
 //     past the end of a ragged tile are clamped to its last valid row (in bounds, finite).
-//   * The keys are divided between teams of workgroups (attn_work.h); parts of a divided unit are written
+//   * The keys are divided between teams of workgroups (attn_division.h); parts of a divided unit are written
 //     unnormalised for the merge kernel.
 #include "attn_work.h"
 #include "mfma_common.h"
@@ -474,7 +474,7 @@ void tree_attn_mfma_kernel(AttnArgs a) {
         }
     } else {
         if (rvalid) {
-            const size_t prow = work::part_row(a, team, cw.tile == 0 ? 1 : 0) + rq;
+            const size_t prow = work::part_row(a, team, work::part_slot(cw)) + rq;
             float* orow = a.ws_o + prow * kD + 4 * g32;
 #pragma unroll
             for (int db = 0; db < kDB; ++db)

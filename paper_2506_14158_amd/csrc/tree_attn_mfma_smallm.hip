@@ -6,7 +6,7 @@
 // the KEYS instead: wave w owns row block w % RBW (32 rows) and key group w / RBW.  A round is one 32-key tile per
 // key group; a ring of NR rounds lives in LDS (direct-to-LDS loads, XOR-swizzled), NR - 1 of them in flight while
 // one is consumed.  Every wave keeps its own online-softmax state over its key group; at the end of a segment (a run
-// of tiles of one unit, attn_work.h) the states of a row are merged through LDS, while the ring already fills for the
+// of tiles of one unit, attn_division.h) the states of a row are merged through LDS, while the ring already fills for the
 // next segment, and written.  Tree rows are the unit's last tiles, masked with the 128-bit ancestor sets built
 // from parent[].
 //   16-bit data: v_mfma_f32_32x32x16, K read as 16-byte row pieces, V^T through the transposing LDS read.
@@ -492,7 +492,7 @@ void tree_attn_smallm_kernel(AttnArgs a) {
                                  make_uint2(round1<F16>(v0) | (round1<F16>(v1) << 16), round1<F16>(v2) | (round1<F16>(v3) << 16));
                     }
             } else {
-                const size_t prow = work::part_row(a, team, cw.tile == 0 ? 1 : 0) + rq;
+                const size_t prow = work::part_row(a, team, work::part_slot(cw)) + rq;
                 float* orow = a.ws_o + prow * kD + 4 * g32;
 #pragma unroll
                 for (int db = 0; db < kDB; ++db)
