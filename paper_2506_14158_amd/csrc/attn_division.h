@@ -151,8 +151,11 @@ S4C_WORK Walk walk_next(const A& a, const L& lens, const Walk w) {
     return n;
 }
 
-// a walk's unit is covered by this segment alone (evaluate before the walk's `tile` moves)
-S4C_WORK bool walk_is_whole(const Walk& w) { return w.tile == 0 && w.tile_end == w.tiles; }
+// This segment is the unit's output rather than a part of it (evaluate before the walk's `tile` moves): it covers the
+// unit, and the merge will not look at it.  A split launch of several runs merges every unit: one of a single tile (an
+// empty prefix, a flagged sequence) is one part and empty ones.
+template <class A>
+S4C_WORK bool walk_is_whole(const A& a, const Walk& w) { return a.split <= 1 && w.tile == 0 && w.tile_end == w.tiles; }
 // Workspace slot of a part: a team leaves at most one part that ends a unit or lies inside it (slot 0) and one
 // that begins a unit (slot 1).
 S4C_WORK int part_slot(const Walk& w) { return w.tile == 0 ? 1 : 0; }

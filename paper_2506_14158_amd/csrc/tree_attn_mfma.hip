@@ -458,7 +458,7 @@ void tree_attn_mfma_kernel(AttnArgs a) {
     const int flagged = (work::tree_is_bad(a, spar) ? S4C_SEQ_BAD_TREE : 0) | (len_bad ? S4C_SEQ_BAD_LEN : 0);
     if (a.status && tid == 0 && cw.tile == 0 && kvh == 0 && mt == 0) a.status[b] = flagged;
     const float l_tot = flagged ? 0.f : l_run + __shfl_xor(l_run, 32);       // a flagged sequence: zero output
-    if (work::walk_is_whole(cw)) {
+    if (work::walk_is_whole(a, cw)) {
         if (rvalid) {
         const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
         bf16_t* orow = (bf16_t*)a.out + (((size_t)b * N + node) * a.Hq + kvh * G + g) * kD + 4 * g32;

@@ -478,7 +478,7 @@ void tree_attn_smallm_kernel(AttnArgs a) {
         if (a.split == 0 && mt == 0 && tid == 0) work::note_parts(a, team, cw);
         // ---- key group 0 writes the row: d = 32 db + 8 (j/4) + 4 g32 + (j%4)
         if (kg == 0 && rvalid) {
-            if (work::walk_is_whole(cw)) {
+            if (work::walk_is_whole(a, cw)) {
                 const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
                 const size_t o0 = (((size_t)b * N + node) * a.Hq + kvh * G + gh) * kD + 4 * g32;
 #pragma unroll
