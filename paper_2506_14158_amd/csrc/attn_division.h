@@ -121,7 +121,10 @@ S4C_WORK Walk walk_first(const A& a, const L& lens, int team) {
         return w;
     }
     const typename L::Order order(a, lens);
-    const Shares s(order.total, a.teams);
+    // Fewer tiles than teams (short sequences under a large max_cache_len): as many teams as tiles, so that every team
+    // between the one that begins a unit and the one that ends it has a part of it.
+    const Shares s(order.total, a.teams < order.total ? a.teams : order.total);
+    if (team >= s.teams) return w;
     const int x = S4C_UNIFORM(s.begin(team)), n = S4C_UNIFORM(s.begin(team + 1)) - x;
     if (n <= 0) return w;
     w.b = order.seq_of(a, lens, x);

@@ -18,7 +18,7 @@ def player(tmp_path_factory):
 
 
 # 20000 random launches of a kind: tiles walked once, the merge reads what this call wrote and all of it
-KINDS = ["split"]
+KINDS = ["split", "balanced"]
 
 
 @pytest.mark.parametrize("kind", KINDS)

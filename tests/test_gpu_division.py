@@ -41,6 +41,14 @@ CASES = [
     Case("rows64", "split", 2, 8, 1, 128, 60, "bf16", 5000, (4, 5001)),
     Case("rows32", "split", 3, 4, 1, 128, 30, "bf16", 5000, (0, 5001, 33)),
     Case("rows32-f32", "split", 2, 4, 2, 64, 15, "f32", 3000, (0, 40)),
+    # fewer key tiles than teams: teams without a share; then enough of them, shares that end inside units; both kinds of rows
+    Case("shares-rows256", "balanced", 13, 8, 4, 128, 47, "f16", 5003, (1, 64, 17, 30)),
+    Case("shares-rows256-mixed", "balanced", 13, 8, 4, 128, 47, "bf16", 5003, (5, 900, 0, 64, 5004, 129)),
+    Case("shares-rows64", "balanced", 3, 32, 1, 128, 37, "bf16", 24000, (64, 33, 1)),
+    Case("shares-rows64-mixed", "balanced", 3, 32, 1, 128, 37, "f16", 24000, (700, 0, 40)),
+    Case("shares-rows32", "balanced", 5, 18, 1, 64, 20, "bf16", 3000, (32, 0, 1, 500, -1)),
+    Case("shares-f32", "balanced", 3, 30, 2, 64, 40, "f32", 3000, (2, 50, 333)),
+    Case("shares-70-sequences", "balanced", 70, 2, 1, 64, 20, "bf16", 3000, (1, 0, 64, 100, 31)),
 ]
 
 
