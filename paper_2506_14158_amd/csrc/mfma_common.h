@@ -98,6 +98,31 @@ __device__ __forceinline__ bf16x8 round8(const f32x16& s, int o) {
         return r;
     }
 }
+// The same, and what rounding left over stays in s (exactly: the difference of a float and its nearest 16-bit value is a
+// float).  For bf16 the third call of a row finds nothing left over: 3 x 8 bits hold the 24 of a float.
+template <bool F16>
+__device__ __forceinline__ bf16x8 take8(f32x16& s, int o) {
+    const bf16x8 r = round8<F16>(s, o);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        if constexpr (F16) s[o + e] -= (float)__builtin_bit_cast(f16x8, r)[e];
+        else s[o + e] -= (float)r[e];
+    }
+    return r;
+}
+// How the probabilities (fp32) enter the second contraction of 16-bit data.  Head size 128: rounded to the storage type.
+// Head size 64: as a sum of 16-bit parts, which keeps them as they are (bf16: 3 x 8 bits are the 24 of a float; fp16:
+// 2 x 11 bits).  Error of the output against 64 bits (2-norm; 24 units of 2049 keys + 37 nodes, bf16): 2.30e-3 with
+// one part, 1.66e-3 with three, which is the rounding of the output alone; fp16 2.89e-4 and 2.07e-4 (two parts).  Time
+// of a step with one part and with these, us: B 3, 2049 keys, 8 x 4 heads, 37 nodes: 25.5 -> 29.3 (bf16), 26.9 (fp16); B 8,
+// 8192 keys, 8 x 4 heads, 64 nodes: 63 -> 93, 80; B 4, 8000 keys, 32 heads, 30 nodes: 55 -> 55.  fp16 parts are taken of 2^7 times the probability, so that
+// what small ones lose below fp16's smallest number stays under 2^-32 of the largest (2^8 at most, while the
+// reference lags; 2^15 is a finite fp16).
+template <bool F16, int D>
+struct Prob {
+    static constexpr int kParts = D == 128 ? 1 : F16 ? 2 : 3;
+    static constexpr float kShift = D == 128 || !F16 ? 0.f : 7.f;
+};
 template <bool F16>
 __device__ __forceinline__ uint32_t round1(float x) {
     if constexpr (F16) return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)x);

@@ -50,6 +50,8 @@ void tree_attn_mfma_kernel(AttnArgs a) {
     constexpr int kLPR = kRowB / 16;             // lanes (16-byte chunks) per row in a direct-to-LDS load
     constexpr int kRPI = 64 / kLPR;              // rows per load instruction
     constexpr int kKT = kD / 16, kDB = kD / 32;  // MFMA steps of the scores; 32-column blocks of the output
+    constexpr int kParts = Prob<F16, kD>::kParts;
+    constexpr float kShift = Prob<F16, kD>::kShift;
     auto k_swz = [](int r) { return kD == 64 ? (r >> 1) & 7 : r & 15; };
     auto v_swz = [](int r) { return kD == 64 ? ((r >> 1) & 1) << 2 : (r & 3) << 2; };
     constexpr int CH = (kBN * kD / 8) / NT;      // direct-to-LDS loads per thread per K (or V) tile
@@ -352,7 +354,7 @@ void tree_attn_mfma_kernel(AttnArgs a) {
             for (int kblk = 0; kblk < 2; ++kblk)
 #pragma unroll
                 for (int j = 0; j < 16; ++j) {
-                    const float p = fast_exp2(fmaf(s[kblk][j], a.scale_log2, -m_run));
+                    const float p = fast_exp2(fmaf(s[kblk][j], a.scale_log2, kShift - m_run));
                     s[kblk][j] = p;
                     psum += p;
                 }
@@ -366,7 +368,7 @@ void tree_attn_mfma_kernel(AttnArgs a) {
             for (int kblk = 0; kblk < 2; ++kblk)
 #pragma unroll
                 for (int j = 0; j < 16; ++j) {
-                    const float p = fast_exp2(fmaf(s[kblk][j], a.scale_log2, -m_safe));
+                    const float p = fast_exp2(fmaf(s[kblk][j], a.scale_log2, kShift - m_safe));
                     s[kblk][j] = p;
                     psum += p;
                 }
@@ -383,10 +385,12 @@ void tree_attn_mfma_kernel(AttnArgs a) {
         // O^T += V^T P^T in four steps of 16 keys; the V^T fragments of step i+1 are requested
         // before the MFMAs of step i.
         {
-            bf16x8 pb[4];
+            bf16x8 pb[kParts][4];
 #pragma unroll
-            for (int st = 0; st < 4; ++st)
-                pb[st] = round8<F16>(s[st >> 1], 8 * (st & 1));
+            for (int part = 0; part < kParts; ++part)
+#pragma unroll
+                for (int st = 0; st < 4; ++st)
+                    pb[part][st] = part + 1 < kParts ? take8<F16>(s[st >> 1], 8 * (st & 1)) : round8<F16>(s[st >> 1], 8 * (st & 1));
             auto vfrag = [&](const lds_u8* p) __attribute__((always_inline)) {     // 8 keys x 1 column of V^T: two transposing reads
                 const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
                 const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 8 * kRowB));
@@ -402,8 +406,10 @@ void tree_attn_mfma_kernel(AttnArgs a) {
                     for (int db = 0; db < kDB; ++db) vf[(st + 1) & 1][db] = vfrag(stage + (st + 1) * 16 * kRowB + v_off[db]);
                 }
 #pragma unroll
-                for (int db = 0; db < kDB; ++db)
-                    o[db] = mma32<F16>(vf[st & 1][db], pb[st], o[db]);
+                for (int part = 0; part < kParts; ++part)
+#pragma unroll
+                    for (int db = 0; db < kDB; ++db)
+                        o[db] = mma32<F16>(vf[st & 1][db], pb[part][st], o[db]);
             }
         }
     };

@@ -72,6 +72,8 @@ void tree_attn_smallm_kernel(AttnArgs a) {
     constexpr int kThreads = C::kThreads, kCH = C::kCH;
     constexpr bool kIs32 = C::kElem == kF32, F16 = C::kElem == kH16;
     constexpr int kDB = kD / 32;                              // 32-column blocks of the output
+    constexpr int kParts = Prob<F16, kD>::kParts;             // (16-bit data)
+    constexpr float kShift = kIs32 ? 0.f : Prob<F16, kD>::kShift;
     constexpr int kLPR = kRowB / 16;                          // lanes (16-byte chunks) per row in a direct-to-LDS load
     constexpr int kRPI = 64 / kLPR;                           // rows per load instruction
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -348,7 +350,7 @@ void tree_attn_smallm_kernel(AttnArgs a) {
             float psum = 0.f;
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
-                const float p = fast_exp2(fmaf(s[j], a.scale_log2, -m_ref));
+                const float p = fast_exp2(fmaf(s[j], a.scale_log2, kShift - m_ref));
                 s[j] = p;
                 psum += p;
             }
@@ -367,9 +369,6 @@ void tree_attn_smallm_kernel(AttnArgs a) {
                         for (int e = 0; e < 4; ++e) o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[e], s[4 * jq + e], o[db], 0, 0, 0);
                     }
             } else {
-                bf16x8 pb[2];
-#pragma unroll
-                for (int st = 0; st < 2; ++st) pb[st] = round8<F16>(s, 8 * st);
                 auto vfrag = [&](const lds_u8* p) __attribute__((always_inline)) {
                     const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
                     const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 8 * kRowB));
@@ -381,9 +380,13 @@ void tree_attn_smallm_kernel(AttnArgs a) {
 #pragma unroll
                     for (int db = 0; db < kDB; ++db) vf[st][db] = vfrag(stage + st * 16 * kRowB + v_off[db]);
 #pragma unroll
-                for (int st = 0; st < 2; ++st)
+                for (int part = 0; part < kParts; ++part)
 #pragma unroll
-                    for (int db = 0; db < kDB; ++db) o[db] = mma32<F16>(vf[st][db], pb[st], o[db]);
+                    for (int st = 0; st < 2; ++st) {
+                        const bf16x8 pb = part + 1 < kParts ? take8<F16>(s, 8 * st) : round8<F16>(s, 8 * st);
+#pragma unroll
+                        for (int db = 0; db < kDB; ++db) o[db] = mma32<F16>(vf[st][db], pb, o[db]);
+                    }
             }
         };
 

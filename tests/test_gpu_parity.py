@@ -616,3 +616,22 @@ def test_consecutive_steps_share_one_growing_cache(dtype):
         assert np.array_equal(bits(d_kc), kc.view(np.uint8)) and np.array_equal(bits(d_vc), vc.view(np.uint8)), rnd
         grown += int(r["accept_len"].sum()) + cfg.B
     assert int((cl - at.cache_len).sum()) == grown and grown >= rounds * cfg.B
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("N,G,P", [(37, 4, 700), (16, 8, 300), (60, 1, 1000), (20, 1, 90), (128, 2, 70)])
+def test_tree_attn_head_size_64_keeps_fp32_probabilities(dtype, N, G, P):
+    """Head size 64: the probabilities enter the second product as the fp32 numbers they are, so nothing but the output's
+    own rounding (half an ulp) and fp32 sums (fewer than 2^11 terms of |v| < 8 against a sum of probabilities of at least
+    1, some 2^-24 each way: 2e-5 allows for all of them) stands between the result and the oracle's doubles.  Rounded
+    to 16 bits the probabilities alone would move elements near zero by many times that."""
+    cfg = synth.scaled(C[4], name="d64-fp32p", B=2, Hq=3 * G, Hkv=3, D=64, P=P, N=N, levels=6, dtype=dtype, ragged=True, index=0)
+    par, at = synth.make_parent(cfg), synth.make_attn_inputs(cfg)
+    d = to_device(cfg, par, at)
+    tv = verifier(cfg, d)
+    tv.tree_attn(d["q"], d["k_tree"], d["v_tree"], d["k_cache"], d["v_cache"], d["cache_len"], d["parent"])
+    ref, _ = O.tree_attn(at.q, at.k_tree, at.v_tree, at.k_cache, at.v_cache, at.cache_len, par)
+    err = np.abs(tv.out.float().cpu().numpy().astype(np.float64) - ref)
+    digits = 8 if dtype == "bf16" else 11
+    half_ulp = np.exp2(np.floor(np.log2(np.maximum(np.abs(ref), 2.0 ** -14))) - digits)
+    assert float((err - half_ulp).max()) <= 2e-5
