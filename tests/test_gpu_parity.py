@@ -635,3 +635,34 @@ def test_tree_attn_head_size_64_keeps_fp32_probabilities(dtype, N, G, P):
     digits = 8 if dtype == "bf16" else 11
     half_ulp = np.exp2(np.floor(np.log2(np.maximum(np.abs(ref), 2.0 ** -14))) - digits)
     assert float((err - half_ulp).max()) <= 2e-5
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("N,G", [(60, 1), (30, 1), (16, 4)])
+@pytest.mark.parametrize("largest", [130, 195])
+def test_tree_attn_rounds_probabilities_against_the_maximum(dtype, N, G, largest):
+    """Up to 64 rows of head size 128 round the probabilities to the storage type, the largest being 1.  Every V row is the same
+    v, 1 <= v < 2, so the output is v times (sum of rounded probabilities) / (their sum).  A row has one key of
+    probability 1 - d in a full tile (key 130) or the ragged one (195), two of at most 2^-4 in earlier tiles of the same key
+    group, and the rest below 2^-60: only the two are rounded, 2 * 2^-4 * (half an ulp at 1) together, which is under an
+    eighth of half an ulp of v, so the output is v exactly.  Against a reference that lagged by 2^4 to 2^8 the largest would be
+    rounded too, by up to half an ulp, and move elements near 2 to a neighbour."""
+    P, H, D = 200, 4, 128
+    t = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    ulp = 2.0 ** {"bf16": -7, "f16": -10}[dtype]
+    g = torch.Generator().manual_seed(N)
+    q = torch.zeros(1, N, H * G, D)
+    q[..., 0] = 63 + torch.arange(N * H * G).view(1, N, H * G) * (60.0 / (N * H * G))     # 4.0 .. 7.8 in log2 between the keys
+    k = torch.zeros(1, H, P + N, D)
+    k[..., 0] = -8.0
+    k[:, :, [0, 70], 0], k[:, :, largest, 0] = 1.0, 1.5
+    kt = torch.zeros(1, N, H, D)
+    kt[..., 0] = -8.0
+    v = 1 + torch.randint(0, int(1 / ulp), (H, D), generator=g) * ulp
+    dev = lambda x: x.to(t).contiguous().cuda()
+    par = torch.tensor([[-1] + [i // 2 for i in range(N - 1)]], dtype=torch.int32, device="cuda")
+    tv = TreeVerifier(1, N, H * G, H, D, P + N, 500, t, 8, P)
+    tv.tree_attn(dev(q), dev(kt), dev(v.view(1, 1, H, D).expand(1, N, H, D)), dev(k), dev(v.view(1, H, 1, D).expand(1, H, P + N, D)),
+                 torch.tensor([P], dtype=torch.int32, device="cuda"), par)
+    want = dev(v.repeat_interleave(G, 0).expand(1, N, H * G, D))
+    assert torch.equal(tv.out, want), int((tv.out != want).sum())
