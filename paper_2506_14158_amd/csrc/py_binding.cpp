@@ -65,14 +65,27 @@ void* ptr(const Tensor* t) { return t ? t->data_ptr() : nullptr; }
 size_t bytes(const Tensor* t) { return t ? t->nbytes() : 0; }
 void* stream() { return (void*)c10::hip::getCurrentHIPStream().stream(); }
 PyObject* answer(long code) { return PyLong_FromLong(code); }
-// The launch itself runs without the interpreter lock: it may have to wait for room in a full queue.
-template <class F>
-PyObject* launch(F f) {
+// The launch itself runs without the interpreter lock: it may have to wait for room in a full queue.  Its arguments are
+// evaluated by the caller, with the lock: a data pointer or the stream can throw (a tensor without storage, an error of
+// the device), which `guarded` catches.
+template <class... P, class... A>
+PyObject* launch(s4c_status (*entry)(P...), A... args) {
     long code;
     Py_BEGIN_ALLOW_THREADS
-    code = f();
+    code = entry(args...);
     Py_END_ALLOW_THREADS
     return answer(code);
+}
+// A C++ exception must not leave a function that the interpreter calls.  Nothing has been launched when one arises, so
+// the call is left to binding.py, where the same access raises it as the Python error that it is.
+template <PyObject* (*call)(PyObject*, PyObject* const*, Py_ssize_t)>
+PyObject* guarded(PyObject* self, PyObject* const* v, Py_ssize_t n) {
+    try {
+        return call(self, v, n);
+    } catch (...) {
+        PyErr_Clear();
+        return answer(kNotMine);
+    }
 }
 
 // s4c_dtype of a tensor; -1 (with ok = false) if it has none
@@ -118,10 +131,8 @@ PyObject* tree_attn(PyObject*, PyObject* const* v, Py_ssize_t n) {
         a.shape(par, {t.s.B, t.s.N});
     }
     if (!a.ok) return answer(kNotMine);
-    return launch([&] {
-        return s4c_tree_attn(&t.s, ptr(t.q), ptr(t.kt), ptr(t.vt), ptr(t.kc), ptr(t.vc), (int32_t*)ptr(len), (int32_t*)ptr(par),
-                                (int32_t)mcl, scale, ptr(t.out), (int32_t*)ptr(status), ptr(ws), bytes(ws), stream());
-    });
+    return launch(s4c_tree_attn, &t.s, ptr(t.q), ptr(t.kt), ptr(t.vt), ptr(t.kc), ptr(t.vc), (int32_t*)ptr(len), (int32_t*)ptr(par),
+                  (int32_t)mcl, scale, ptr(t.out), (int32_t*)ptr(status), ptr(ws), bytes(ws), stream());
 }
 
 // (q, k_tree, v_tree, k_pool, v_pool, block_table, cache_len, parent, max_cache_len, out, scale, status, workspace)
@@ -140,11 +151,9 @@ PyObject* tree_attn_paged(PyObject*, PyObject* const* v, Py_ssize_t n) {
         a.shape(bt, {t.s.B, blocks});
     } else a.ok = false;
     if (!a.ok) return answer(kNotMine);
-    return launch([&] {
-        return s4c_tree_attn_paged(&t.s, ptr(t.q), ptr(t.kt), ptr(t.vt), ptr(t.kc), ptr(t.vc), (int32_t*)ptr(bt), blocks, page, pages,
-                                      (int32_t*)ptr(len), (int32_t*)ptr(par), (int32_t)mcl, scale, ptr(t.out), (int32_t*)ptr(status),
-                                      ptr(ws), bytes(ws), stream());
-    });
+    return launch(s4c_tree_attn_paged, &t.s, ptr(t.q), ptr(t.kt), ptr(t.vt), ptr(t.kc), ptr(t.vc), (int32_t*)ptr(bt), blocks, page, pages,
+                  (int32_t*)ptr(len), (int32_t*)ptr(par), (int32_t)mcl, scale, ptr(t.out), (int32_t*)ptr(status),
+                  ptr(ws), bytes(ws), stream());
 }
 
 // the tensors that both acceptance entry points take
@@ -176,23 +185,19 @@ PyObject* accept_path(PyObject*, PyObject* const* v, Py_ssize_t n) {
     const AcceptTensors t = accept_tensors(a);
     const Tensor* ws = a.maybe(13);
     if (!a.ok) return answer(kNotMine);
-    return launch([&] {
-        return s4c_accept_path(t.B, t.N, t.V, t.dt, (int32_t)t.mode, t.temperature, ptr(t.logits), (int32_t*)ptr(t.par), (int32_t*)ptr(t.tok),
-                                  (float*)ptr(t.pd), (float*)ptr(t.u), (int32_t)t.max_path, (int32_t*)ptr(t.path), (int32_t*)ptr(t.len),
-                                  (int32_t*)ptr(t.acc), (int32_t*)ptr(t.bonus), (int32_t*)ptr(t.status), ptr(ws), bytes(ws), stream());
-    });
+    return launch(s4c_accept_path, t.B, t.N, t.V, t.dt, (int32_t)t.mode, t.temperature, ptr(t.logits), (int32_t*)ptr(t.par), (int32_t*)ptr(t.tok),
+                  (float*)ptr(t.pd), (float*)ptr(t.u), (int32_t)t.max_path, (int32_t*)ptr(t.path), (int32_t*)ptr(t.len),
+                  (int32_t*)ptr(t.acc), (int32_t*)ptr(t.bonus), (int32_t*)ptr(t.status), ptr(ws), bytes(ws), stream());
 }
 
 PyObject* accept_path_static(PyObject*, PyObject* const* v, Py_ssize_t n) {
     Args a(v, n, 13);
     const AcceptTensors t = accept_tensors(a);
     if (!a.ok) return answer(kNotMine);
-    return launch([&] {
-        return s4c_accept_path_static(t.B, t.N, t.V, t.dt, (int32_t)t.mode, t.temperature, ptr(t.logits), (int32_t*)ptr(t.par),
-                                         (int32_t*)ptr(t.tok), (float*)ptr(t.pd), (float*)ptr(t.u), (int32_t)t.max_path,
-                                         (int32_t*)ptr(t.path), (int32_t*)ptr(t.len), (int32_t*)ptr(t.acc), (int32_t*)ptr(t.bonus),
-                                         (int32_t*)ptr(t.status), stream());
-    });
+    return launch(s4c_accept_path_static, t.B, t.N, t.V, t.dt, (int32_t)t.mode, t.temperature, ptr(t.logits), (int32_t*)ptr(t.par),
+                  (int32_t*)ptr(t.tok), (float*)ptr(t.pd), (float*)ptr(t.u), (int32_t)t.max_path,
+                  (int32_t*)ptr(t.path), (int32_t*)ptr(t.len), (int32_t*)ptr(t.acc), (int32_t*)ptr(t.bonus),
+                  (int32_t*)ptr(t.status), stream());
 }
 
 // (logits, draft_probs, parent, tokens, uniforms, u_resample, max_path, path, accept_len, accepted_tokens, bonus_token, workspace,
@@ -215,11 +220,9 @@ PyObject* accept_resample(PyObject*, PyObject* const* v, Py_ssize_t n) {
     a.shape(path, {B, mp});
     a.shape(acc, {B, mp});
     if (!a.ok) return answer(kNotMine);
-    return launch([&] {
-        return s4c_accept_resample((int32_t)B, (int32_t)N, (int32_t)V, dt, temperature, ptr(lg), (float*)ptr(dp), (int32_t*)ptr(par),
-                                      (int32_t*)ptr(tok), (float*)ptr(u), (float*)ptr(ur), (int32_t)mp, (int32_t*)ptr(path), (int32_t*)ptr(len),
-                                      (int32_t*)ptr(acc), (int32_t*)ptr(bonus), (int32_t*)ptr(status), ptr(ws), bytes(ws), stream());
-    });
+    return launch(s4c_accept_resample, (int32_t)B, (int32_t)N, (int32_t)V, dt, temperature, ptr(lg), (float*)ptr(dp), (int32_t*)ptr(par),
+                  (int32_t*)ptr(tok), (float*)ptr(u), (float*)ptr(ur), (int32_t)mp, (int32_t*)ptr(path), (int32_t*)ptr(len),
+                  (int32_t*)ptr(acc), (int32_t*)ptr(bonus), (int32_t*)ptr(status), ptr(ws), bytes(ws), stream());
 }
 
 // (k_tree, v_tree, k_cache, v_cache, cache_len, path, accept_len, dst_index, status)
@@ -236,10 +239,8 @@ PyObject* kv_compact(PyObject*, PyObject* const* v, Py_ssize_t n) {
     a.same(vc, kc);
     a.need(kc->scalar_type() == kt->scalar_type());
     if (!a.ok) return answer(kNotMine);
-    return launch([&] {
-        return s4c_kv_compact(&s, ptr(kt), ptr(vt), ptr(kc), ptr(vc), (int32_t*)ptr(len), (int32_t*)ptr(path), (int32_t*)ptr(alen),
-                                 (int32_t)path->size(1), (int32_t*)ptr(dst), (int32_t*)ptr(status), stream());
-    });
+    return launch(s4c_kv_compact, &s, ptr(kt), ptr(vt), ptr(kc), ptr(vc), (int32_t*)ptr(len), (int32_t*)ptr(path), (int32_t*)ptr(alen),
+                  (int32_t)path->size(1), (int32_t*)ptr(dst), (int32_t*)ptr(status), stream());
 }
 
 // (k_tree, v_tree, k_pool, v_pool, block_table, cache_len, path, accept_len, dst_index, status)
@@ -259,11 +260,9 @@ PyObject* kv_compact_paged(PyObject*, PyObject* const* v, Py_ssize_t n) {
     a.same(vc, kc);
     a.need(kc->scalar_type() == kt->scalar_type());
     if (!a.ok) return answer(kNotMine);
-    return launch([&] {
-        return s4c_kv_compact_paged(&s, ptr(kt), ptr(vt), ptr(kc), ptr(vc), (int32_t*)ptr(bt), blocks, page, pages, (int32_t*)ptr(len),
-                                       (int32_t*)ptr(path), (int32_t*)ptr(alen), (int32_t)path->size(1), (int32_t*)ptr(dst),
-                                       (int32_t*)ptr(status), stream());
-    });
+    return launch(s4c_kv_compact_paged, &s, ptr(kt), ptr(vt), ptr(kc), ptr(vc), (int32_t*)ptr(bt), blocks, page, pages, (int32_t*)ptr(len),
+                  (int32_t*)ptr(path), (int32_t*)ptr(alen), (int32_t)path->size(1), (int32_t*)ptr(dst),
+                  (int32_t*)ptr(status), stream());
 }
 
 // bytes of a feature row; features [B][N][...] and features_out [B][max_path][...] go together
@@ -294,11 +293,9 @@ PyObject* commit_path(PyObject*, PyObject* const* v, Py_ssize_t n) {
     a.need(kc->scalar_type() == kt->scalar_type());
     const int64_t fb = feature_bytes(a, f, fo, s.B, s.N, path->size(1));
     if (!a.ok) return answer(kNotMine);
-    return launch([&] {
-        return s4c_commit_path(&s, (int32_t)kt->size(0), ptr(kt), ptr(vt), ptr(kc), ptr(vc), (int32_t*)ptr(len), (int32_t*)ptr(path),
-                                  (int32_t*)ptr(alen), (int32_t)path->size(1), ptr(f), (int32_t)fb, ptr(fo), (int32_t*)ptr(dst),
-                                  (int32_t*)ptr(status), stream());
-    });
+    return launch(s4c_commit_path, &s, (int32_t)kt->size(0), ptr(kt), ptr(vt), ptr(kc), ptr(vc), (int32_t*)ptr(len), (int32_t*)ptr(path),
+                  (int32_t*)ptr(alen), (int32_t)path->size(1), ptr(f), (int32_t)fb, ptr(fo), (int32_t*)ptr(dst),
+                  (int32_t*)ptr(status), stream());
 }
 
 // (k_tree, v_tree, k_pool, v_pool, block_table, cache_len, path, accept_len, features, features_out, dst_index, status)
@@ -319,11 +316,9 @@ PyObject* commit_path_paged(PyObject*, PyObject* const* v, Py_ssize_t n) {
     a.need(kc->scalar_type() == kt->scalar_type());
     const int64_t fb = feature_bytes(a, f, fo, s.B, s.N, path->size(1));
     if (!a.ok) return answer(kNotMine);
-    return launch([&] {
-        return s4c_commit_path_paged(&s, (int32_t)kt->size(0), ptr(kt), ptr(vt), ptr(kc), ptr(vc), (int32_t*)ptr(bt), blocks, page, pages,
-                                        (int32_t*)ptr(len), (int32_t*)ptr(path), (int32_t*)ptr(alen), (int32_t)path->size(1), ptr(f),
-                                        (int32_t)fb, ptr(fo), (int32_t*)ptr(dst), (int32_t*)ptr(status), stream());
-    });
+    return launch(s4c_commit_path_paged, &s, (int32_t)kt->size(0), ptr(kt), ptr(vt), ptr(kc), ptr(vc), (int32_t*)ptr(bt), blocks, page, pages,
+                  (int32_t*)ptr(len), (int32_t*)ptr(path), (int32_t*)ptr(alen), (int32_t)path->size(1), ptr(f),
+                  (int32_t)fb, ptr(fo), (int32_t*)ptr(dst), (int32_t*)ptr(status), stream());
 }
 
 // (draft_logits, nchild, root_token, kmax, parent, tokens, p_draft, workspace, temperature, level, status)
@@ -343,11 +338,9 @@ PyObject* build_tree(PyObject*, PyObject* const* v, Py_ssize_t n) {
     a.shape(pd, {B, N});
     if (level) a.shape(level, {B, N});
     if (!a.ok) return answer(kNotMine);
-    return launch([&] {
-        return s4c_build_tree((int32_t)B, (int32_t)N, (int32_t)lg->size(2), dt, temperature, ptr(lg), (int32_t*)ptr(nc), (int32_t*)ptr(root),
-                                 (int32_t)kmax, (int32_t*)ptr(par), (int32_t*)ptr(tok), (float*)ptr(pd), (int32_t*)ptr(level),
-                                 (int32_t*)ptr(status), ptr(ws), bytes(ws), stream());
-    });
+    return launch(s4c_build_tree, (int32_t)B, (int32_t)N, (int32_t)lg->size(2), dt, temperature, ptr(lg), (int32_t*)ptr(nc), (int32_t*)ptr(root),
+                  (int32_t)kmax, (int32_t*)ptr(par), (int32_t*)ptr(tok), (float*)ptr(pd), (int32_t*)ptr(level),
+                  (int32_t*)ptr(status), ptr(ws), bytes(ws), stream());
 }
 
 // (e, f, W, out, bias, workspace)
@@ -366,10 +359,8 @@ PyObject* draft_linear(PyObject*, PyObject* const* v, Py_ssize_t n) {
         a.need(bias->scalar_type() == e->scalar_type());
     }
     if (!a.ok) return answer(kNotMine);
-    return launch([&] {
-        return s4c_draft_linear((int32_t)T, (int32_t)H, (int32_t)Hout, dt, ptr(e), ptr(f), ptr(W), ptr(bias), ptr(out), ptr(ws), bytes(ws),
-                                   stream());
-    });
+    return launch(s4c_draft_linear, (int32_t)T, (int32_t)H, (int32_t)Hout, dt, ptr(e), ptr(f), ptr(W), ptr(bias), ptr(out), ptr(ws), bytes(ws),
+                  stream());
 }
 
 // (q, k_tree, v_tree, k_cache, v_cache, cache_len, parent, logits, tokens, mode, p_draft, uniforms, temperature, scale,
@@ -409,10 +400,10 @@ PyObject* verify_step(PyObject*, PyObject* const* v, Py_ssize_t n) {
     p.dst_index = (int32_t*)ptr(dst); p.attn_status = (int32_t*)ptr(ast); p.accept_status = (int32_t*)ptr(cst);
     p.compact_status = (int32_t*)ptr(kst); p.attn_workspace = ptr(aws); p.accept_workspace = ptr(cws);
     p.attn_workspace_bytes = bytes(aws); p.accept_workspace_bytes = bytes(cws);
-    return launch([&] { return s4c_verify_step(&p, stream()); });
+    return launch(s4c_verify_step, &p, stream());
 }
 
-#define S4C_PY(name) {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL, nullptr}
+#define S4C_PY(name) {#name, (PyCFunction)(void (*)(void))guarded<name>, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {S4C_PY(tree_attn), S4C_PY(tree_attn_paged), S4C_PY(accept_path), S4C_PY(accept_path_static),
                          S4C_PY(accept_resample), S4C_PY(kv_compact), S4C_PY(kv_compact_paged), S4C_PY(commit_path),
                          S4C_PY(commit_path_paged), S4C_PY(build_tree), S4C_PY(draft_linear), S4C_PY(verify_step), {nullptr, nullptr, 0, nullptr}};
