@@ -463,7 +463,14 @@ void tree_attn_mfma_kernel(AttnArgs a) {
     // ---- write this lane's row: d = 32 db + 8 (j/4) + 4 g32 + (j%4)
     const int flagged = (work::tree_is_bad(a, spar) ? S4C_SEQ_BAD_TREE : 0) | (len_bad ? S4C_SEQ_BAD_LEN : 0);
     if (a.status && tid == 0 && cw.tile == 0 && kvh == 0 && mt == 0) a.status[b] = flagged;
-    const float l_tot = flagged ? 0.f : l_run + __shfl_xor(l_run, 32);       // a flagged sequence: zero output
+    float l_tot = l_run + __shfl_xor(l_run, 32);
+    if (flagged) {                             // zero output, whatever was read in place of a bad page
+        l_tot = 0.f;
+#pragma unroll
+        for (int db = 0; db < kDB; ++db)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) o[db][j] = 0.f;
+    }
     if (work::walk_is_whole(a, cw)) {
         if (rvalid) {
         const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;

@@ -434,7 +434,14 @@ void tree_attn_smallm_kernel(AttnArgs a) {
         // ---- merge the key groups of each row into key group 0, one 32-column block at a time
         const int flagged = (work::tree_is_bad(a, spar) ? S4C_SEQ_BAD_TREE : 0) | (len_bad ? S4C_SEQ_BAD_LEN : 0);
         if (a.status && tid == 0 && cw.tile == 0 && kvh == 0 && mt == 0) a.status[b] = flagged;
-        float l_tot = flagged ? 0.f : l_run + __shfl_xor(l_run, 32);              // a flagged sequence: zero output
+        float l_tot = l_run + __shfl_xor(l_run, 32);
+        if (flagged) {                                        // zero output, whatever was read in place of a bad page
+            l_tot = 0.f;
+#pragma unroll
+            for (int db = 0; db < kDB; ++db)
+#pragma unroll
+                for (int j = 0; j < 16; ++j) o[db][j] = 0.f;
+        }
         float* mo = (float*)(smem + C::kRingB + kAuxB);                       // [KG-1][RBW][32 rows][kMergeRow]
         float* mml = mo + (kKG - 1) * kRBW * 32 * C::kMergeRow;               // [KG-1][RBW][32 rows][2]
         const int mslot = ((kg - 1) * kRBW + rb) * 32 + (lane & 31);          // (kg > 0)

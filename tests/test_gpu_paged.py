@@ -140,3 +140,37 @@ def test_paged_rejects_bad_arguments():
                               i(1), i(1, 4), 10, t(1, 4, 2, 128))
     with pytest.raises(B.S4CError):
         B.s4c_kv_compact_paged(t(1, 4, 1, 128), t(1, 4, 1, 128), t(3, 1, 32, 128), t(3, 1, 32, 128), i(1, 2), i(1), i(1, 3), i(1))
+
+
+@pytest.mark.parametrize("dtype,D,N,G,P", [("bf16", 128, 16, 1, 150), ("f16", 128, 60, 1, 150), ("bf16", 64, 20, 1, 150), ("f32", 128, 40, 3, 150),
+                                           ("f32", 64, 10, 1, 150), ("bf16", 128, 30, 4, 150), ("f16", 64, 50, 4, 150), ("bf16", 128, 64, 4, 5000)])
+def test_bad_page_gives_zeros_whatever_page_zero_holds(dtype, D, N, G, P):
+    """A page id outside the pool (beyond it, or negative): an all-zero output and the status word, also where the pool's first page, read
+    in its place, holds NaN; the other sequences get what they get under a good table.  Undivided units and divided ones, both kernels."""
+    t = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    Bn, H, page = 3, 2, 64
+    blocks = -(-(P + N) // page)
+    g = torch.Generator(device="cuda").manual_seed(D + N)
+    r = lambda *s: torch.randn(*s, device="cuda", generator=g).to(t)
+    q, kt, vt = r(Bn, N, H * G, D), r(Bn, N, H, D), r(Bn, N, H, D)
+    kp, vp = r(1 + Bn * blocks, H, page, D), r(1 + Bn * blocks, H, page, D)
+    kp[0], vp[0] = float("nan"), float("nan")
+    table = (1 + torch.arange(Bn * blocks, device="cuda")).to(torch.int32).view(Bn, blocks).contiguous()
+    n = torch.full((Bn,), P, dtype=torch.int32, device="cuda")
+    par = torch.tensor([[-1] + [i // 2 for i in range(N - 1)]] * Bn, dtype=torch.int32, device="cuda")
+    tv = TreeVerifier(Bn, N, H * G, H, D, blocks * page, 500, t, 9, P)
+
+    def run(tab):
+        out = torch.full_like(tv.out, float("nan"))
+        B.s4c_tree_attn_paged(q, kt, vt, kp, vp, tab, n, par, P, out, 0.0, tv.attn_status, tv.attn_ws)
+        return out, tv.attn_status.tolist()
+
+    good, st = run(table)
+    assert st == [0] * Bn and torch.isfinite(good.float()).all()
+    for bad_id in (1 + Bn * blocks, -1):
+        bad = table.clone()
+        bad[1, 1] = bad_id
+        out, st = run(bad)
+        assert st == [0, B.S4C_SEQ_BAD_LEN, 0]
+        assert (out[1] == 0).all()
+        assert torch.equal(out[0], good[0]) and torch.equal(out[2], good[2])
