@@ -299,7 +299,9 @@ s4c_status s4c_draft_linear(int32_t T, int32_t H, int32_t Hout, int32_t dtype, c
 /* One verification step in one call: s4c_tree_attn, then s4c_accept_path, then s4c_kv_compact, same results, arguments
  * and device status words as the three calls with these arguments.  The attention merge, the acceptance and
  * the compaction share one launch where the logits have the shape's dtype.  S4C_SEQ_TIMEOUT may also appear in
- * compact_status, if the workgroups that copy a sequence's rows did not hear of its path within 2 s.
+ * compact_status, if a workgroup that copies a sequence's rows did not hear of its path within the collector's waiting
+ * time (s4c_accept_path) plus 2 s, or within S4C_COPY_WAIT_US microseconds (environment, an integer >= 0, read at
+ * every call): that sequence's rows are not (all) appended, its cache_len stays and its dst_index is -1.
  *   attn_workspace    as s4c_tree_attn (s4c_tree_attn_workspace_size)
  *   accept_workspace  >= s4c_verify_step_workspace_size(&shape, V) bytes, 256-byte aligned, otherwise as
  *                     s4c_accept_path's */

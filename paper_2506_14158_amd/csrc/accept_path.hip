@@ -132,31 +132,55 @@ constexpr float kLazyLog2 = 24.0f;
 // ---- what step_kernel adds
 struct StepArgs {
     CompactArgs compact;
-    rec_t* messages;            // [B][copiers][kMessage]
+    rec_t* messages;            // [B][copiers][kMessageWords]
+    long long copy_ticks;       // how long a copier waits for its message (100 MHz wall clock)
     int32_t merge_wgs, merge_chunks, merge_passes, attn_D;
     int32_t scan_wgs;
     int32_t copiers, heads;     // workgroups per sequence that append rows, KV heads of each
 };
 constexpr int kMessage = 2 + kMaxNodes;          // records: cache length (or -1), accepted length, path nodes
+constexpr int kMessageWords = kMessage + 1;      // and one in which the copier tells that it has given up
 constexpr int kMostCopiers = 8;
-constexpr long long kCopyTicks = 200000000;      // 2 s of the 100 MHz wall clock
 
 // The collector's half of the compaction, as s4c_kv_compact: checks that the rows fit, writes dst_index and status,
 // advances cache_len, and tells the sequence's copiers, each in a message of its own (it clears the message when
 // it has read it, so that a captured graph can replay the call).  Path of L + 1 nodes in `node`; all threads.
-__device__ __forceinline__ void announce_path(const StepArgs& x, const AcceptArgs& a, int b, int base, int L, const int32_t* node) {
+//
+// A copier waits longer than the collector does before it gives up (copy_ticks; it starts after the collector), so it
+// is only ever alone if the collector was held up on its way here.  A collector that comes here after half that time
+// looks whether a copier has left: then rows are missing, so the sequence is flagged and its length stays.  Copier: tell that it has given
+// up, then look once more; collector: publish, then look: at least one of the two sees the other.
+__device__ __forceinline__ void announce_path(const StepArgs& x, const AcceptArgs& a, int b, int base, int L, const int32_t* node,
+                                              long long started) {
     const CompactArgs& c = x.compact;
     const int i = threadIdx.x;
     const bool bad = base < 0 || (long long)base + L + 1 > c.S_cap;
+    rec_t* const first = x.messages + (size_t)b * x.copiers * kMessageWords;
     if (i < kMessage) {
         const int32_t word = i == 0 ? (bad ? -1 : base) : i == 1 ? L : i - 2 <= L ? node[i - 2] : -1;
-        for (int w = 0; w < x.copiers; ++w) publish(x.messages + ((size_t)b * x.copiers + w) * kMessage + i, a.nonce, (uint32_t)word);
+        for (int w = 0; w < x.copiers; ++w) publish(first + w * kMessageWords + i, a.nonce, (uint32_t)word);
+    }
+    int gone = 0;
+    if (__syncthreads_or((long long)wall_clock64() - started >= x.copy_ticks / 2)) {
+        __threadfence();
+        __syncthreads();
+        __threadfence();
+        for (int w = 0; w < x.copiers; ++w)
+            if ((uint32_t)(__hip_atomic_load(first + w * kMessageWords + kMessage, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32) == a.nonce) {
+                gone = 1;
+                if (i < kMessage) publish(first + w * kMessageWords + i, ~a.nonce, 0u);
+            }
+        gone = __syncthreads_or(gone);                           // (every thread has looked before a mark is cleared)
+        if (gone && i < x.copiers) {
+            rec_t* mark = first + i * kMessageWords + kMessage;
+            if ((uint32_t)(__hip_atomic_load(mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32) == a.nonce) publish(mark, ~a.nonce, 0u);
+        }
     }
     if (c.dst_index)
-        for (int k = i; k < c.max_path; k += kThreads) c.dst_index[(size_t)b * c.max_path + k] = (!bad && k <= L) ? base + k : -1;
+        for (int k = i; k < c.max_path; k += kThreads) c.dst_index[(size_t)b * c.max_path + k] = (!bad && !gone && k <= L) ? base + k : -1;
     if (i == 0) {
-        if (c.status) c.status[b] = bad ? S4C_SEQ_BAD_LEN : 0;
-        if (!bad) c.cache_len[b] = base + L + 1;
+        if (c.status) c.status[b] = (bad ? S4C_SEQ_BAD_LEN : 0) | (gone ? S4C_SEQ_TIMEOUT : 0);
+        if (!bad && !gone) c.cache_len[b] = base + L + 1;
     }
 }
 
@@ -165,25 +189,30 @@ __device__ __forceinline__ void copy_rows(const StepArgs& x, const AcceptArgs& a
     const CompactArgs& c = x.compact;
     __shared__ int32_t s_msg[kMessage];
     const int tid = threadIdx.x;
+    rec_t* const m = x.messages + ((size_t)b * x.copiers + w) * kMessageWords;
+    // this thread's word, if it is this call's
+    auto look = [&]() {
+        const rec_t v = __hip_atomic_load(m + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_msg[tid] = (int32_t)(uint32_t)v;
+        return (uint32_t)(v >> 32) == a.nonce;
+    };
     int late = 0;
     if (tid < kMessage) {
-        rec_t* m = x.messages + ((size_t)b * x.copiers + w) * kMessage + tid;
-        const long long deadline = (long long)wall_clock64() + kCopyTicks;
-        rec_t v;
-        for (;;) {
-            v = __hip_atomic_load(m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if ((uint32_t)(v >> 32) == a.nonce) break;
+        const long long deadline = (long long)wall_clock64() + x.copy_ticks;
+        while (!look()) {
             if ((long long)wall_clock64() - deadline >= 0) { late = 1; break; }
             __builtin_amdgcn_s_sleep(4);
         }
-        s_msg[tid] = (int32_t)(uint32_t)v;
-        if (!late) publish(m, ~a.nonce, 0u);
     }
-    late = __syncthreads_or(late);
-    if (late) {
-        if (tid == 0 && c.status) atomicOr(&c.status[b], S4C_SEQ_TIMEOUT);
-        return;
+    if (__syncthreads_or(late)) {
+        if (tid == 0) publish(m + kMessage, a.nonce, 1u);
+        __threadfence();
+        __syncthreads();
+        __threadfence();
+        if (__syncthreads_or(tid < kMessage && !look())) return;       // the collector flags the sequence (announce_path)
+        if (tid == 0) publish(m + kMessage, ~a.nonce, 0u);
     }
+    if (tid < kMessage) publish(m + tid, ~a.nonce, 0u);
     const int base = s_msg[0], L = s_msg[1];
     if (base < 0) return;
     const int h0 = w * x.heads, nh = min(c.Hkv, h0 + x.heads) - h0;
@@ -217,7 +246,7 @@ __device__ __forceinline__ void copy_rows(const StepArgs& x, const AcceptArgs& a
 template <typename T, bool STEP>
 __device__ __forceinline__ void path_step(const AcceptArgs& a, const StepArgs& x, int b) {
     __shared__ Rows rows;
-    const long long deadline = (long long)wall_clock64() + a.wait_ticks;
+    const long long started = (long long)wall_clock64(), deadline = started + a.wait_ticks;
     const int i = threadIdx.x;
     const int N = a.N;
     __shared__ int32_t spar[kMaxNodes];
@@ -305,7 +334,7 @@ __device__ __forceinline__ void path_step(const AcceptArgs& a, const StepArgs& x
         }
         if constexpr (STEP) {
             __syncthreads();
-            announce_path(x, a, b, base, s_len, s_node);
+            announce_path(x, a, b, base, s_len, s_node, started);
         }
         return;
     }
@@ -351,7 +380,7 @@ __device__ __forceinline__ void path_step(const AcceptArgs& a, const StepArgs& x
         }
         if constexpr (STEP) {
             __syncthreads();
-            announce_path(x, a, b, base, s_len, s_node);
+            announce_path(x, a, b, base, s_len, s_node, started);
         }
         return;
     }
@@ -375,7 +404,7 @@ __device__ __forceinline__ void path_step(const AcceptArgs& a, const StepArgs& x
     }
     if constexpr (STEP) {
         __syncthreads();
-        announce_path(x, a, b, base, s_len, s_node);
+        announce_path(x, a, b, base, s_len, s_node, started);
     }
 }
 
@@ -592,14 +621,15 @@ static hipError_t launch_step_as(const AttnArgs& attn, const AcceptArgs& a, cons
 
 // up to kMostCopiers per sequence, whole KV heads each
 size_t step_message_bytes(int B, int Hkv) {
-    return (size_t)B * (Hkv < kMostCopiers ? Hkv : kMostCopiers) * kMessage * sizeof(rec_t);
+    return (size_t)B * (Hkv < kMostCopiers ? Hkv : kMostCopiers) * kMessageWords * sizeof(rec_t);
 }
 
 hipError_t launch_step(const AttnArgs& attn, bool merged, const AcceptArgs& a, const CompactArgs& compact, unsigned long long* messages,
-                       hipStream_t st) {
+                       long long copy_ticks, hipStream_t st) {
     StepArgs x;
     x.compact = compact;
     x.messages = messages;
+    x.copy_ticks = copy_ticks;
     x.merge_wgs = 0;
     x.merge_chunks = x.merge_passes = 1;
     x.attn_D = attn.D;

@@ -117,7 +117,7 @@ struct CompactArgs;
 // The rest of a verification step after the attention kernel in one launch: the merge of divided attention (if
 // `merge`), acceptance, and the accepted path's rows appended to the cache.  All three of one element type.
 hipError_t launch_step(const AttnArgs& attn, bool merge, const AcceptArgs& accept, const CompactArgs& compact,
-                       unsigned long long* messages, hipStream_t st);
+                       unsigned long long* messages, long long copy_ticks, hipStream_t st);
 size_t step_message_bytes(int B, int Hkv);
 int accept_chunk_elems();
 void accept_plan(int B, int N, int V, int head, int* chunks, int* seg, int* nseg);

@@ -260,6 +260,16 @@ s4c_status accept_args_ok(int32_t B, int32_t N, int32_t V, int32_t logits_dtype,
     return S4C_OK;
 }
 
+// A waiting time in microseconds, up to a minute, replaced by an environment variable (read at every call).
+long long wait_us(const char* name, long long otherwise) {
+    if (const char* env = getenv(name)) {
+        char* end = nullptr;
+        const long long v = strtoll(env, &end, 10);
+        if (end != env && v >= 0 && v <= 60000000ll) return v;
+    }
+    return otherwise;
+}
+
 // `workspace` holds at least s4c_accept_path_workspace_size(B, N, V) bytes, 256-byte aligned
 AcceptArgs accept_prepare(int32_t B, int32_t N, int32_t V, int32_t logits_dtype, int32_t mode, float temperature,
                           const void* logits, const int32_t* parent, const int32_t* tokens, const float* p_draft,
@@ -274,13 +284,7 @@ AcceptArgs accept_prepare(int32_t B, int32_t N, int32_t V, int32_t logits_dtype,
     // S4C_ACCEPT_WAIT_US (environment, >= 0): how long a sequence's collecting workgroup waits for the
     // statistics of the others before it flags the sequence.  A diagnostic knob: 0 makes a collector that
     // does not find everything at its first look give up, which exercises the flagged path on a healthy GPU.
-    long long wait_us = 2000000;
-    if (const char* env = getenv("S4C_ACCEPT_WAIT_US")) {
-        char* end = nullptr;
-        const long long v = strtoll(env, &end, 10);
-        if (end != env && v >= 0 && v <= 60000000ll) wait_us = v;
-    }
-    a.wait_ticks = wait_us * 100;
+    a.wait_ticks = wait_us("S4C_ACCEPT_WAIT_US", 2000000) * 100;
     a.B = B; a.N = N; a.V = V;
     const size_t es = logits_dtype == S4C_F32 ? 4 : 2;
     a.plan = scan_plan(B, N, V, (int)es, device_cus());
@@ -632,7 +636,9 @@ s4c_status s4c_verify_step(const s4c_step* p, void* hip_stream) {
     if (p->logits_dtype == p->shape.dtype) {
         if (e == hipSuccess)
             e = launch_step(attn, plan.division.split != 1, accept, compact,
-                            (unsigned long long*)((char*)p->accept_workspace + s4c_accept_path_workspace_size(B, N, V)), st);
+                            (unsigned long long*)((char*)p->accept_workspace + s4c_accept_path_workspace_size(B, N, V)),
+                            // the copying workgroups wait 2 s longer than the collector they hear from (S4C_COPY_WAIT_US: that long)
+                            wait_us("S4C_COPY_WAIT_US", accept.wait_ticks / 100 + 2000000) * 100, st);
     } else {
         if (e == hipSuccess && plan.division.split != 1) e = launch_attn_merge(attn, p->shape.dtype, st);
         if (e == hipSuccess) e = launch_accept(accept, st);
