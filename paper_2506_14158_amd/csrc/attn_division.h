@@ -30,8 +30,9 @@
 
 namespace s4c {
 
-// What one workgroup of the kernel for a shape takes: query rows, keys per tile, and how many fit on a CU.
-struct AttnTile { int rows, keys, per_cu; };
+// What one workgroup of the kernel for a shape takes: query rows, keys per tile, and how many fit on a CU; `wide`: 16-bit
+// data of head size 128.
+struct AttnTile { int rows, keys, per_cu; bool wide; };
 
 struct AttnDivision {
     int teams, split, mtiles;
@@ -48,21 +49,45 @@ inline AttnDivision plan_division(int B, int Hkv, int N, int M, int max_cache_le
     const long long tiles = (max_cache_len + t.keys - 1) / t.keys + (N + t.keys - 1) / t.keys;   // of the longest unit
     // Teams: one round of the chip, a team's workgroups all on one XCD (an eighth of it); fewer when a share would get
     // shorter than kMinKeys keys, below which a part's fixed costs (prologue, partial results, its share of the merge)
-    // outweigh what the extra workgroups stream; at most kMaxParts runs per unit.
+    // outweigh what the extra workgroups stream, but never fewer than units for that: whole units have no parts, and several
+    // short ones in a row are a chain (512 units of 20 keys + 20 nodes: 28.0 us on 192 teams, 8.6 on 512).  At most
+    // kMaxParts runs per unit.
     const long long kMinKeys = 256, kMaxParts = 24, per_xcd = slots / 8;
     long long teams = per_xcd >= p.mtiles ? per_xcd / p.mtiles * 8 : 8;
-    const long long most = units * tiles * t.keys / kMinKeys;
+    long long most = units * tiles * t.keys / kMinKeys;
+    if (most < units) most = units;
     if (teams > most) teams = most;
     if (teams > units * kMaxParts) teams = units * kMaxParts;
     // A share that ends inside a unit has a second segment to start and finish, which costs as much as kSwitchKeys keys:
     // whole numbers of runs per unit where the longer runs cost less than that, and where no unit would get a second.
-    const long long kSwitchKeys = 256;
+    //
+    // And a unit that is not divided has no parts, of as many rows as a workgroup has, to write and to merge, nor a merge at
+    // all if no unit is.  Undivided units leave part of the chip's (last) round idle, `idle` keys of each team's time.  Whole
+    // and divided, us (where they meet depends on the rows that go through the workspace):
+    //   prefixes below kShortKeys, unless most of the chip would be idle: 160 units, 60 rows, 500 keys 15.7 and 20.2; 24 units, 80 rows 17.8 and 15.8
+    //   the kernel with 32-key tiles, at three units on four CUs (it waits for memory, of which a workgroup that has a
+    //     CU to itself gets more): 224 units, 60 rows, 1200 keys 27.1 and 32.8, 2600 keys 60.6 and 60.9; 320 units 38.4 and 47.2
+    //   the kernel with 64-key tiles, one round: 136 units, 240 rows, 500 keys 24.6 and 40.0, 2600 keys 70.1 and 75.6, 5000 keys 131 and 120
+    //   more than one round: 1280 units, 60 rows, 1200 keys 164 and 180; 544 units of 4800 keys 291 and 269 (20 rows: 285 and 242);
+    //     264 units, 80 rows, 150 keys 23.9 and 27.2, 300 keys 31.1 and 30.6, 1200 keys 58.9 and 45.8
+    // (Several rounds of equal shares that are whole units need no merge either, and load a unit behind the last one.)
+    // fp32 data and head size 64 do more arithmetic per byte, and shares win from short prefixes on: 136 units, 80 rows, 800 keys
+    // of fp32 130 and 87 (640 units of head size 64, 40 keys + 20 nodes: 18.1 and 19.9).
+    const long long kSwitchKeys = 256, kShortKeys = 512;
+    const long long rounds = (units + teams - 1) / teams, idle = tiles * t.keys * (rounds * teams - units) / (rounds * teams);
+    const long long rows = M < t.rows ? M : t.rows;
     long long split = 0;
     if (units * tiles > 0x3FFFFFFFll) split = 1;                             // beyond the kernels' 32-bit tile numbers
     else if (teams >= units) {
         const long long q = teams / units;
         if ((tiles + q - 1) / q * t.keys <= units * tiles * t.keys / teams + kSwitchKeys) split = q;
-    } else if (units * p.mtiles <= slots) split = 1;
+        if (t.wide && (max_cache_len < kShortKeys ? units * p.mtiles * 8 > cus
+                       : t.keys == 32             ? units * 4 >= cus * 3ll
+                                                  : q == 1 && idle <= 400 + 5 * rows))
+            split = 1;
+    } else if (units * p.mtiles <= slots || (idle > 0 && (tiles * t.keys <= 128 || (t.wide && idle * 16 <= rows * (t.keys == 32 ? 256 : 28))))) {
+        split = 1;
+    }
     p.split = (int)split;
     p.teams = (int)(split > 0 ? units * split : teams < 1 ? 1 : teams);
     if (split == 1) {

@@ -68,6 +68,7 @@ struct AttnArgs {
     int32_t teams;      // teams the work is divided between (attn_division.h)
     int32_t split;      // teams per (sequence, KV head); 0: equal shares of all units' tiles laid end to end
     int32_t mtiles;     // query-row tiles per (sequence, KV head) = workgroups per team
+    int32_t tile_rows;  // query rows per workgroup
     int32_t tile_keys, tile_shift;   // keys per tile of the kernel that will run, and its log2
     float scale_log2; // softmax scale * log2(e)
     // paged cache (block_table != null): k_cache / v_cache are pools [num_pages][Hkv][page][D],
@@ -81,7 +82,7 @@ hipError_t launch_tree_attn_large(const AttnArgs& a, int dtype, hipStream_t st);
 hipError_t launch_tree_attn_small(const AttnArgs& a, int dtype, hipStream_t st);    // at most 64 query rows, or fp32 data
 hipError_t launch_attn_merge(const AttnArgs& a, int dtype, hipStream_t st);
 AttnTile attn_tile_large(const s4c_attn_shape& s);
-AttnTile attn_tile_small(const s4c_attn_shape& s);
+AttnTile attn_tile_small(const s4c_attn_shape& s, int32_t max_cache_len, int cus);
 
 // How a call's scan is divided: see scan_plan in accept_path.hip
 struct AcceptPlan {

@@ -91,7 +91,7 @@ AttnPlan plan_attn(const s4c_attn_shape& s, int32_t max_cache_len) {
     AttnPlan p;
     const int M = s.N * (s.Hq / s.Hkv);
     p.large = s.dtype != S4C_F32 && M > 64;
-    p.tile = p.large ? attn_tile_large(s) : attn_tile_small(s);
+    p.tile = p.large ? attn_tile_large(s) : attn_tile_small(s, max_cache_len, device_cus());
     p.division = plan_division(s.B, s.Hkv, s.N, M, max_cache_len, p.tile, device_cus());
     if (p.division.split == 1) {
         p.ws_o_bytes = p.ws_ml_bytes = p.ws_parts_bytes = 0;
@@ -173,7 +173,7 @@ s4c_status tree_attn_prepare(const s4c_attn_shape* shape, const void* q, const v
     a.B = shape->B; a.Hq = shape->Hq; a.Hkv = shape->Hkv; a.D = shape->D; a.N = shape->N;
     a.S_cap = shape->S_cap; a.G = shape->Hq / shape->Hkv; a.M = a.N * a.G;
     a.max_cache_len = max_cache_len; a.teams = p.division.teams; a.split = p.division.split; a.mtiles = p.division.mtiles;
-    a.tile_keys = p.tile.keys; a.tile_shift = __builtin_ctz((unsigned)p.tile.keys);
+    a.tile_rows = p.tile.rows; a.tile_keys = p.tile.keys; a.tile_shift = __builtin_ctz((unsigned)p.tile.keys);
     a.scale_log2 = (scale > 0.f ? scale : 1.0f / sqrtf((float)shape->D)) * kLog2e;
     a.block_table = block_table; a.max_blocks = max_blocks; a.page_shift = page_shift; a.num_pages = num_pages;
     *plan = p;

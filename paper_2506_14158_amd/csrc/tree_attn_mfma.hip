@@ -535,7 +535,7 @@ hipError_t launch_by_shape(const AttnArgs& a, hipStream_t st) {
 // 32 rows per wave.  (Head size 64 leaves room for two four-wave workgroups on a CU.)
 AttnTile attn_tile_large(const s4c_attn_shape& s) {
     const int wr = pick_wr(s.N * (s.Hq / s.Hkv));
-    return AttnTile{32 * wr, kBN, wr == 4 && 2 * lds_bytes_for(4, s.D) <= 160 * 1024 ? 2 : 1};
+    return AttnTile{32 * wr, kBN, wr == 4 && 2 * lds_bytes_for(4, s.D) <= 160 * 1024 ? 2 : 1, s.D == 128};
 }
 
 hipError_t launch_tree_attn_large(const AttnArgs& a, int dtype, hipStream_t st) {

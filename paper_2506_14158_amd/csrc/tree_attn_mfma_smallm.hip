@@ -534,35 +534,42 @@ hipError_t launch(const AttnArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-// The configuration for an element type, head size and row count, handed to `use` as a type.  Up to 32 rows: one
-// row block, four key groups, so that no wave works on rows that do not exist.
+// The configuration for an element type, head size and rows per workgroup (attn_tile_small), handed to `use` as a type.
+// 32 rows: one row block, four key groups, so that no wave works on rows that do not exist.
 template <Elem E, class Use>
-auto with_cfg(int D, int M, Use use) {
+auto with_cfg(int D, int rows, Use use) {
     if constexpr (E == kF32) {
-        if (D == 64) return M <= 32 ? use(Cfg<E, 64, 4, 1, 2>{}) : use(Cfg<E, 64, 2, 2, 2>{});
+        if (D == 64) return rows == 32 ? use(Cfg<E, 64, 4, 1, 2>{}) : use(Cfg<E, 64, 2, 2, 2>{});
         return use(Cfg<E, 128, 2, 2, 2>{});          // (four key groups of 32 KB tiles would not fit twice)
     } else {
-        if (D == 64) return M <= 32 ? use(Cfg<E, 64, 4, 1, 2>{}) : use(Cfg<E, 64, 2, 2, 4>{});
-        return M <= 32 ? use(Cfg<E, 128, 4, 1, 2>{}) : use(Cfg<E, 128, 2, 2, 2>{});
+        // (64 rows of head size 64: tiles of 8 KB, so four rounds are the same 64 KB of loads in flight)
+        if (D == 64) return rows == 32 ? use(Cfg<E, 64, 4, 1, 2>{}) : use(Cfg<E, 64, 2, 2, 4>{});
+        return rows == 32 ? use(Cfg<E, 128, 4, 1, 2>{}) : use(Cfg<E, 128, 2, 2, 2>{});
     }
 }
 template <class Use>
-auto with_cfg(int dtype, int D, int M, Use use) {
-    if (dtype == S4C_F32) return with_cfg<kF32>(D, M, use);
-    return dtype == S4C_F16 ? with_cfg<kH16>(D, M, use) : with_cfg<kB16>(D, M, use);
+auto with_cfg(int dtype, int D, int rows, Use use) {
+    if (dtype == S4C_F32) return with_cfg<kF32>(D, rows, use);
+    return dtype == S4C_F16 ? with_cfg<kH16>(D, rows, use) : with_cfg<kB16>(D, rows, use);
 }
 
 }  // namespace
 
-AttnTile attn_tile_small(const s4c_attn_shape& s) {
-    return with_cfg(s.dtype, s.D, s.N * (s.Hq / s.Hkv), [](auto c) {
+// Up to 32 rows take the configuration of one row block.  16-bit data of head size 128 only where a CU has more than
+// 8192 keys to stream: four key groups fill a CU's LDS with one workgroup, and two workgroups hide each other's starts and
+// merges (512 units of 20 rows, 20 keys: 28.0 us and 8.6 with two; 640 units of 300 keys 38 and 29, 2400 keys 151 and 150, 4800 keys
+// 273 and 279; 256 units of 8192 keys 180 and 189).
+AttnTile attn_tile_small(const s4c_attn_shape& s, int32_t max_cache_len, int cus) {
+    const bool deep = (long long)s.B * s.Hkv * max_cache_len >= 8192ll * cus;
+    const int rows = s.N * (s.Hq / s.Hkv) <= 32 && (s.D == 64 || (s.dtype != S4C_F32 && deep)) ? 32 : 64;
+    return with_cfg(s.dtype, s.D, rows, [](auto c) {
         typedef decltype(c) C;
-        return AttnTile{32 * C::kRBW, kBN, C::kPerCu};
+        return AttnTile{32 * C::kRBW, kBN, C::kPerCu, C::kElem != kF32 && C::kD == 128};
     });
 }
 
 hipError_t launch_tree_attn_small(const AttnArgs& a, int dtype, hipStream_t st) {
-    return with_cfg(dtype, a.D, a.M, [&](auto c) {
+    return with_cfg(dtype, a.D, a.tile_rows, [&](auto c) {
         typedef decltype(c) C;
         return a.block_table ? launch<C, true>(a, st) : launch<C, false>(a, st);
     });

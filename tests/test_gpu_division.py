@@ -48,20 +48,23 @@ CASES = [
     Case("shares-rows64-mixed", "balanced", 3, 32, 1, 128, 37, "f16", 24000, (700, 0, 40)),
     Case("shares-rows32", "balanced", 5, 18, 1, 64, 20, "bf16", 3000, (32, 0, 1, 500, -1)),
     Case("shares-f32", "balanced", 3, 30, 2, 64, 40, "f32", 3000, (2, 50, 333)),
+    Case("shares-rows32-deep", "balanced", 33, 8, 1, 128, 20, "bf16", 7960, (500, 0, 33, 7961, 64)),   # four key groups
     Case("shares-70-sequences", "balanced", 70, 2, 1, 64, 20, "bf16", 3000, (1, 0, 64, 100, 31)),
 ]
 
 
 def plan_inputs(c):
-    """B, Hkv, N, M, max_cache_len, then rows, keys and workgroups per CU of the kernel's tile for the case, and CUs"""
+    """B, Hkv, N, M, max_cache_len, then rows, keys and workgroups per CU of the kernel's tile for the case, whether it is 16-bit
+    data of head size 128, and CUs"""
     M = c.N * c.G
+    wide = c.dtype != "f32" and c.D == 128
     if c.dtype != "f32" and M > 64:
         tile = (128, 64, 2 if c.D == 64 else 1) if M <= 128 else (256, 64, 1)
-    elif M <= 32 and (c.dtype != "f32" or c.D == 64):
+    elif M <= 32 and (c.D == 64 or (wide and c.B * c.Hkv * c.max_len >= 8192 * 256)):
         tile = (32, 32, 1)
     else:
         tile = (64, 32, 1 if c.dtype == "f32" and c.D == 128 else 2)
-    return (c.B, c.Hkv, c.N, M, c.max_len) + tile + (256,)
+    return (c.B, c.Hkv, c.N, M, c.max_len) + tile + (int(wide), 256)
 
 
 def inputs(c):
