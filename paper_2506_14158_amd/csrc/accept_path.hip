@@ -468,12 +468,19 @@ __device__ __forceinline__ void scan_run(const AcceptArgs& a, int b, int j) {
                 }
                 const float ref = m_t > -INFINITY ? m_t * a.inv_temp_log2 : 0.f;
                 float sum[2] = {0.f, 0.f};
+                // (a reference beyond the range of fp32: rows masked with the type's lowest value, for one)
+                const bool in_range = fabsf(ref) <= 3.0e38f;
 #pragma unroll
                 for (int q = 0; q < NV; ++q) {
                     float x[VN];
                     decode<T>(cur[q], x);
+                    if (in_range) {
 #pragma unroll
-                    for (int e = 0; e < VN; ++e) sum[e & 1] += fast_exp2(fmaf(x[e], a.inv_temp_log2, -ref));   // padding: 0
+                        for (int e = 0; e < VN; ++e) sum[e & 1] += fast_exp2(fmaf(x[e], a.inv_temp_log2, -ref));   // padding: 0
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < VN; ++e) sum[e & 1] += fast_exp2((x[e] - m_t) * a.inv_temp_log2);
+                    }
                 }
                 s_t += sum[0] + sum[1];
             }

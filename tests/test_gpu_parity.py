@@ -373,6 +373,34 @@ def test_stochastic_acceptance_never_reads_leaf_rows():
     assert (tv.bonus_token.cpu().numpy() == -1).all()
 
 
+@pytest.mark.parametrize("dtype, temperature", [("bf16", 1.0), ("f32", 0.7), ("f16", 1.0)])
+def test_stochastic_acceptance_of_rows_masked_with_the_lowest_value(dtype, temperature):
+    """More than a chunk of every row's logits is the type's lowest finite value, the way a sampler masks tokens; times
+    log2(e) / T that is beyond fp32 (bf16, fp32).  One row is masked altogether: every token has probability 1 / V there."""
+    cfg = synth.scaled(C[3], name="masked-" + dtype, B=3, V=20003, dtype=dtype, temperature=temperature, index=0)
+    par = synth.make_parent(cfg)
+    lowest = {"bf16": np.uint16(0xFF7F), "f16": np.uint16(0xFBFF), "f32": np.finfo(np.float32).min}[dtype]
+    for k in range(8):
+        ac = synth.make_accept_inputs(cfg, par, seed=cfg.seed() + 1000 * k)
+        lg = ac.logits.copy()
+        lg = lg.view(np.uint16) if dtype == "f16" else lg
+        for b in range(cfg.B):
+            for u in range(cfg.N):
+                masked = np.ones(cfg.V, dtype=bool)
+                masked[12000:] = u == par[1].max() and b == 1
+                masked[ac.tokens[b, par[b] == u]] &= masked[-1]
+                lg[b, u, masked] = lowest
+        lg = lg.view(ac.logits.dtype)
+        r = O.accept_path(lg, par, ac.tokens, cfg.mode, cfg.levels, ac.p_draft, ac.uniforms, cfg.temperature)
+        if float(r["margin"].min()) > 2e-5:
+            break
+    assert float(r["margin"].min()) > 2e-5 and r["accept_len"].max() > 0
+    tv = run_accept(cfg, par, synth.AcceptInputs(lg, ac.tokens, ac.p_draft, ac.uniforms))
+    assert np.array_equal(tv.accept_status.cpu().numpy(), r["status"])
+    assert np.array_equal(tv.path.cpu().numpy(), r["path"])
+    assert np.array_equal(tv.accepted_tokens.cpu().numpy(), r["accepted_tokens"])
+
+
 def test_accept_repeated_calls_need_no_workspace_initialisation():
     """The acceptance workspace carries per-call tags instead of counters that would have to start at
     zero: the same answer must come out of many calls in a row, whatever the workspace held before each
