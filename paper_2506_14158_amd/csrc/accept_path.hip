@@ -3,11 +3,13 @@
 //
 // Scan (the HBM-bound part).  The rows to scan of a sequence -- every row in greedy mode (the bonus token may come from
 // any), the rows of nodes that have children in stochastic mode -- are laid end to end and cut into equal runs of
-// 8192-logit chunks, one for each of the sequence's scanning workgroups; all of a launch's workgroups fit on the chip
-// at once, so none waits for a second turn.  (Fixed segments of up to 8 chunks made config 5 2612 workgroups on
-// 1280 places, the third turn almost empty.)  Measured, whole calls back to back, against fixed segments: 345 MB of bf16
+// 8192-logit chunks, one for each of the sequence's scanning workgroups.  For batches of no more sequences than the chip
+// holds workgroups (scan_plan) the scanning workgroups are resident at once, so none of them waits for a second turn; what
+// else the launch holds comes behind them in grid order.  (Fixed segments of up to 8 chunks made config 5 2612 workgroups on
+// 1280 places, the third turn almost empty.)  Measured, whole calls back to back on one input, against fixed segments: 345 MB of bf16
 // logits 72.3 -> 70.5 us, 131 MB 29.0 -> 28.0, 9 MB 11.9 -> 9.1, 4 MB 10.8 -> 6.7; 51 MB in rows of odd length 71.7 -> 18.7.
-// Of what is left about 6 us are the launch, the first loads and the collector's look; the rest streams at 5.4 - 6 TB/s.
+// About 6 us of that are the launch, the first loads and the collector's look.  With inputs that the last-level cache does not
+// hold from the call before, 335 MB take 76 us and 131 MB 32: 4.8 - 5 TB/s behind those 6 us.
 // A chunk is read exactly once with 16-byte loads, the next one in
 // flight while it is reduced, across the ends of rows too.
 //   Greedy: per thread a running maximum; the raw words of the chunk that holds it are kept aside, and its position

@@ -19,7 +19,7 @@ C = synth.CONFIGS
 f16 = lambda c, **kw: synth.scaled(c, dtype="f16", index=0, **kw)
 
 ATTN = [
-    f16(C[1], name="tiny-f16"),                                                    # D = 64: scalar kernel
+    f16(C[1], name="tiny-f16"),                                                    # D = 64
     f16(C[1], name="tiny-f16-ragged", B=3, P=77, ragged=True),
     f16(C[2], name="7b-f16", Hq=4, Hkv=4, P=333),                                  # <= 64 rows, ragged tail
     f16(C[2], name="7b-f16-splits", Hq=2, Hkv=2, P=2500),                          # KV splits + merge

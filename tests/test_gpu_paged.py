@@ -32,7 +32,7 @@ def scatter_to_pool(cache_np, page_size, rng, spare=5):
 
 
 SHAPES = [
-    (synth.scaled(C[1], name="tiny-f32", B=2, P=200, ragged=True, index=0), 64),                    # scalar kernel
+    (synth.scaled(C[1], name="tiny-f32", B=2, P=200, ragged=True, index=0), 64),                    # fp32
     (synth.scaled(C[2], name="7b-splits", Hq=2, Hkv=2, P=2500, index=0), 128),                      # <= 64 rows, splits
     (synth.scaled(C[3], name="13b-small", B=2, Hq=3, Hkv=3, P=1000, ragged=True, index=0), 64),
     (synth.scaled(C[5], name="70b-mid", B=1, Hq=8, Hkv=1, P=300, N=16, levels=5, index=0), 256),    # 128 rows

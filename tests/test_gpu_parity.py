@@ -83,7 +83,7 @@ def test_tree_attn_elementwise(cfg):
 
 
 def _random_shapes():
-    """Seeded sweep over shapes that land in each attention kernel (scalar; matrix-core with <= 64,
+    """Seeded sweep over shapes that land in each attention kernel (few rows, fp32; with <= 64,
     <= 128 and > 128 query rows per KV head), with odd sizes, ragged lengths and forced KV splits."""
     rng = np.random.default_rng(20250614)
     shapes = []
@@ -111,7 +111,7 @@ PEAKED = [
     synth.scaled(C[4], name="peaked-256rows-splits", B=1, Hq=4, Hkv=1, P=5000, ragged=False, index=0),
     synth.scaled(C[5], name="peaked-128rows", B=1, Hq=8, Hkv=1, P=1500, N=16, levels=5, index=0),   # 4 waves
     synth.scaled(C[3], name="peaked-64rows", B=2, Hq=3, Hkv=3, P=2000, ragged=True, index=0),       # key-group kernel
-    synth.scaled(C[1], name="peaked-f32", B=2, P=300, index=0),                                      # scalar kernel
+    synth.scaled(C[1], name="peaked-f32", B=2, P=300, index=0),                                      # few-row kernel, fp32 products
     synth.scaled(C[4], name="peaked-f16", B=2, Hq=8, Hkv=2, P=3000, dtype="f16", index=0),
 ]
 
@@ -430,10 +430,10 @@ def test_accept_repeated_calls_need_no_workspace_initialisation():
 
 def test_accept_collector_that_gives_up_flags_the_sequence(monkeypatch):
     """The bounded wait of the collecting workgroups, forced from the host: with a waiting time of zero a
-    collector that does not find all of its sequence's statistics at its first look gives up.  The launch
-    below has more scanning workgroups than fit on the GPU at once, and the collectors (which have no
-    segment of their own in stochastic mode) are the last of the grid, so they start while the last
-    scanning workgroups have only just begun 128 KB segments.  Every kernel must exit, the sequences
+    collector that does not find all of its sequence's statistics at its first look gives up.  The scanning
+    workgroups of the launch below take all the room on the GPU, with runs of seven or eight 16 KB chunks each, so
+    the collectors (the last of the grid) start when the first of those end and look while others are in the middle
+    of theirs.  Every kernel must exit, the sequences
     must come back flagged and empty, and the next call with the default wait must give the oracle's
     answer on the same buffers."""
     cfg = synth.scaled(C[3], name="accept-timeout", B=2, V=1_000_003, index=0)
