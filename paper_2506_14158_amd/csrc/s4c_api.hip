@@ -87,11 +87,11 @@ struct AttnPlan {
 };
 
 // a fixed function of (shape, max_cache_len), so that the workspace query and the launch agree
-AttnPlan plan_attn(const s4c_attn_shape& s, int32_t max_cache_len) {
+AttnPlan plan_attn(const s4c_attn_shape& s, int32_t max_cache_len, AttnTile small) {
     AttnPlan p;
     const int M = s.N * (s.Hq / s.Hkv);
     p.large = s.dtype != S4C_F32 && M > 64;
-    p.tile = p.large ? attn_tile_large(s) : attn_tile_small(s, max_cache_len, device_cus());
+    p.tile = p.large ? attn_tile_large(s) : small;
     p.division = plan_division(s.B, s.Hkv, s.N, M, max_cache_len, p.tile, device_cus());
     if (p.division.split == 1) {
         p.ws_o_bytes = p.ws_ml_bytes = p.ws_parts_bytes = 0;
@@ -103,6 +103,10 @@ AttnPlan plan_attn(const s4c_attn_shape& s, int32_t max_cache_len) {
     }
     return p;
 }
+AttnPlan plan_attn(const s4c_attn_shape& s, int32_t max_cache_len) {
+    return plan_attn(s, max_cache_len, attn_tile_small(s, max_cache_len, device_cus()));
+}
+size_t workspace_bytes_of(const AttnPlan& p) { return p.ws_o_bytes + p.ws_ml_bytes + p.ws_parts_bytes; }
 
 }  // namespace
 
@@ -125,8 +129,10 @@ const char* s4c_strerror(int code) {
 size_t s4c_tree_attn_workspace_size(const s4c_attn_shape* shape, int32_t max_cache_len) {
     s4c_status why;
     if (!shape || !shape_ok(shape, &why) || max_cache_len < 0) return 0;
-    const AttnPlan p = plan_attn(*shape, max_cache_len);
-    return p.ws_o_bytes + p.ws_ml_bytes + p.ws_parts_bytes;
+    // Also what short units' configuration takes, so that a workspace serves every call up to the length it was made for.
+    const size_t own = workspace_bytes_of(plan_attn(*shape, max_cache_len));
+    const size_t shorter = workspace_bytes_of(plan_attn(*shape, max_cache_len, attn_tile_small(*shape, 0, device_cus())));
+    return own > shorter ? own : shorter;
 }
 
 int32_t s4c_tree_attn_num_splits(const s4c_attn_shape* shape, int32_t max_cache_len) {
@@ -161,7 +167,7 @@ s4c_status tree_attn_prepare(const s4c_attn_shape* shape, const void* q, const v
         !aligned16(out))
         return S4C_ERR_SHAPE;
     const AttnPlan p = plan_attn(*shape, max_cache_len);
-    const size_t need = p.ws_o_bytes + p.ws_ml_bytes + p.ws_parts_bytes;
+    const size_t need = workspace_bytes_of(p);
     if (need > 0 && (!workspace || workspace_bytes < need || (((uintptr_t)workspace) & 255))) return S4C_ERR_WORKSPACE;
 
     AttnArgs& a = *args;

@@ -2,6 +2,7 @@
 rejects host-checkable mistakes before touching the device."""
 import ctypes as C
 import os
+import random
 import re
 
 import pytest
@@ -129,6 +130,18 @@ def test_paged_and_multi_layer_host_errors(L):
     need = B.s4c_draft_linear_workspace_size(60, 4096, 4096)
     assert need >= 60 * 4096 * 4 and need % 256 == 0
     assert dl(T=60, H=4096, Hout=4096) == -4 and dl(T=60, H=4096, Hout=4096, ws=one, wsb=need - 1) == -4
+
+
+def test_attention_workspace_serves_every_shorter_call(L):
+    """A loop sizes the workspace once, for its longest sequence, and calls with the length of the moment."""
+    rng = random.Random(7)
+    lengths = sorted({0, 1, 33, 64, 100, 256, 511, 512, 4095, 4096, 8192, 30000} | {int(1.25 ** k) for k in range(48)})
+    for _ in range(300):
+        Hkv, G = rng.choice([1, 2, 4, 8, 16, 32, 40]), rng.choice([1, 1, 2, 4, 8])
+        s = shape(B=rng.choice([1, 2, 3, 5, 8, 13, 17, 24, 40, 64]), Hq=Hkv * G, Hkv=Hkv, N=rng.choice([rng.randint(1, 128), rng.randint(1, 32)]),
+                  D=rng.choice([64, 128, 128]), S_cap=50000, dtype=rng.choice([0, 1, 2]))
+        sizes = [B.s4c_tree_attn_workspace_size(s, n) for n in lengths]
+        assert sizes == sorted(sizes), (s.B, s.Hq, s.Hkv, s.N, s.D, s.dtype, list(zip(lengths, sizes)))
 
 
 def test_missing_library_fails_loudly(monkeypatch):
