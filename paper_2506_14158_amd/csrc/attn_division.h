@@ -85,7 +85,7 @@ inline AttnDivision plan_division(int B, int Hkv, int N, int M, int max_cache_le
                        : t.keys == 32             ? units * 4 >= cus * 3ll
                                                   : q == 1 && idle <= 400 + 5 * rows))
             split = 1;
-    } else if (units * p.mtiles <= slots || (idle > 0 && (tiles * t.keys <= 128 || (t.wide && idle * 16 <= rows * (t.keys == 32 ? 256 : 28))))) {
+    } else if (units * p.mtiles <= slots || (units % teams != 0 && (tiles * t.keys <= 128 || (t.wide && idle * 16 <= rows * (t.keys == 32 ? 256 : 28))))) {
         split = 1;
     }
     p.split = (int)split;

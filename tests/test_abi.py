@@ -136,10 +136,12 @@ def test_attention_workspace_serves_every_shorter_call(L):
     """A loop sizes the workspace once, for its longest sequence, and calls with the length of the moment."""
     rng = random.Random(7)
     lengths = sorted({0, 1, 33, 64, 100, 256, 511, 512, 4095, 4096, 8192, 30000} | {int(1.25 ** k) for k in range(48)})
+    shapes = [(13, 40, 8, 33, 128, 0)]                                  # units just short of whole rounds of teams
     for _ in range(300):
-        Hkv, G = rng.choice([1, 2, 4, 8, 16, 32, 40]), rng.choice([1, 1, 2, 4, 8])
-        s = shape(B=rng.choice([1, 2, 3, 5, 8, 13, 17, 24, 40, 64]), Hq=Hkv * G, Hkv=Hkv, N=rng.choice([rng.randint(1, 128), rng.randint(1, 32)]),
-                  D=rng.choice([64, 128, 128]), S_cap=50000, dtype=rng.choice([0, 1, 2]))
+        shapes.append((rng.choice([1, 2, 3, 5, 8, 13, 17, 24, 40, 64]), rng.choice([1, 2, 4, 8, 16, 32, 40]), rng.choice([1, 1, 2, 4, 8]),
+                       rng.choice([rng.randint(1, 128), rng.randint(1, 32)]), rng.choice([64, 128, 128]), rng.choice([0, 1, 2])))
+    for batch, Hkv, G, N, D, dtype in shapes:
+        s = shape(B=batch, Hq=Hkv * G, Hkv=Hkv, N=N, D=D, S_cap=50000, dtype=dtype)
         sizes = [B.s4c_tree_attn_workspace_size(s, n) for n in lengths]
         assert sizes == sorted(sizes), (s.B, s.Hq, s.Hkv, s.N, s.D, s.dtype, list(zip(lengths, sizes)))
 
