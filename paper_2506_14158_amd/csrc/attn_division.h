@@ -65,9 +65,11 @@ inline AttnDivision plan_division(int B, int Hkv, int N, int M, int max_cache_le
     // all if no unit is.  Undivided units leave part of the chip's (last) round idle, `idle` keys of each team's time.  Whole
     // and divided, us (where they meet depends on the rows that go through the workspace):
     //   prefixes below kShortKeys, unless most of the chip would be idle: 160 units, 60 rows, 500 keys 15.7 and 20.2; 24 units, 80 rows 17.8 and 15.8
-    //   the kernel with 32-key tiles, at three units on four CUs (it waits for memory, of which a workgroup that has a
-    //     CU to itself gets more): 224 units, 60 rows, 1200 keys 27.1 and 32.8, 2600 keys 60.6 and 60.9; 320 units 38.4 and 47.2
-    //   the kernel with 64-key tiles, one round: 136 units, 240 rows, 500 keys 24.6 and 40.0, 2600 keys 70.1 and 75.6, 5000 keys 131 and 120
+    //   the kernel with 32-key tiles, two workgroups a CU, at three units on four CUs (it waits for memory, of which a workgroup that has a
+    //     CU to itself gets more): 224 units, 60 rows, 1200 keys 27.1 and 32.8, 2600 keys 60.6 and 60.9; 20 rows, 1200 keys 26.2 and 29.2,
+    //     2600 keys 57.3 and 53.5; 320 units, 60 rows, 1200 keys 38.4 and 47.2; a step of 240 units of 5 rows, 8253 keys 221 and 192
+    //   the kernel with 64-key tiles, one round: 136 units, 240 rows, 500 keys 24.6 and 40.0, 5000 keys 131 and 120; 200 units, 80 rows,
+    //     1200 keys 31.1 and 39.5 (at lengths between half and all of 2184, 88 rows: a step of 66 and 60)
     //   more than one round: 1280 units, 60 rows, 1200 keys 164 and 180; 544 units of 4800 keys 291 and 269 (20 rows: 285 and 242);
     //     264 units, 80 rows, 150 keys 23.9 and 27.2, 300 keys 31.1 and 30.6, 1200 keys 58.9 and 45.8
     // (Several rounds of equal shares that are whole units need no merge either, and load a unit behind the last one.)
@@ -82,8 +84,8 @@ inline AttnDivision plan_division(int B, int Hkv, int N, int M, int max_cache_le
         const long long q = teams / units;
         if ((tiles + q - 1) / q * t.keys <= units * tiles * t.keys / teams + kSwitchKeys) split = q;
         if (t.wide && (max_cache_len < kShortKeys ? units * p.mtiles * 8 > cus
-                       : t.keys == 32             ? units * 4 >= cus * 3ll
-                                                  : q == 1 && idle <= 400 + 5 * rows))
+                       : t.keys == 32             ? t.per_cu == 2 && units * 4 >= cus * 3ll && idle <= 400 + 50 * rows
+                                                  : q == 1 && idle <= 200 + 5 * rows / 2))
             split = 1;
     } else if (units * p.mtiles <= slots || (units % teams != 0 && (tiles * t.keys <= 128 || (t.wide && idle * 16 <= rows * (t.keys == 32 ? 256 : 28))))) {
         split = 1;

@@ -556,11 +556,11 @@ auto with_cfg(int dtype, int D, int rows, Use use) {
 }  // namespace
 
 // Up to 32 rows take the configuration of one row block.  16-bit data of head size 128 only where a CU has more than
-// 8192 keys to stream, in long units: four key groups fill a CU's LDS with one workgroup, and two workgroups hide each other's starts and
+// 7168 keys to stream, in long units: four key groups fill a CU's LDS with one workgroup, and two workgroups hide each other's starts and
 // merges (512 units of 20 rows, 20 keys: 28.0 us and 8.6 with two; 640 units of 300 keys 38 and 29, 2400 keys 151 and 150, 4800 keys
 // 273 and 279; 256 units of 8192 keys 180 and 189; 1280 units of 900 to 1800 keys 192 and 167).
 AttnTile attn_tile_small(const s4c_attn_shape& s, int32_t max_cache_len, int cus) {
-    const bool deep = max_cache_len >= 4096 && (long long)s.B * s.Hkv * max_cache_len >= 8192ll * cus;
+    const bool deep = max_cache_len >= 4096 && (long long)s.B * s.Hkv * max_cache_len >= 7168ll * cus;
     const int rows = s.N * (s.Hq / s.Hkv) <= 32 && (s.D == 64 || (s.dtype != S4C_F32 && deep)) ? 32 : 64;
     return with_cfg(s.dtype, s.D, rows, [](auto c) {
         typedef decltype(c) C;

@@ -60,7 +60,7 @@ def plan_inputs(c):
     wide = c.dtype != "f32" and c.D == 128
     if c.dtype != "f32" and M > 64:
         tile = (128, 64, 2 if c.D == 64 else 1) if M <= 128 else (256, 64, 1)
-    elif M <= 32 and (c.D == 64 or (wide and c.max_len >= 4096 and c.B * c.Hkv * c.max_len >= 8192 * 256)):
+    elif M <= 32 and (c.D == 64 or (wide and c.max_len >= 4096 and c.B * c.Hkv * c.max_len >= 7168 * 256)):
         tile = (32, 32, 1)
     else:
         tile = (64, 32, 1 if c.dtype == "f32" and c.D == 128 else 2)
