@@ -192,7 +192,7 @@ s4c_status s4c_accept_path_static(int32_t B, int32_t N, int32_t V, int32_t logit
  *              partial sums that the workgroups sharing one sequence exchange, so two calls that
  *              may overlap in time must not share it.
  * Arithmetic is fp64 (row maxima exact).  V <= 2^21.  The kernel polls device memory with a
- * bounded number of tries (S4C_SEQ_TIMEOUT); it needs at most 256 workgroups resident at once.
+ * bounded number of tries (S4C_SEQ_TIMEOUT); a launch has at most one workgroup per compute unit wait for others.
  * One workgroup per sequence writes all of that sequence's outputs, so a flagged sequence never
  * carries a partial result.  The environment variable S4C_RESAMPLE_SPIN_LIMIT (an integer >= 0,
  * read at every call) replaces the number of tries; 0 makes every exchange between several

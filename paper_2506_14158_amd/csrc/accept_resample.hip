@@ -2,30 +2,32 @@
 // paragraph: accept with probability min(1, p/q), redraw a rejected token from
 // norm(max(0, p - q)); Sec. 3.2, second equation: the correction at a fork of the tree).
 //
-// The walk from the root is a chain of data-dependent decisions, each needing a reduction over
-// the vocabulary, so the parallelism is inside a row, not across nodes.  A team of G workgroups
-// walks one sequence: every workgroup owns a contiguous slice of the vocabulary, reduces it,
-// and the G partial results are exchanged through a per-pass slot array in device memory
-// (one relaxed 64-bit atomic store and G polled atomic loads; a slot still holding the
-// sentinel has not been written yet).  All G workgroups then add the partials in slot order,
-// obtain bit-identical sums and so take the same branches without any other communication.
-// The poll is bounded: a workgroup that cannot complete an exchange exits.  Workgroup 0 of the team
-// is the only one that writes the sequence's outputs (the owner of the correction token hands it over
-// through one more slot), so what the caller sees is either a complete result or, if workgroup 0
-// itself gave up anywhere, the flagged empty one -- never a mixture.
+// The walk from the root is a chain of data-dependent decisions, each needing a reduction over the vocabulary.  What
+// one node decides (which child is accepted; if none, the correction token) depends on its own two rows only, so:
+//   rows    (few and short rows, see resample_by_rows) every node of every sequence is decided at the same time, a
+//           workgroup each, whether the walk will come by or not, and a workgroup per sequence behind them follows the
+//           decisions from the root.  A chain of a handful of reductions inside one CU instead of one of all levels'
+//           across several.
+//   teams   (the rest) a team of G workgroups walks one sequence, each with a slice of the vocabulary; the G partial
+//           results are exchanged through a per-pass slot array in device memory (struct Team).  All G workgroups then add
+//           the partials in slot order, obtain bit-identical sums and so take the same branches without any other
+//           communication.  Workgroup 0 of the team is the only one that writes the sequence's outputs (the owner of
+//           the correction token hands it over through one more slot), so what the caller sees is either a complete
+//           result or, if workgroup 0 itself gave up anywhere, the flagged empty one -- never a mixture.
+// Every poll is bounded: a workgroup that cannot complete an exchange exits.
 //
-// Everything is kept unnormalised so no row is ever rewritten:
+// A node's rows are read once and stay in registers (8 tokens x NG blocks a thread: the weights as fp64, the draft
+// probabilities as fp32), so a rejected child costs arithmetic and a reduction, no memory:
 //   a_0[v] = exp((l[v] - max l) / T)              S_0 = sum_v a_0[v]        (target row)
 //   a_{j+1}[v] = max(0, a_j[v] - S_j q[v])        S_{j+1} = sum_v a_{j+1}[v] (after j+1 rejections)
 // so that a_j / S_j is the j-times-corrected distribution.  A child with token x passes iff
-// u q[x] < a_j[x] / S_j.  a_j[v] is recomputed from l[v], q[v] and the j scalars S_0..S_{j-1}
-// whenever it is needed.  The correction token is the inverse CDF of a_j in token-id order.
+// u q[x] < a_j[x] / S_j.  The correction token is the inverse CDF of a_j in token-id order.
 // The arithmetic is fp64: the decisions compare sums of 10^5 terms against a uniform number,
 // and the work is a few rows per sequence, so accuracy is worth more than VALU rate here.
 //
-// Vocabulary traversal (all passes): blocks of 512 tokens; workgroup g owns blocks
-// [g*bpg, (g+1)*bpg), wave w of it the blocks [w*ipw, (w+1)*ipw) of those; in a block lane l owns
-// the 8 tokens 8l..8l+7 (one 16-byte load of 16-bit logits, two of fp32).
+// Vocabulary order: blocks of 512 tokens; workgroup g owns blocks [g*bpg, (g+1)*bpg), wave w of it the blocks
+// [w*ipw, (w+1)*ipw) of those; in a block lane l owns the 8 tokens 8l..8l+7 (one 16-byte load of 16-bit logits,
+// two of fp32).
 #include "common.h"
 
 namespace s4c {
@@ -35,16 +37,37 @@ namespace {
 constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
 constexpr int kBlock = 512;            // tokens per (wave, iteration)
-constexpr int kMaxBlocks = 4096;       // => V <= 2^21
-constexpr int kMaxTeam = 16;           // workgroups per sequence
-constexpr int kTeamBudget = 256;       // teams * team size never exceeds this many workgroups
-constexpr uint64_t kEmpty = ~0ull;     // slot not written yet (a NaN pattern no partial result has)
+constexpr int kMaxIters = 8;           // blocks per wave: 8 x 8 x (2 + 1) registers, of the 256 that two waves per SIMD have
+constexpr int kMaxSlice = kMaxIters * kWaves * kBlock;     // tokens of a workgroup: 32768
+constexpr int kMaxRow = kMaxSlice / 2;                     // longest row that one workgroup decides alone (resample_by_rows)
+constexpr int kMaxVocab = 1 << 21;
+constexpr int kTeam = 16;              // workgroups per sequence (more only where a slice would outgrow the registers)
+constexpr int kMaxTeam = kMaxVocab / kMaxSlice;
 constexpr int kSpinLimit = 1 << 20;    // default number of polls (each followed by a short sleep) before giving up
 
+// lane's value of x from another lane of the row of 16 or from the row below, through the data-parallel-primitive path of the
+// vector ALUs (a shuffle through LDS is several times the latency, and a walk is a chain of these); 0 where there is none
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp(double x) {
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROWS, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROWS, 0xF, false);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+__device__ __forceinline__ double of_lane(double x, int lane) {            // (lane wave-uniform)
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, lane), hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), lane);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+// sum over the wave, in every lane
 __device__ __forceinline__ double wave_sum(double x) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off);
-    return x;
+    x += dpp<0x111, 0xF>(x);          // row_shr:1, 2, 4, 8: lane 15 of each row holds its row's sum
+    x += dpp<0x112, 0xF>(x);
+    x += dpp<0x114, 0xF>(x);
+    x += dpp<0x118, 0xF>(x);
+    x += dpp<0x142, 0xA>(x);          // row_bcast:15 into rows 1 and 3
+    x += dpp<0x143, 0xC>(x);          // row_bcast:31 into rows 2 and 3
+    return of_lane(x, 63);
 }
 
 __device__ __forceinline__ double wave_incl_scan(double x, int lane) {
@@ -58,7 +81,9 @@ __device__ __forceinline__ double wave_incl_scan(double x, int lane) {
 
 __device__ __forceinline__ double bits_to_f64(uint64_t u) { return __longlong_as_double((long long)u); }
 __device__ __forceinline__ uint64_t f64_to_bits(double x) { return (uint64_t)__double_as_longlong(x); }
-__device__ __forceinline__ float bits_to_f32(uint64_t u) { return __uint_as_float((uint32_t)u); }
+
+// One block after the other: interleaved, the blocks' temporaries would not fit the registers beside the weights.
+__device__ __forceinline__ void keep_order() { __builtin_amdgcn_sched_barrier(0); }
 
 struct Row {
     const void* lg;       // logits row
@@ -97,354 +122,514 @@ __device__ __forceinline__ void load_draft8(const Row& r, int base, float (&qv)[
     }
 }
 
-// a_j of one token: the target weight corrected by j rejections
-__device__ __forceinline__ double corrected(float l, float qv, float m, double invT, const double* S, int j) {
-    double a = exp(((double)l - (double)m) * invT);  // exp(-inf) = 0 for padding
-    for (int i = 0; i < j; ++i) a = fmax(0.0, a - S[i] * (double)qv);
-    return a;
-}
+// What the threads of a workgroup share.
+struct Shared {
+    int32_t par[kMaxNodes], tok[kMaxNodes], child[kMaxNodes];      // the tree; the current node's children
+    int32_t count[2], fail, token;
+    double ax[kMaxNodes], lhs[kMaxNodes];                          // per node: weight and u q of its token in its parent's rows
+    double red[2][kWaves];
+    float redf[kWaves];
+    uint32_t got[4][kMaxTeam];                                     // the team's words of an exchange
+};
 
-// the 8 weights a_j of a lane's tokens in one block
-template <typename T>
-__device__ __forceinline__ void weights8(const Row& r, int base, float m, double invT, const double* S, int j,
-                                         double (&w)[8]) {
-    float x[8], qv[8];
-    load_logits8<T>(r, base, x);
-    if (j > 0) load_draft8(r, base, qv);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) w[k] = corrected(x[k], j > 0 ? qv[k] : 0.f, m, invT, S, j);
-}
+// A team's exchanges (a workgroup that works alone, G = 1, makes none).  Workgroup g's words of an exchange are 8-byte
+// records (tag << 32) | 32 bits of payload, written with device-coherent stores by thread 0 and polled by all workgroups
+// of the team.  Nothing has to be cleared before a call: a record without the tag is not there yet.  In the first exchange
+// the tag is the call's nonce, and workgroup 0 adds the time; of nonce and time the tag of the later ones is made, so that a
+// captured graph, which replays the call nonce and all, does not take the previous replay's records for its own.
+// The first exchange's records are overwritten behind the second one, when everybody has read them.  (Clearing the
+// slots in a launch of its own, as this did before, cost 3 to 5 us a call.)
+struct Team {
+    uint64_t* slots;      // of the sequence: [max_pass][4][G]
+    int g, G, max_pass, spin_limit, pass;
+    uint32_t nonce, tag;
 
-// One exchange among the G workgroups of a team.  `slots` are this exchange's 2G words: thread 0
-// contributes mineA to slots[g] and (if two) mineB to slots[G + g]; on return gotA[0..G) and
-// gotB[0..G) hold everyone's words (the same in all workgroups of the team).  *s_fail is set
-// (and stays set) if some word never arrived.
-__device__ __forceinline__ void team_exchange(uint64_t* slots, int g, int G, bool two, uint64_t mineA, uint64_t mineB,
-                                              uint64_t* gotA, uint64_t* gotB, int* s_fail, int tid, int spin_limit) {
-    if (G == 1) {
-        if (tid == 0) { gotA[0] = mineA; gotB[0] = mineB; }
-        __syncthreads();
-        return;
+    static __device__ __forceinline__ void put(uint64_t* p, uint32_t tag, uint32_t bits) {
+        __hip_atomic_store(p, ((uint64_t)tag << 32) | bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (tid == 0) {
-        __hip_atomic_store(&slots[g], mineA, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (two) __hip_atomic_store(&slots[G + g], mineB, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    if (tid < (two ? 2 * G : G)) {
-        uint64_t v = __hip_atomic_load(&slots[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        for (int spin = 0; v == kEmpty && spin < spin_limit; ++spin) {
-            __builtin_amdgcn_s_sleep(2);
-            v = __hip_atomic_load(&slots[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // the payload of a record; false if it never came
+    __device__ __forceinline__ bool get(const uint64_t* p, uint32_t* bits) const {
+        for (int spin = 0; spin < spin_limit; ++spin) {
+            const uint64_t v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            *bits = (uint32_t)v;
+            if ((uint32_t)(v >> 32) == tag) return true;
+            __builtin_amdgcn_s_sleep(1);
         }
-        if (tid < G) gotA[tid] = v; else gotB[tid - G] = v;
-        if (v == kEmpty) *s_fail = 1;
+        return false;
+    }
+    // Everybody's a; with a maximum, everybody's b too (got[2]).
+    template <bool MAX>
+    __device__ __forceinline__ bool exchange(Shared& sh, double a, float b = 0.f) {
+        if (pass >= max_pass) return false;                // (more than a valid tree can need)
+        const bool first = pass == 0;                      // (an exchange with a maximum)
+        uint64_t* const w = slots + (size_t)pass * 4 * G;
+        const int tid = threadIdx.x;
+        const uint64_t bits = f64_to_bits(a);
+        if (tid == 0) {
+            put(w + g, tag, (uint32_t)(bits >> 32));
+            put(w + G + g, tag, (uint32_t)bits);
+            if (MAX) put(w + 2 * G + g, tag, __float_as_uint(b));
+            if (MAX && first) put(w + 3 * G + g, tag, (uint32_t)wall_clock64());
+        }
+        if (tid < (!MAX ? 2 : first ? 4 : 3) * G) {
+            uint32_t x = 0;
+            if (!get(w + tid, &x)) sh.fail = 1;
+            sh.got[tid / G][tid % G] = x;
+        }
+        __syncthreads();
+        if (sh.fail) return false;
+        if (first) tag = nonce ^ (sh.got[3][0] * 0x9E3779B1u);
+        else if (pass == 1) clear();
+        ++pass;
+        return true;
+    }
+    __device__ __forceinline__ double value(const Shared& sh, int i) const { return bits_to_f64(((uint64_t)sh.got[0][i] << 32) | sh.got[1][i]); }
+    // this workgroup's records of the first exchange
+    __device__ __forceinline__ void clear() const {
+        if (threadIdx.x < 4) put(slots + threadIdx.x * G + g, ~nonce, 0u);
+    }
+};
+
+// Decides node `cur`: its accepted child, or -1 and the correction token, or kLeave if the team could not complete an
+// exchange.  (All threads of all workgroups of the team return the same; with several workgroups the token is known to
+// workgroup 0 only.)
+constexpr int kLeave = -2;
+template <typename T, int NG, bool TEAM>
+__device__ __forceinline__ int decide(const ResampleArgs& a, Shared& sh, Team& team, int b, int cur, int blk0, int blk1, int32_t* token) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, N = a.N, V = a.V;
+    Row row;
+    row.V = V;
+    row.lg = (const T*)a.logits + ((size_t)b * N + cur) * V;
+    row.q = a.draft + ((size_t)b * N + cur) * V;
+    row.vec = (((uintptr_t)row.lg | (uintptr_t)row.q) & 15) == 0;
+    const double invT = 1.0 / a.temperature;
+
+    double w[NG][8];
+    float q[NG][8];
+    {
+        float x[NG][8];
+#pragma unroll
+        for (int it = 0; it < NG; ++it) {
+            if (blk0 + it < blk1) {
+                load_logits8<T>(row, (blk0 + it) * kBlock + lane * 8, x[it]);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) x[it][k] = -INFINITY;
+            }
+        }
+        // ---- children of cur, in increasing node index (a token that is no token id is rejected, and nothing carried)
+        const int tok = tid < N ? sh.tok[tid] : -1;
+        const bool mine = tid < N && tid > cur && sh.par[tid] == cur && tok >= 0 && tok < V;
+        float lx = 0.f, qx = 0.f, ux = 0.f;
+        if (mine) {
+            lx = to_f32<T>(((const T*)row.lg)[tok]);
+            qx = row.q[tok];
+            ux = a.uniforms[(size_t)b * N + tid];
+        }
+        const unsigned long long mask = __ballot(mine);
+        if (wave < 2 && lane == 0) sh.count[wave] = __popcll(mask);
+        __syncthreads();
+        if (mine) sh.child[__popcll(mask & ((1ull << lane) - 1ull)) + (wave == 1 ? sh.count[0] : 0)] = tid;
+        const int n_child = sh.count[0] + sh.count[1];
+#pragma unroll
+        for (int it = 0; it < NG; ++it) {
+            if (n_child > 0 && blk0 + it < blk1) {
+                load_draft8(row, (blk0 + it) * kBlock + lane * 8, q[it]);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) q[it][k] = 0.f;
+            }
+        }
+        // ---- row maximum (exact), the weights against the slice's, and their sum
+        float ms = x[0][0];
+#pragma unroll
+        for (int it = 0; it < NG; ++it)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) ms = fmaxf(ms, x[it][k]);
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) ms = fmaxf(ms, __shfl_xor(ms, off));
+        if (lane == 0) sh.redf[wave] = ms;
+        __syncthreads();
+        ms = sh.redf[0];
+#pragma unroll
+        for (int i = 1; i < kWaves; ++i) ms = fmaxf(ms, sh.redf[i]);
+        double s = 0.0;
+        if (ms > -INFINITY) {                                       // (a slice behind the vocabulary's end: no weights)
+#pragma unroll
+            for (int it = 0; it < NG; ++it) {
+                keep_order();
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    w[it][k] = exp(((double)x[it][k] - (double)ms) * invT);     // padding: exp(-inf) = 0
+                    s += w[it][k];
+                }
+            }
+        } else {
+#pragma unroll
+            for (int it = 0; it < NG; ++it)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) w[it][k] = 0.0;
+        }
+        s = wave_sum(s);
+        if (lane == 0) sh.red[0][wave] = s;
+        __syncthreads();
+        double sg = 0.0;
+#pragma unroll
+        for (int i = 0; i < kWaves; ++i) sg += sh.red[0][i];
+        float m = ms;
+        if (TEAM && team.G > 1) {
+            if (!team.template exchange<true>(sh, sg, ms)) return kLeave;
+            for (int i = 0; i < team.G; ++i) m = fmaxf(m, __uint_as_float(sh.got[2][i]));
+            // lane i brings workgroup i's sum to the row's maximum; added in order
+            double part = 0.0;
+            if (lane < team.G) {
+                const float mi = __uint_as_float(sh.got[2][lane]);
+                if (mi > -INFINITY) part = team.value(sh, lane) * exp(((double)mi - (double)m) * invT);
+            }
+            sg = 0.0;
+            for (int i = 0; i < team.G; ++i) sg += of_lane(part, i);
+            const double f = ms > -INFINITY ? exp(((double)ms - (double)m) * invT) : 0.0;
+#pragma unroll
+            for (int it = 0; it < NG; ++it)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) w[it][k] *= f;
+        }
+        if (mine) {
+            sh.ax[tid] = exp(((double)lx - (double)m) * invT);
+            sh.lhs[tid] = (double)ux * (double)qx;
+        }
+        __syncthreads();
+
+        // ---- the children, one after the other (every thread of every workgroup of the team takes the same branches).
+        // The weights in registers lag by the last rejection: w' = max(0, w - owed q).
+        double S = sg, owed = 0.0;
+        int buf = 1;
+        for (int i = 0; i < n_child; ++i) {
+            const int c = sh.child[i];
+            if (sh.lhs[c] < sh.ax[c] / S) return c;
+            double z = 0.0;                                          // rejected: mass of max(0, w' - S q)
+#pragma unroll
+            for (int it = 0; it < NG; ++it) {
+                keep_order();
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const double qd = (double)q[it][k];
+                    w[it][k] = fmax(0.0, w[it][k] - owed * qd);
+                    z += fmax(0.0, w[it][k] - S * qd);
+                }
+            }
+            owed = 0.0;
+            z = wave_sum(z);
+            if (lane == 0) sh.red[buf][wave] = z;
+            __syncthreads();
+            double t = 0.0;
+#pragma unroll
+            for (int j = 0; j < kWaves; ++j) t += sh.red[buf][j];
+            buf ^= 1;
+            if (TEAM && team.G > 1) {
+                if (!team.template exchange<false>(sh, t)) return kLeave;
+                t = 0.0;
+                for (int j = 0; j < team.G; ++j) t += team.value(sh, j);
+            }
+            if (t > 0.0) {                                           // same value in every thread; no mass left: nothing carried
+                if (mine) sh.ax[tid] = fmax(0.0, sh.ax[tid] - S * (double)qx);
+                owed = S;
+                S = t;
+            }
+            __syncthreads();
+        }
+        // (behind this point w are the weights that the correction token is drawn from)
+#pragma unroll
+        for (int it = 0; it < NG; ++it) {
+            keep_order();
+#pragma unroll
+            for (int k = 0; k < 8; ++k) w[it][k] = fmax(0.0, w[it][k] - owed * (double)q[it][k]);
+        }
+    }
+
+    // ---- correction / bonus token: inverse CDF at u_resample, token-id order: the first of the team's workgroups, of its
+    // waves, of the wave's blocks, of the block's lanes and of the lane's tokens whose inclusive sum exceeds the target; the
+    // last one with any mass if none does (the target reaches the total by rounding only)
+    double ls[NG], s = 0.0;
+#pragma unroll
+    for (int it = 0; it < NG; ++it) {
+        ls[it] = ((w[it][0] + w[it][1]) + (w[it][2] + w[it][3])) + ((w[it][4] + w[it][5]) + (w[it][6] + w[it][7]));
+        s += ls[it];
+    }
+    s = wave_sum(s);
+    __syncthreads();
+    if (lane == 0) sh.red[0][wave] = s;
+    if (tid == 0) sh.token = 0;
+    __syncthreads();
+    double slice = 0.0;
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i) slice += sh.red[0][i];
+    double excl = 0.0, total = slice;
+    int gsel = 0;
+    if (TEAM && team.G > 1) {
+        if (!team.template exchange<false>(sh, slice)) return kLeave;
+        total = 0.0;
+        for (int i = 0; i < team.G; ++i) total += team.value(sh, i);
+    }
+    const double tgt = (double)a.u_resample[b] * total;
+    if (TEAM && team.G > 1) {
+        int glast = 0;
+        double run = 0.0, glexcl = 0.0;
+        gsel = -1;
+        for (int i = 0; i < team.G; ++i) {
+            const double v = team.value(sh, i);
+            if (v > 0.0) { glast = i; glexcl = run; }
+            if (gsel < 0 && run + v > tgt) { gsel = i; excl = run; }
+            run += v;
+        }
+        if (gsel < 0) { gsel = glast; excl = glexcl; }
+    }
+    if (team.g == gsel) {
+        int wsel = -1, wlast = 0;
+        double wexcl = excl, run = excl, wlexcl = excl;
+        for (int i = 0; i < kWaves; ++i) {
+            const double v = sh.red[0][i];
+            if (v > 0.0) { wlast = i; wlexcl = run; }
+            if (wsel < 0 && run + v > tgt) { wsel = i; wexcl = run; }
+            run += v;
+        }
+        if (wsel < 0) { wsel = wlast; wexcl = wlexcl; }
+        if (wave == wsel) {
+            double incl[NG], e_sel = 0.0;
+            int isel = -1, ilast = 0;
+            double ilexcl = wexcl;
+            run = wexcl;
+#pragma unroll
+            for (int it = 0; it < NG; ++it) {
+                incl[it] = wave_incl_scan(ls[it], lane);
+                const double v = of_lane(incl[it], 63);
+                if (v > 0.0) { ilast = it; ilexcl = run; }
+                if (isel < 0 && run + v > tgt) { isel = it; e_sel = run; }
+                run += v;
+            }
+            if (isel < 0) { isel = ilast; e_sel = ilexcl; }
+#pragma unroll
+            for (int it = 0; it < NG; ++it)
+                if (it == isel) {
+                    const bool hit = (e_sel + incl[it] > tgt) && ls[it] > 0.0;
+                    const unsigned long long hits = __ballot(hit), pos = __ballot(ls[it] > 0.0);
+                    const int lsel = hits ? __ffsll((long long)hits) - 1 : 63 - __clzll((long long)(pos ? pos : 1ull));
+                    if (lane == lsel) {
+                        double r3 = e_sel + (incl[it] - ls[it]);
+                        int pick = -1, lastpos = -1;
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) {
+                            r3 += w[it][k];
+                            if (w[it][k] > 0.0) lastpos = k;
+                            if (pick < 0 && r3 > tgt && w[it][k] > 0.0) pick = k;
+                        }
+                        if (pick < 0) pick = max(lastpos, 0);
+                        sh.token = (blk0 + it) * kBlock + lane * 8 + pick;
+                    }
+                }
+        }
     }
     __syncthreads();
+    if (gsel != 0) {                                   // the token goes to workgroup 0, through one more slot
+        if (team.pass >= team.max_pass) return kLeave;
+        uint64_t* slot = team.slots + (size_t)team.pass++ * 4 * team.G;
+        if (team.g == gsel && tid == 0) Team::put(slot, team.tag, (uint32_t)sh.token);
+        if (team.g == 0 && tid == 0) {
+            uint32_t x = 0;
+            if (team.get(slot, &x)) sh.token = (int)x; else sh.fail = 1;
+        }
+        __syncthreads();
+        if (sh.fail) return kLeave;
+    }
+    *token = sh.token;
+    return -1;
 }
 
-__global__ void fill_slots_kernel(uint64_t* p, size_t n) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        p[i] = kEmpty;
-}
-
-template <typename T>
-__global__ __launch_bounds__(kThreads) void accept_resample_kernel(ResampleArgs a) {
-    const int G = a.team, b = blockIdx.x / G, g = blockIdx.x % G;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int N = a.N, V = a.V;
-    __shared__ int32_t spar[kMaxNodes], stok[kMaxNodes];
-    __shared__ double sS[kMaxNodes + 1];          // S_0 .. S_j of the current node
-    __shared__ double s_red[kWaves];
-    __shared__ float s_redf[kWaves];
-    __shared__ double s_blk[kMaxBlocks];          // per-block sums of the sampling pass (this slice)
-    __shared__ uint64_t s_gotA[kMaxTeam], s_gotB[kMaxTeam];
-    __shared__ int s_fail;
-
-    // ---- tree validation: node 0 is the only root, parents precede children, depth < max_path
+// The tree of sequence b into LDS; true if it is none: node 0 is the only root, parents precede children, depth < max_path.
+__device__ __forceinline__ bool load_tree(const ResampleArgs& a, Shared& sh, int b, bool check) {
+    const int tid = threadIdx.x, N = a.N;
     int bad = 0;
-    if (tid == 0) s_fail = 0;
+    if (tid == 0) sh.fail = 0;
     if (tid < N) {
         const int p = a.parent[(size_t)b * N + tid];
-        spar[tid] = p;
-        stok[tid] = a.tokens[(size_t)b * N + tid];
+        sh.par[tid] = p;
+        sh.tok[tid] = a.tokens[(size_t)b * N + tid];
         bad = (tid == 0) ? (p != -1) : (p < 0 || p >= tid);
     }
     bad = __syncthreads_or(bad);
+    if (!check) return bad;
     if (!bad && tid < N) {
         int depth = 0;
-        for (int i = tid; i > 0; i = spar[i]) ++depth;
+        for (int i = tid; i > 0; i = sh.par[i]) ++depth;
         bad = depth >= a.max_path;
     }
-    bad = __syncthreads_or(bad);
+    return __syncthreads_or(bad);
+}
 
+// nothing accepted, no token
+__device__ __forceinline__ void write_empty(const ResampleArgs& a, int b, int status) {
+    for (int k = threadIdx.x; k < a.max_path; k += kThreads) {
+        a.path[(size_t)b * a.max_path + k] = (k == 0) ? 0 : -1;
+        a.accepted_tokens[(size_t)b * a.max_path + k] = -1;
+    }
+    if (threadIdx.x == 0) {
+        a.accept_len[b] = 0;
+        a.bonus_token[b] = -1;
+        if (a.status) a.status[b] = status;
+    }
+}
+
+// ---- teams: workgroup g of sequence b's team walks from the root
+template <typename T, int NG>
+__global__ __launch_bounds__(kThreads) void accept_resample_kernel(ResampleArgs a) {
+    __shared__ Shared sh;
+    const int G = a.team, b = a.first + blockIdx.x / G, g = blockIdx.x % G, tid = threadIdx.x;
+    if (load_tree(a, sh, b, true)) {                       // every workgroup of the team sees the same tree
+        if (g == 0) write_empty(a, b, S4C_SEQ_BAD_TREE);
+        return;
+    }
+    const int nblocks = (a.V + kBlock - 1) / kBlock;
+    const int bpg = (nblocks + G - 1) / G, ipw = (bpg + kWaves - 1) / kWaves;              // blocks per workgroup and wave
+    const int gblk1 = min(nblocks, (g + 1) * bpg), blk0 = min(gblk1, g * bpg + (tid >> 6) * ipw), blk1 = min(gblk1, blk0 + ipw);
+    Team team = {a.slots + (size_t)b * a.max_pass * 4 * G, g, G, a.max_pass, a.spin_limit, 0, a.nonce, a.nonce};
+    int cur = 0, L = 0;
+    int32_t token = -1;
     int32_t* pth = a.path + (size_t)b * a.max_path;
     int32_t* atk = a.accepted_tokens + (size_t)b * a.max_path;
     if (g == 0)
         for (int k = tid; k < a.max_path; k += kThreads) { pth[k] = (k == 0) ? 0 : -1; atk[k] = -1; }
-    if (bad) {                                     // every workgroup of the team sees the same tree
-        if (g == 0 && tid == 0) {
-            a.accept_len[b] = 0;
-            a.bonus_token[b] = -1;
-            if (a.status) a.status[b] = S4C_SEQ_BAD_TREE;
-        }
-        return;
-    }
-
-    const int nblocks = (V + kBlock - 1) / kBlock;
-    const int bpg = (nblocks + G - 1) / G;                 // blocks per workgroup
-    const int gblk0 = min(nblocks, g * bpg), gblk1 = min(nblocks, gblk0 + bpg);
-    const int ipw = (bpg + kWaves - 1) / kWaves;           // blocks per wave
-    const int blk0 = min(gblk1, gblk0 + wave * ipw), blk1 = min(gblk1, blk0 + ipw);
-    const double invT = 1.0 / a.temperature;
-    if (g == 0 && tid == 0 && a.status) a.status[b] = 0;   // a failed exchange overwrites this later
-    uint64_t* slots = a.slots + (size_t)b * a.max_pass * 2 * G;   // [max_pass][2][G]
-    int pass = 0;
-
-    // An exchange that cannot complete (or more exchanges than the slot array holds, which a valid
-    // tree cannot need): the workgroup leaves; workgroup 0 flags the sequence and empties its outputs
-    // on the way out.  The condition is uniform across the workgroup.
-#define S4C_TEAM_CHECK()                                                                                   \
-    if (s_fail || pass > a.max_pass) {                                                                     \
-        if (g == 0) {                                                                                      \
-            __syncthreads();   /* thread 0's earlier path entries are ordered before the reset */          \
-            for (int k = tid; k < a.max_path; k += kThreads) { pth[k] = (k == 0) ? 0 : -1; atk[k] = -1; }  \
-            if (tid == 0) {                                                                                \
-                if (a.status) a.status[b] = S4C_SEQ_TIMEOUT;                                               \
-                a.accept_len[b] = 0;                                                                       \
-                a.bonus_token[b] = -1;                                                                     \
-            }                                                                                              \
-        }                                                                                                  \
-        return;                                                                                            \
-    }
-
-    Row row;
-    row.V = V;
-    int cur = 0, L = 0, j = 0;
-    float m = 0.f;
     for (;;) {
-        row.lg = (const T*)a.logits + ((size_t)b * N + cur) * V;
-        row.q = a.draft + ((size_t)b * N + cur) * V;
-        row.vec = (((uintptr_t)row.lg | (uintptr_t)row.q) & 15) == 0;
-
-        // ---- row maximum (exact) and S_0 in ONE pass over the row: every lane keeps a running
-        // maximum and a sum relative to it, rescaled when the maximum grows (rare after the
-        // first blocks); lanes, waves and workgroups are combined the same way.
-        float m_run = -INFINITY;
-        double s = 0.0;
-        for (int blk = blk0; blk < blk1; ++blk) {
-            const int base = blk * kBlock + lane * 8;
-            if (base >= V) continue;
-            float x[8];
-            load_logits8<T>(row, base, x);
-            float bm = x[0];
-#pragma unroll
-            for (int k = 1; k < 8; ++k) bm = fmaxf(bm, x[k]);
-            if (bm > m_run) {
-                s *= exp(((double)m_run - (double)bm) * invT);     // first block: 0 * exp(-inf) = 0
-                m_run = bm;
-            }
-            double e8[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) e8[k] = exp(((double)x[k] - (double)m_run) * invT);
-            s += ((e8[0] + e8[1]) + (e8[2] + e8[3])) + ((e8[4] + e8[5]) + (e8[6] + e8[7]));
-        }
-        float mw = m_run;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) mw = fmaxf(mw, __shfl_xor(mw, off));
-        s = (m_run == -INFINITY) ? 0.0 : s * exp(((double)m_run - (double)mw) * invT);
-        s = wave_sum(s);
-        if (lane == 0) { s_redf[wave] = mw; s_red[wave] = s; }
-        __syncthreads();
-        float mg = s_redf[0];
-#pragma unroll
-        for (int w = 1; w < kWaves; ++w) mg = fmaxf(mg, s_redf[w]);
-        double sg = 0.0;
-        if (tid == 0)
-            for (int w = 0; w < kWaves; ++w)
-                if (s_redf[w] != -INFINITY) sg += s_red[w] * exp(((double)s_redf[w] - (double)mg) * invT);
-        // exchange (slice maximum, slice sum relative to it)
-        ++pass;
-        S4C_TEAM_CHECK();
-        team_exchange(slots + (size_t)(pass - 1) * 2 * G, g, G, true, (uint64_t)__float_as_uint(mg), f64_to_bits(sg),
-                      s_gotA, s_gotB, &s_fail, tid, a.spin_limit);
-        S4C_TEAM_CHECK();
-        m = bits_to_f32(s_gotA[0]);
-        for (int i = 1; i < G; ++i) m = fmaxf(m, bits_to_f32(s_gotA[i]));
-        if (tid == 0) {
-            double t = 0.0;
-            for (int i = 0; i < G; ++i) {
-                const float mi = bits_to_f32(s_gotA[i]);
-                if (mi != -INFINITY) t += bits_to_f64(s_gotB[i]) * exp(((double)mi - (double)m) * invT);
-            }
-            sS[0] = t;
-        }
-        __syncthreads();
-        j = 0;
-
-        // ---- children of cur in increasing node index (every thread of every workgroup of the
-        // team takes the same branches)
-        int next = -1;
-        for (int c = cur + 1; c < N; ++c) {
-            if (spar[c] != cur) continue;
-            const int x = stok[c];
-            if (x < 0 || x >= V) continue;                          // not a token id: rejected, nothing carried
-            const float qx = row.q[x];
-            const double ax = corrected(to_f32<T>(((const T*)row.lg)[x]), qx, m, invT, sS, j);
-            const double lhs = (double)a.uniforms[(size_t)b * N + c] * (double)qx;
-            if (lhs < ax / sS[j]) { next = c; break; }
-            // rejected: mass of max(0, a_j - S_j q)
-            double z = 0.0;
-            const double Sj = sS[j];
-            for (int blk = blk0; blk < blk1; ++blk) {
-                const int base = blk * kBlock + lane * 8;
-                float lx[8], qv[8];
-                load_logits8<T>(row, base, lx);
-                load_draft8(row, base, qv);
-#pragma unroll
-                for (int k = 0; k < 8; ++k)
-                    z += fmax(0.0, corrected(lx[k], qv[k], m, invT, sS, j) - Sj * (double)qv[k]);
-            }
-            z = wave_sum(z);
-            __syncthreads();                                         // s_red free again
-            if (lane == 0) s_red[wave] = z;
-            __syncthreads();
-            double zg = 0.0;
-            for (int w = 0; w < kWaves; ++w) zg += s_red[w];
-            ++pass;
-            S4C_TEAM_CHECK();
-            team_exchange(slots + (size_t)(pass - 1) * 2 * G, g, G, false, f64_to_bits(zg), 0, s_gotA, s_gotB, &s_fail, tid, a.spin_limit);
-            S4C_TEAM_CHECK();
-            double t = 0.0;
-            for (int i = 0; i < G; ++i) t += bits_to_f64(s_gotA[i]);
-            if (t > 0.0) {                                           // same value in every thread
-                __syncthreads();
-                if (tid == 0) sS[j + 1] = t;
-                ++j;
-                __syncthreads();
-            }
+        const int next = decide<T, NG, true>(a, sh, team, b, cur, blk0, blk1, &token);
+        if (next == kLeave) {                              // workgroup 0 flags the sequence and empties its outputs
+            __syncthreads();                               // (thread 0's earlier path entries come before)
+            if (G > 1) team.clear();
+            if (g == 0) write_empty(a, b, S4C_SEQ_TIMEOUT);
+            return;
         }
         if (next < 0) break;
         ++L;
-        if (g == 0 && tid == 0) { pth[L] = next; atk[L - 1] = stok[next]; }
+        if (g == 0 && tid == 0) { pth[L] = next; atk[L - 1] = sh.tok[next]; }
         cur = next;
-        __syncthreads();                                             // sS, s_red are rewritten for the next node
+        __syncthreads();                                   // the node's shared words are written again
     }
+    if (g == 0 && tid == 0) {
+        a.accept_len[b] = L;
+        a.bonus_token[b] = token;
+        if (a.status) a.status[b] = 0;
+    }
+}
 
-    // ---- correction / bonus token: inverse CDF of a_j at u_resample, token-id order
-    for (int blk = blk0; blk < blk1; ++blk) {
-        double w8[8];
-        weights8<T>(row, blk * kBlock + lane * 8, m, invT, sS, j, w8);
-        double s = 0.0;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) s += w8[k];
-        s = wave_sum(s);
-        if (lane == 0) s_blk[blk - gblk0] = s;
+// ---- rows: workgroup b N + i decides node i of sequence b and publishes (call nonce, decision); workgroup B N + b waits
+// for its sequence's decisions, overwrites them (so that a captured graph can replay the call) and follows them.  Workgroups
+// start in grid order, so when it starts every other one of its sequence has a compute unit or is done.
+constexpr uint32_t kAccepted = 0x80000000u;                // decision: kAccepted | child, or the correction token
+template <typename T, int NG>
+__global__ __launch_bounds__(kThreads) void resample_rows_kernel(ResampleArgs a) {
+    __shared__ Shared sh;
+    const int tid = threadIdx.x, N = a.N;
+    if ((int)blockIdx.x < a.B * N) {
+        const int b = blockIdx.x / N, node = blockIdx.x - b * N;
+        load_tree(a, sh, b, false);                        // (whatever it holds: rows and tokens are checked where they are used)
+        const int nblocks = (a.V + kBlock - 1) / kBlock, ipw = (nblocks + kWaves - 1) / kWaves;
+        const int blk0 = min(nblocks, (tid >> 6) * ipw), blk1 = min(nblocks, blk0 + ipw);
+        Team team = {nullptr, 0, 1, 0, 0, 0, 0, 0};
+        int32_t token = 0;
+        const int next = decide<T, NG, false>(a, sh, team, b, node, blk0, blk1, &token);
+        if (tid == 0)
+            __hip_atomic_store(a.slots + blockIdx.x, ((uint64_t)a.nonce << 32) | (next >= 0 ? kAccepted | (uint32_t)next : (uint32_t)token),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
     }
-    __syncthreads();
-    // slice total: this workgroup's blocks added in order
-    double slice = 0.0;
-    for (int blk = gblk0; blk < gblk1; ++blk) slice += s_blk[blk - gblk0];
-    ++pass;
-    S4C_TEAM_CHECK();
-    team_exchange(slots + (size_t)(pass - 1) * 2 * G, g, G, false, f64_to_bits(slice), 0, s_gotA, s_gotB, &s_fail, tid, a.spin_limit);
-    S4C_TEAM_CHECK();
-    // owning workgroup: the first whose inclusive prefix (slices added in order) exceeds tgt
-    double total = 0.0;
-    for (int i = 0; i < G; ++i) total += bits_to_f64(s_gotA[i]);
-    const double tgt = (double)a.u_resample[b] * total;
-    int gsel = -1, glast = 0;
-    double gexcl = 0.0, run = 0.0, glexcl = 0.0;
-    for (int i = 0; i < G; ++i) {
-        const double v = bits_to_f64(s_gotA[i]);
-        if (v > 0.0) { glast = i; glexcl = run; }
-        if (gsel < 0 && run + v > tgt) { gsel = i; gexcl = run; }
-        run += v;
+    const int b = blockIdx.x - a.B * N;
+    const bool bad = load_tree(a, sh, b, true);
+    __shared__ uint32_t s_said[kMaxNodes];
+    int late = 0;
+    if (tid < N) {
+        uint64_t* const rec = a.slots + (size_t)b * N + tid;
+        uint64_t v = 0;
+        late = 1;
+        for (int spin = 0; late && spin < a.spin_limit; ++spin) {
+            v = __hip_atomic_load(rec, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            late = (uint32_t)(v >> 32) != a.nonce;
+            if (late) __builtin_amdgcn_s_sleep(8);
+        }
+        s_said[tid] = (uint32_t)v;
+        if (!late) __hip_atomic_store(rec, (uint64_t)(~a.nonce) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (gsel < 0) { gsel = glast; gexcl = glexcl; }     // tgt >= total can only come from rounding
-    if (g != gsel && g != 0) return;
-    __shared__ int s_token;
-    if (tid == 0) s_token = -1;
-    __syncthreads();
-    if (g == gsel) {
-        // owning block inside the slice, same rule; every thread runs the same loop
-        int bsel = -1, blast = gblk0;
-        double bexcl = gexcl, r2 = gexcl, blexcl = gexcl;
-        for (int blk = gblk0; blk < gblk1; ++blk) {
-            const double v = s_blk[blk - gblk0];
-            if (v > 0.0) { blast = blk; blexcl = r2; }
-            if (bsel < 0 && r2 + v > tgt) { bsel = blk; bexcl = r2; }
-            r2 += v;
-        }
-        if (bsel < 0) { bsel = blast; bexcl = blexcl; }
-        if (wave == 0) {
-            // owning lane, then owning token
-            double w8[8];
-            weights8<T>(row, bsel * kBlock + lane * 8, m, invT, sS, j, w8);
-            double ls = 0.0;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) ls += w8[k];
-            const double incl = wave_incl_scan(ls, lane);
-            const bool hit = (bexcl + incl > tgt) && ls > 0.0;
-            const unsigned long long hits = __ballot(hit);
-            const unsigned long long pos = __ballot(ls > 0.0);
-            int lsel;
-            if (hits) lsel = __ffsll((long long)hits) - 1;
-            else lsel = 63 - __clzll((long long)(pos ? pos : 1ull));      // rounding: last lane with mass
-            if (lane == lsel) {
-                double r3 = bexcl + (incl - ls);
-                int pick = -1, lastpos = -1;
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    r3 += w8[k];
-                    if (w8[k] > 0.0) lastpos = k;
-                    if (pick < 0 && r3 > tgt && w8[k] > 0.0) pick = k;
-                }
-                if (pick < 0) pick = max(lastpos, 0);
-                s_token = bsel * kBlock + lane * 8 + pick;
-            }
-        }
+    late = __syncthreads_or(late);
+    if (late || bad) {
+        write_empty(a, b, late ? S4C_SEQ_TIMEOUT : S4C_SEQ_BAD_TREE);
+        return;
     }
-    __syncthreads();
-    // ---- the token goes to workgroup 0, which alone writes the outputs of the sequence
-    if (gsel != 0) {
-        ++pass;
-        S4C_TEAM_CHECK();
-        uint64_t* slot = slots + (size_t)(pass - 1) * 2 * G;
-        if (g == gsel) {
-            if (tid == 0) __hip_atomic_store(slot, (uint64_t)(uint32_t)s_token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            return;
-        }
-        if (tid == 0) {
-            uint64_t v = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            for (int spin = 0; v == kEmpty && spin < a.spin_limit; ++spin) {
-                __builtin_amdgcn_s_sleep(2);
-                v = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            if (v == kEmpty) s_fail = 1; else s_token = (int)(uint32_t)v;
-        }
-        __syncthreads();
-        S4C_TEAM_CHECK();
+    // every thread follows the path, thread k writes entry k
+    int cur = 0, L = 0, my_node = tid == 0 ? 0 : -1, my_tok = -1;
+    while (s_said[cur] & kAccepted) {
+        cur = (int)(s_said[cur] & ~kAccepted);
+        ++L;
+        if (L == tid) my_node = cur;
+        if (L == tid + 1) my_tok = sh.tok[cur];
+    }
+    for (int k = tid; k < a.max_path; k += kThreads) {
+        a.path[(size_t)b * a.max_path + k] = k == tid ? my_node : -1;         // (a path has at most kMaxNodes < kThreads nodes)
+        a.accepted_tokens[(size_t)b * a.max_path + k] = k == tid ? my_tok : -1;
     }
     if (tid == 0) {
         a.accept_len[b] = L;
-        a.bonus_token[b] = s_token;
+        a.bonus_token[b] = (int32_t)s_said[cur];
+        if (a.status) a.status[b] = 0;
     }
-#undef S4C_TEAM_CHECK
+}
+
+int iters_of(int blocks) { return (blocks + kWaves - 1) / kWaves; }          // blocks per wave of a workgroup that has this many
+
+template <typename T, int NG>
+hipError_t launch(const ResampleArgs& a, hipStream_t st) {
+    if constexpr (NG * kWaves * kBlock <= kMaxRow) if (a.team == 0) {
+        hipLaunchKernelGGL((resample_rows_kernel<T, NG>), dim3((unsigned)(a.B * (a.N + 1))), dim3(kThreads), 0, st, a);
+        return hipGetLastError();
+    }
+    // as many sequences in a launch as have all their workgroups on the chip together (which wait for each other)
+    const int per = a.team == 1 ? a.B : a.resident / a.team < 1 ? 1 : a.resident / a.team;
+    for (int b = 0; b < a.B; b += per) {
+        ResampleArgs k = a;
+        k.first = b;
+        hipLaunchKernelGGL((accept_resample_kernel<T, NG>), dim3((unsigned)((a.B - b < per ? a.B - b : per) * a.team)), dim3(kThreads), 0, st, k);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+template <typename T>
+hipError_t launch_sized(const ResampleArgs& a, hipStream_t st) {
+    const int nblocks = (a.V + kBlock - 1) / kBlock, n = iters_of(a.team ? (nblocks + a.team - 1) / a.team : nblocks);
+    return n <= 1 ? launch<T, 1>(a, st) : n <= 2 ? launch<T, 2>(a, st) : n <= 4 ? launch<T, 4>(a, st) : launch<T, 8>(a, st);
 }
 
 }  // namespace
 
-int resample_max_vocab() { return kMaxBlocks * kBlock; }
+int resample_max_vocab() { return kMaxVocab; }
 
-// Workgroups per sequence: enough blocks per workgroup to keep its waves busy, at most 16, and
-// few enough that all teams are resident together (two 8-wave workgroups fit on each of the
-// 256 CUs, so 256 workgroups leave a factor two of slack).
-int resample_team(int B, int V) {
+// Workgroups per sequence: enough blocks per workgroup to keep its waves busy, at most 16, and few enough that all
+// teams are resident together (one workgroup per CU is certain), but no slice larger than a workgroup's registers hold.
+int resample_team(int B, int V, int cus) {
     const int nblocks = (V + kBlock - 1) / kBlock;
     int G = (nblocks + kWaves - 1) / kWaves;
-    if (G > kMaxTeam) G = kMaxTeam;
-    while (G > 1 && (long long)B * G > kTeamBudget) G >>= 1;
-    return G < 1 ? 1 : G;
+    if (G > kTeam) G = kTeam;
+    while (G > 1 && (long long)B * G > cus) G >>= 1;
+    const int least = (V + kMaxSlice - 1) / kMaxSlice;
+    return G < least ? least : G;
+}
+
+// Whether every node is decided at once, a workgroup each: up to two turns of the chip of rows of 16384 tokens, or as many
+// tokens in shorter rows; half of that where rows lie on odd addresses and are read by the element.  Teams and rows, us a call
+// (B x N, V): 1 x 20, 1000: 17.5 and 8.4; 3 x 64, 16000 fp32: 36.1 and 18.5; 4 x 128, 16384: 34.6 and 29.9; 8 x 128, 16384: 36.9
+// and 50.0; 16 x 40, 8000: 38.2 and 19.9; 16 x 128, 8000: 47.5 and 41.9; 16 x 128, 4000: 35.8 and 24.7; 8 x 64, 16001: 41.6 and
+// 45.2.  Rows of 32000 would fit the registers too, but the slowest node (many children, all rejected) is alone on its CU
+// then: 4 x 64: 37.6 and 42.3.  (Rows were reloaded and their weights recomputed for every rejected child before, by
+// teams: 4 x 64, 32000 58.1, 16 x 128, 128256 106.6, 3 x 64, 16000 fp32 52.9.)
+bool resample_by_rows(int B, int N, int V, int cus) {
+    const long long tokens = (long long)B * N * (V < 4096 ? 4096 : V);
+    return V <= kMaxRow && tokens <= (V % 8 == 0 ? 2ll : 1ll) * cus * kMaxRow;
 }
 
 // exchanges per sequence: one per visited node, one per rejected child, one for the sampling, one
@@ -452,24 +637,13 @@ int resample_team(int B, int V) {
 int resample_max_pass(int N, int max_path) { return max_path + N + 2; }
 int resample_default_spin_limit() { return kSpinLimit; }
 
-size_t resample_slot_words(int B, int N, int V, int max_path) {
-    const int G = resample_team(B, V);
-    return G == 1 ? 0 : (size_t)B * resample_max_pass(N, max_path) * 2 * G;
+size_t resample_slot_words(int B, int N, int V, int max_path, int cus) {
+    const int G = resample_team(B, V, cus);
+    return G == 1 ? 0 : (size_t)B * resample_max_pass(N, max_path) * 4 * G;
 }
 
 hipError_t launch_accept_resample(const ResampleArgs& a, hipStream_t st) {
-    if (a.team > 1) {
-        const size_t n = (size_t)a.B * a.max_pass * 2 * a.team;
-        const size_t want = (n + 255) / 256;
-        hipLaunchKernelGGL(fill_slots_kernel, dim3((unsigned)(want < 1024 ? want : 1024)), dim3(256), 0, st, a.slots, n);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    const dim3 grid((unsigned)(a.B * a.team));
-    if (a.dtype == S4C_F32) hipLaunchKernelGGL(accept_resample_kernel<float>, grid, dim3(kThreads), 0, st, a);
-    else if (a.dtype == S4C_F16) hipLaunchKernelGGL(accept_resample_kernel<f16_t>, grid, dim3(kThreads), 0, st, a);
-    else hipLaunchKernelGGL(accept_resample_kernel<bf16_t>, grid, dim3(kThreads), 0, st, a);
-    return hipGetLastError();
+    return a.dtype == S4C_F32 ? launch_sized<float>(a, st) : a.dtype == S4C_F16 ? launch_sized<f16_t>(a, st) : launch_sized<bf16_t>(a, st);
 }
 
 }  // namespace s4c

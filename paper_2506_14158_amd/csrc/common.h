@@ -135,19 +135,22 @@ struct ResampleArgs {
     int32_t* accepted_tokens;
     int32_t* bonus_token;
     int32_t* status;
-    uint64_t* slots;           // [B][max_pass][2][team] exchange words (team > 1)
+    uint64_t* slots;           // team > 1: [B][max_pass][4][team] exchange words; team == 0: [B][N] (nonce << 32) | decision
     int32_t B, N, V, max_path, dtype;
-    int32_t team;              // workgroups per sequence
+    int32_t team;              // workgroups per sequence; 0: one per node
+    int32_t first, resident;   // first sequence of a launch of teams (set by the launcher); workgroups that are resident together
+    uint32_t nonce;            // tells this call's words from whatever they held before
     int32_t max_pass;          // exchanges a sequence may need
     int32_t spin_limit;        // polls before a workgroup gives up on an exchange
     double temperature;
 };
 hipError_t launch_accept_resample(const ResampleArgs& a, hipStream_t st);
 int resample_max_vocab();
-int resample_team(int B, int V);
+int resample_team(int B, int V, int cus);
+bool resample_by_rows(int B, int N, int V, int cus);
 int resample_max_pass(int N, int max_path);
 int resample_default_spin_limit();
-size_t resample_slot_words(int B, int N, int V, int max_path);
+size_t resample_slot_words(int B, int N, int V, int max_path, int cus);      // of the teams
 
 struct CompactArgs {
     const void* k_tree;

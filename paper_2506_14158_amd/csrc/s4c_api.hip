@@ -363,7 +363,9 @@ s4c_status s4c_accept_path_static(int32_t B, int32_t N, int32_t V, int32_t logit
 
 size_t s4c_accept_resample_workspace_size(int32_t B, int32_t N, int32_t V, int32_t max_path) {
     if (B <= 0 || N <= 0 || V <= 0 || max_path <= 0 || N > kMaxNodes || V > resample_max_vocab()) return 0;
-    return resample_slot_words(B, N, V, max_path) * sizeof(uint64_t);
+    const size_t words = resample_slot_words(B, N, V, max_path, device_cus());
+    const size_t rows = resample_by_rows(B, N, V, device_cus()) ? (size_t)B * N : 0;
+    return (words > rows ? words : rows) * sizeof(uint64_t);
 }
 
 s4c_status s4c_accept_resample(int32_t B, int32_t N, int32_t V, int32_t logits_dtype, float temperature,
@@ -378,14 +380,20 @@ s4c_status s4c_accept_resample(int32_t B, int32_t N, int32_t V, int32_t logits_d
     if (B <= 0 || N <= 0 || V <= 0 || max_path <= 0 || !(temperature > 0.f)) return S4C_ERR_SHAPE;
     if (N > kMaxNodes || V > resample_max_vocab() || !dtype_ok(logits_dtype))
         return S4C_ERR_UNSUPPORTED;
-    const size_t need = s4c_accept_resample_workspace_size(B, N, V, max_path);
-    if (need > 0 && (!workspace || workspace_bytes < need || (((uintptr_t)workspace) & 255))) return S4C_ERR_WORKSPACE;
+    // (teams of one workgroup need no workspace; without one they do what the workgroups per node would)
+    const size_t need = resample_slot_words(B, N, V, max_path, device_cus()) * sizeof(uint64_t);
+    const bool usable = workspace && !(((uintptr_t)workspace) & 255);
+    if (need > 0 && (!usable || workspace_bytes < need)) return S4C_ERR_WORKSPACE;
+    const bool by_rows = resample_by_rows(B, N, V, device_cus()) && usable && workspace_bytes >= (size_t)B * N * sizeof(uint64_t);
     ResampleArgs a;
     a.logits = logits; a.draft = draft_probs; a.parent = parent; a.tokens = tokens; a.uniforms = uniforms;
     a.u_resample = u_resample; a.path = path; a.accept_len = accept_len; a.accepted_tokens = accepted_tokens;
     a.bonus_token = bonus_token; a.status = status; a.slots = (uint64_t*)workspace;
     a.B = B; a.N = N; a.V = V; a.max_path = max_path; a.dtype = logits_dtype; a.temperature = (double)temperature;
-    a.team = resample_team(B, V);
+    a.team = by_rows ? 0 : resample_team(B, V, device_cus());
+    a.first = 0;
+    a.resident = device_cus();
+    a.nonce = next_nonce();
     a.max_pass = resample_max_pass(N, max_path);
     // S4C_RESAMPLE_SPIN_LIMIT (environment, >= 0): polls before a workgroup gives up on an exchange.  A
     // diagnostic knob: 0 makes every exchange between several workgroups fail, which is how the give-up

@@ -178,3 +178,53 @@ def test_rejects_bad_arguments():
     with pytest.raises(B.S4CError):      # more nodes than a tree may hold
         B.s4c_accept_resample(t(1, 129, 8), t(1, 129, 8), i(1, 129), i(1, 129), t(1, 129), t(1), 2, i(1, 2), i(1),
                               i(1, 2), i(1))
+
+
+@pytest.mark.parametrize("Bn,N,V,dtype", [(2, 20, 1, "bf16"), (1, 2, 4095, "f32"), (3, 33, 4097, "bf16"), (5, 64, 8193, "f16"),
+                                          (2, 40, 16384, "f32"), (2, 40, 16385, "bf16"), (2, 12, 32768, "f16"), (2, 12, 32769, "bf16"),
+                                          (1, 9, 65544, "f32"), (2, 5, 524289, "bf16")])
+def test_one_workgroup_per_node_teams_and_replays(Bn, N, V, dtype):
+    """Block, register and route edges.  The same call decides every node at once where rows are few and short, walks with
+    teams where its workspace is too small for that, and replays from a captured graph; all of them as the oracle."""
+    levels = min(N, 5)
+    par = np.stack([synth.random_tree_parent(N, levels, (8, 4, 3, 2, 2), np.random.default_rng([7, b])) for b in range(Bn)]).astype(np.int32)
+    g = torch.Generator().manual_seed(V + N)
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    logits = (2 * torch.randn(Bn, N, V, generator=g)).to(dt)
+    pd = torch.softmax(logits.float() + 0.5 * torch.randn(Bn, N, V, generator=g), 2)
+    top = pd.topk(min(8, V), 2).indices
+    tokens = torch.zeros(Bn, N, dtype=torch.int32)
+    for b in range(Bn):
+        for i in range(1, N):
+            rank = sum(1 for j in range(1, i) if par[b, j] == par[b, i])
+            tokens[b, i] = top[b, par[b, i], min(rank, top.shape[2] - 1)]
+    u, ur = torch.rand(Bn, N, generator=g), torch.rand(Bn, generator=g)
+    u[0] = 0.9999                                        # (sequence 0 rejects nearly everything)
+    bits = lambda t: t.numpy() if dtype == "f32" else t.view(torch.int16).numpy().view(np.uint16) if dtype == "bf16" else t.numpy()
+    r = O.accept_resample(bits(logits), pd.numpy(), par, tokens.numpy(), u.numpy(), ur.numpy(), levels)
+    assert min(float(r["margin_accept"].min()), float(r["margin_sample"].min())) > RESAMPLE_MARGIN_MIN
+    d = [t.cuda() for t in (logits, pd, torch.from_numpy(par), tokens, u, ur)]
+    tv = TreeVerifier(Bn, N, 1, 1, 64, 1, V, dt, levels, 0)
+    outs = (tv.path, tv.accept_len, tv.accepted_tokens, tv.bonus_token, tv.accept_status)
+
+    def call(ws):
+        for t in outs:
+            t.fill_(-7)
+        B.s4c_accept_resample(*d, levels, tv.path, tv.accept_len, tv.accepted_tokens, tv.bonus_token, ws, 1.0, tv.accept_status)
+        torch.cuda.synchronize()
+        same(tv, r)
+
+    for t in (0xFF, 0x00):                               # whatever the workspace holds
+        tv.resample_ws.fill_(t)
+        call(tv.resample_ws)
+    if V <= 4096:
+        call(None)                                       # one workgroup per sequence needs no workspace
+    gr = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(gr):
+        tv.accept_resample(*d, 1.0)
+    for _ in range(4):
+        for t in outs:
+            t.fill_(-7)
+        gr.replay()
+        torch.cuda.synchronize()
+        same(tv, r)
