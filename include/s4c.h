@@ -284,13 +284,12 @@ s4c_status s4c_commit_path_paged(const s4c_attn_shape* shape, int32_t layers, co
  *   dtype S4C_BF16 or S4C_F16 (products and sums in fp32, output rounded to nearest even);
  *   H a multiple of 32 (<= 16384), Hout a multiple of 256, T*H < 2^30; all pointers 16-byte
  *   aligned device pointers.
- *   workspace  >= s4c_draft_linear_workspace_size(T, H, Hout) bytes, 256-byte aligned, contents need
- *              not be initialised; that size is 0 (and the pointer may be NULL) for T > 512.  Up to
- *              512 tokens the op is a stream over W: it runs in passes of at most 128 tokens -- one
- *              pass for a draft tree at batch 1, the operating point of Sec. 4.1.2 -- each split
- *              over the reduction dimension to fill the chip, and the workspace holds the slices'
- *              fp32 partial sums (added in a fixed order: results are deterministic).  S4C_ERR_WORKSPACE
- *              if it is missing, too small or misaligned. */
+ *   workspace  s4c_draft_linear_workspace_size(T, H, Hout) bytes, 256-byte aligned, contents need
+ *              not be initialised.  The reduction dimension is split to fill the chip, and the workspace holds
+ *              the slices' fp32 partial sums (added in a fixed order: results are deterministic for a
+ *              given workspace size).  S4C_ERR_WORKSPACE if it is missing, too small or misaligned with T <= 512; for T > 512
+ *              it may be smaller or NULL, and fewer slices are used (it may be for T > 128 as well, down to the partial
+ *              sums of ceil(T / 128) equal passes over the tokens). */
 size_t s4c_draft_linear_workspace_size(int32_t T, int32_t H, int32_t Hout);
 s4c_status s4c_draft_linear(int32_t T, int32_t H, int32_t Hout, int32_t dtype, const void* e, const void* f,
                             const void* W, const void* bias, void* out, void* workspace, size_t workspace_bytes,

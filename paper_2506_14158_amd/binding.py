@@ -444,7 +444,7 @@ def s4c_draft_linear_workspace_size(T: int, H: int, Hout: int) -> int:
 
 def s4c_draft_linear(e, f, W, out, bias=None, workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """out[t] = W @ concat(e[t], f[t]) + bias (bf16 or fp16, fp32 accumulate); returns ``out``.  Up to 512 tokens
-    the call needs ``workspace`` (s4c_draft_linear_workspace_size bytes)."""
+    the call needs ``workspace`` (s4c_draft_linear_workspace_size bytes); beyond, it is slower without one."""
     if _taken((_nat or _native()).draft_linear(e, f, W, out, bias, workspace)):
         return out
     T, H = e.shape

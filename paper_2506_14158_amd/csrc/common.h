@@ -219,15 +219,16 @@ struct LinearArgs {
     const void* W;       // [Hout][2H]
     const void* bias;    // [Hout] or null
     void* out;           // [T][Hout]
-    float* ws;           // few-token path: [nslices][T][Hout] partial sums
+    float* ws;           // [nslices][T][Hout] partial sums
     int32_t T, H, Hout, dtype;
     int32_t ttiles, otiles;   // set by the launcher
-    int32_t ksub, kslice, nslices;   // few-token path: reduction elements per LDS fill, per workgroup, workgroups per tile
+    int32_t ksub, kslice, nslices;   // few tokens: reduction elements per LDS fill, per workgroup, workgroups per tile; tiled: stages and slices
 };
-hipError_t launch_draft_linear(const LinearArgs& a, hipStream_t st);
+hipError_t launch_draft_linear(const LinearArgs& a, hipStream_t st);         // nslices > 1: partial sums in ws
+hipError_t launch_draft_linear_reduce(const LinearArgs& a, hipStream_t st);  // adds the slices' partial sums
+int draft_linear_slices(int T, int H, int Hout, int cus, size_t most, int* kslice);      // of the tiled kernel, kslice stages each
 hipError_t launch_draft_linear_small(const LinearArgs& a, hipStream_t st);   // T <= draft_linear_small_max_tokens()
-int draft_linear_small_max_tokens();      // tokens per launch of the weight-streaming kernel
-int draft_linear_stream_max_tokens();     // token count up to which the entry point uses it (in passes)
+int draft_linear_small_max_tokens();      // tokens that the weight-streaming kernel takes
 void draft_linear_small_plan(int T, int H, int Hout, int cus, int* ksub, int* kslice, int* nslices);
 int draft_linear_tile_out();
 int draft_linear_tile_k();

@@ -33,9 +33,6 @@ constexpr int kWaves = 8;
 constexpr int kThreads = kWaves * 64;
 constexpr int kStepK = 128;             // reduction elements per step (4 MFMAs per token block)
 constexpr int kMaxT = 128;
-#ifndef S4C_DL_STREAM_MAX
-#define S4C_DL_STREAM_MAX 512
-#endif
 constexpr int kLdsX = 128 * 1024;       // LDS for the x sub-slice: a CU holds one workgroup, so it may take most of the 160 KB
 constexpr int kPadB = 16;               // row padding: 16 tokens x 16-byte reads hit 16 different bank groups
 
@@ -151,6 +148,7 @@ __global__ __launch_bounds__(256) void draft_linear_reduce_kernel(LinearArgs a) 
     const size_t t = i / per_row, o = (i % per_row) * 4;
     const size_t plane = (size_t)a.T * a.Hout;
     f32x4 s = *(const f32x4*)(a.ws + t * a.Hout + o);
+#pragma unroll 8
     for (int sl = 1; sl < a.nslices; ++sl) s += *(const f32x4*)(a.ws + sl * plane + t * a.Hout + o);
     if (a.bias) {
         const uint16_t* bp = (const uint16_t*)a.bias + o;
@@ -163,6 +161,18 @@ __global__ __launch_bounds__(256) void draft_linear_reduce_kernel(LinearArgs a) 
     *(uint2*)((uint16_t*)a.out + t * a.Hout + o) = pk;
 }
 
+}  // namespace
+
+hipError_t launch_draft_linear_reduce(const LinearArgs& a, hipStream_t st) {
+    const size_t n = (size_t)a.T * (a.Hout / 4);
+    const dim3 grid((unsigned)((n + 255) / 256)), block(256);
+    if (a.dtype == S4C_F16) hipLaunchKernelGGL(draft_linear_reduce_kernel<true>, grid, block, 0, st, a);
+    else hipLaunchKernelGGL(draft_linear_reduce_kernel<false>, grid, block, 0, st, a);
+    return hipGetLastError();
+}
+
+namespace {
+
 template <bool F16, int TB>
 hipError_t launch_small(const LinearArgs& a, hipStream_t st) {
     static std::atomic<uint64_t> lds_set{0};
@@ -171,11 +181,8 @@ hipError_t launch_small(const LinearArgs& a, hipStream_t st) {
     const hipError_t ea = ensure_dynamic_lds((const void*)draft_linear_small_kernel<F16, TB>, kLdsX + kMaxT * kPadB, lds_set);
     if (ea != hipSuccess) return ea;
     hipLaunchKernelGGL((draft_linear_small_kernel<F16, TB>), dim3((unsigned)(a.otiles * a.nslices)), dim3(kThreads), bytes, st, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const size_t n = (size_t)a.T * (a.Hout / 4);
-    hipLaunchKernelGGL(draft_linear_reduce_kernel<F16>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? launch_draft_linear_reduce(a, st) : e;
 }
 
 template <bool F16>
@@ -195,7 +202,6 @@ hipError_t launch_small_by_tokens(const LinearArgs& a, hipStream_t st) {
 }  // namespace
 
 int draft_linear_small_max_tokens() { return kMaxT; }
-int draft_linear_stream_max_tokens() { return S4C_DL_STREAM_MAX; }
 
 // The split of the reduction dimension for this shape (a fixed function of the sizes and the CU count): as
 // many slices as give every CU at most one workgroup, each a whole number of equal sub-slices that fit in LDS.

@@ -564,13 +564,16 @@ s4c_status s4c_commit_path_paged(const s4c_attn_shape* shape, int32_t layers, co
                        path, accept_len, max_path, features, feature_bytes, features_out, dst_index, status, hip_stream);
 }
 
-size_t s4c_draft_linear_workspace_size(int32_t T, int32_t H, int32_t Hout) {
-    if (T <= 0 || H <= 0 || Hout <= 0 || T > draft_linear_stream_max_tokens() || H % draft_linear_tile_k() != 0 ||
-        Hout % draft_linear_tile_out() != 0)
-        return 0;
-    // the largest need of any pass (passes as in s4c_draft_linear: equal sizes, the last one may be shorter)
-    const int step = draft_linear_small_max_tokens();
-    const int passes = (T + step - 1) / step, per = (T + passes - 1) / passes;
+#pragma GCC visibility pop
+}  // extern "C"
+
+namespace {
+// Up to kNeedsWorkspace tokens a call must bring a workspace, of at least this size (what the weight-streaming kernel's partial sums
+// take, for equal passes of at most as many tokens as it has room for).
+constexpr int kNeedsWorkspace = 512;
+size_t least_linear_bytes(int32_t T, int32_t H, int32_t Hout) {
+    if (T > kNeedsWorkspace) return 0;
+    const int step = draft_linear_small_max_tokens(), passes = (T + step - 1) / step, per = (T + passes - 1) / passes;
     size_t need = 0;
     for (int t0 = 0; t0 < T; t0 += per) {
         const int Tp = T - t0 < per ? T - t0 : per;
@@ -579,7 +582,30 @@ size_t s4c_draft_linear_workspace_size(int32_t T, int32_t H, int32_t Hout) {
         const size_t b = (size_t)nslices * Tp * Hout * sizeof(float);
         if (b > need) need = b;
     }
-    return ((need + 255) / 256) * 256;
+    return need;
+}
+// The tiled kernel rather than the one that streams W for few tokens: from 65 tokens on where W is large, whose stream the tiled kernel,
+// all its loads asynchronous, keeps up better, and always where tokens would not fit the other.  Streamed and tiled, us: 128
+// tokens H 2048 18.4 and 20.6, 4096 32.7 and 32.6, 5120 53.0 and 40.9, 8192 99.9 and 85.3; 80 tokens 4096 28.2 and 29.8, 5120 41.8
+// and 37.9, 8192 88.7 and 82.2; 64 tokens 5120 36.8 and 35.9, 8192 81.2 and 79.5; 33 tokens 4096 22.9 and 26.6.  (More than 128
+// tokens used to be streamed in passes up to 512, W each time: 150, 1024 21.9 and 17.8, 8192 145 and 91; 512, 8192 377 and 140.)
+bool linear_is_tiled(int32_t T, int32_t H, int32_t Hout) {
+    return T > draft_linear_small_max_tokens() || (T > 64 && (long long)H * Hout >= 5120ll * 5120);
+}
+size_t tiled_bytes(int32_t T, int32_t H, int32_t Hout) {
+    int kslice;
+    const int n = draft_linear_slices(T, H, Hout, device_cus(), ~(size_t)0, &kslice);
+    return n > 1 ? (size_t)n * T * Hout * sizeof(float) : 0;
+}
+}  // namespace
+
+extern "C" {
+#pragma GCC visibility push(default)
+
+size_t s4c_draft_linear_workspace_size(int32_t T, int32_t H, int32_t Hout) {
+    if (T <= 0 || H <= 0 || Hout <= 0 || H % draft_linear_tile_k() != 0 || Hout % draft_linear_tile_out() != 0) return 0;
+    const size_t least = least_linear_bytes(T, H, Hout), tiled = linear_is_tiled(T, H, Hout) ? tiled_bytes(T, H, Hout) : 0;
+    return (((least > tiled ? least : tiled) + 255) / 256) * 256;
 }
 
 s4c_status s4c_draft_linear(int32_t T, int32_t H, int32_t Hout, int32_t dtype, const void* e, const void* f,
@@ -594,27 +620,20 @@ s4c_status s4c_draft_linear(int32_t T, int32_t H, int32_t Hout, int32_t dtype, c
     LinearArgs a;
     a.e = e; a.f = f; a.W = W; a.bias = bias; a.out = out; a.ws = nullptr; a.T = T; a.H = H; a.Hout = Hout; a.dtype = dtype;
     a.ttiles = a.otiles = 0; a.ksub = a.kslice = a.nslices = 0;
-    if (T <= draft_linear_stream_max_tokens()) {
-        // few tokens: the weight-streaming kernel with split-K partial sums in the workspace, in passes of at most
-        // 128 tokens (each pass streams W once; up to four passes still beat the tiled kernel, which has no split-K
-        // and fills few workgroups at these sizes)
-        const size_t need = s4c_draft_linear_workspace_size(T, H, Hout);
-        if (!workspace || workspace_bytes < need || (((uintptr_t)workspace) & 255)) return S4C_ERR_WORKSPACE;
-        const int step = draft_linear_small_max_tokens();
-        const int passes = (T + step - 1) / step, per = (T + passes - 1) / passes;      // equal passes
-        a.ws = (float*)workspace;
-        for (int t0 = 0; t0 < T; t0 += per) {
-            LinearArgs p = a;
-            p.T = T - t0 < per ? T - t0 : per;
-            p.e = (const char*)e + (size_t)t0 * H * 2;
-            p.f = (const char*)f + (size_t)t0 * H * 2;
-            p.out = (char*)out + (size_t)t0 * Hout * 2;
-            draft_linear_small_plan(p.T, H, Hout, device_cus(), &p.ksub, &p.kslice, &p.nslices);
-            if (launch_draft_linear_small(p, (hipStream_t)hip_stream) != hipSuccess) return S4C_ERR_HIP;
-        }
-        return S4C_OK;
+    const bool usable = workspace && !(((uintptr_t)workspace) & 255);
+    if (T <= kNeedsWorkspace && (!usable || workspace_bytes < least_linear_bytes(T, H, Hout))) return S4C_ERR_WORKSPACE;
+    a.ws = (float*)workspace;
+    hipError_t err;
+    if (linear_is_tiled(T, H, Hout)) {
+        // (as many slices as the workspace has room for)
+        const size_t most = usable ? workspace_bytes / ((size_t)T * Hout * sizeof(float)) : 0;
+        a.nslices = draft_linear_slices(T, H, Hout, device_cus(), most, &a.kslice);
+        err = launch_draft_linear(a, (hipStream_t)hip_stream);
+    } else {
+        draft_linear_small_plan(T, H, Hout, device_cus(), &a.ksub, &a.kslice, &a.nslices);
+        err = launch_draft_linear_small(a, (hipStream_t)hip_stream);
     }
-    return launch_draft_linear(a, (hipStream_t)hip_stream) == hipSuccess ? S4C_OK : S4C_ERR_HIP;
+    return err == hipSuccess ? S4C_OK : S4C_ERR_HIP;
 }
 
 size_t s4c_verify_step_workspace_size(const s4c_attn_shape* shape, int32_t V) {

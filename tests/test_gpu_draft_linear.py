@@ -110,3 +110,21 @@ def test_rejects_unsupported_shapes():
         B.s4c_draft_linear(t(4, 64), t(4, 64), t(256, 128), t(4, 256))
     with pytest.raises(TypeError):
         B.s4c_draft_linear(t(4, 64).float(), t(4, 64).float(), t(256, 128).float(), t(4, 256).float())
+
+
+@pytest.mark.parametrize("T,H,Hout", [(129, 32, 256), (130, 992, 256), (255, 1056, 512), (257, 1120, 256), (300, 160, 2560),
+                                      (513, 2080, 256), (600, 4096, 768), (1025, 544, 512), (80, 5152, 5120)])
+def test_tiled_kernel_divided_reductions(T, H, Hout):
+    """Edges of token tiles, stages (hidden sizes that are odd multiples of 32 have a stage half of e, half of f), slices that
+    are not equally long, and workspaces that leave room for fewer slices or none: every element against the oracle."""
+    e, f, W, b = make(T, H, Hout, 4000 + T + H, True)
+    want = O.draft_linear(e, f, W, b)
+    close(run(e, f, W, b), want)
+    te, tf, tW, tb = (np_to_torch(x) for x in (e, f, W, b))
+    one = T * Hout * 4                                       # a slice
+    sizes = [0, one, 2 * one] if T > 512 else []
+    for n in sizes:
+        out = torch.full((T, Hout), float("nan"), dtype=torch.bfloat16, device="cuda")
+        B.s4c_draft_linear(te, tf, tW, out, tb, torch.full((n // 4,), float("nan"), device="cuda") if n else None)
+        torch.cuda.synchronize()
+        close(out.float().cpu().numpy().astype(np.float64), want)
