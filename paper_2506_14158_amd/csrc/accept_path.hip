@@ -574,7 +574,7 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd<T>) void step_kernel(AttnAr
 
 int accept_chunk_elems() { return kChunk; }
 
-// Segments of the candidate-tree scan: up to 8 chunks of a row, fewer when that would leave less than about 1024 workgroups
+// Segments by which the acceptance workspace is sized (scan_plan): up to 8 chunks of a row, fewer when that would leave less than about 1024 workgroups
 // to spread over the chip.  `head`: elements by which rows may begin inside a vector.
 void accept_plan(int B, int N, int V, int head, int* chunks, int* seg, int* nseg) {
     const long long ch = ((long long)V + head + kChunk - 1) / kChunk;

@@ -288,6 +288,21 @@ __global__ __launch_bounds__(64) void topk_row_kernel(BuildArgs a) {
 int build_tree_max_children() { return kK; }
 int build_tree_chunk_elems() { return kChunk; }
 
+// Segments of up to 8 chunks (a segment's first chunk fills the lists, later ones seldom change them), shorter where that would leave
+// fewer than about 2048 workgroups counting all rows, of which about half have children: four fit on a CU, and the last turn of
+// the chip should not be a long one.  With 1024 (us a call) and with 2048: 16 rows x 30 nodes, V 50000 27.6 and 21.3; 8 x 128, 32000
+// 34.6 and 27.1; 4 x 100, 128256 37.2 and 30.6; 2 x 128, 128256 32.9 and 28.1; 8 x 100, 60001 fp32 39.5 and 36.6; 16 x 128, 128256 (8
+// chunks in both) 83.6; with 4096: 16 x 60, 128256 51.5 (45.2), 8 x 100 fp32 45.2.  Equal runs of chunks across the rows' ends, as the acceptance scan has
+// them, measured 87 on the largest: the scan is bound by its selection and exponentials, not by its last turn.
+void build_tree_plan(BuildArgs& a) {
+    long long seg = (long long)a.B * a.N * a.chunks / 2048;
+    if (seg > 8) seg = 8;
+    if (seg > a.chunks) seg = a.chunks;
+    if (seg < 1) seg = 1;
+    a.seg = (int)seg;
+    a.nseg = (a.chunks + a.seg - 1) / a.seg;
+}
+
 // Rows on 16-byte boundaries are read in plain chunks, others through RowReader.  Read through RowReader too, 335 MB of
 // aligned bf16 rows take 88 us instead of 82; rows of odd length read two bytes at a time, as the plain chunks would be,
 // 71.4 us instead of 43.6 (103 MB).

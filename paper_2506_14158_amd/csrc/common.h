@@ -186,6 +186,7 @@ struct BuildArgs {
     int32_t seg, nseg;         // chunks per workgroup of the scan, workgroups per row
     float inv_temp_log2;
 };
+void build_tree_plan(BuildArgs& a);       // seg and nseg
 hipError_t launch_build_tree(const BuildArgs& a, hipStream_t st);
 int build_tree_max_children();
 int build_tree_chunk_elems();

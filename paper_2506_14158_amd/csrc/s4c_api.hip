@@ -493,7 +493,8 @@ s4c_status s4c_build_tree(int32_t B, int32_t N, int32_t V, int32_t logits_dtype,
     {   // rows that begin inside a 16-byte vector may reach into one chunk more (row_chunk.h)
         const int vec = logits_dtype == S4C_F32 ? 4 : 8;
         const int head = V % vec == 0 && aligned16(draft_logits) ? 0 : vec - 1;
-        accept_plan(B, N, V, head, &a.chunks, &a.seg, &a.nseg);
+        a.chunks = (int)(((long long)V + head + build_tree_chunk_elems() - 1) / build_tree_chunk_elems());
+        build_tree_plan(a);
     }
     a.inv_temp_log2 = kLog2e / temperature;
     return launch_build_tree(a, (hipStream_t)hip_stream) == hipSuccess ? S4C_OK : S4C_ERR_HIP;
