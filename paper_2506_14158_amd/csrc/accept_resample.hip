@@ -520,7 +520,8 @@ __global__ __launch_bounds__(kThreads) void accept_resample_kernel(ResampleArgs 
 }
 
 // ---- rows: workgroup b N + i decides node i of sequence b and publishes (call nonce, decision); workgroup B N + b waits
-// for its sequence's decisions, overwrites them (so that a captured graph can replay the call) and follows them.  Workgroups
+// for its sequence's decisions, overwrites them (so that a captured graph can replay the call) and follows them.  A decision that
+// it gave up on is overwritten by the node's own workgroup, which finds the word (~nonce, 1) left for it there.  Workgroups
 // start in grid order, so when it starts every other one of its sequence has a compute unit or is done.
 constexpr uint32_t kAccepted = 0x80000000u;                // decision: kAccepted | child, or the correction token
 template <typename T, int NG>
@@ -535,9 +536,12 @@ __global__ __launch_bounds__(kThreads) void resample_rows_kernel(ResampleArgs a)
         Team team = {nullptr, 0, 1, 0, 0, 0, 0, 0};
         int32_t token = 0;
         const int next = decide<T, NG, false>(a, sh, team, b, node, blk0, blk1, &token);
-        if (tid == 0)
-            __hip_atomic_store(a.slots + blockIdx.x, ((uint64_t)a.nonce << 32) | (next >= 0 ? kAccepted | (uint32_t)next : (uint32_t)token),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) {
+            const uint64_t before = __hip_atomic_exchange(a.slots + blockIdx.x, ((uint64_t)a.nonce << 32) | (next >= 0 ? kAccepted | (uint32_t)next : (uint32_t)token),
+                                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (before == (((uint64_t)(~a.nonce) << 32) | 1u))
+                __hip_atomic_store(a.slots + blockIdx.x, (uint64_t)(~a.nonce) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
         return;
     }
     const int b = blockIdx.x - a.B * N;
@@ -554,7 +558,8 @@ __global__ __launch_bounds__(kThreads) void resample_rows_kernel(ResampleArgs a)
             if (late) __builtin_amdgcn_s_sleep(8);
         }
         s_said[tid] = (uint32_t)v;
-        if (!late) __hip_atomic_store(rec, (uint64_t)(~a.nonce) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!late || (uint32_t)(__hip_atomic_exchange(rec, ((uint64_t)(~a.nonce) << 32) | 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32) == a.nonce)
+            __hip_atomic_store(rec, (uint64_t)(~a.nonce) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     late = __syncthreads_or(late);
     if (late || bad) {

@@ -165,6 +165,28 @@ def test_team_that_cannot_exchange_is_flagged_and_every_kernel_exits(monkeypatch
     same(tv, r)
 
 
+def test_decisions_given_up_on_are_not_left_behind(monkeypatch):
+    """One workgroup per node, and the one that follows the decisions gives up at once: none of them may stay in the
+    workspace, where a replay of the same captured call would take it for its own."""
+    cfg = synth.scaled(C[3], name="timeout-rows", B=3, V=4000, index=0)
+    par = synth.make_parent(cfg)
+    ac, r = resample_inputs_with_margin(cfg, par, O)
+    d = to_device(cfg, par, None, ac)
+    tv = TreeVerifier(cfg.B, cfg.N, 1, 1, 64, 1, cfg.V, d["logits"].dtype, cfg.levels, 0)
+    call = lambda: tv.accept_resample(d["logits"], d["draft_probs"], d["parent"], d["tokens"], d["uniforms"],
+                                      d["u_resample"], cfg.temperature)
+    monkeypatch.setenv("S4C_RESAMPLE_SPIN_LIMIT", "0")
+    call()
+    torch.cuda.synchronize()
+    assert tv.accept_status.cpu().tolist() == [B.S4C_SEQ_TIMEOUT] * cfg.B
+    words = tv.resample_ws.view(torch.int32)[:2 * cfg.B * cfg.N].cpu().reshape(-1, 2)
+    assert (words[:, 0] == 0).all() and (words[:, 1] == words[0, 1]).all()
+    monkeypatch.delenv("S4C_RESAMPLE_SPIN_LIMIT")
+    call()
+    torch.cuda.synchronize()
+    same(tv, r)
+
+
 def test_rejects_bad_arguments():
     t = lambda *s, dt=torch.float32: torch.zeros(*s, dtype=dt, device="cuda")
     i = lambda *s: torch.zeros(*s, dtype=torch.int32, device="cuda")
