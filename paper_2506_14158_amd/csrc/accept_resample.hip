@@ -16,8 +16,8 @@
 //           result or, if workgroup 0 itself gave up anywhere, the flagged empty one -- never a mixture.
 // Every poll is bounded: a workgroup that cannot complete an exchange exits.
 //
-// A node's rows are read once and stay in registers (8 tokens x NG blocks a thread: the weights as fp64, the draft
-// probabilities as fp32), so a rejected child costs arithmetic and a reduction, no memory:
+// A node's rows are read once and stay in registers (8 tokens x NG blocks a thread: the weights as fp64 and, up to four blocks, the
+// draft probabilities as fp32), so a rejected child costs arithmetic and a reduction, no memory:
 //   a_0[v] = exp((l[v] - max l) / T)              S_0 = sum_v a_0[v]        (target row)
 //   a_{j+1}[v] = max(0, a_j[v] - S_j q[v])        S_{j+1} = sum_v a_{j+1}[v] (after j+1 rejections)
 // so that a_j / S_j is the j-times-corrected distribution.  A child with token x passes iff
@@ -37,7 +37,7 @@ namespace {
 constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
 constexpr int kBlock = 512;            // tokens per (wave, iteration)
-constexpr int kMaxIters = 8;           // blocks per wave: 8 x 8 x (2 + 1) registers, of the 256 that two waves per SIMD have
+constexpr int kMaxIters = 8;           // blocks per wave (registers: see decide)
 constexpr int kMaxSlice = kMaxIters * kWaves * kBlock;     // tokens of a workgroup: 32768
 constexpr int kMaxRow = kMaxSlice / 2;                     // longest row that one workgroup decides alone (resample_by_rows)
 constexpr int kMaxVocab = 1 << 21;
@@ -59,24 +59,27 @@ __device__ __forceinline__ double of_lane(double x, int lane) {            // (l
     const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, lane), hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), lane);
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
-// sum over the wave, in every lane
-__device__ __forceinline__ double wave_sum(double x) {
-    x += dpp<0x111, 0xF>(x);          // row_shr:1, 2, 4, 8: lane 15 of each row holds its row's sum
+__device__ __forceinline__ float uniform_f32(float x) { return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(x))); }
+// inclusive sums over the wave's lanes
+__device__ __forceinline__ double wave_incl_scan(double x) {
+    x += dpp<0x111, 0xF>(x);          // row_shr:1, 2, 4, 8: sums inside each row of 16
     x += dpp<0x112, 0xF>(x);
     x += dpp<0x114, 0xF>(x);
     x += dpp<0x118, 0xF>(x);
     x += dpp<0x142, 0xA>(x);          // row_bcast:15 into rows 1 and 3
     x += dpp<0x143, 0xC>(x);          // row_bcast:31 into rows 2 and 3
-    return of_lane(x, 63);
-}
-
-__device__ __forceinline__ double wave_incl_scan(double x, int lane) {
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const double y = __shfl_up(x, off);
-        if (lane >= off) x += y;
-    }
     return x;
+}
+__device__ __forceinline__ double wave_sum(double x) { return of_lane(wave_incl_scan(x), 63); }      // in every lane
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_max(float x) {                         // (lanes without a source see their own value)
+    const int i = (int)__float_as_uint(x);
+    return fmaxf(x, __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(i, i, CTRL, ROWS, 0xF, false)));
+}
+__device__ __forceinline__ float wave_max(float x) {                        // in every lane
+    x = dpp_max<0x118, 0xF>(dpp_max<0x114, 0xF>(dpp_max<0x112, 0xF>(dpp_max<0x111, 0xF>(x))));
+    x = dpp_max<0x143, 0xC>(dpp_max<0x142, 0xA>(x));
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), 63));
 }
 
 __device__ __forceinline__ double bits_to_f64(uint64_t u) { return __longlong_as_double((long long)u); }
@@ -122,6 +125,9 @@ __device__ __forceinline__ void load_draft8(const Row& r, int base, float (&qv)[
     }
 }
 
+// Workgroups of a team kernel that a CU has room for (by the registers that its launch bounds leave it)
+__host__ __device__ constexpr int per_cu(int blocks) { return blocks <= 2 ? 2 : 1; }
+
 // What the threads of a workgroup share.
 struct Shared {
     int32_t par[kMaxNodes], tok[kMaxNodes], child[kMaxNodes];      // the tree; the current node's children
@@ -129,7 +135,7 @@ struct Shared {
     double ax[kMaxNodes], lhs[kMaxNodes];                          // per node: weight and u q of its token in its parent's rows
     double red[2][kWaves];
     float redf[kWaves];
-    uint32_t got[4][kMaxTeam];                                     // the team's words of an exchange
+    uint32_t got[4 * kMaxTeam];                                    // the team's words of an exchange: [4][G]
 };
 
 // A team's exchanges (a workgroup that works alone, G = 1, makes none).  Workgroup g's words of an exchange are 8-byte
@@ -163,7 +169,8 @@ struct Team {
         if (pass >= max_pass) return false;                // (more than a valid tree can need)
         const bool first = pass == 0;                      // (an exchange with a maximum)
         uint64_t* const w = slots + (size_t)pass * 4 * G;
-        const int tid = threadIdx.x;
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));                      // (as in decide)
         const uint64_t bits = f64_to_bits(a);
         if (tid == 0) {
             put(w + g, tag, (uint32_t)(bits >> 32));
@@ -174,16 +181,16 @@ struct Team {
         if (tid < (!MAX ? 2 : first ? 4 : 3) * G) {
             uint32_t x = 0;
             if (!get(w + tid, &x)) sh.fail = 1;
-            sh.got[tid / G][tid % G] = x;
+            sh.got[tid] = x;
         }
         __syncthreads();
-        if (sh.fail) return false;
-        if (first) tag = nonce ^ (sh.got[3][0] * 0x9E3779B1u);
+        if (__builtin_amdgcn_readfirstlane(sh.fail)) return false;
+        if (first) tag = nonce ^ (sh.got[3 * G] * 0x9E3779B1u);
         else if (pass == 1) clear();
         ++pass;
         return true;
     }
-    __device__ __forceinline__ double value(const Shared& sh, int i) const { return bits_to_f64(((uint64_t)sh.got[0][i] << 32) | sh.got[1][i]); }
+    __device__ __forceinline__ double value(const Shared& sh, int i) const { return bits_to_f64(((uint64_t)sh.got[i] << 32) | sh.got[G + i]); }
     // this workgroup's records of the first exchange
     __device__ __forceinline__ void clear() const {
         if (threadIdx.x < 4) put(slots + threadIdx.x * G + g, ~nonce, 0u);
@@ -196,16 +203,27 @@ struct Team {
 constexpr int kLeave = -2;
 template <typename T, int NG, bool TEAM>
 __device__ __forceinline__ int decide(const ResampleArgs& a, Shared& sh, Team& team, int b, int cur, int blk0, int blk1, int32_t* token) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, N = a.N, V = a.V;
+    // Registers: a block's weights take 16, its draft probabilities 8, its logits 8 until they are weights; the rest, the constants of the
+    // exponential foremost, about 65.  A team's kernel has 89, 112 and 162 with 1, 2 and 4 blocks, and 244 with 8, whose draft probabilities
+    // are read again at every use; nothing is spilled.  What that takes: the draft probabilities are requested when the logits are
+    // weights; branches that all threads take alike are scalar ones, and the weights are not changed under a condition (both would keep
+    // them twice); and the compiler must not know that a thread's number is the same for every node of a walk, or addresses and
+    // the masks of a row's end are computed once and kept.  With all of it left out, 8 blocks took 256 registers and spilled
+    // 497.  us a call, before and after: 256 x 32 nodes, V 32000 (8 blocks) 350 and 90; 16 x 128, 128256 (2) 57.4 and 47.4;
+    // 4 x 64, 32000 (1) 41.5 and 37.3.
+    int tid = threadIdx.x;
+    if (TEAM) asm volatile("" : "+v"(tid));
+    const int V = a.V, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), N = a.N;
     Row row;
     row.V = V;
     row.lg = (const T*)a.logits + ((size_t)b * N + cur) * V;
     row.q = a.draft + ((size_t)b * N + cur) * V;
     row.vec = (((uintptr_t)row.lg | (uintptr_t)row.q) & 15) == 0;
-    const double invT = 1.0 / a.temperature;
+    const double invT = a.inv_temperature;
 
+    constexpr bool kKeepQ = NG <= 4;                       // (eight blocks' weights leave no room for it: read again at every use)
     double w[NG][8];
-    float q[NG][8];
+    float q[kKeepQ ? NG : 1][8];
     {
         float x[NG][8];
 #pragma unroll
@@ -230,45 +248,57 @@ __device__ __forceinline__ int decide(const ResampleArgs& a, Shared& sh, Team& t
         if (wave < 2 && lane == 0) sh.count[wave] = __popcll(mask);
         __syncthreads();
         if (mine) sh.child[__popcll(mask & ((1ull << lane) - 1ull)) + (wave == 1 ? sh.count[0] : 0)] = tid;
-        const int n_child = sh.count[0] + sh.count[1];
-#pragma unroll
-        for (int it = 0; it < NG; ++it) {
+        const int n_child = __builtin_amdgcn_readfirstlane(sh.count[0] + sh.count[1]);
+        auto load_q = [&](int it, int at, float (&to)[8]) __attribute__((always_inline)) {
             if (n_child > 0 && blk0 + it < blk1) {
-                load_draft8(row, (blk0 + it) * kBlock + lane * 8, q[it]);
+                load_draft8(row, (blk0 + it) * kBlock + at, to);
             } else {
 #pragma unroll
-                for (int k = 0; k < 8; ++k) q[it][k] = 0.f;
+                for (int k = 0; k < 8; ++k) to[k] = 0.f;
             }
-        }
+        };
+        auto load_all_q = [&]() __attribute__((always_inline)) {
+            if constexpr (kKeepQ) {
+#pragma unroll
+                for (int it = 0; it < NG; ++it) load_q(it, lane * 8, q[it]);
+            }
+        };
+        auto q_of = [&](int it) __attribute__((always_inline)) -> float (&)[8] {
+            if constexpr (kKeepQ) return q[it];
+            int at = lane * 8;
+            asm volatile("" : "+v"(at));
+            load_q(it, at, q[0]);
+            return q[0];
+        };
+        if (!TEAM) load_all_q();
         // ---- row maximum (exact), the weights against the slice's, and their sum
         float ms = x[0][0];
 #pragma unroll
         for (int it = 0; it < NG; ++it)
 #pragma unroll
             for (int k = 0; k < 8; ++k) ms = fmaxf(ms, x[it][k]);
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) ms = fmaxf(ms, __shfl_xor(ms, off));
+        ms = wave_max(ms);
         if (lane == 0) sh.redf[wave] = ms;
         __syncthreads();
         ms = sh.redf[0];
 #pragma unroll
         for (int i = 1; i < kWaves; ++i) ms = fmaxf(ms, sh.redf[i]);
+        ms = uniform_f32(ms);
         double s = 0.0;
-        if (ms > -INFINITY) {                                       // (a slice behind the vocabulary's end: no weights)
+        const double md = ms > -INFINITY ? (double)ms : 0.0;         // (a slice behind the vocabulary's end: no weights)
 #pragma unroll
-            for (int it = 0; it < NG; ++it) {
-                keep_order();
+        for (int it = 0; it < NG; ++it) {
+            keep_order();
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    w[it][k] = exp(((double)x[it][k] - (double)ms) * invT);     // padding: exp(-inf) = 0
-                    s += w[it][k];
-                }
+            for (int k = 0; k < 8; ++k) {
+                if (TEAM && k % 2 == 0) keep_order();
+                w[it][k] = exp(((double)x[it][k] - md) * invT);      // padding: exp(-inf) = 0
+                s += w[it][k];
             }
-        } else {
-#pragma unroll
-            for (int it = 0; it < NG; ++it)
-#pragma unroll
-                for (int k = 0; k < 8; ++k) w[it][k] = 0.0;
+        }
+        if (TEAM) {              // (where the logits were; they arrive while the sums are exchanged)
+            keep_order();
+            load_all_q();
         }
         s = wave_sum(s);
         if (lane == 0) sh.red[0][wave] = s;
@@ -277,18 +307,16 @@ __device__ __forceinline__ int decide(const ResampleArgs& a, Shared& sh, Team& t
 #pragma unroll
         for (int i = 0; i < kWaves; ++i) sg += sh.red[0][i];
         float m = ms;
+        double f = 1.0;
         if (TEAM && team.G > 1) {
             if (!team.template exchange<true>(sh, sg, ms)) return kLeave;
-            for (int i = 0; i < team.G; ++i) m = fmaxf(m, __uint_as_float(sh.got[2][i]));
-            // lane i brings workgroup i's sum to the row's maximum; added in order
-            double part = 0.0;
-            if (lane < team.G) {
-                const float mi = __uint_as_float(sh.got[2][lane]);
-                if (mi > -INFINITY) part = team.value(sh, lane) * exp(((double)mi - (double)m) * invT);
-            }
-            sg = 0.0;
-            for (int i = 0; i < team.G; ++i) sg += of_lane(part, i);
-            const double f = ms > -INFINITY ? exp(((double)ms - (double)m) * invT) : 0.0;
+            // lane i brings workgroup i's sum to the row's maximum
+            const float mi = lane < team.G ? __uint_as_float(sh.got[2 * team.G + lane]) : -INFINITY;
+            m = wave_max(mi);
+            sg = wave_sum(mi > -INFINITY ? team.value(sh, lane) * exp(((double)mi - (double)m) * invT) : 0.0);
+            f = ms > -INFINITY ? exp(((double)ms - (double)m) * invT) : 0.0;
+        }
+        if (TEAM) {              // (also where there is nothing to change: under the condition above, the weights would be kept twice)
 #pragma unroll
             for (int it = 0; it < NG; ++it)
 #pragma unroll
@@ -305,15 +333,18 @@ __device__ __forceinline__ int decide(const ResampleArgs& a, Shared& sh, Team& t
         double S = sg, owed = 0.0;
         int buf = 1;
         for (int i = 0; i < n_child; ++i) {
-            const int c = sh.child[i];
-            if (sh.lhs[c] < sh.ax[c] / S) return c;
+            const int c = __builtin_amdgcn_readfirstlane(sh.child[i]);
+            if (__builtin_amdgcn_readfirstlane(sh.lhs[c] < sh.ax[c] / S)) return c;
             double z = 0.0;                                          // rejected: mass of max(0, w' - S q)
 #pragma unroll
             for (int it = 0; it < NG; ++it) {
                 keep_order();
+                float (&qi)[8] = q_of(it);
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
-                    const double qd = (double)q[it][k];
+                    if (TEAM && k % 2 == 0) keep_order();
+                    if (TEAM) asm volatile("" : "+v"(qi[k]));            // (or all of them would be held as doubles, converted in front of the loop)
+                    const double qd = (double)qi[k];
                     w[it][k] = fmax(0.0, w[it][k] - owed * qd);
                     z += fmax(0.0, w[it][k] - S * qd);
                 }
@@ -328,8 +359,7 @@ __device__ __forceinline__ int decide(const ResampleArgs& a, Shared& sh, Team& t
             buf ^= 1;
             if (TEAM && team.G > 1) {
                 if (!team.template exchange<false>(sh, t)) return kLeave;
-                t = 0.0;
-                for (int j = 0; j < team.G; ++j) t += team.value(sh, j);
+                t = wave_sum(lane < team.G ? team.value(sh, lane) : 0.0);
             }
             if (t > 0.0) {                                           // same value in every thread; no mass left: nothing carried
                 if (mine) sh.ax[tid] = fmax(0.0, sh.ax[tid] - S * (double)qx);
@@ -342,8 +372,9 @@ __device__ __forceinline__ int decide(const ResampleArgs& a, Shared& sh, Team& t
 #pragma unroll
         for (int it = 0; it < NG; ++it) {
             keep_order();
+            const float (&qi)[8] = q_of(it);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) w[it][k] = fmax(0.0, w[it][k] - owed * (double)q[it][k]);
+            for (int k = 0; k < 8; ++k) w[it][k] = fmax(0.0, w[it][k] - owed * (double)qi[k]);
         }
     }
 
@@ -366,23 +397,18 @@ __device__ __forceinline__ int decide(const ResampleArgs& a, Shared& sh, Team& t
     for (int i = 0; i < kWaves; ++i) slice += sh.red[0][i];
     double excl = 0.0, total = slice;
     int gsel = 0;
+    double part = 0.0, incl_g = 0.0;                   // of workgroup `lane`: its sum, and the sum up to and with it
     if (TEAM && team.G > 1) {
         if (!team.template exchange<false>(sh, slice)) return kLeave;
-        total = 0.0;
-        for (int i = 0; i < team.G; ++i) total += team.value(sh, i);
+        part = lane < team.G ? team.value(sh, lane) : 0.0;
+        incl_g = wave_incl_scan(part);
+        total = of_lane(incl_g, 63);
     }
     const double tgt = (double)a.u_resample[b] * total;
     if (TEAM && team.G > 1) {
-        int glast = 0;
-        double run = 0.0, glexcl = 0.0;
-        gsel = -1;
-        for (int i = 0; i < team.G; ++i) {
-            const double v = team.value(sh, i);
-            if (v > 0.0) { glast = i; glexcl = run; }
-            if (gsel < 0 && run + v > tgt) { gsel = i; excl = run; }
-            run += v;
-        }
-        if (gsel < 0) { gsel = glast; excl = glexcl; }
+        const unsigned long long hits = __ballot(part > 0.0 && incl_g > tgt), pos = __ballot(part > 0.0);
+        gsel = hits ? __ffsll((long long)hits) - 1 : pos ? 63 - __clzll((long long)pos) : 0;
+        if (gsel > 0) excl = of_lane(incl_g, gsel - 1);
     }
     if (team.g == gsel) {
         int wsel = -1, wlast = 0;
@@ -401,7 +427,7 @@ __device__ __forceinline__ int decide(const ResampleArgs& a, Shared& sh, Team& t
             run = wexcl;
 #pragma unroll
             for (int it = 0; it < NG; ++it) {
-                incl[it] = wave_incl_scan(ls[it], lane);
+                incl[it] = wave_incl_scan(ls[it]);
                 const double v = of_lane(incl[it], 63);
                 if (v > 0.0) { ilast = it; ilexcl = run; }
                 if (isel < 0 && run + v > tgt) { isel = it; e_sel = run; }
@@ -439,7 +465,7 @@ __device__ __forceinline__ int decide(const ResampleArgs& a, Shared& sh, Team& t
             if (team.get(slot, &x)) sh.token = (int)x; else sh.fail = 1;
         }
         __syncthreads();
-        if (sh.fail) return kLeave;
+        if (__builtin_amdgcn_readfirstlane(sh.fail)) return kLeave;
     }
     *token = sh.token;
     return -1;
@@ -466,12 +492,17 @@ __device__ __forceinline__ bool load_tree(const ResampleArgs& a, Shared& sh, int
     return __syncthreads_or(bad);
 }
 
-// nothing accepted, no token
-__device__ __forceinline__ void write_empty(const ResampleArgs& a, int b, int status) {
-    for (int k = threadIdx.x; k < a.max_path; k += kThreads) {
+__device__ __forceinline__ void empty_path(const ResampleArgs& a, int b) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));                 // (as in decide)
+    for (int k = tid; k < a.max_path; k += kThreads) {
         a.path[(size_t)b * a.max_path + k] = (k == 0) ? 0 : -1;
         a.accepted_tokens[(size_t)b * a.max_path + k] = -1;
     }
+}
+// nothing accepted, no token
+__device__ __forceinline__ void write_empty(const ResampleArgs& a, int b, int status) {
+    empty_path(a, b);
     if (threadIdx.x == 0) {
         a.accept_len[b] = 0;
         a.bonus_token[b] = -1;
@@ -481,7 +512,7 @@ __device__ __forceinline__ void write_empty(const ResampleArgs& a, int b, int st
 
 // ---- teams: workgroup g of sequence b's team walks from the root
 template <typename T, int NG>
-__global__ __launch_bounds__(kThreads) void accept_resample_kernel(ResampleArgs a) {
+__global__ __launch_bounds__(kThreads, per_cu(NG) * kWaves / 4) void accept_resample_kernel(ResampleArgs a) {
     __shared__ Shared sh;
     const int G = a.team, b = a.first + blockIdx.x / G, g = blockIdx.x % G, tid = threadIdx.x;
     if (load_tree(a, sh, b, true)) {                       // every workgroup of the team sees the same tree
@@ -490,14 +521,12 @@ __global__ __launch_bounds__(kThreads) void accept_resample_kernel(ResampleArgs 
     }
     const int nblocks = (a.V + kBlock - 1) / kBlock;
     const int bpg = (nblocks + G - 1) / G, ipw = (bpg + kWaves - 1) / kWaves;              // blocks per workgroup and wave
-    const int gblk1 = min(nblocks, (g + 1) * bpg), blk0 = min(gblk1, g * bpg + (tid >> 6) * ipw), blk1 = min(gblk1, blk0 + ipw);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int gblk1 = min(nblocks, (g + 1) * bpg), blk0 = min(gblk1, g * bpg + wave * ipw), blk1 = min(gblk1, blk0 + ipw);
     Team team = {a.slots + (size_t)b * a.max_pass * 4 * G, g, G, a.max_pass, a.spin_limit, 0, a.nonce, a.nonce};
     int cur = 0, L = 0;
     int32_t token = -1;
-    int32_t* pth = a.path + (size_t)b * a.max_path;
-    int32_t* atk = a.accepted_tokens + (size_t)b * a.max_path;
-    if (g == 0)
-        for (int k = tid; k < a.max_path; k += kThreads) { pth[k] = (k == 0) ? 0 : -1; atk[k] = -1; }
+    if (g == 0) empty_path(a, b);
     for (;;) {
         const int next = decide<T, NG, true>(a, sh, team, b, cur, blk0, blk1, &token);
         if (next == kLeave) {                              // workgroup 0 flags the sequence and empties its outputs
@@ -508,7 +537,10 @@ __global__ __launch_bounds__(kThreads) void accept_resample_kernel(ResampleArgs 
         }
         if (next < 0) break;
         ++L;
-        if (g == 0 && tid == 0) { pth[L] = next; atk[L - 1] = sh.tok[next]; }
+        if (g == 0 && threadIdx.x == 0) {
+            a.path[(size_t)b * a.max_path + L] = next;
+            a.accepted_tokens[(size_t)b * a.max_path + L - 1] = sh.tok[next];
+        }
         cur = next;
         __syncthreads();                                   // the node's shared words are written again
     }
@@ -533,7 +565,7 @@ __global__ __launch_bounds__(kThreads) void resample_rows_kernel(ResampleArgs a)
         const int b = blockIdx.x / N, node = blockIdx.x - b * N;
         load_tree(a, sh, b, false);                        // (whatever it holds: rows and tokens are checked where they are used)
         const int nblocks = (a.V + kBlock - 1) / kBlock, ipw = (nblocks + kWaves - 1) / kWaves;
-        const int blk0 = min(nblocks, (tid >> 6) * ipw), blk1 = min(nblocks, blk0 + ipw);
+        const int blk0 = min(nblocks, __builtin_amdgcn_readfirstlane(tid >> 6) * ipw), blk1 = min(nblocks, blk0 + ipw);
         Team team = {nullptr, 0, 1, 0, 0, 0, 0, 0};
         int32_t token = 0;
         const int next = decide<T, NG, false>(a, sh, team, b, node, blk0, blk1, &token);

@@ -142,7 +142,7 @@ struct ResampleArgs {
     uint32_t nonce;            // tells this call's words from whatever they held before
     int32_t max_pass;          // exchanges a sequence may need
     int32_t spin_limit;        // polls before a workgroup gives up on an exchange
-    double temperature;
+    double inv_temperature;
 };
 hipError_t launch_accept_resample(const ResampleArgs& a, hipStream_t st);
 int resample_max_vocab();

@@ -389,7 +389,7 @@ s4c_status s4c_accept_resample(int32_t B, int32_t N, int32_t V, int32_t logits_d
     a.logits = logits; a.draft = draft_probs; a.parent = parent; a.tokens = tokens; a.uniforms = uniforms;
     a.u_resample = u_resample; a.path = path; a.accept_len = accept_len; a.accepted_tokens = accepted_tokens;
     a.bonus_token = bonus_token; a.status = status; a.slots = (uint64_t*)workspace;
-    a.B = B; a.N = N; a.V = V; a.max_path = max_path; a.dtype = logits_dtype; a.temperature = (double)temperature;
+    a.B = B; a.N = N; a.V = V; a.max_path = max_path; a.dtype = logits_dtype; a.inv_temperature = 1.0 / (double)temperature;
     a.team = by_rows ? 0 : resample_team(B, V, device_cus());
     a.first = 0;
     a.resident = device_cus();
