@@ -13,6 +13,7 @@
 // row's top nchild tokens, turns their logits into probabilities, and writes its children.  The numbering needs 128
 // words that are requested with everything else, so doing it once per row costs less than a launch of its own did.
 // HBM bounds kernel 1; kernel 2 is a chain of two memory latencies.
+#include "build_plan.h"
 #include "row_chunk.h"
 
 namespace s4c {
@@ -177,7 +178,7 @@ __global__ __launch_bounds__(64) void topk_row_kernel(BuildArgs a) {
     const size_t o = (size_t)row * parts;
     // the sequence's child counts, this lane's part statistics and (few parts) its whole list are requested together: the
     // kernel is a chain of memory latencies, not of work
-    const bool few = parts <= 64, mine = lane < parts;
+    const bool few = parts <= kBuildListsInRegisters, mine = lane < parts;
     const int32_t* counts = a.nchild + (size_t)b * N;
     const int c0 = lane < N ? counts[lane] : 0, c1 = lane + 64 < N ? counts[lane + 64] : 0;
     const int32_t root = i == 0 ? a.root_token[b] : -1;
@@ -262,7 +263,7 @@ __global__ __launch_bounds__(64) void topk_row_kernel(BuildArgs a) {
         }
         return;
     }
-    // more than 64 parts (rows beyond 131072 logits): nc rounds of "largest remaining candidate" over the lists in
+    // more than 64 parts (rows beyond 1048576 logits): nc rounds of "largest remaining candidate" over the lists in
     // memory; a lane owns candidates lane, lane+64, ...
     const int ncand = parts * kK;
     MaxIdx prev = {INFINITY, -1};                         // the winner of the previous round
@@ -288,18 +289,8 @@ __global__ __launch_bounds__(64) void topk_row_kernel(BuildArgs a) {
 int build_tree_max_children() { return kK; }
 int build_tree_chunk_elems() { return kChunk; }
 
-// Segments of up to 8 chunks (a segment's first chunk fills the lists, later ones seldom change them), shorter where that would leave
-// fewer than about 2048 workgroups counting all rows, of which about half have children: four fit on a CU, and the last turn of
-// the chip should not be a long one.  With 1024 (us a call) and with 2048: 16 rows x 30 nodes, V 50000 27.6 and 21.3; 8 x 128, 32000
-// 34.6 and 27.1; 4 x 100, 128256 37.2 and 30.6; 2 x 128, 128256 32.9 and 28.1; 8 x 100, 60001 fp32 39.5 and 36.6; 16 x 128, 128256 (8
-// chunks in both) 83.6; with 4096: 16 x 60, 128256 51.5 (45.2), 8 x 100 fp32 45.2.  Equal runs of chunks across the rows' ends, as the acceptance scan has
-// them, measured 87 on the largest: the scan is bound by its selection and exponentials, not by its last turn.
 void build_tree_plan(BuildArgs& a) {
-    long long seg = (long long)a.B * a.N * a.chunks / 2048;
-    if (seg > 8) seg = 8;
-    if (seg > a.chunks) seg = a.chunks;
-    if (seg < 1) seg = 1;
-    a.seg = (int)seg;
+    a.seg = build_segment((long long)a.B * a.N, a.chunks);
     a.nseg = (a.chunks + a.seg - 1) / a.seg;
 }
 

@@ -117,12 +117,13 @@ def test_rejects_bad_arguments():
 
 
 @pytest.mark.parametrize("size", [(2, 5, 1, 0), (3, 9, 7, 3), (2, 17, 8191, 1), (3, 65, 8192, 5), (1, 128, 8193, 0),
-                                  (2, 33, 16377, 7), (18, 60, 16385, 2), (2, 64, 128256, 1)], ids=str)
+                                  (2, 33, 16377, 7), (18, 60, 16385, 2), (2, 64, 128256, 1),
+                                  (1, 20, 131072, 0), (1, 20, 131073, 3), (1, 6, 1048576, 0), (1, 6, 1048577, 1)], ids=str)
 @pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
 def test_rows_at_any_alignment(size, dtype):
     """(B, N, V, elements that the logits start behind a 16-byte boundary): rows that begin anywhere in a 16-byte vector,
-    vocabularies around a chunk, the first and last token of a row among the children, ties, nodes in both words of
-    a lane's counts."""
+    vocabularies around a chunk and around as many lists as the row kernel holds, the first and last token of a row among the
+    children, ties, nodes in both words of a lane's counts."""
     Bn, N, V, off = size
     rng = np.random.default_rng([Bn, N, V])
     par = np.stack([synth.random_tree_parent(N, min(N, 6), (8,) * 6, rng) for _ in range(Bn)])
