@@ -29,20 +29,18 @@
 // [w*ipw, (w+1)*ipw) of those; in a block lane l owns the 8 tokens 8l..8l+7 (one 16-byte load of 16-bit logits,
 // two of fp32).
 #include "common.h"
+#include "resample_plan.h"
 
 namespace s4c {
 
 namespace {
 
-constexpr int kThreads = 512;
-constexpr int kWaves = kThreads / 64;
-constexpr int kBlock = 512;            // tokens per (wave, iteration)
-constexpr int kMaxIters = 8;           // blocks per wave (registers: see decide)
-constexpr int kMaxSlice = kMaxIters * kWaves * kBlock;     // tokens of a workgroup: 32768
-constexpr int kMaxRow = kMaxSlice / 2;                     // longest row that one workgroup decides alone (resample_by_rows)
+constexpr int kWaves = kResampleWaves;
+constexpr int kThreads = 64 * kWaves;
+constexpr int kBlock = kResampleBlock;
+constexpr int kMaxRow = kResampleMaxRow;
 constexpr int kMaxVocab = 1 << 21;
-constexpr int kTeam = 16;              // workgroups per sequence (more only where a slice would outgrow the registers)
-constexpr int kMaxTeam = kMaxVocab / kMaxSlice;
+constexpr int kMaxTeam = kMaxVocab / kResampleMaxSlice;
 constexpr int kSpinLimit = 1 << 20;    // default number of polls (each followed by a short sleep) before giving up
 
 // lane's value of x from another lane of the row of 16 or from the row below, through the data-parallel-primitive path of the
@@ -124,9 +122,6 @@ __device__ __forceinline__ void load_draft8(const Row& r, int base, float (&qv)[
         for (int k = 0; k < 8; ++k) qv[k] = (base + k < r.V) ? r.q[base + k] : 0.f;
     }
 }
-
-// Workgroups of a team kernel that a CU has room for (by the registers that its launch bounds leave it)
-__host__ __device__ constexpr int per_cu(int blocks) { return blocks <= 2 ? 2 : 1; }
 
 // What the threads of a workgroup share.
 struct Shared {
@@ -512,9 +507,12 @@ __device__ __forceinline__ void write_empty(const ResampleArgs& a, int b, int st
 
 // ---- teams: workgroup g of sequence b's team walks from the root
 template <typename T, int NG>
-__global__ __launch_bounds__(kThreads, per_cu(NG) * kWaves / 4) void accept_resample_kernel(ResampleArgs a) {
+__global__ __launch_bounds__(kThreads, resample_per_cu(NG) * kWaves / 4) void accept_resample_kernel(ResampleArgs a) {
     __shared__ Shared sh;
-    const int G = a.team, b = a.first + blockIdx.x / G, g = blockIdx.x % G, tid = threadIdx.x;
+    const int G = a.team, tid = threadIdx.x;
+    const ResampleMember me = resample_member(blockIdx.x, G, a.groups);
+    const int b = a.first + me.sequence, g = me.g;
+    if (b >= a.B) return;                                  // (fills up the last round of groups)
     if (load_tree(a, sh, b, true)) {                       // every workgroup of the team sees the same tree
         if (g == 0) write_empty(a, b, S4C_SEQ_BAD_TREE);
         return;
@@ -618,20 +616,19 @@ __global__ __launch_bounds__(kThreads) void resample_rows_kernel(ResampleArgs a)
     }
 }
 
-int iters_of(int blocks) { return (blocks + kWaves - 1) / kWaves; }          // blocks per wave of a workgroup that has this many
-
 template <typename T, int NG>
 hipError_t launch(const ResampleArgs& a, hipStream_t st) {
     if constexpr (NG * kWaves * kBlock <= kMaxRow) if (a.team == 0) {
         hipLaunchKernelGGL((resample_rows_kernel<T, NG>), dim3((unsigned)(a.B * (a.N + 1))), dim3(kThreads), 0, st, a);
         return hipGetLastError();
     }
-    // as many sequences in a launch as have all their workgroups on the chip together (which wait for each other)
-    const int per = a.team == 1 ? a.B : a.resident / a.team < 1 ? 1 : a.resident / a.team;
-    for (int b = 0; b < a.B; b += per) {
+    const ResampleLaunch l = resample_launch(a.B, a.team, NG, a.cus);
+    for (int b = 0; b < a.B; b += l.sequences) {
         ResampleArgs k = a;
         k.first = b;
-        hipLaunchKernelGGL((accept_resample_kernel<T, NG>), dim3((unsigned)((a.B - b < per ? a.B - b : per) * a.team)), dim3(kThreads), 0, st, k);
+        k.groups = l.groups;
+        const int n = a.B - b < l.sequences ? a.B - b : l.sequences;
+        hipLaunchKernelGGL((accept_resample_kernel<T, NG>), dim3((unsigned)resample_grid(n, a.team, l.groups)), dim3(kThreads), 0, st, k);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -639,24 +636,13 @@ hipError_t launch(const ResampleArgs& a, hipStream_t st) {
 }
 template <typename T>
 hipError_t launch_sized(const ResampleArgs& a, hipStream_t st) {
-    const int nblocks = (a.V + kBlock - 1) / kBlock, n = iters_of(a.team ? (nblocks + a.team - 1) / a.team : nblocks);
-    return n <= 1 ? launch<T, 1>(a, st) : n <= 2 ? launch<T, 2>(a, st) : n <= 4 ? launch<T, 4>(a, st) : launch<T, 8>(a, st);
+    const int nblocks = resample_blocks(a.V), n = resample_iters(a.team ? (nblocks + a.team - 1) / a.team : nblocks);
+    return n == 1 ? launch<T, 1>(a, st) : n == 2 ? launch<T, 2>(a, st) : n == 4 ? launch<T, 4>(a, st) : launch<T, 8>(a, st);
 }
 
 }  // namespace
 
 int resample_max_vocab() { return kMaxVocab; }
-
-// Workgroups per sequence: enough blocks per workgroup to keep its waves busy, at most 16, and few enough that all
-// teams are resident together (one workgroup per CU is certain), but no slice larger than a workgroup's registers hold.
-int resample_team(int B, int V, int cus) {
-    const int nblocks = (V + kBlock - 1) / kBlock;
-    int G = (nblocks + kWaves - 1) / kWaves;
-    if (G > kTeam) G = kTeam;
-    while (G > 1 && (long long)B * G > cus) G >>= 1;
-    const int least = (V + kMaxSlice - 1) / kMaxSlice;
-    return G < least ? least : G;
-}
 
 // Whether every node is decided at once, a workgroup each: up to two turns of the chip of rows of 16384 tokens, or as many
 // tokens in shorter rows; half of that where rows lie on odd addresses and are read by the element.  Teams and rows, us a call

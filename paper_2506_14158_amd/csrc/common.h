@@ -138,7 +138,8 @@ struct ResampleArgs {
     uint64_t* slots;           // team > 1: [B][max_pass][4][team] exchange words; team == 0: [B][N] (nonce << 32) | decision
     int32_t B, N, V, max_path, dtype;
     int32_t team;              // workgroups per sequence; 0: one per node
-    int32_t first, resident;   // first sequence of a launch of teams (set by the launcher); workgroups that are resident together
+    int32_t cus;               // of the device
+    int32_t first, groups;     // set by the launcher: first sequence of a launch of teams, resample_launch
     uint32_t nonce;            // tells this call's words from whatever they held before
     int32_t max_pass;          // exchanges a sequence may need
     int32_t spin_limit;        // polls before a workgroup gives up on an exchange
@@ -146,7 +147,6 @@ struct ResampleArgs {
 };
 hipError_t launch_accept_resample(const ResampleArgs& a, hipStream_t st);
 int resample_max_vocab();
-int resample_team(int B, int V, int cus);
 bool resample_by_rows(int B, int N, int V, int cus);
 int resample_max_pass(int N, int max_path);
 int resample_default_spin_limit();

@@ -1,5 +1,6 @@
 // C ABI of libs4c: argument checks, launch planning, kernel launches.  See include/s4c.h.
 #include "common.h"
+#include "resample_plan.h"
 
 #include <math.h>
 #include <stdlib.h>
@@ -391,8 +392,8 @@ s4c_status s4c_accept_resample(int32_t B, int32_t N, int32_t V, int32_t logits_d
     a.bonus_token = bonus_token; a.status = status; a.slots = (uint64_t*)workspace;
     a.B = B; a.N = N; a.V = V; a.max_path = max_path; a.dtype = logits_dtype; a.inv_temperature = 1.0 / (double)temperature;
     a.team = by_rows ? 0 : resample_team(B, V, device_cus());
-    a.first = 0;
-    a.resident = device_cus();
+    a.cus = device_cus();
+    a.first = a.groups = 0;
     a.nonce = next_nonce();
     a.max_pass = resample_max_pass(N, max_path);
     // S4C_RESAMPLE_SPIN_LIMIT (environment, >= 0): polls before a workgroup gives up on an exchange.  A

@@ -202,12 +202,8 @@ def test_rejects_bad_arguments():
                               i(1, 2), i(1))
 
 
-@pytest.mark.parametrize("Bn,N,V,dtype", [(2, 20, 1, "bf16"), (1, 2, 4095, "f32"), (3, 33, 4097, "bf16"), (5, 64, 8193, "f16"),
-                                          (2, 40, 16384, "f32"), (2, 40, 16385, "bf16"), (2, 12, 32768, "f16"), (2, 12, 32769, "bf16"),
-                                          (1, 9, 65544, "f32"), (2, 5, 524289, "bf16")])
-def test_one_workgroup_per_node_teams_and_replays(Bn, N, V, dtype):
-    """Block, register and route edges.  The same call decides every node at once where rows are few and short, walks with
-    teams where its workspace is too small for that, and replays from a captured graph; all of them as the oracle."""
+def random_call(Bn, N, V, dtype):
+    """Inputs of a call on the device, their type, the tree's levels, and what the oracle says."""
     levels = min(N, 5)
     par = np.stack([synth.random_tree_parent(N, levels, (8, 4, 3, 2, 2), np.random.default_rng([7, b])) for b in range(Bn)]).astype(np.int32)
     g = torch.Generator().manual_seed(V + N)
@@ -225,7 +221,16 @@ def test_one_workgroup_per_node_teams_and_replays(Bn, N, V, dtype):
     bits = lambda t: t.numpy() if dtype == "f32" else t.view(torch.int16).numpy().view(np.uint16) if dtype == "bf16" else t.numpy()
     r = O.accept_resample(bits(logits), pd.numpy(), par, tokens.numpy(), u.numpy(), ur.numpy(), levels)
     assert min(float(r["margin_accept"].min()), float(r["margin_sample"].min())) > RESAMPLE_MARGIN_MIN
-    d = [t.cuda() for t in (logits, pd, torch.from_numpy(par), tokens, u, ur)]
+    return [t.cuda() for t in (logits, pd, torch.from_numpy(par), tokens, u, ur)], dt, levels, r
+
+
+@pytest.mark.parametrize("Bn,N,V,dtype", [(2, 20, 1, "bf16"), (1, 2, 4095, "f32"), (3, 33, 4097, "bf16"), (5, 64, 8193, "f16"),
+                                          (2, 40, 16384, "f32"), (2, 40, 16385, "bf16"), (2, 12, 32768, "f16"), (2, 12, 32769, "bf16"),
+                                          (1, 9, 65544, "f32"), (2, 5, 524289, "bf16")])
+def test_one_workgroup_per_node_teams_and_replays(Bn, N, V, dtype):
+    """Block, register and route edges.  The same call decides every node at once where rows are few and short, walks with
+    teams where its workspace is too small for that, and replays from a captured graph; all of them as the oracle."""
+    d, dt, levels, r = random_call(Bn, N, V, dtype)
     tv = TreeVerifier(Bn, N, 1, 1, 64, 1, V, dt, levels, 0)
     outs = (tv.path, tv.accept_len, tv.accepted_tokens, tv.bonus_token, tv.accept_status)
 
@@ -250,3 +255,36 @@ def test_one_workgroup_per_node_teams_and_replays(Bn, N, V, dtype):
         gr.replay()
         torch.cuda.synchronize()
         same(tv, r)
+
+
+def test_more_sequences_than_a_launch_of_teams_takes():
+    """130 teams of 2: 128 in a launch, and the last two in one that is filled up with workgroups without a sequence."""
+    d, dt, levels, r = random_call(130, 2, 33000, "bf16")
+    tv = TreeVerifier(130, 2, 1, 1, 64, 1, 33000, dt, levels, 0)
+    for _ in range(2):
+        for t in (tv.path, tv.accept_len, tv.accepted_tokens, tv.bonus_token, tv.accept_status):
+            t.fill_(-7)
+        tv.accept_resample(*d, 1.0)
+        torch.cuda.synchronize()
+        same(tv, r)
+
+
+def test_calls_on_two_streams():
+    """Each call's teams take the chip's CUs one by one (40 x 4 slices of 32768) or two to a CU (16 x 16 of 8192), with a workspace
+    of its own; together they complete."""
+    calls = []
+    for Bn, N, V in ((40, 4, 128256), (16, 10, 128256), (33, 5, 128256)):
+        d, dt, levels, r = random_call(Bn, N, V, "bf16")
+        calls.append((TreeVerifier(Bn, N, 1, 1, 64, 1, V, dt, levels, 0), d, r))
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    for i, k in ((0, 1), (0, 2), (1, 2)):
+        for c, st in ((calls[i], streams[0]), (calls[k], streams[1])):
+            with torch.cuda.stream(st):
+                for _ in range(5):
+                    c[0].accept_resample(*c[1], 1.0)
+        torch.cuda.synchronize()
+        for tv, _, r in (calls[i], calls[k]):
+            same(tv, r)
+            for t in (tv.path, tv.accept_len, tv.accepted_tokens, tv.bonus_token, tv.accept_status):
+                t.fill_(-7)
