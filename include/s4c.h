@@ -189,10 +189,14 @@ s4c_status s4c_accept_path_static(int32_t B, int32_t N, int32_t V, int32_t logit
  *   always a token id here (-1 only for a flagged sequence).
  *   workspace  >= s4c_accept_resample_workspace_size(B, N, V, max_path) bytes, 256-byte aligned,
  *              contents need not be initialised; may be NULL if that size is 0.  It carries the
- *              partial sums that the workgroups sharing one sequence exchange, so two calls that
- *              may overlap in time must not share it.
- * Arithmetic is fp64 (row maxima exact).  V <= 2^21.  The kernel polls device memory with a
- * bounded number of tries (S4C_SEQ_TIMEOUT); a launch has at most one workgroup per compute unit wait for others.
+ *              partial sums that the workgroups sharing one sequence exchange, or the decision of every
+ *              node where each has a workgroup of its own, so two calls that may overlap in time must not
+ *              share it.  Where one workgroup per sequence would do (V <= 4096; V <= 32768 and more than half as
+ *              many sequences as compute units) a workspace that is NULL, too small or misaligned is taken too, and the call
+ *              may be slower.
+ * Arithmetic is fp64 (row maxima exact).  V <= 2^21.  Workgroups that wait for others poll device memory with a
+ * bounded number of tries (S4C_SEQ_TIMEOUT).  A call by itself always completes, and so do two that overlap in time, whatever
+ * their sizes; of three, large ones may hold each other up until the tries run out.
  * One workgroup per sequence writes all of that sequence's outputs, so a flagged sequence never
  * carries a partial result.  The environment variable S4C_RESAMPLE_SPIN_LIMIT (an integer >= 0,
  * read at every call) replaces the number of tries; 0 makes every exchange between several

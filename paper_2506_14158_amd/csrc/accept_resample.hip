@@ -552,8 +552,8 @@ __global__ __launch_bounds__(kThreads, resample_per_cu(NG) * kWaves / 4) void ac
 // ---- rows: workgroup b N + i decides node i of sequence b and publishes (call nonce, decision); workgroup B N + b waits
 // for its sequence's decisions, overwrites them (so that a captured graph can replay the call) and follows them.  A decision that
 // it gave up on is overwritten by the node's own workgroup, which finds the word (~nonce, 1) left for it there (an exchange in place
-// of a store: 1 x 20, V 1000 8.75 and 8.70 us, 3 x 64, 16000 fp32 17.7 and 17.9, 4 x 40, 8000 11.6 and 11.7).  Workgroups
-// start in grid order, so when it starts every other one of its sequence has a compute unit or is done.
+// of a store: 1 x 20, V 1000 8.75 and 8.70 us, 3 x 64, 16000 fp32 17.7 and 17.9, 4 x 40, 8000 11.6 and 11.7).  Every
+// XCD starts its share of the workgroups in grid order, the waiting ones behind the nodes', which wait for nobody.
 constexpr uint32_t kAccepted = 0x80000000u;                // decision: kAccepted | child, or the correction token
 template <typename T, int NG>
 __global__ __launch_bounds__(kThreads) void resample_rows_kernel(ResampleArgs a) {
@@ -643,18 +643,6 @@ hipError_t launch_sized(const ResampleArgs& a, hipStream_t st) {
 }  // namespace
 
 int resample_max_vocab() { return kMaxVocab; }
-
-// Whether every node is decided at once, a workgroup each: up to two turns of the chip of rows of 16384 tokens, or as many
-// tokens in shorter rows; half of that where rows lie on odd addresses and are read by the element.  Teams and rows, us a call
-// (B x N, V): 1 x 20, 1000: 17.5 and 8.4; 3 x 64, 16000 fp32: 36.1 and 18.5; 4 x 128, 16384: 34.6 and 29.9; 8 x 128, 16384: 36.9
-// and 50.0; 16 x 40, 8000: 38.2 and 19.9; 16 x 128, 8000: 47.5 and 41.9; 16 x 128, 4000: 35.8 and 24.7; 8 x 64, 16001: 41.6 and
-// 45.2.  Rows of 32000 would fit the registers too, but the slowest node (many children, all rejected) is alone on its CU
-// then: 4 x 64: 37.6 and 42.3.  (Rows were reloaded and their weights recomputed for every rejected child before, by
-// teams: 4 x 64, 32000 58.1, 16 x 128, 128256 106.6, 3 x 64, 16000 fp32 52.9.)
-bool resample_by_rows(int B, int N, int V, int cus) {
-    const long long tokens = (long long)B * N * (V < 4096 ? 4096 : V);
-    return V <= kMaxRow && tokens <= (V % 8 == 0 ? 2ll : 1ll) * cus * kMaxRow;
-}
 
 // exchanges per sequence: one per visited node, one per rejected child, one for the sampling, one
 // to hand the token to workgroup 0

@@ -147,7 +147,6 @@ struct ResampleArgs {
 };
 hipError_t launch_accept_resample(const ResampleArgs& a, hipStream_t st);
 int resample_max_vocab();
-bool resample_by_rows(int B, int N, int V, int cus);
 int resample_max_pass(int N, int max_path);
 int resample_default_spin_limit();
 size_t resample_slot_words(int B, int N, int V, int max_path, int cus);      // of the teams

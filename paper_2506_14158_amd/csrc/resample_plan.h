@@ -27,7 +27,8 @@ S4C_PLAN int resample_iters(int blocks) {
 S4C_PLAN constexpr int resample_per_cu(int iters) { return iters <= 2 ? 2 : 1; }
 
 // Workgroups per sequence: enough blocks per workgroup to keep its waves busy, at most 16, and few enough that all
-// teams are resident together (one workgroup per CU is certain), but no slice larger than a workgroup's registers hold.
+// teams are resident together (one workgroup per CU is certain), but no slice larger than a workgroup's registers hold
+// (which makes up to 64 of them for rows beyond 524288).
 S4C_PLAN int resample_team(int B, int V, int cus) {
     int G = (resample_blocks(V) + kResampleWaves - 1) / kResampleWaves;
     if (G > kResampleTeam) G = kResampleTeam;
@@ -63,6 +64,21 @@ struct ResampleMember { int sequence, g; };
 S4C_PLAN ResampleMember resample_member(int i, int G, int groups) {
     const int slot = i / groups;
     return {slot / G * groups + i % groups, slot % G};
+}
+
+// Whether every node is decided at once, a workgroup each: up to two turns of the chip of rows of 16384 tokens, or as many
+// tokens in shorter rows; half of that where rows lie on odd addresses and are read by the element.  Teams and rows, us a call
+// (B x N, V): 1 x 20, 1000: 13.5 and 7.8; 3 x 64, 16000 fp32: 29.3 and 15.7; 4 x 128, 16384: 40.4 and 24.8; 8 x 128, 16384: 38.7
+// and 42.0; 16 x 40, 8000: 36.5 and 19.6; 16 x 128, 8000: 35.9 and 38.8; 16 x 128, 4000: 26.2 and 22.6; 8 x 64, 16001: 39.5 and
+// 42.0.  Rows of 32000 would fit the registers too, but the slowest node (many children, all rejected) is alone on its CU
+// then: 4 x 64: 33.2 and 42.3.
+// The sequences' own workgroups wait for the nodes': no more of them than half of the places on the chip, so that whatever a
+// second call has waiting, there is room for the nodes' (which wait for nobody).  That also keeps most calls of many sequences with few nodes
+// each from this route, where a workgroup a sequence is as good: 512 x 4, 4000: 18.3 and 22.9; 1000 x 2, 1000: 23.6 and 19.8.
+S4C_PLAN bool resample_by_rows(int B, int N, int V, int cus) {
+    const long long tokens = (long long)B * N * (V < 4096 ? 4096 : V);
+    return V <= kResampleMaxRow && tokens <= (V % 8 == 0 ? 2ll : 1ll) * cus * kResampleMaxRow &&
+           2 * B <= cus * resample_per_cu(resample_iters(resample_blocks(V)));
 }
 
 }  // namespace s4c
