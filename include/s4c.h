@@ -292,8 +292,8 @@ s4c_status s4c_commit_path_paged(const s4c_attn_shape* shape, int32_t layers, co
  *              not be initialised.  The reduction dimension is split to fill the chip, and the workspace holds
  *              the slices' fp32 partial sums (added in a fixed order: results are deterministic for a
  *              given workspace size).  S4C_ERR_WORKSPACE if it is missing, too small or misaligned with T <= 512; for T > 512
- *              it may be smaller or NULL, and fewer slices are used (it may be for T > 128 as well, down to the partial
- *              sums of ceil(T / 128) equal passes over the tokens). */
+ *              it may be smaller or NULL, and fewer slices are used (it may be smaller for 128 < T <= 512 as well, down to
+ *              the size for ceil(T / ceil(T / 128)) tokens). */
 size_t s4c_draft_linear_workspace_size(int32_t T, int32_t H, int32_t Hout);
 s4c_status s4c_draft_linear(int32_t T, int32_t H, int32_t Hout, int32_t dtype, const void* e, const void* f,
                             const void* W, const void* bias, void* out, void* workspace, size_t workspace_bytes,

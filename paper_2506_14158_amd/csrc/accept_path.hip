@@ -574,16 +574,15 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd<T>) void step_kernel(AttnAr
 
 int accept_chunk_elems() { return kChunk; }
 
-// Segments by which the acceptance workspace is sized (scan_plan): up to 8 chunks of a row, fewer when that would leave less than about 1024 workgroups
-// to spread over the chip.  `head`: elements by which rows may begin inside a vector.
-void accept_plan(int B, int N, int V, int head, int* chunks, int* seg, int* nseg) {
-    const long long ch = ((long long)V + head + kChunk - 1) / kChunk;
+// Segments by which the acceptance workspace is sized (scan_plan): up to 8 chunks of a row, fewer when that would leave less
+// than about 1024 workgroups to spread over the chip.
+void accept_plan(int B, int N, int V, int* seg, int* nseg) {
+    const long long ch = ((long long)V + kChunk - 1) / kChunk;
     const long long units = (long long)B * N * ch;
     long long sg = units / 1024;
     if (sg > 8) sg = 8;
     if (sg > ch) sg = ch;
     if (sg < 1) sg = 1;
-    *chunks = (int)ch;
     *seg = (int)sg;
     *nseg = (int)((ch + sg - 1) / sg);
 }
@@ -592,8 +591,8 @@ void accept_plan(int B, int N, int V, int head, int* chunks, int* seg, int* nseg
 // has for each segment of accept_plan.  A row's chunks lie in at most ceil(chunks / seg) + 1 runs; where seg is
 // a whole row, runs are made of whole rows.
 AcceptPlan scan_plan(int B, int N, int V, int elem_bytes, int cus) {
-    int plain, seg, nseg;
-    accept_plan(B, N, V, 0, &plain, &seg, &nseg);
+    int seg, nseg;
+    accept_plan(B, N, V, &seg, &nseg);
     AcceptPlan p;
     p.chunks = (int)(((long long)V + 7 + kChunk - 1) / kChunk);          // a row may begin up to 7 elements into its first vector
     auto slots = [&](int sg) { return sg >= p.chunks ? 1 : sg == 1 ? p.chunks : (p.chunks + sg - 1) / sg + 1; };

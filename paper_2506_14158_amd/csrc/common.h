@@ -121,7 +121,7 @@ hipError_t launch_step(const AttnArgs& attn, bool merge, const AcceptArgs& accep
                        unsigned long long* messages, long long copy_ticks, hipStream_t st);
 size_t step_message_bytes(int B, int Hkv);
 int accept_chunk_elems();
-void accept_plan(int B, int N, int V, int head, int* chunks, int* seg, int* nseg);
+void accept_plan(int B, int N, int V, int* seg, int* nseg);
 
 struct ResampleArgs {
     const void* logits;

@@ -238,8 +238,8 @@ s4c_status s4c_tree_attn_paged(const s4c_attn_shape* shape, const void* q, const
 
 size_t s4c_accept_path_workspace_size(int32_t B, int32_t N, int32_t V) {
     if (B <= 0 || N <= 0 || V <= 0) return 0;
-    int chunks, seg, nseg;
-    accept_plan(B, N, V, 0, &chunks, &seg, &nseg);
+    int seg, nseg;
+    accept_plan(B, N, V, &seg, &nseg);
     return (((size_t)B * N * nseg * 3 * sizeof(unsigned long long) + 255) / 256) * 256;   // room for two records per (row, run): scan_plan
 }
 
@@ -570,8 +570,9 @@ s4c_status s4c_commit_path_paged(const s4c_attn_shape* shape, int32_t layers, co
 }  // extern "C"
 
 namespace {
-// Up to kNeedsWorkspace tokens a call must bring a workspace, of at least this size (what the weight-streaming kernel's partial sums
-// take, for equal passes of at most as many tokens as it has room for).
+// Up to kNeedsWorkspace tokens a call must bring a workspace of at least this size: what the weight-streaming kernel's partial
+// sums take.  More tokens than that kernel has room for go to the tiled one, which makes do with any workspace or none; for them the size, that of
+// equal passes over the tokens, is only the line between calls that are taken and calls that are refused, which callers rely on.
 constexpr int kNeedsWorkspace = 512;
 size_t least_linear_bytes(int32_t T, int32_t H, int32_t Hout) {
     if (T > kNeedsWorkspace) return 0;
