@@ -55,9 +55,9 @@ def test_few_tokens_element_by_element(T, H, Hout, bias):
 
 
 @pytest.mark.parametrize("T,H,Hout", [(256, 5120, 5120), (200, 4096, 4096), (512, 1024, 512), (513, 1024, 512), (129, 96, 256)])
-def test_a_few_hundred_tokens_run_in_passes(T, H, Hout):
-    """129 .. 512 tokens (config 3's four trees are 256): the weight-streaming kernel in equal passes of at most
-    128 tokens, the last one possibly shorter; 513 tokens is the first size of the tiled kernel."""
+def test_a_few_hundred_tokens(T, H, Hout):
+    """From 129 tokens on (config 3's four trees are 256) the tiled kernel, its reduction divided over the idle CUs; 513 tokens is the
+    first size that needs no workspace."""
     e, f, W, b = make(T, H, Hout, 2000 + T + H, True)
     close(run(e, f, W, b), O.draft_linear(e, f, W, b))
 
@@ -122,9 +122,14 @@ def test_tiled_kernel_divided_reductions(T, H, Hout):
     close(run(e, f, W, b), want)
     te, tf, tW, tb = (np_to_torch(x) for x in (e, f, W, b))
     one = T * Hout * 4                                       # a slice
-    sizes = [0, one, 2 * one] if T > 512 else []
+    # (up to 512 tokens, the least that a call must bring: as much as passes of at most 128 tokens would take)
+    passes = -(-T // 128)
+    sizes = [0, one, 2 * one] if T > 512 else [B.s4c_draft_linear_workspace_size(-(-T // passes), H, Hout)] if T > 128 else []
     for n in sizes:
         out = torch.full((T, Hout), float("nan"), dtype=torch.bfloat16, device="cuda")
         B.s4c_draft_linear(te, tf, tW, out, tb, torch.full((n // 4,), float("nan"), device="cuda") if n else None)
         torch.cuda.synchronize()
         close(out.float().cpu().numpy().astype(np.float64), want)
+    if 128 < T <= 512:
+        with pytest.raises(B.S4CError):
+            B.s4c_draft_linear(te, tf, tW, out, tb, torch.empty(sizes[0] // 4 - 1, device="cuda"))

@@ -1,5 +1,5 @@
 """HIP-graph replay of the entry points beyond the three-call step: s4c_build_tree, s4c_draft_linear,
-s4c_accept_resample (whose slot array is cleared by a fill kernel, not a memset node) and
+s4c_accept_resample (whose exchanged words are told from a previous replay's by their tags) and
 s4c_commit_path with feature rows.  The sequence is captured once and replayed several times with
 eager work and synchronisations in between; every replay must reproduce the eager results bit for bit."""
 import numpy as np
@@ -38,8 +38,8 @@ def test_drafter_side_calls_replay_from_a_hip_graph():
     e, f = (torch.randn(T, H, device="cuda", generator=g).bfloat16() for _ in range(2))
     W = (torch.randn(H, 2 * H, device="cuda", generator=g) / (2 * H) ** 0.5).bfloat16()
     h_out = torch.empty(T, H, dtype=torch.bfloat16, device="cuda")
-    dl_ws = B.alloc_workspace(B.s4c_draft_linear_workspace_size(T, H, H))      # None above 128 tokens
-    # the same projection on one sequence's tokens (<= 128: the weight-streaming kernel and its workspace)
+    dl_ws = B.alloc_workspace(B.s4c_draft_linear_workspace_size(T, H, H))
+    # the same projection on one sequence's tokens (the weight-streaming kernel and its partial sums)
     h_small = torch.empty(N, H, dtype=torch.bfloat16, device="cuda")
     dl_ws_small = B.alloc_workspace(B.s4c_draft_linear_workspace_size(N, H, H))
     # commit: 3 layers + feature rows

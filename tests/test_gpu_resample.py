@@ -226,10 +226,10 @@ def random_call(Bn, N, V, dtype):
 
 @pytest.mark.parametrize("Bn,N,V,dtype", [(2, 20, 1, "bf16"), (1, 2, 4095, "f32"), (3, 33, 4097, "bf16"), (5, 64, 8193, "f16"),
                                           (2, 40, 16384, "f32"), (2, 40, 16385, "bf16"), (2, 12, 32768, "f16"), (2, 12, 32769, "bf16"),
-                                          (1, 9, 65544, "f32"), (2, 5, 524289, "bf16")])
+                                          (1, 9, 65544, "f32"), (2, 5, 524289, "bf16"), (129, 3, 8000, "bf16")])
 def test_one_workgroup_per_node_teams_and_replays(Bn, N, V, dtype):
-    """Block, register and route edges.  The same call decides every node at once where rows are few and short, walks with
-    teams where its workspace is too small for that, and replays from a captured graph; all of them as the oracle."""
+    """Block, register and route edges.  The same call decides every node at once where rows are few and short, or
+    walks with teams; it does without a workspace where a workgroup a sequence is enough, and replays from a captured graph; all of them as the oracle."""
     d, dt, levels, r = random_call(Bn, N, V, dtype)
     tv = TreeVerifier(Bn, N, 1, 1, 64, 1, V, dt, levels, 0)
     outs = (tv.path, tv.accept_len, tv.accepted_tokens, tv.bonus_token, tv.accept_status)
@@ -244,8 +244,9 @@ def test_one_workgroup_per_node_teams_and_replays(Bn, N, V, dtype):
     for t in (0xFF, 0x00):                               # whatever the workspace holds
         tv.resample_ws.fill_(t)
         call(tv.resample_ws)
-    if V <= 4096:
+    if V <= 4096 or Bn > 128:
         call(None)                                       # one workgroup per sequence needs no workspace
+        call(tv.resample_ws[:8])                         # (too small for a word per node)
     gr = torch.cuda.CUDAGraph()
     with torch.cuda.graph(gr):
         tv.accept_resample(*d, 1.0)
