@@ -71,7 +71,7 @@ S4C_PLAN ResampleMember resample_member(int i, int G, int groups) {
 // (B x N, V): 1 x 20, 1000: 13.5 and 7.8; 3 x 64, 16000 fp32: 29.3 and 15.7; 4 x 128, 16384: 40.4 and 24.8; 8 x 128, 16384: 38.7
 // and 42.0; 16 x 40, 8000: 36.5 and 19.6; 16 x 128, 8000: 35.9 and 38.8; 16 x 128, 4000: 26.2 and 22.6; 8 x 64, 16001: 39.5 and
 // 42.0.  Rows of 32000 would fit the registers too, but the slowest node (many children, all rejected) is alone on its CU
-// then: 4 x 64: 33.2 and 42.3.
+// then: 4 x 64: 33.2 and, as the kernels were before, 42.3.
 // The sequences' own workgroups wait for the nodes': no more of them than half of the places on the chip, so that whatever a
 // second call has waiting, there is room for the nodes' (which wait for nobody).  That also keeps most calls of many sequences with few nodes
 // each from this route, where a workgroup a sequence is as good: 512 x 4, 4000: 18.3 and 22.9; 1000 x 2, 1000: 23.6 and 19.8.

@@ -226,7 +226,8 @@ def random_call(Bn, N, V, dtype):
 
 @pytest.mark.parametrize("Bn,N,V,dtype", [(2, 20, 1, "bf16"), (1, 2, 4095, "f32"), (3, 33, 4097, "bf16"), (5, 64, 8193, "f16"),
                                           (2, 40, 16384, "f32"), (2, 40, 16385, "bf16"), (2, 12, 32768, "f16"), (2, 12, 32769, "bf16"),
-                                          (1, 9, 65544, "f32"), (2, 5, 524289, "bf16"), (129, 3, 8000, "bf16")])
+                                          (1, 9, 65544, "f32"), (2, 5, 524289, "bf16"), (129, 3, 8000, "bf16"),
+                                          (40, 4, 128256, "bf16")])
 def test_one_workgroup_per_node_teams_and_replays(Bn, N, V, dtype):
     """Block, register and route edges.  The same call decides every node at once where rows are few and short, or
     walks with teams; it does without a workspace where a workgroup a sequence is enough, and replays from a captured graph; all of them as the oracle."""
