@@ -31,8 +31,8 @@
 namespace s4c {
 
 // What one workgroup of the kernel for a shape takes: query rows, keys per tile, and how many fit on a CU; `wide`: 16-bit
-// data of head size 128.
-struct AttnTile { int rows, keys, per_cu; bool wide; };
+// data of head size 128; part_keys: waves that share the columns of a row when it writes.
+struct AttnTile { int rows, keys, per_cu; bool wide; int part_keys = 1; };
 
 struct AttnDivision {
     int teams, split, mtiles;

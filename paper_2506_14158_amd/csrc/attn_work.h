@@ -111,12 +111,5 @@ __device__ __forceinline__ int node_of_row(int r, int G, float inv_G) {
     return rem < 0 ? q - 1 : rem >= G ? q + 1 : q;
 }
 
-// the empty parts of a team without tiles, for the rows of row tile mt
-__device__ __forceinline__ void note_empty(const AttnArgs& a, int team, int mt, int rows) {
-    if (leaves_empty(a, team))
-        for (int r = mt * rows + (int)threadIdx.x; r < min(a.M, (mt + 1) * rows); r += blockDim.x)
-            *(float2*)(a.ws_ml + (part_row(a, team, empty_slot(a, team)) + r) * 2) = make_float2(-INFINITY, 0.f);
-}
-
 }  // namespace work
 }  // namespace s4c

@@ -70,6 +70,10 @@ struct AttnArgs {
     int32_t mtiles;     // query-row tiles per (sequence, KV head) = workgroups per team
     int32_t tile_rows;  // query rows per workgroup
     int32_t tile_keys, tile_shift;   // keys per tile of the kernel that will run, and its log2
+    int32_t part_keys;  // waves that share the columns of a row in a part (attn_parts.h)
+    int32_t attn_wgs;   // set by the launcher: workgroups of the launch that attend
+    uint64_t tag;       // of this call's parts; 0: the next launch merges them
+    long long wait_ticks;     // how long a merging workgroup waits for its parts (100 MHz wall clock)
     float scale_log2; // softmax scale * log2(e)
     // paged cache (block_table != null): k_cache / v_cache are pools [num_pages][Hkv][page][D],
     // row j of sequence b is row j & (page-1) of page block_table[b][j >> page_shift]
@@ -78,8 +82,18 @@ struct AttnArgs {
 };
 
 // launchers (defined in the kernel translation units); return hipGetLastError()
-hipError_t launch_tree_attn_large(const AttnArgs& a, int dtype, hipStream_t st);    // 16-bit data, more than 64 query rows
-hipError_t launch_tree_attn_small(const AttnArgs& a, int dtype, hipStream_t st);    // at most 64 query rows, or fp32 data
+// (`step`: with the rest of a verification step behind it, attn_step.h; the kind is accept.mode, known to the compiler)
+enum StepKind { kNoStep = 0, kGreedyStep = 1, kStochasticStep = 2 };
+template <StepKind KIND>
+struct StepTail;
+hipError_t launch_tree_attn_large(const AttnArgs& a, int dtype, const StepTail<kGreedyStep>* step, hipStream_t st);    // 16-bit data, more than 64 query rows
+hipError_t launch_tree_attn_small(const AttnArgs& a, int dtype, const StepTail<kGreedyStep>* step, hipStream_t st);    // at most 64 query rows, or fp32 data
+// (of one type each)
+hipError_t launch_large_bf16(const AttnArgs& a, const StepTail<kGreedyStep>* step, hipStream_t st);
+hipError_t launch_large_f16(const AttnArgs& a, const StepTail<kGreedyStep>* step, hipStream_t st);
+hipError_t launch_smallm_bf16(const AttnArgs& a, const StepTail<kGreedyStep>* step, hipStream_t st);
+hipError_t launch_smallm_f16(const AttnArgs& a, const StepTail<kGreedyStep>* step, hipStream_t st);
+hipError_t launch_smallm_f32(const AttnArgs& a, const StepTail<kGreedyStep>* step, hipStream_t st);
 hipError_t launch_attn_merge(const AttnArgs& a, int dtype, hipStream_t st);
 AttnTile attn_tile_large(const s4c_attn_shape& s);
 AttnTile attn_tile_small(const s4c_attn_shape& s, int32_t max_cache_len, int cus);
@@ -115,9 +129,8 @@ struct AcceptArgs {
 hipError_t launch_accept(const AcceptArgs& a, hipStream_t st);
 struct AttnArgs;
 struct CompactArgs;
-// The rest of a verification step after the attention kernel in one launch: the merge of divided attention (if
-// `merge`), acceptance, and the accepted path's rows appended to the cache.  All three of one element type.
-hipError_t launch_step(const AttnArgs& attn, bool merge, const AcceptArgs& accept, const CompactArgs& compact,
+// The rest of a verification step after the attention kernel in one launch: the merge of divided attention, acceptance, and the accepted path's rows appended to the cache.  All three of one element type.
+hipError_t launch_step(const AttnArgs& attn, const AcceptArgs& accept, const CompactArgs& compact,
                        unsigned long long* messages, long long copy_ticks, hipStream_t st);
 size_t step_message_bytes(int B, int Hkv);
 int accept_chunk_elems();

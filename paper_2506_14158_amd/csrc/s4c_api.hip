@@ -1,4 +1,5 @@
 // C ABI of libs4c: argument checks, launch planning, kernel launches.  See include/s4c.h.
+#include "attn_step.h"
 #include "common.h"
 #include "resample_plan.h"
 
@@ -62,6 +63,25 @@ uint32_t next_nonce() {
         x ^= x >> 16; x *= 0x7FEB352Du; x ^= x >> 15; x *= 0x846CA68Bu; x ^= x >> 16;      // a bijection of 32-bit words
         if (x != 0u && x != 0xFFFFFFFFu) return x;
     }
+}
+
+// A different 64-bit number for every attention call of the process, under which its parts are published.  They lie where other
+// calls keep numbers of any kind, so all 64 bits are mixed: what is there is not taken for this call's.
+uint64_t next_tag() {
+    static std::atomic<uint64_t> counter{0};
+    uint64_t x = (counter.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9E3779B97F4A7C15ull;
+    x ^= x >> 30; x *= 0xBF58476D1CE4E5B9ull; x ^= x >> 27; x *= 0x94D049BB133111EBull; x ^= x >> 31;
+    return x;
+}
+
+// A waiting time in microseconds, up to a minute, replaced by an environment variable (read at every call).
+long long wait_us(const char* name, long long otherwise) {
+    if (const char* env = getenv(name)) {
+        char* end = nullptr;
+        const long long v = strtoll(env, &end, 10);
+        if (end != env && v >= 0 && v <= 60000000ll) return v;
+    }
+    return otherwise;
 }
 
 bool dtype_ok(int32_t d) { return d == S4C_F32 || d == S4C_BF16 || d == S4C_F16; }
@@ -183,12 +203,32 @@ s4c_status tree_attn_prepare(const s4c_attn_shape* shape, const void* q, const v
     a.tile_rows = p.tile.rows; a.tile_keys = p.tile.keys; a.tile_shift = __builtin_ctz((unsigned)p.tile.keys);
     a.scale_log2 = (scale > 0.f ? scale : 1.0f / sqrtf((float)shape->D)) * kLog2e;
     a.block_table = block_table; a.max_blocks = max_blocks; a.page_shift = page_shift; a.num_pages = num_pages;
+    a.part_keys = p.tile.part_keys;
+    a.attn_wgs = 0;
+    a.tag = 0;
+    a.wait_ticks = 0;
     *plan = p;
     return S4C_OK;
 }
 
-hipError_t launch_tree_attn(const AttnPlan& p, const AttnArgs& a, int dtype, hipStream_t st) {
-    return p.large ? launch_tree_attn_large(a, dtype, st) : launch_tree_attn_small(a, dtype, st);
+// Equal runs are merged by the attention launch itself.
+void merge_in_launch(AttnArgs& a) {
+    if (a.split > 1) {
+        a.tag = next_tag();
+        // S4C_MERGE_WAIT_US (environment, >= 0): how long a merging workgroup waits for its parts before it flags the sequence;
+        // a diagnostic knob as S4C_ACCEPT_WAIT_US.
+        a.wait_ticks = wait_us("S4C_MERGE_WAIT_US", 2000000) * 100;
+    }
+}
+
+hipError_t launch_tree_attn(const AttnPlan& p, const AttnArgs& a, int dtype, const StepTail<kGreedyStep>* step, hipStream_t st) {
+    return p.large ? launch_tree_attn_large(a, dtype, step, st) : launch_tree_attn_small(a, dtype, step, st);
+}
+// attention and its merge
+hipError_t launch_attn_and_merge(const AttnPlan& p, AttnArgs a, int dtype, hipStream_t st) {
+    merge_in_launch(a);
+    const hipError_t e = launch_tree_attn(p, a, dtype, nullptr, st);
+    return e == hipSuccess && a.split == 0 ? launch_attn_merge(a, dtype, st) : e;       // the parts of balanced shares
 }
 
 s4c_status tree_attn_impl(const s4c_attn_shape* shape, const void* q, const void* k_tree, const void* v_tree,
@@ -201,12 +241,7 @@ s4c_status tree_attn_impl(const s4c_attn_shape* shape, const void* q, const void
     const s4c_status ok = tree_attn_prepare(shape, q, k_tree, v_tree, k_cache, v_cache, block_table, max_blocks, page_shift, num_pages,
                                             cache_len, parent, max_cache_len, scale, out, status, workspace, workspace_bytes, &p, &a);
     if (ok != S4C_OK) return ok;
-    hipStream_t st = (hipStream_t)hip_stream;
-    // Parts are combined by a second kernel: the kernel boundary is what makes one workgroup's
-    // partial results visible to another across the chip's separate L2s at no extra cost.
-    hipError_t e = launch_tree_attn(p, a, shape->dtype, st);
-    if (e == hipSuccess && p.division.split != 1) e = launch_attn_merge(a, shape->dtype, st);
-    return e == hipSuccess ? S4C_OK : S4C_ERR_HIP;
+    return launch_attn_and_merge(p, a, shape->dtype, (hipStream_t)hip_stream) == hipSuccess ? S4C_OK : S4C_ERR_HIP;
 }
 }  // namespace
 
@@ -265,16 +300,6 @@ s4c_status accept_args_ok(int32_t B, int32_t N, int32_t V, int32_t logits_dtype,
     const AcceptPlan p = scan_plan(B, N, V, 2, device_cus());
     if ((size_t)B * N * p.slots > 0x7FFFFFFFull || (size_t)N * p.chunks > 0x7FFFFFFFull) return S4C_ERR_UNSUPPORTED;
     return S4C_OK;
-}
-
-// A waiting time in microseconds, up to a minute, replaced by an environment variable (read at every call).
-long long wait_us(const char* name, long long otherwise) {
-    if (const char* env = getenv(name)) {
-        char* end = nullptr;
-        const long long v = strtoll(env, &end, 10);
-        if (end != env && v >= 0 && v <= 60000000ll) return v;
-    }
-    return otherwise;
 }
 
 // `workspace` holds at least s4c_accept_path_workspace_size(B, N, V) bytes, 256-byte aligned
@@ -639,10 +664,42 @@ s4c_status s4c_draft_linear(int32_t T, int32_t H, int32_t Hout, int32_t dtype, c
     return err == hipSuccess ? S4C_OK : S4C_ERR_HIP;
 }
 
+#pragma GCC visibility pop
+}  // extern "C"
+
+namespace {
+// what a step needs, and what one in a single launch needs behind it (a call without that much takes two)
+size_t step_bytes(const s4c_attn_shape& s, int32_t V) {
+    return s4c_accept_path_workspace_size(s.B, s.N, V) + (step_message_bytes(s.B, s.Hkv) + 255) / 256 * 256;
+}
+constexpr int kOneLaunchMostSequences = 32;
+size_t one_launch_bytes(const s4c_attn_shape& s) {
+    return s.B > kOneLaunchMostSequences ? 0 : (size_t)s.B * device_cus() * 2 * sizeof(word::Pair);      // at most two workgroups a CU
+}
+
+// A step in one launch: where the attention leaves places for the collectors and for enough scanning workgroups that the scan
+// is not the longer half.
+bool plan_one_launch(const s4c_step& p, const AttnPlan& plan, const AttnArgs& attn, AcceptArgs& accept) {
+    if (p.logits_dtype != p.shape.dtype || attn.split == 0 || attn.B > kOneLaunchMostSequences) return false;
+    if (p.accept_workspace_bytes < step_bytes(p.shape, p.V) + (size_t)attn.B * attn_workgroups(attn) * sizeof(word::Pair)) return false;
+    const int places = device_cus() * plan.tile.per_cu - attn_workgroups(attn) - attn.B;
+    const int wgs = places / attn.B < accept.plan.wgs ? places / attn.B : accept.plan.wgs;
+    if (wgs < 1) return false;
+    const long long chunks = ((long long)attn.N * accept.chunks + wgs - 1) / wgs;
+    const long long tiles = ((attn.max_cache_len + attn.tile_keys - 1) / attn.tile_keys + (attn.N + attn.tile_keys - 1) / attn.tile_keys + attn.split - 1) / attn.split;
+    if (chunks > 4 + tiles) return false;
+    accept.plan.wgs = wgs;
+    return true;
+}
+}  // namespace
+
+extern "C" {
+#pragma GCC visibility push(default)
+
 size_t s4c_verify_step_workspace_size(const s4c_attn_shape* shape, int32_t V) {
     s4c_status why;
     if (!shape || !shape_ok(shape, &why) || V <= 0) return 0;
-    return s4c_accept_path_workspace_size(shape->B, shape->N, V) + (step_message_bytes(shape->B, shape->Hkv) + 255) / 256 * 256;
+    return step_bytes(*shape, V) + one_launch_bytes(*shape);
 }
 
 s4c_status s4c_verify_step(const s4c_step* p, void* hip_stream) {
@@ -659,24 +716,33 @@ s4c_status s4c_verify_step(const s4c_step* p, void* hip_stream) {
     ok = accept_args_ok(B, N, V, p->logits_dtype, p->mode, p->temperature, p->logits, p->parent, p->tokens, p->p_draft, p->uniforms,
                         p->max_path, p->path, p->accept_len, p->accepted_tokens, p->bonus_token);
     if (ok != S4C_OK) return ok;
-    if (!p->accept_workspace || p->accept_workspace_bytes < s4c_verify_step_workspace_size(&p->shape, V) ||
+    if (!p->accept_workspace || p->accept_workspace_bytes < step_bytes(p->shape, V) ||
         (((uintptr_t)p->accept_workspace) & 255))
         return S4C_ERR_WORKSPACE;
     ok = compact_prepare(&p->shape, p->k_tree, p->v_tree, p->k_cache, p->v_cache, p->cache_len, p->path, p->accept_len, p->max_path,
                          p->dst_index, p->compact_status, &compact);
     if (ok != S4C_OK) return ok;
-    const AcceptArgs accept = accept_prepare(B, N, V, p->logits_dtype, p->mode, p->temperature, p->logits, p->parent, p->tokens, p->p_draft,
+    AcceptArgs accept = accept_prepare(B, N, V, p->logits_dtype, p->mode, p->temperature, p->logits, p->parent, p->tokens, p->p_draft,
                                              p->uniforms, p->max_path, p->path, p->accept_len, p->accepted_tokens, p->bonus_token,
                                              p->accept_status, p->accept_workspace);
-    hipError_t e = launch_tree_attn(plan, attn, p->shape.dtype, st);
-    if (p->logits_dtype == p->shape.dtype) {
-        if (e == hipSuccess)
-            e = launch_step(attn, plan.division.split != 1, accept, compact,
-                            (unsigned long long*)((char*)p->accept_workspace + s4c_accept_path_workspace_size(B, N, V)),
-                            // the copying workgroups wait 2 s longer than the collector they hear from (S4C_COPY_WAIT_US: that long)
-                            wait_us("S4C_COPY_WAIT_US", accept.wait_ticks / 100 + 2000000) * 100, st);
+    accept::rec_t* const messages = (accept::rec_t*)((char*)p->accept_workspace + s4c_accept_path_workspace_size(B, N, V));
+    // the copying workgroups wait 2 s longer than the collector they hear from (S4C_COPY_WAIT_US: that long)
+    const long long copy_ticks = wait_us("S4C_COPY_WAIT_US", accept.wait_ticks / 100 + 2000000) * 100;
+    hipError_t e;
+    if (plan_one_launch(*p, plan, attn, accept)) {
+        merge_in_launch(attn);
+        StepTail<kGreedyStep> tail;
+        tail.accept = accept;
+        tail.step = accept::make_step(accept, compact, messages, copy_ticks);
+        tail.step.lens = (word::Pair*)((char*)p->accept_workspace + step_bytes(p->shape, V));
+        tail.step.attn_wgs = attn_workgroups(attn);
+        tail.step.tag = next_tag();
+        e = launch_tree_attn(plan, attn, p->shape.dtype, &tail, st);
+    } else if (p->logits_dtype == p->shape.dtype) {
+        e = launch_tree_attn(plan, attn, p->shape.dtype, nullptr, st);
+        if (e == hipSuccess) e = launch_step(attn, accept, compact, messages, copy_ticks, st);
     } else {
-        if (e == hipSuccess && plan.division.split != 1) e = launch_attn_merge(attn, p->shape.dtype, st);
+        e = launch_attn_and_merge(plan, attn, p->shape.dtype, st);
         if (e == hipSuccess) e = launch_accept(accept, st);
         if (e == hipSuccess) e = launch_compact(compact, st);
     }

@@ -1,5 +1,5 @@
 // Tree-masked attention on the CDNA4 matrix cores (paper Sec. 3.2, Fig. 3): bf16 or fp16 in, fp32
-// accumulate, more than 64 query rows per KV head (fewer: tree_attn_mfma_smallm.hip); head size 64 or 128.
+// accumulate, more than 64 query rows per KV head (fewer: tree_attn_smallm.h); head size 64 or 128.
 //
 // The N tree nodes times the G query heads that share one KV head form a dense tile of
 // M = N*G query rows, so both contractions run on v_mfma_f32_32x32x16_bf16 (_f16 for fp16 data).
@@ -26,8 +26,8 @@
 //     past the end of a ragged tile are clamped to its last valid row (in bounds, finite).
 //   * The keys are divided between teams of workgroups (attn_division.h); parts of a divided unit are written
 //     unnormalised for the merge kernel.
-#include "attn_work.h"
-#include "mfma_common.h"
+#pragma once
+#include "attn_step.h"
 
 namespace s4c {
 
@@ -39,9 +39,9 @@ constexpr int kBN = 64;                     // keys per tile
 constexpr float kLazyLog2 = 8.0f;           // full tiles rescale only when a row maximum grew by more than 2^8
 constexpr int lds_bytes_for(int ns, int d) { return ns * 2 * kBN * d * 2 + kMaxNodes * 16 + kMaxNodes * 4; }
 
-template <int WR, int NS, int WPE, bool PAGED, bool F16, int kD>
+template <int WR, int NS, int WPE, bool PAGED, bool F16, int kD, StepKind STEP>
 __global__ __launch_bounds__(WR * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
-void tree_attn_mfma_kernel(AttnArgs a) {
+void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP>) {
     constexpr int NT = WR * 64;
     constexpr int BM = WR * 32;
     constexpr int kRowB = kD * 2;                // bytes per K/V row
@@ -58,7 +58,12 @@ void tree_attn_mfma_kernel(AttnArgs a) {
     static_assert(CH >= 1, "tile smaller than the workgroup");
     static_assert(NS >= 2 && 2 * CH * (NS - 2) < 64, "too many loads in flight for vmcnt");
 
+    static_assert(sizeof(accept::Shared) <= NS * kStageB, "the ring is also what the other workgroups of a step have");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    if (blockIdx.y > 0) {
+        rest_of_launch<kD, F16 ? parts::kH16 : parts::kB16, NT, STEP>(smem);
+        return;
+    }
     uint32_t* anc = (uint32_t*)(smem + NS * kStageB);        // [kMaxNodes][4]
     int32_t* spar = (int32_t*)(anc + kMaxNodes * 4);         // [kMaxNodes]
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem;
@@ -96,8 +101,13 @@ void tree_attn_mfma_kernel(AttnArgs a) {
 
     const work::Lens lens(a);
     work::Walk cw = work::walk_first(a, lens, team);      // what is multiplied
+    const long long started = STEP != kNoStep || a.tag != 0 ? (long long)wall_clock64() : 0;
     if (cw.b < 0) {
-        work::note_empty(a, team, mt, BM);
+        if constexpr (STEP != kNoStep) {
+            __syncthreads();
+            lens_read<STEP>(lens, started);
+        }
+        if (work::leaves_empty(a, team)) parts::put_empty<kD, 1>(a, team, mt * WR + wave, 0, started);
         return;
     }
     work::Walk pw = cw;                                   // what is loaded
@@ -226,6 +236,7 @@ void tree_attn_mfma_kernel(AttnArgs a) {
 #pragma unroll
     for (int t = 0; t < kKT; ++t) asm volatile("" : "+v"(qf[t]));          // in registers before the barrier
     __syncthreads();                                      // Q and parent[] are here, their stages free
+    if constexpr (STEP != kNoStep) lens_read<STEP>(lens, started);
     while (issued < NS - 1 && issued < n_share) issue_next();
 
     int parent = -1, b_known = cw.b;
@@ -485,6 +496,10 @@ void tree_attn_mfma_kernel(AttnArgs a) {
                 *(uint2*)(orow + 32 * db + 8 * jq) = pk;
             }
         }
+    } else if (a.split > 0) {
+        parts::put<kD, 1>(a, team, mt * WR + wave, 0, m_run, l_tot, started, [&](int q) __attribute__((always_inline)) {
+            return f32x4{o[q >> 2][4 * (q & 3)], o[q >> 2][4 * (q & 3) + 1], o[q >> 2][4 * (q & 3) + 2], o[q >> 2][4 * (q & 3) + 3]};
+        });
     } else {
         if (rvalid) {
             const size_t prow = work::part_row(a, team, work::part_slot(cw)) + rq;
@@ -507,39 +522,35 @@ void tree_attn_mfma_kernel(AttnArgs a) {
 
 int pick_wr(int M) { return M <= 128 ? 4 : 8; }
 
-template <int WR, int NS, int WPE, bool PAGED, bool F16, int D>
-hipError_t launch(const AttnArgs& a, hipStream_t st) {
+template <int WR, int NS, int WPE, bool PAGED, bool F16, int D, StepKind STEP>
+hipError_t launch(AttnArgs a, const StepTail<STEP>& tail, hipStream_t st) {
     constexpr int kLds = lds_bytes_for(NS, D);
     static std::atomic<uint64_t> lds_set{0};
-    const hipError_t ea = ensure_dynamic_lds((const void*)tree_attn_mfma_kernel<WR, NS, WPE, PAGED, F16, D>, kLds, lds_set);
+    const hipError_t ea = ensure_dynamic_lds((const void*)tree_attn_mfma_kernel<WR, NS, WPE, PAGED, F16, D, STEP>, kLds, lds_set);
     if (ea != hipSuccess) return ea;
-    const long teams8 = ((long)a.teams + 7) / 8 * 8;              // padded to whole XCD rounds
-    dim3 grid((unsigned)(teams8 * a.mtiles)), block(WR * 64);
-    hipLaunchKernelGGL((tree_attn_mfma_kernel<WR, NS, WPE, PAGED, F16, D>), grid, block, kLds, st, a);
+    a.attn_wgs = attn_workgroups(a);
+    const dim3 grid = launch_grid(a, rest_workgroups(a, tail, WR * 64)), block(WR * 64);
+    hipLaunchKernelGGL((tree_attn_mfma_kernel<WR, NS, WPE, PAGED, F16, D, STEP>), grid, block, kLds, st, a, tail);
     return hipGetLastError();
 }
 
 // four waves (up to 128 rows): one workgroup per CU and wave per SIMD; eight: two waves per SIMD
-template <bool PAGED, bool F16, int D>
-hipError_t launch_rows(const AttnArgs& a, hipStream_t st) {
-    return pick_wr(a.M) == 4 ? launch<4, 4, 1, PAGED, F16, D>(a, st) : launch<8, 4, 2, PAGED, F16, D>(a, st);
+template <bool PAGED, bool F16, int D, StepKind STEP>
+hipError_t launch_rows(const AttnArgs& a, const StepTail<STEP>& tail, hipStream_t st) {
+    return pick_wr(a.M) == 4 ? launch<4, 4, 1, PAGED, F16, D>(a, tail, st) : launch<8, 4, 2, PAGED, F16, D>(a, tail, st);
+}
+template <bool F16, int D>
+hipError_t launch_as(const AttnArgs& a, const StepTail<kGreedyStep>* step, hipStream_t st) {
+    if (step)
+        return step->accept.mode == S4C_GREEDY ? launch_rows<false, F16, D>(a, StepTail<kGreedyStep>(*step), st)
+                                               : launch_rows<false, F16, D>(a, StepTail<kStochasticStep>(*step), st);
+    return a.block_table ? launch_rows<true, F16, D>(a, StepTail<kNoStep>(), st) : launch_rows<false, F16, D>(a, StepTail<kNoStep>(), st);
 }
 template <bool F16>
-hipError_t launch_by_shape(const AttnArgs& a, hipStream_t st) {
-    if (a.D == 64) return a.block_table ? launch_rows<true, F16, 64>(a, st) : launch_rows<false, F16, 64>(a, st);
-    return a.block_table ? launch_rows<true, F16, 128>(a, st) : launch_rows<false, F16, 128>(a, st);
+hipError_t launch_by_shape(const AttnArgs& a, const StepTail<kGreedyStep>* step, hipStream_t st) {
+    return a.D == 64 ? launch_as<F16, 64>(a, step, st) : launch_as<F16, 128>(a, step, st);
 }
 
 }  // namespace
-
-// 32 rows per wave.  (Head size 64 leaves room for two four-wave workgroups on a CU.)
-AttnTile attn_tile_large(const s4c_attn_shape& s) {
-    const int wr = pick_wr(s.N * (s.Hq / s.Hkv));
-    return AttnTile{32 * wr, kBN, wr == 4 && 2 * lds_bytes_for(4, s.D) <= 160 * 1024 ? 2 : 1, s.D == 128};
-}
-
-hipError_t launch_tree_attn_large(const AttnArgs& a, int dtype, hipStream_t st) {
-    return dtype == S4C_F16 ? launch_by_shape<true>(a, st) : launch_by_shape<false>(a, st);
-}
 
 }  // namespace s4c

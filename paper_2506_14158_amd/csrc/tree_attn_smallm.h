@@ -15,14 +15,18 @@
 //                permuted (lane half g takes elements 8 t + 4 g .. + 3) so that both operands are 16-byte reads, and
 //                P^T is used straight out of the score accumulator: register j of lane half g holds key
 //                8 (j/4) + 4 g + j%4, so step j multiplies V rows that far apart.
-#include "attn_work.h"
-#include "mfma_common.h"
+#pragma once
+#include "attn_step.h"
 
 namespace s4c {
 
 namespace {
 
 using namespace mfma;
+using parts::Elem;
+using parts::kB16;
+using parts::kF32;
+using parts::kH16;
 
 constexpr int kBN = 32;                      // keys per tile
 // By how much (log2) a row's maximum may outgrow the reference that its exponentials are taken against.  Where the
@@ -33,8 +37,6 @@ constexpr int kBN = 32;                      // keys per tile
 template <bool ROUNDED>
 constexpr float kLagLog2 = ROUNDED ? 0.0f : 8.0f;
 constexpr int kAuxB = kMaxNodes * 16 + kMaxNodes * 4;
-
-enum Elem { kB16 = 0, kH16 = 1, kF32 = 2 };  // bf16, fp16, fp32
 
 // KG key groups x RBW row blocks of 32 = waves; NR rounds in the ring.
 template <Elem E, int D_, int KG_, int RBW_, int NR_>
@@ -50,11 +52,14 @@ struct Cfg {
     static constexpr int kWaves = kKG * kRBW;
     static constexpr int kThreads = 64 * kWaves;
     static constexpr int kCH = kTileKB / 1024 / kRBW;    // direct-to-LDS loads per wave for its share of K (or V)
-    // the key groups' states of a row meet in LDS one 32-column block at a time (a region of its own, so that the
-    // ring keeps filling for the next segment): padded rows of 36 floats, and each row's (maximum, sum)
-    static constexpr int kMergeRow = 36;
-    static constexpr int kMergeB = (kKG - 1) * kRBW * 32 * (kMergeRow + 2) * 4;
+    // Where the key groups' states of a row meet (a region of its own, so that the ring keeps filling for the next segment): every
+    // wave's (maximum, sum), and two of the eight-column pieces it sends.  kOwners groups share the output's 32-column blocks;
+    // each adds up kOwn blocks of all groups.
+    static constexpr int kDB = kD / 32, kOwners = kKG < kDB ? kKG : kDB, kOwn = kDB / kOwners;
+    static constexpr int kMergeB = kWaves * (32 * 8 + 2 * 1024);
     static constexpr int kLdsBytes = kRingB + kAuxB + kMergeB;
+    static_assert(kWaves * kDB * 4096 <= kRingB, "after a launch's only segment they meet in the ring");
+    static_assert(sizeof(accept::Shared) <= kRingB, "the ring is also what the other workgroups of a step have");
     static constexpr int kPerCu = 2 * kLdsBytes <= 160 * 1024 ? 2 : 1;
     static_assert(kLdsBytes <= 160 * 1024, "LDS of one CU");
     static_assert(kCH >= 1 && 2 * kCH * (kNR - 1) < 64, "loads in flight are counted in vmcnt");
@@ -71,19 +76,23 @@ struct Cfg {
     }
 };
 
-template <class C, bool PAGED>
+template <class C, bool PAGED, StepKind STEP>
 __global__ __launch_bounds__(C::kThreads) __attribute__((amdgpu_waves_per_eu(C::kPerCu * C::kWaves / 4, 2)))
-void tree_attn_smallm_kernel(AttnArgs a) {
+void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP>) {
     constexpr int kD = C::kD, kKG = C::kKG, kRBW = C::kRBW, kNR = C::kNR, kRowB = C::kRowB;
     constexpr int kThreads = C::kThreads, kCH = C::kCH;
     constexpr bool kIs32 = C::kElem == kF32, F16 = C::kElem == kH16;
-    constexpr int kDB = kD / 32;                              // 32-column blocks of the output
+    constexpr int kDB = C::kDB, kOwners = C::kOwners, kOwn = C::kOwn;
     constexpr int kParts = Prob<F16, kD>::kParts;             // (16-bit data)
     constexpr float kShift = kIs32 ? 0.f : Prob<F16, kD>::kShift;
     constexpr float kLag = kLagLog2<!kIs32 && kParts == 1>;
     constexpr int kLPR = kRowB / 16;                          // lanes (16-byte chunks) per row in a direct-to-LDS load
     constexpr int kRPI = 64 / kLPR;                           // rows per load instruction
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    if (blockIdx.y > 0) {
+        rest_of_launch<kD, C::kElem, kThreads, STEP>(smem);
+        return;
+    }
     uint32_t* anc = (uint32_t*)(smem + C::kRingB);            // [kMaxNodes][4]
     int32_t* spar = (int32_t*)(anc + kMaxNodes * 4);          // [kMaxNodes]
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem;
@@ -108,18 +117,20 @@ void tree_attn_smallm_kernel(AttnArgs a) {
     }
     const int i16 = lane & 15, dhalf = (lane >> 4) & 1;
     constexpr int kKT = kIs32 ? kD / 8 : kD / 16;             // 16-byte K pieces per row and lane half
+    // (block db of the accumulator is column block (db + kg kOwn) % kDB of the output, so that the blocks a group adds up are its first ones)
     uint32_t k_off[kKT], v_off[kDB];
+    auto column_block = [&](int db) __attribute__((always_inline)) { return (db + kg * kOwn) % kDB; };
 #pragma unroll
     for (int tt = 0; tt < kKT; ++tt) k_off[tt] = (lane & 31) * kRowB + (((2 * tt + g32) ^ C::k_swz(lane & 31)) << 4);
 #pragma unroll
     for (int db = 0; db < kDB; ++db) {
         if constexpr (kIs32) {
             // element d = 32 db + lane % 32 of row 4 g32 (rows 8 q + 4 g32 + e follow at constant distances)
-            const int d = 32 * db + (lane & 31);
+            const int d = 32 * column_block(db) + (lane & 31);
             v_off[db] = C::kTileKB + 4 * g32 * kRowB + (((d >> 2) ^ (g32 << 3)) << 4) + 4 * (d & 3);
         } else {
             const int vrow = 4 * g32 + (i16 >> 2);
-            v_off[db] = C::kTileKB + vrow * kRowB + (((4 * db + 2 * dhalf + ((i16 & 3) >> 1)) ^ C::v_swz(vrow)) << 4) + 8 * (i16 & 1);
+            v_off[db] = C::kTileKB + vrow * kRowB + (((4 * column_block(db) + 2 * dhalf + ((i16 & 3) >> 1)) ^ C::v_swz(vrow)) << 4) + 8 * (i16 & 1);
         }
     }
     const ptrdiff_t v_minus_k = (const unsigned char*)a.v_cache - (const unsigned char*)a.k_cache;
@@ -128,8 +139,13 @@ void tree_attn_smallm_kernel(AttnArgs a) {
 
     const work::Lens lens(a);
     work::Walk cw = work::walk_first(a, lens, team);      // what is multiplied
+    const long long started = STEP != kNoStep || a.tag != 0 ? (long long)wall_clock64() : 0;
     if (cw.b < 0) {
-        work::note_empty(a, team, mt, 32 * kRBW);
+        if constexpr (STEP != kNoStep) {
+            __syncthreads();
+            lens_read<STEP>(lens, started);
+        }
+        if (work::leaves_empty(a, team) && kg < kOwners) parts::put_empty<kD, kOwners>(a, team, mt * kRBW + rb, kg, started);
         return;
     }
     work::Walk pw = cw;                                   // what is loaded
@@ -234,6 +250,11 @@ void tree_attn_smallm_kernel(AttnArgs a) {
     for (int r = 0; r < kNR - 1; ++r)
         if (pw.b >= 0) issue_round();
     if (issued == kNR - 1) wait_vmcnt<2 * kCH * (kNR - 1)>(); else wait_vmcnt<0>();
+
+    if constexpr (STEP != kNoStep) {
+        __syncthreads();
+        lens_read<STEP>(lens, started);
+    }
 
     // ---- this lane's query row; a later segment's Q fragments (and parent[]) are loaded before the previous one is
     // written out
@@ -431,7 +452,6 @@ void tree_attn_smallm_kernel(AttnArgs a) {
             if (nw.b != b && tid < N) parent = a.parent[(size_t)nw.b * N + tid];
             load_q(nw.b, nw.kvh);
         }
-        // ---- merge the key groups of each row into key group 0, one 32-column block at a time
         const int flagged = (work::tree_is_bad(a, spar) ? S4C_SEQ_BAD_TREE : 0) | (len_bad ? S4C_SEQ_BAD_LEN : 0);
         if (a.status && tid == 0 && cw.tile == 0 && kvh == 0 && mt == 0) a.status[b] = flagged;
         float l_tot = l_run + __shfl_xor(l_run, 32);
@@ -442,95 +462,112 @@ void tree_attn_smallm_kernel(AttnArgs a) {
 #pragma unroll
                 for (int j = 0; j < 16; ++j) o[db][j] = 0.f;
         }
-        float* mo = (float*)(smem + C::kRingB + kAuxB);                       // [KG-1][RBW][32 rows][kMergeRow]
-        float* mml = mo + (kKG - 1) * kRBW * 32 * C::kMergeRow;               // [KG-1][RBW][32 rows][2]
-        const int mslot = ((kg - 1) * kRBW + rb) * 32 + (lane & 31);          // (kg > 0)
-        if (kg > 0 && g32 == 0) *(float2*)(mml + mslot * 2) = make_float2(m_run, l_tot);
-        float wg[kKG];                                                        // weights of the groups (kg == 0)
+        // ---- The key groups of each row meet in LDS: a group sends its later blocks and adds up its first kOwn.  The sums of
+        // block db come from the groups that are db / kOwn before this one, modulo kOwners.
+        // (One group that added up everything, a block at a time: 1.8 us from the last tile to the last store; 1.1 so.)
+        float* const mml = (float*)(smem + C::kRingB + kAuxB);                // [waves][32 rows][2]
+        if (g32 == 0) *(float2*)(mml + (wave * 32 + lane) * 2) = make_float2(m_run, l_tot);
+        float m_max = -INFINITY, w_own = 0.f;
+        auto weight = [&](int g) __attribute__((always_inline)) {             // 0: the group saw nothing visible
+            const float2 ml = *(const float2*)(mml + ((g * kRBW + rb) * 32 + (lane & 31)) * 2);
+            return ml.y > 0.f ? fast_exp2(ml.x - m_max) : 0.f;
+        };
+        auto meet = [&](auto alone_tag) __attribute__((always_inline)) {
+            // the launch's only segment: the ring is free once every wave is through, and holds everything at once;
+            // else two pieces of every wave at a time
+            constexpr bool ALONE = decltype(alone_tag)::value;
+            constexpr int kJ = ALONE ? 4 : 2;
+            f32x4* const ex = (f32x4*)(ALONE ? smem : (unsigned char*)(mml + C::kWaves * 64));
+            auto at = [&](int w, int db, int jq) __attribute__((always_inline)) { return ex + (ALONE ? (w * kDB + db) * 4 + jq : w * 2 + (jq & 1)) * 64 + lane; };
+            auto send = [&](int db, int j0) __attribute__((always_inline)) {
+                if (db < kOwn && kg < kOwners) return;
 #pragma unroll
-        for (int db = 0; db < kDB; ++db) {
-            if (kg > 0) {
+                for (int jq = j0; jq < j0 + kJ; ++jq)
+                    *at(wave, db, jq) = f32x4{o[db][4 * jq], o[db][4 * jq + 1], o[db][4 * jq + 2], o[db][4 * jq + 3]};
+            };
+            constexpr int kFirst = kKG > kOwners ? 0 : kOwn;                  // first block that some group sends
+            if constexpr (ALONE) {
+                __syncthreads();
 #pragma unroll
-                for (int jq = 0; jq < 4; ++jq)
-                    *(float4*)(mo + mslot * C::kMergeRow + 8 * jq + 4 * g32) =
-                        make_float4(o[db][4 * jq], o[db][4 * jq + 1], o[db][4 * jq + 2], o[db][4 * jq + 3]);
+                for (int db = kFirst; db < kDB; ++db) send(db, 0);
+            } else {
+                send(kFirst, 0);
             }
             __syncthreads();
-            if (kg == 0) {
-                if (db == 0) {
-                    float m_max = l_tot > 0.f ? m_run : -INFINITY, mg[kKG], lg[kKG];
-                    mg[0] = m_run;
-                    lg[0] = l_tot;
+            l_tot = 0.f;
 #pragma unroll
-                    for (int g = 1; g < kKG; ++g) {
-                        const float2 ml = *(const float2*)(mml + (((g - 1) * kRBW + rb) * 32 + (lane & 31)) * 2);
-                        mg[g] = ml.x;
-                        lg[g] = ml.y;
-                        m_max = fmaxf(m_max, lg[g] > 0.f ? mg[g] : -INFINITY);
-                    }
-                    l_tot = 0.f;
-#pragma unroll
-                    for (int g = 0; g < kKG; ++g) {
-                        wg[g] = lg[g] > 0.f ? fast_exp2(mg[g] - m_max) : 0.f;     // 0: this key group saw nothing visible
-                        l_tot = fmaf(lg[g], wg[g], l_tot);
-                    }
-                    m_run = m_max;
-                }
-#pragma unroll
-                for (int j = 0; j < 16; ++j) o[db][j] *= wg[0];
-#pragma unroll
-                for (int g = 1; g < kKG; ++g)
-#pragma unroll
-                    for (int jq = 0; jq < 4; ++jq) {
-                        const float4 v = *(const float4*)(mo + (((g - 1) * kRBW + rb) * 32 + (lane & 31)) * C::kMergeRow + 8 * jq + 4 * g32);
-                        o[db][4 * jq] = fmaf(v.x, wg[g], o[db][4 * jq]);
-                        o[db][4 * jq + 1] = fmaf(v.y, wg[g], o[db][4 * jq + 1]);
-                        o[db][4 * jq + 2] = fmaf(v.z, wg[g], o[db][4 * jq + 2]);
-                        o[db][4 * jq + 3] = fmaf(v.w, wg[g], o[db][4 * jq + 3]);
-                    }
+            for (int g = 0; g < kKG; ++g) {
+                const float2 ml = *(const float2*)(mml + ((g * kRBW + rb) * 32 + (lane & 31)) * 2);
+                m_max = fmaxf(m_max, ml.y > 0.f ? ml.x : -INFINITY);
             }
-            if (db + 1 < kDB) __syncthreads();
-        }
+#pragma unroll
+            for (int g = 0; g < kKG; ++g) l_tot = fmaf(mml[((g * kRBW + rb) * 32 + (lane & 31)) * 2 + 1], weight(g), l_tot);
+            w_own = weight(kg);
+#pragma unroll
+            for (int db = 0; db < kOwn; ++db)
+#pragma unroll
+                for (int j = 0; j < 16; ++j) o[db][j] *= w_own;
+#pragma unroll
+            for (int db = kFirst; db < kDB; ++db)
+#pragma unroll
+                for (int j0 = 0; j0 < 4; j0 += kJ) {
+                    if (!ALONE && (db > kFirst || j0 > 0)) {
+                        __syncthreads();
+                        send(db, j0);
+                        __syncthreads();
+                    }
+                    if (kg < kOwners)
+#pragma unroll
+                        for (int g0 = 0; g0 < kKG; g0 += kOwners) {
+                            const int g = g0 + (kg - db / kOwn + kOwners) % kOwners;
+                            if (g == kg) continue;
+                            const float w = weight(g);
+#pragma unroll
+                            for (int jq = j0; jq < j0 + kJ; ++jq) {
+                                const f32x4 v = *at(g * kRBW + rb, db, jq);
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) o[db % kOwn][4 * jq + e] = fmaf(v[e], w, o[db % kOwn][4 * jq + e]);
+                            }
+                        }
+                }
+        };
+        if (a.split > 0) meet(std::integral_constant<bool, true>{});
+        else meet(std::integral_constant<bool, false>{});
         if (a.split == 0 && mt == 0 && tid == 0) work::note_parts(a, team, cw);
-        // ---- key group 0 writes the row: d = 32 db + 8 (j/4) + 4 g32 + (j%4)
-        if (kg == 0 && rvalid) {
+        // ---- the row's columns: d = 32 column_block(db) + 8 (j/4) + 4 g32 + (j%4)
+        auto piece = [&](int q) __attribute__((always_inline)) {
+            return f32x4{o[q >> 2][4 * (q & 3)], o[q >> 2][4 * (q & 3) + 1], o[q >> 2][4 * (q & 3) + 2], o[q >> 2][4 * (q & 3) + 3]};
+        };
+        if (kg < kOwners) {
             if (work::walk_is_whole(a, cw)) {
                 const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
-                const size_t o0 = (((size_t)b * N + node) * a.Hq + kvh * G + gh) * kD + 4 * g32;
+                const size_t o0 = (((size_t)b * N + node) * a.Hq + kvh * G + gh) * kD + 32 * kOwn * kg + 4 * g32;
+                if (rvalid)
 #pragma unroll
-                for (int db = 0; db < kDB; ++db)
-#pragma unroll
-                    for (int jq = 0; jq < 4; ++jq) {
-                        const float v0 = o[db][4 * jq] * inv, v1 = o[db][4 * jq + 1] * inv, v2 = o[db][4 * jq + 2] * inv,
-                                    v3 = o[db][4 * jq + 3] * inv;
-                        if constexpr (kIs32) *(float4*)((float*)a.out + o0 + 32 * db + 8 * jq) = make_float4(v0, v1, v2, v3);
-                        else *(uint2*)((bf16_t*)a.out + o0 + 32 * db + 8 * jq) =
-                                 make_uint2(round1<F16>(v0) | (round1<F16>(v1) << 16), round1<F16>(v2) | (round1<F16>(v3) << 16));
-                    }
-            } else {
+                    for (int q = 0; q < 4 * kOwn; ++q) parts::store_out<C::kElem>(a.out, o0 + 8 * q, piece(q) * inv);
+            } else if (a.split > 0) {
+                parts::put<kD, kOwners>(a, team, mt * kRBW + rb, kg, m_max, l_tot, started, piece);
+            } else if (rvalid) {
                 const size_t prow = work::part_row(a, team, work::part_slot(cw)) + rq;
-                float* orow = a.ws_o + prow * kD + 4 * g32;
+                float* orow = a.ws_o + prow * kD + 32 * kOwn * kg + 4 * g32;
 #pragma unroll
-                for (int db = 0; db < kDB; ++db)
-#pragma unroll
-                    for (int jq = 0; jq < 4; ++jq)
-                        *(float4*)(orow + 32 * db + 8 * jq) =
-                            make_float4(o[db][4 * jq], o[db][4 * jq + 1], o[db][4 * jq + 2], o[db][4 * jq + 3]);
-                if (g32 == 0) *(float2*)(a.ws_ml + prow * 2) = make_float2(m_run, l_tot);
+                for (int q = 0; q < 4 * kOwn; ++q) *(f32x4*)(orow + 8 * q) = piece(q);
+                if (kg == 0 && g32 == 0) *(float2*)(a.ws_ml + prow * 2) = make_float2(m_max, l_tot);
             }
         }
+        if (a.split > 0) return;
         cw = nw;
     }
 }
 
-template <class C, bool PAGED>
-hipError_t launch(const AttnArgs& a, hipStream_t st) {
+template <class C, bool PAGED, StepKind STEP>
+hipError_t launch(AttnArgs a, const StepTail<STEP>& tail, hipStream_t st) {
     static std::atomic<uint64_t> lds_set{0};
-    const hipError_t ea = ensure_dynamic_lds((const void*)tree_attn_smallm_kernel<C, PAGED>, C::kLdsBytes, lds_set);
+    const hipError_t ea = ensure_dynamic_lds((const void*)tree_attn_smallm_kernel<C, PAGED, STEP>, C::kLdsBytes, lds_set);
     if (ea != hipSuccess) return ea;
-    const long teams8 = ((long)a.teams + 7) / 8 * 8;
-    dim3 grid((unsigned)(teams8 * a.mtiles)), block(C::kThreads);
-    hipLaunchKernelGGL((tree_attn_smallm_kernel<C, PAGED>), grid, block, C::kLdsBytes, st, a);
+    a.attn_wgs = attn_workgroups(a);
+    const dim3 grid = launch_grid(a, rest_workgroups(a, tail, C::kThreads)), block(C::kThreads);
+    hipLaunchKernelGGL((tree_attn_smallm_kernel<C, PAGED, STEP>), grid, block, C::kLdsBytes, st, a, tail);
     return hipGetLastError();
 }
 
@@ -547,32 +584,18 @@ auto with_cfg(int D, int rows, Use use) {
         return rows == 32 ? use(Cfg<E, 128, 4, 1, 2>{}) : use(Cfg<E, 128, 2, 2, 2>{});
     }
 }
-template <class Use>
-auto with_cfg(int dtype, int D, int rows, Use use) {
-    if (dtype == S4C_F32) return with_cfg<kF32>(D, rows, use);
-    return dtype == S4C_F16 ? with_cfg<kH16>(D, rows, use) : with_cfg<kB16>(D, rows, use);
+// A launch for one element type; instantiated in a translation unit of its own each (they take a minute to compile).
+template <Elem E>
+hipError_t launch_smallm(const AttnArgs& a, const StepTail<kGreedyStep>* step, hipStream_t st) {
+    return with_cfg<E>(a.D, a.tile_rows, [&](auto c) {
+        typedef decltype(c) C;
+        if (step)
+            return step->accept.mode == S4C_GREEDY ? launch<C, false>(a, StepTail<kGreedyStep>(*step), st)
+                                                   : launch<C, false>(a, StepTail<kStochasticStep>(*step), st);
+        return a.block_table ? launch<C, true>(a, StepTail<kNoStep>(), st) : launch<C, false>(a, StepTail<kNoStep>(), st);
+    });
 }
 
 }  // namespace
-
-// Up to 32 rows take the configuration of one row block.  16-bit data of head size 128 only where a CU has more than
-// 7168 keys to stream, in long units: four key groups fill a CU's LDS with one workgroup, and two workgroups hide each other's starts and
-// merges (512 units of 20 rows, 20 keys: 28.0 us and 8.6 with two; 640 units of 300 keys 38 and 29, 2400 keys 151 and 150, 4800 keys
-// 273 and 279; 256 units of 8192 keys 180 and 189; 1280 units of 900 to 1800 keys 192 and 167).
-AttnTile attn_tile_small(const s4c_attn_shape& s, int32_t max_cache_len, int cus) {
-    const bool deep = max_cache_len >= 4096 && (long long)s.B * s.Hkv * max_cache_len >= 7168ll * cus;
-    const int rows = s.N * (s.Hq / s.Hkv) <= 32 && (s.D == 64 || (s.dtype != S4C_F32 && deep)) ? 32 : 64;
-    return with_cfg(s.dtype, s.D, rows, [](auto c) {
-        typedef decltype(c) C;
-        return AttnTile{32 * C::kRBW, kBN, C::kPerCu, C::kElem != kF32 && C::kD == 128};
-    });
-}
-
-hipError_t launch_tree_attn_small(const AttnArgs& a, int dtype, hipStream_t st) {
-    return with_cfg(dtype, a.D, a.tile_rows, [&](auto c) {
-        typedef decltype(c) C;
-        return a.block_table ? launch<C, true>(a, st) : launch<C, false>(a, st);
-    });
-}
 
 }  // namespace s4c

@@ -1,0 +1,8 @@
+// tree_attn_smallm.h for bf16 data.
+#include "tree_attn_smallm.h"
+
+namespace s4c {
+
+hipError_t launch_smallm_bf16(const AttnArgs& a, const StepTail<kGreedyStep>* step, hipStream_t st) { return launch_smallm<kB16>(a, step, st); }
+
+}  // namespace s4c
