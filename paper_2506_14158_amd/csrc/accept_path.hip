@@ -10,7 +10,7 @@ using namespace accept;
 template <typename T, bool STOCHASTIC>
 __global__ __launch_bounds__(kThreads, kWavesPerSimd<T>) void accept_kernel(AcceptArgs a) {
     __shared__ Shared sh;
-    scan_or_collect<T, STOCHASTIC, false, 1>(a, StepArgs{}, sh, blockIdx.x);
+    scan_or_collect<T, STOCHASTIC, kAlone, 1>(a, StepArgs{}, sh, blockIdx.x);
 }
 
 template <typename T, bool STOCHASTIC>
@@ -18,7 +18,7 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd<T>) void step_kernel(AttnAr
     __shared__ Shared sh;
     int wg = blockIdx.x;
     if (wg < x.scan_wgs) {
-        scan_or_collect<T, STOCHASTIC, true, 1>(a, x, sh, wg);
+        scan_or_collect<T, STOCHASTIC, kBehindAttention, 1>(a, x, sh, wg);
         return;
     }
     wg -= x.scan_wgs;

@@ -76,7 +76,7 @@ __device__ __forceinline__ bool await4(const rec_t* p, int runs, uint32_t nonce,
         }
         if (all) return true;
         if ((long long)wall_clock64() - deadline >= 0) return false;
-        __builtin_amdgcn_s_sleep(8);
+        __builtin_amdgcn_s_sleep(2);
     }
 }
 
@@ -92,7 +92,8 @@ struct Shared {
     int32_t any[4];
     float v[4], s[4];                                        // a scanning workgroup's waves
     int32_t i[4];
-    int32_t parent[kMaxNodes], ok[kMaxNodes], g[kMaxNodes], tok[kMaxNodes], node[kMaxNodes], best, len;     // a collector's nodes, its result
+    int32_t parent[kMaxNodes], g[kMaxNodes], node[kMaxNodes], best, len;     // a collector's nodes, its result
+    uint64_t above[kMaxNodes][2], ok[2];                     // each node's ancestors and itself; the nodes that pass their test
     float m[kMaxNodes], S[kMaxNodes];
     int32_t msg[2 + kMaxNodes];                              // a copier's message
 };
@@ -150,7 +151,8 @@ struct Runs {
 };
 constexpr float kLazyLog2 = 24.0f;
 
-// ---- what step_kernel adds
+// ---- what a step adds
+enum Part { kAlone, kBehindAttention, kBesideAttention };     // acceptance by itself; a step's second launch; its only one
 struct StepArgs {
     CompactArgs compact;
     rec_t* messages;            // [B][copiers][kMessageWords]
@@ -174,26 +176,10 @@ constexpr int kMostCopiers = 8;
 // is only ever alone if the collector was held up on its way here.  A collector that comes here after half that time
 // looks whether a copier has left: then rows are missing, so the sequence is flagged and its length stays.  Copier: tell that it has given
 // up, then look once more; collector: publish, then look: at least one of the two sees the other.
-__device__ __forceinline__ void announce_path(const StepArgs& x, const AcceptArgs& a, Shared& sh, int b, int base, long long started) {
+__device__ __forceinline__ void announce_path(const StepArgs& x, const AcceptArgs& a, Shared& sh, int b, int base, bool unread, long long started) {
     const CompactArgs& c = x.compact;
     const int i = threadIdx.x;
     const int L = sh.len;
-    // the attention workgroups of this launch have read the length that is about to change
-    bool unread = false;
-    if (x.attn_wgs > 0) {
-        word::Pair* const p = x.lens + (size_t)b * x.attn_wgs;
-        for (int w = i; w < x.attn_wgs; w += kThreads) {
-            bool here = word::here(p + w, x.tag);
-            while (!here) {
-                if ((long long)wall_clock64() - started >= x.copy_ticks / 2) { here = word::give_up(p + w, x.tag); break; }
-                __builtin_amdgcn_s_sleep(4);
-                here = word::here(p + w, x.tag);
-            }
-            if (here) word::taken(p + w, x.tag);
-            unread = unread || !here;
-        }
-        unread = any_of(sh, unread);
-    }
     const bool bad = unread || base < 0 || (long long)base + L + 1 > c.S_cap;
     rec_t* const first = x.messages + (size_t)b * x.copiers * kMessageWords;
     if (i < kMessage) {
@@ -230,6 +216,20 @@ __device__ __forceinline__ void copy_rows(const StepArgs& x, const AcceptArgs& a
     int32_t* const s_msg = sh.msg;
     const int tid = threadIdx.x;
     rec_t* const m = x.messages + ((size_t)b * x.copiers + w) * kMessageWords;
+    const int h0 = w * x.heads, nh = min(c.Hkv, h0 + x.heads) - h0, shift = 31 - __builtin_clz(c.row_bytes / 16);   // (vectors of a row: 8, 16 or 32)
+    constexpr int kInFlight = 4;
+    // vector e of the rows belongs to row k of the path and KV head h (those of the first pass are found before the message is here)
+    int row[kInFlight], head[kInFlight];
+    const size_t v16 = (size_t)(tid & ((1 << shift) - 1)) * 16;              // (kThreads is a multiple of a row's vectors)
+    auto place = [&](int e0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) {
+            const int q = (e0 + u * kThreads) >> shift;
+            row[u] = q / nh;
+            head[u] = h0 + q - row[u] * nh;
+        }
+    };
+    place(tid);
     // this thread's word, if it is this call's
     auto look = [&]() {
         const rec_t v = __hip_atomic_load(m + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -255,41 +255,58 @@ __device__ __forceinline__ void copy_rows(const StepArgs& x, const AcceptArgs& a
     if (tid < kMessage) publish(m + tid, ~a.nonce, 0u);
     const int base = s_msg[0], L = s_msg[1];
     if (base < 0) return;
-    const int h0 = w * x.heads, nh = min(c.Hkv, h0 + x.heads) - h0;
-    const int vpr = c.row_bytes / 16, total = (L + 1) * nh * vpr;
-    constexpr int kInFlight = 4;
+    const int total = (L + 1) * nh << shift;
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll 1
     for (int e0 = tid; e0 < total; e0 += kThreads * kInFlight) {
         u32x4 kv[kInFlight], vv[kInFlight];
-        size_t dst[kInFlight];
-#pragma unroll
-        for (int u = 0; u < kInFlight; ++u) {
-            const int e = e0 + u * kThreads;
-            if (e < total) {
-                const int q = e / vpr, v = e - q * vpr, k = q / nh, h = h0 + q - k * nh;
-                const size_t src = (((size_t)b * c.N + s_msg[2 + k]) * c.Hkv + h) * c.row_bytes + (size_t)v * 16;
-                dst[u] = (((size_t)b * c.Hkv + h) * c.S_cap + (size_t)(base + k)) * c.row_bytes + (size_t)v * 16;
-                kv[u] = *(const u32x4*)((const char*)c.k_tree + src);
-                vv[u] = *(const u32x4*)((const char*)c.v_tree + src);
-            }
-        }
+        if (e0 != tid) place(e0);
 #pragma unroll
         for (int u = 0; u < kInFlight; ++u)
             if (e0 + u * kThreads < total) {
-                *(u32x4*)((char*)c.k_cache + dst[u]) = kv[u];
-                *(u32x4*)((char*)c.v_cache + dst[u]) = vv[u];
+                const size_t src = (((size_t)b * c.N + s_msg[2 + row[u]]) * c.Hkv + head[u]) * c.row_bytes + v16;
+                kv[u] = *(const u32x4*)((const char*)c.k_tree + src);
+                vv[u] = *(const u32x4*)((const char*)c.v_tree + src);
+            }
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u)
+            if (e0 + u * kThreads < total) {
+                const size_t dst = (((size_t)b * c.Hkv + head[u]) * c.S_cap + (size_t)(base + row[u])) * c.row_bytes + v16;
+                *(u32x4*)((char*)c.k_cache + dst) = kv[u];
+                *(u32x4*)((char*)c.v_cache + dst) = vv[u];
             }
     }
 }
 
-// The path step for sequence b, run by all kThreads threads of one workgroup (thread i = node i).
-template <typename T, bool STEP>
+// Whether some attention workgroup of this launch has not read the lengths yet, which are about to change, and does not come to
+// it in time.  This thread's share of them.
+__device__ __forceinline__ bool lens_unread(const StepArgs& x, int b, long long started) {
+    bool unread = false;
+    word::Pair* const p = x.lens + (size_t)b * x.attn_wgs;
+    for (int w = threadIdx.x; w < x.attn_wgs; w += kThreads) {
+        bool here = word::here(p + w, x.tag);
+        while (!here) {
+            if ((long long)wall_clock64() - started >= x.copy_ticks / 2) { here = word::give_up(p + w, x.tag); break; }
+            __builtin_amdgcn_s_sleep(4);
+            here = word::here(p + w, x.tag);
+        }
+        if (here) word::taken(p + w, x.tag);
+        unread = unread || !here;
+    }
+    return unread;
+}
+
+// The path step for sequence b, run by all kThreads threads of one workgroup (thread i = node i).  Everything that the tree alone
+// decides (each node's ancestors, as a bit set; its depth) is found before the scan's records are there; behind them there is a
+// ballot, a maximum over the accepted nodes, and the path's nodes are the deepest one's bit set in ascending order, all written at once.
+// (From the records to the message: 4.5 us with a walk up the tree per node and one down the path, and the lengths' words looked at in between.)
+template <typename T, Part PART>
 __device__ __forceinline__ void path_step(const AcceptArgs& a, const StepArgs& x, Shared& sh, int b) {
     Rows& rows = sh.rows;
     const long long started = (long long)wall_clock64(), deadline = started + a.wait_ticks;
     const int i = threadIdx.x;
     const int N = a.N;
-    const int base = STEP ? x.compact.cache_len[b] : 0;
+    const int base = PART != kAlone ? x.compact.cache_len[b] : 0;
 
     // ---- everything node i needs that does not depend on another load is requested up front (the
     // step is a chain of dependent memory latencies, not of work)
@@ -305,7 +322,6 @@ __device__ __forceinline__ void path_step(const AcceptArgs& a, const StepArgs& x
         }
         // tree validation: node 0 is the only root, parents precede children
         sh.parent[i] = p;
-        sh.tok[i] = tok;
         bad = (i == 0) ? (p != -1) : (p < 0 || p >= i);
     }
     // the target logit of this node's token in its parent's row (needs only parent and token)
@@ -315,6 +331,22 @@ __device__ __forceinline__ void path_step(const AcceptArgs& a, const StepArgs& x
     const int n_rows = find_rows(a, b, rows);
     if (i == 0) sh.best = 0;
     bad = any_of(sh, bad);
+    uint64_t lo = 0, hi = 0;                                   // this node and its ancestors
+    int depth = 0;
+    if (!bad && i < N) {
+        for (int j = i; j >= 0; j = sh.parent[j]) {
+            if (j < 64) lo |= 1ull << j; else hi |= 1ull << (j - 64);
+            ++depth;
+        }
+        --depth;
+        sh.above[i][0] = lo;
+        sh.above[i][1] = hi;
+    }
+    bool unread = false;
+    if constexpr (PART == kBesideAttention) unread = lens_unread(x, b, started);
+    const bool too_deep = any_of(sh, depth >= a.max_path);
+    if constexpr (PART == kBesideAttention) unread = any_of(sh, unread);
+    bad = bad || too_deep;
 
     // ---- combine the statistics of row i's runs.  In stochastic mode only the rows of nodes with
     // children were scanned, and only those are combined (nothing reads a leaf's statistics: a node
@@ -324,9 +356,9 @@ __device__ __forceinline__ void path_step(const AcceptArgs& a, const StepArgs& x
     int late = 0;
     const Runs runs(a, n_rows);
     const int rank = i < N ? rows.rank[i] : -1;      // (of a malformed tree too: every record of the call is consumed)
+    rec_t* const r = a.rec + ((size_t)b * N + i) * a.plan.slots * 2;
+    const int parts = rank < 0 ? 0 : runs.of_chunk(rank * a.chunks + a.chunks - 1) - runs.of_chunk(rank * a.chunks) + 1;
     if (rank >= 0) {
-        const int j0 = runs.of_chunk(rank * a.chunks), parts = runs.of_chunk(rank * a.chunks + a.chunks - 1) - j0 + 1;
-        rec_t* r = a.rec + ((size_t)b * N + i) * a.plan.slots * 2;
         for (int c0 = 0; c0 < parts && !late; c0 += 4) {
             uint32_t bits[8];
             if (!await4(r + 2 * c0, min(4, parts - c0), a.nonce, deadline, bits)) { late = 1; break; }
@@ -349,96 +381,72 @@ __device__ __forceinline__ void path_step(const AcceptArgs& a, const StepArgs& x
                         S += __uint_as_float(bits[2 * s + 1]) * fast_exp2((__uint_as_float(bits[2 * s]) - m) * a.inv_temp_log2);
             }
         }
-        // consumed: a replay of this very call (same nonce) must not mistake them for its own
-        const uint32_t spent = ~a.nonce;
-        if (!late)
-            for (int c = 0; c < 2 * parts; ++c) publish(r + c, spent, 0u);
     }
-    late = any_of(sh, late);
-    if (late) {
-        int32_t* pth = a.path + (size_t)b * a.max_path;
-        int32_t* atk = a.accepted_tokens + (size_t)b * a.max_path;
+    // consumed: a replay of this very call (same nonce) must not mistake them for its own
+    auto spend = [&]() __attribute__((always_inline)) {
+        if (rank >= 0 && !late)
+            for (int c = 0; c < 2 * parts; ++c) publish(r + c, ~a.nonce, 0u);
+    };
+    if (i < N) { sh.g[i] = g; sh.m[i] = m; sh.S[i] = S; }
+    const bool some_late = any_of(sh, late);
+    int32_t* pth = a.path + (size_t)b * a.max_path;
+    int32_t* atk = a.accepted_tokens + (size_t)b * a.max_path;
+    if (some_late || bad) {
         for (int k = i; k < a.max_path; k += kThreads) { pth[k] = (k == 0) ? 0 : -1; atk[k] = -1; }
         if (i == 0) {
             a.accept_len[b] = 0;
             a.bonus_token[b] = -1;
-            if (a.status) a.status[b] = S4C_SEQ_TIMEOUT;
+            if (a.status) a.status[b] = some_late ? S4C_SEQ_TIMEOUT : S4C_SEQ_BAD_TREE;
             sh.node[0] = sh.len = 0;
         }
-        if constexpr (STEP) {
+        if constexpr (PART != kAlone) {
             __syncthreads();
-            announce_path(x, a, sh, b, base, started);
+            announce_path(x, a, sh, b, base, unread, started);
         }
+        spend();
         return;
     }
-    if (i < N) { sh.g[i] = g; sh.m[i] = m; sh.S[i] = S; }
+    // ---- local test of node i against its parent's row
+    bool ok = i < N;
+    if (ok && i > 0) {
+        if (a.mode == S4C_GREEDY) {
+            ok = tok == sh.g[par_i];
+        } else if (tok < 0 || tok >= a.V) {
+            ok = false;
+        } else {
+            const float pt = fast_exp2((lx - sh.m[par_i]) * a.inv_temp_log2) / sh.S[par_i];
+            ok = u_i * pd_i < pt;
+        }
+    }
+    const uint64_t passed = __ballot(ok);
+    if (i < 128 && (i & 63) == 0) sh.ok[i >> 6] = passed;
     __syncthreads();
-
-    int depth = 0;
-    if (!bad && i < N) {
-        // ---- local test of node i against its parent's row
-        int ok = 1;
-        if (i > 0) {
-            const int p = sh.parent[i];
-            if (a.mode == S4C_GREEDY) {
-                ok = (tok == sh.g[p]);
-            } else if (tok < 0 || tok >= a.V) {
-                ok = 0;
-            } else {
-                const float pt = fast_exp2((lx - sh.m[p]) * a.inv_temp_log2) / sh.S[p];
-                const float lhs = u_i * pd_i;
-                ok = (lhs < pt);
-            }
-        }
-        sh.ok[i] = ok;
-    }
-    __syncthreads();
-    int accepted = 0;
-    if (!bad && i < N) {
-        accepted = 1;
-        for (int j = i; j > 0; j = sh.parent[j]) { accepted &= sh.ok[j]; ++depth; }
-        if (depth >= a.max_path) bad = 1;
-    }
-    bad = any_of(sh, bad);
-
-    int32_t* pth = a.path + (size_t)b * a.max_path;
-    int32_t* atk = a.accepted_tokens + (size_t)b * a.max_path;
-    for (int k = i; k < a.max_path; k += kThreads) { pth[k] = (k == 0) ? 0 : -1; atk[k] = -1; }
-    if (bad) {
-        if (i == 0) {
-            a.accept_len[b] = 0;
-            a.bonus_token[b] = -1;
-            if (a.status) a.status[b] = S4C_SEQ_BAD_TREE;
-            sh.node[0] = sh.len = 0;
-        }
-        if constexpr (STEP) {
-            __syncthreads();
-            announce_path(x, a, sh, b, base, started);
-        }
-        return;
-    }
     // deepest accepted node, lowest index among equals: maximise depth*256 + (255 - i)
-    if (accepted && i < N) atomicMax(&sh.best, depth * 256 + (255 - i));
+    if (i < N && !(lo & ~sh.ok[0]) && !(hi & ~sh.ok[1])) atomicMax(&sh.best, depth * 256 + (255 - i));
     __syncthreads();
-    const int best = 255 - (sh.best & 255);
+    const int best = 255 - (sh.best & 255), L = sh.best >> 8;
+    const uint64_t path_lo = sh.above[best][0], path_hi = sh.above[best][1];
+    const bool on_path = i < N && (((i < 64 ? path_lo : path_hi) >> (i & 63)) & 1);
+    if (on_path) {                                             // its ancestors have lower numbers: it is node `depth` of the path
+        pth[depth] = i;
+        if (depth > 0) atk[depth - 1] = tok;
+        if constexpr (PART != kAlone) sh.node[depth] = i;
+    }
     if (i == best) {
-        const int L = depth;
-        int node = i;
-        for (int k = L; k >= 1; --k) {
-            pth[k] = node;
-            atk[k - 1] = sh.tok[node];
-            if constexpr (STEP) sh.node[k] = node;
-            node = sh.parent[node];
-        }
-        if constexpr (STEP) { sh.node[0] = 0; sh.len = L; }
+        if constexpr (PART != kAlone) sh.len = L;
         a.accept_len[b] = L;
-        a.bonus_token[b] = (a.mode == S4C_GREEDY) ? sh.g[i] : -1;
+        a.bonus_token[b] = (a.mode == S4C_GREEDY) ? g : -1;
         if (a.status) a.status[b] = 0;
     }
-    if constexpr (STEP) {
+    if constexpr (PART != kAlone) {
         __syncthreads();
-        announce_path(x, a, sh, b, base, started);
+        announce_path(x, a, sh, b, base, unread, started);
     }
+    for (int k = i; k < a.max_path; k += kThreads) {
+        if (k > L) pth[k] = -1;
+        if (k >= L) atk[k] = -1;
+    }
+    spend();
 }
 
 // one workgroup of the scan: run j of sequence b.  AHEAD chunks are in flight behind the one that is reduced.
@@ -530,9 +538,7 @@ __device__ __forceinline__ void scan_run(const AcceptArgs& a, Shared& sh, int b,
         float out_v;
         uint32_t out_w;
         if constexpr (STOCHASTIC) {
-            float mw = m_t;
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) mw = fmaxf(mw, __shfl_xor(mw, off));
+            const float mw = wave_max(m_t);
             float sw = m_t > -INFINITY ? s_t * fast_exp2((m_t - mw) * a.inv_temp_log2) : 0.f;
             sw = wave_sum(sw);
             if (lane == 0) { sh.v[wave] = mw; sh.s[wave] = sw; }
@@ -579,11 +585,11 @@ __device__ __forceinline__ void scan_run(const AcceptArgs& a, Shared& sh, int b,
 
 // Workgroup wg of the scan: the runs of all sequences (run number slowest, so that the ones without work are the last of
 // the grid rather than interleaved with the working ones), then the sequences' collectors.
-template <typename T, bool STOCHASTIC, bool STEP, int AHEAD>
+template <typename T, bool STOCHASTIC, Part PART, int AHEAD>
 __device__ __forceinline__ void scan_or_collect(const AcceptArgs& a, const StepArgs& x, Shared& sh, int wg) {
     const int j = wg / a.B, b = wg - j * a.B;
     if (j < a.plan.wgs) scan_run<T, STOCHASTIC, AHEAD>(a, sh, b, j);
-    else path_step<T, STEP>(a, x, sh, b);
+    else path_step<T, PART>(a, x, sh, b);
 }
 
 // (without a merge)

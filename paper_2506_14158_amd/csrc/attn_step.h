@@ -77,7 +77,7 @@ __device__ __forceinline__ void rest_of_launch(unsigned char* smem) {
         if (scan || copy) {
             if (threadIdx.x >= accept::kThreads) return;      // (barriers count the waves that are left)
             if (copy && wg - t.step.scan_wgs - merging >= a.B * t.step.copiers) return;          // (the grid's last row is not full)
-            if (scan) accept::scan_or_collect<T, KIND == kStochasticStep, true, 4>(t.accept, t.step, sh, wg);
+            if (scan) accept::scan_or_collect<T, KIND == kStochasticStep, accept::kBesideAttention, 4>(t.accept, t.step, sh, wg);
             else {
                 wg -= t.step.scan_wgs + merging;
                 accept::copy_rows(t.step, t.accept, sh, wg / t.step.copiers, wg % t.step.copiers);
