@@ -41,11 +41,8 @@ struct Arguments {
 
 // the first wave, once all waves of the workgroup have the lengths
 template <StepKind KIND>
-__device__ __forceinline__ void lens_read(const work::Lens& lens, long long started) {
+__device__ __forceinline__ void lens_read(const StepTail<KIND>& t, const AttnArgs& a, const work::Lens& lens, long long started) {
     asm volatile("" ::"v"(lens.mine));
-    const Arguments args;
-    const AttnArgs& a = args.attn();
-    const StepTail<KIND>& t = args.tail<KIND>();
     const int lane = threadIdx.x;
     if (lane < a.B) word::publish(t.step.lens + (size_t)lane * a.attn_wgs + blockIdx.x, t.step.tag, started, t.step.copy_ticks);
 }

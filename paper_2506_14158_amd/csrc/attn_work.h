@@ -104,12 +104,6 @@ __device__ __forceinline__ void build_masks(const AttnArgs& a, const int32_t* sp
         *(uint4*)(anc + tid * 4) = make_uint4(m[0], m[1], m[2], m[3]);
     }
 }
-// node of query row r (r / G without an integer division per row)
-__device__ __forceinline__ int node_of_row(int r, int G, float inv_G) {
-    int q = (int)((float)r * inv_G);
-    const int rem = r - q * G;
-    return rem < 0 ? q - 1 : rem >= G ? q + 1 : q;
-}
 
 }  // namespace work
 }  // namespace s4c

@@ -41,7 +41,7 @@ constexpr int lds_bytes_for(int ns, int d) { return ns * 2 * kBN * d * 2 + kMaxN
 
 template <int WR, int NS, int WPE, bool PAGED, bool F16, int kD, StepKind STEP>
 __global__ __launch_bounds__(WR * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
-void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP>) {
+void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
     constexpr int NT = WR * 64;
     constexpr int BM = WR * 32;
     constexpr int kRowB = kD * 2;                // bytes per K/V row
@@ -100,12 +100,34 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP>) {
     }
 
     const work::Lens lens(a);
+    // ---- while the lengths are on their way: this lane's query row, and where its pieces of the wave's Q rows lie in a unit's
+    const int rq0 = mt * BM + wave * 32;
+    const bool wave_on = rq0 < M;                         // some of this wave's rows exist
+    const int rq = rq0 + (lane & 31);
+    const bool rvalid = rq < M;
+    const int node = rvalid ? rq / G : 0, g = rvalid ? rq - node * G : 0;
+    size_t q_off[32 / kRPI];
+    {
+        // rows rq0 + kRPI c + lane / kLPR, one step of kRPI rows after the other; past the last row: the last
+        const int r0 = rq0 + lane / kLPR, step_nd = kRPI / G, step_g = kRPI - step_nd * G;
+        int nd = r0 / G, gg = r0 - nd * G;
+        const size_t last = (size_t)(N - 1) * a.Hq + (G - 1);
+#pragma unroll
+        for (int c = 0; c < 32 / kRPI; ++c) {
+            const int row = kRPI * c + lane / kLPR, pc = lane % kLPR;
+            const size_t at = (size_t)nd * a.Hq + gg;
+            q_off[c] = (at < last ? at : last) * kRowB + ((pc ^ k_swz(row)) << 4);
+            nd += step_nd;
+            gg += step_g;
+            if (gg >= G) { gg -= G; ++nd; }
+        }
+    }
     work::Walk cw = work::walk_first(a, lens, team);      // what is multiplied
     const long long started = STEP != kNoStep || a.tag != 0 ? (long long)wall_clock64() : 0;
     if (cw.b < 0) {
         if constexpr (STEP != kNoStep) {
             __syncthreads();
-            lens_read<STEP>(lens, started);
+            lens_read(tail, a, lens, started);
         }
         if (work::leaves_empty(a, team)) parts::put_empty<kD, 1>(a, team, mt * WR + wave, 0, started);
         return;
@@ -191,32 +213,21 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP>) {
     // other stages.  All of it goes straight to LDS, so that waiting for Q does not mean waiting for the tiles behind it
     // (the compiler knows nothing of these loads; a wait of its own for a register load counts them in).
     const uint32_t q_stage = (NS - 2) * kStageB + wave * (32 * kRowB);
-    const int rq0 = mt * BM + wave * 32;
     bool len_bad = work::usable(a, lens.at(a, cw.b)) != lens.at(a, cw.b);
     if constexpr (PAGED) len_bad = len_bad || work::pages_are_bad(a, cw.b, work::usable(a, lens.at(a, cw.b)));
     if (wave < 2 && wave * 64 + lane < N)
         dma4(a.parent + (size_t)cw.b * N + wave * 64 + lane,
              __builtin_amdgcn_readfirstlane(lds0 + NS * kStageB + kMaxNodes * 16 + wave * 256));
     {
-        const float inv_G = 1.0f / (float)G;
         const unsigned char* qb = (const unsigned char*)a.q + ((size_t)cw.b * N * a.Hq + cw.kvh * G) * kRowB;
 #pragma unroll
-        for (int c = 0; c < 32 / kRPI; ++c) {
-            const int row = kRPI * c + lane / kLPR, pc = lane % kLPR;
-            const int r = min(rq0 + row, M - 1), nd = work::node_of_row(r, G, inv_G);        // past the last row: any row
-            dma16(qb + ((size_t)nd * a.Hq + (r - nd * G)) * kRowB + ((pc ^ k_swz(row)) << 4),
-                  __builtin_amdgcn_readfirstlane(lds0 + q_stage + c * 1024));
-        }
+        for (int c = 0; c < 32 / kRPI; ++c) dma16(qb + q_off[c], __builtin_amdgcn_readfirstlane(lds0 + q_stage + c * 1024));
     }
     for (int t = 0; t < NS - 2 && t < n_share; ++t) issue_next();
     if (issued == NS - 2) wait_vmcnt<2 * CH * (NS - 2)>(); else wait_vmcnt<0>();
 
     // ---- this lane's query row.  Q^T fragments: B operand of step t holds d = 16 t + 8 g32 + (0..7) of the row.
     // A later segment's fragments (and parent[]) are loaded before the previous one is written out.
-    const bool wave_on = rq0 < M;                         // some of this wave's rows exist
-    const int rq = rq0 + (lane & 31);
-    const bool rvalid = rq < M;
-    const int node = rvalid ? rq / G : 0, g = rvalid ? rq - node * G : 0;
     bf16x8 qf[kKT];
 #pragma unroll
     for (int t = 0; t < kKT; ++t) {
@@ -236,7 +247,7 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP>) {
 #pragma unroll
     for (int t = 0; t < kKT; ++t) asm volatile("" : "+v"(qf[t]));          // in registers before the barrier
     __syncthreads();                                      // Q and parent[] are here, their stages free
-    if constexpr (STEP != kNoStep) lens_read<STEP>(lens, started);
+    if constexpr (STEP != kNoStep) lens_read(tail, a, lens, started);
     while (issued < NS - 1 && issued < n_share) issue_next();
 
     int parent = -1, b_known = cw.b;

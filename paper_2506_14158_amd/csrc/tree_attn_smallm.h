@@ -78,7 +78,7 @@ struct Cfg {
 
 template <class C, bool PAGED, StepKind STEP>
 __global__ __launch_bounds__(C::kThreads) __attribute__((amdgpu_waves_per_eu(C::kPerCu * C::kWaves / 4, 2)))
-void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP>) {
+void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP> tail) {
     constexpr int kD = C::kD, kKG = C::kKG, kRBW = C::kRBW, kNR = C::kNR, kRowB = C::kRowB;
     constexpr int kThreads = C::kThreads, kCH = C::kCH;
     constexpr bool kIs32 = C::kElem == kF32, F16 = C::kElem == kH16;
@@ -138,12 +138,33 @@ void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP>) {
     const uint32_t tree_stride = (uint32_t)a.Hkv * kRowB;
 
     const work::Lens lens(a);
+    // ---- while the lengths are on their way: this lane's query row, and where its pieces of the wave's Q rows lie in a unit's
+    const int rq0 = (mt * kRBW + rb) * 32;
+    const int rq = rq0 + (lane & 31);
+    const bool rvalid = rq < M;
+    const int node = rvalid ? rq / G : 0, gh = rvalid ? rq - node * G : 0;
+    size_t q_off[C::kTileKB / 1024];
+    {
+        // rows rq0 + kRPI c + lane / kLPR, one step of kRPI rows after the other; past the last row: the last
+        const int r0 = rq0 + lane / kLPR, step_nd = kRPI / G, step_g = kRPI - step_nd * G;
+        int nd = r0 / G, g = r0 - nd * G;
+        const size_t last = (size_t)(N - 1) * a.Hq + (G - 1);
+#pragma unroll
+        for (int c = 0; c < C::kTileKB / 1024; ++c) {
+            const int row = kRPI * c + lane / kLPR, pc = lane % kLPR;
+            const size_t at = (size_t)nd * a.Hq + g;
+            q_off[c] = (at < last ? at : last) * kRowB + ((pc ^ C::k_swz(row)) << 4);
+            nd += step_nd;
+            g += step_g;
+            if (g >= G) { g -= G; ++nd; }
+        }
+    }
     work::Walk cw = work::walk_first(a, lens, team);      // what is multiplied
     const long long started = STEP != kNoStep || a.tag != 0 ? (long long)wall_clock64() : 0;
     if (cw.b < 0) {
         if constexpr (STEP != kNoStep) {
             __syncthreads();
-            lens_read<STEP>(lens, started);
+            lens_read(tail, a, lens, started);
         }
         if (work::leaves_empty(a, team) && kg < kOwners) parts::put_empty<kD, kOwners>(a, team, mt * kRBW + rb, kg, started);
         return;
@@ -229,38 +250,27 @@ void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP>) {
     // rounds.  All of it goes straight to LDS, so that waiting for Q does not mean waiting for the rounds behind it
     // (the compiler knows nothing of these loads; a wait of its own for a register load counts them in).
     const uint32_t q_stage = (uint32_t)(kNR - 1) * C::kRoundB + wave * C::kTileKB;
-    const int rq0 = (mt * kRBW + rb) * 32;
     bool len_bad = work::usable(a, lens.at(a, cw.b)) != lens.at(a, cw.b);
     if constexpr (PAGED) len_bad = len_bad || work::pages_are_bad(a, cw.b, work::usable(a, lens.at(a, cw.b)));
     if (wave < 2 && wave * 64 + lane < N)
         dma4(a.parent + (size_t)cw.b * N + wave * 64 + lane,
              __builtin_amdgcn_readfirstlane(lds0 + C::kRingB + kMaxNodes * 16 + wave * 256));
     {
-        const float inv_G = 1.0f / (float)G;
         const unsigned char* qb = (const unsigned char*)a.q + ((size_t)cw.b * N * a.Hq + cw.kvh * G) * kRowB;
 #pragma unroll
-        for (int c = 0; c < C::kTileKB / 1024; ++c) {
-            const int row = kRPI * c + lane / kLPR, pc = lane % kLPR;
-            const int r = min(rq0 + row, M - 1), nd = work::node_of_row(r, G, inv_G);        // past the last row: any row
-            dma16(qb + ((size_t)nd * a.Hq + (r - nd * G)) * kRowB + ((pc ^ C::k_swz(row)) << 4),
-                  __builtin_amdgcn_readfirstlane(lds0 + q_stage + c * 1024));
-        }
+        for (int c = 0; c < C::kTileKB / 1024; ++c) dma16(qb + q_off[c], __builtin_amdgcn_readfirstlane(lds0 + q_stage + c * 1024));
     }
 #pragma unroll
     for (int r = 0; r < kNR - 1; ++r)
         if (pw.b >= 0) issue_round();
-    if (issued == kNR - 1) wait_vmcnt<2 * kCH * (kNR - 1)>(); else wait_vmcnt<0>();
-
     if constexpr (STEP != kNoStep) {
         __syncthreads();
-        lens_read<STEP>(lens, started);
+        lens_read(tail, a, lens, started);
     }
+    if (issued == kNR - 1) wait_vmcnt<2 * kCH * (kNR - 1)>(); else wait_vmcnt<0>();
 
     // ---- this lane's query row; a later segment's Q fragments (and parent[]) are loaded before the previous one is
     // written out
-    const int rq = rq0 + (lane & 31);
-    const bool rvalid = rq < M;
-    const int node = rvalid ? rq / G : 0, gh = rvalid ? rq - node * G : 0;
     uint4 qf[kKT];           // 16-bit: elements 16 t + 8 g32 .. + 7; fp32: elements 8 t + 4 g32 .. + 3
 #pragma unroll
     for (int t = 0; t < kKT; ++t) {
