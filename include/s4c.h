@@ -58,7 +58,9 @@ typedef enum { S4C_GREEDY = 0, S4C_STOCHASTIC = 1 } s4c_accept_mode;
 #define S4C_SEQ_BAD_LEN  2     /* cache_len out of range / accepted rows do not fit S_cap */
 #define S4C_SEQ_TIMEOUT  4     /* s4c_accept_path, s4c_accept_resample: the workgroups of a sequence could not
                                   hand their partial results to each other within the waiting limit (a GPU
-                                  that stopped scheduling them); accept_len = 0, path = [0], bonus = -1 */
+                                  that stopped scheduling them); accept_len = 0, path = [0], bonus = -1.
+                                  s4c_tree_attn and s4c_tree_attn_paged: the same between workgroups that attend and
+                                  that merge; rows whose parts did not come are zero */
 
 typedef struct {
     int32_t B;       /* sequences */
@@ -89,6 +91,9 @@ size_t s4c_tree_attn_workspace_size(const s4c_attn_shape* shape, int32_t max_cac
  *                   gets an all-zero output.
  *   workspace       >= s4c_tree_attn_workspace_size(shape, max_cache_len) bytes, 256-byte
  *                   aligned; contents need not be initialised; may be NULL if that size is 0.
+ * Workgroups that merge the parts of divided sequences wait for them in the same launch: 2 s, or S4C_MERGE_WAIT_US
+ * microseconds (environment, an integer >= 0, read at every call), then the sequence is flagged S4C_SEQ_TIMEOUT.  A call by
+ * itself always completes, and so do two that overlap in time.  Calls that may overlap must not share a workspace.
  * Results are deterministic: how the keys are divided between workgroups, and the order in which parts are merged,
  * follow from the shape, max_cache_len and cache_len[]. */
 s4c_status s4c_tree_attn(const s4c_attn_shape* shape, const void* q, const void* k_tree,
@@ -300,8 +305,8 @@ s4c_status s4c_draft_linear(int32_t T, int32_t H, int32_t Hout, int32_t dtype, c
                             void* hip_stream);
 
 /* One verification step in one call: s4c_tree_attn, then s4c_accept_path, then s4c_kv_compact, same results, arguments
- * and device status words as the three calls with these arguments.  The attention merge, the acceptance and
- * the compaction share one launch where the logits have the shape's dtype.  S4C_SEQ_TIMEOUT may also appear in
+ * and device status words as the three calls with these arguments.  Where the logits have the shape's dtype, the attention merge, the
+ * acceptance and the compaction share one launch, which is also the attention's where that leaves room on the chip.  S4C_SEQ_TIMEOUT may also appear in
  * compact_status, if a workgroup that copies a sequence's rows did not hear of its path within the collector's waiting
  * time (s4c_accept_path) plus 2 s, or within S4C_COPY_WAIT_US microseconds (environment, an integer >= 0, read at
  * every call): that sequence's rows are not (all) appended, its cache_len stays and its dst_index is -1.

@@ -101,6 +101,33 @@ inline AttnDivision plan_division(int B, int Hkv, int N, int M, int max_cache_le
     return p;
 }
 
+// Workgroups of an attention launch that wait for others of it: merging ones, and in a step's only launch a collector for each
+// sequence and its copiers.  Every XCD starts a launch's workgroups in order, but which of two streams it serves first is its own
+// affair: with one XCD full of waiting workgroups of one call and another full of the other's, neither call's attention would
+// be started, until the waits run out.  So a launch keeps to four fifths of an XCD's CUs with all of its waiting
+// workgroups together: whatever an XCD serves first, a call's waiting workgroups and the collectors (at most one sequence
+// in eight CUs) of another leave a CU of it to those that are waited for.
+// Merging waves beyond that take several turns, and a sequence has fewer copiers, each with more heads.
+struct AttnWaiting { int merging, heads; };            // workgroups that merge; KV heads of a copier
+inline int copiers_of(int Hkv, int heads) { return (Hkv + heads - 1) / heads; }
+// merging: workgroups that would merge in one turn; sequences: of a step's only launch (0: none), at most an eighth of the CUs;
+// most_copiers: of a sequence
+inline AttnWaiting plan_waiting(int merging, int sequences, int Hkv, int most_copiers, int cus) {
+    const int all = cus / 8 * 4 / 5 * 8;
+    AttnWaiting w = {merging, 1};
+    int taken = 0;
+    if (sequences > 0) {
+        int copiers = all / 3 / sequences;
+        copiers = copiers < 1 ? 1 : copiers > most_copiers ? most_copiers : copiers;
+        w.heads = (Hkv + copiers - 1) / copiers;
+        taken = sequences * (1 + copiers_of(Hkv, w.heads));
+    }
+    const int rest = all - taken > 1 ? all - taken : 1;
+    const int turns = (merging + rest - 1) / rest;
+    if (turns > 1) w.merging = (merging + turns - 1) / turns;
+    return w;
+}
+
 namespace work {
 
 // prefix length used for the division: an out-of-range cache_len (the sequence is flagged) counts as empty

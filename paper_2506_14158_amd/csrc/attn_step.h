@@ -6,7 +6,8 @@
 // in this order, each waiting only for workgroups before it.  The appended rows lie behind every key that the attention
 // reads; the lengths, which all its workgroups read, are advanced when all of them have said that they have.
 // Two launches and one, a whole step, us: fp32, 4 heads, 128 keys + 15 nodes 20.9 and 13.4; 32 heads, 1024 keys + 60 nodes, V 32000
-// 22.3 and 17.0; 3 x 8 heads of size 64, 2049 keys 28.1 and 23.8; 4 x 40 heads, 4096 keys 84.1 and 75.0.
+// 22.3 and 16.9; 3 x 8 heads of size 64, 2049 keys 28.1 and 23.4; 4 x 40 heads, 4096 keys 84.3 and 76.6 (merging waves in two turns;
+// in one, more workgroups than plan_waiting allows: 74.5).
 #pragma once
 #include "accept_roles.h"
 #include "attn_parts.h"
@@ -50,10 +51,16 @@ __device__ __forceinline__ void lens_read(const StepTail<KIND>& t, const AttnArg
 // workgroups of a launch: the attention's, whole rounds over the XCDs, and the others
 inline int attn_workgroups(const AttnArgs& a) { return (int)(((long)a.teams + 7) / 8 * 8 * a.mtiles); }
 inline int merge_workgroups(const AttnArgs& a, int threads) { return a.tag != 0 ? (parts::tasks(a) + threads / 64 - 1) / (threads / 64) : 0; }
-inline int rest_workgroups(const AttnArgs& a, const StepTail<kNoStep>&, int threads) { return merge_workgroups(a, threads); }
+inline int rest_of(AttnArgs& a, StepTail<kNoStep>&, int threads) {
+    return a.merge_wgs = plan_waiting(merge_workgroups(a, threads), 0, a.Hkv, 0, a.cus).merging;
+}
 template <StepKind KIND>
-inline int rest_workgroups(const AttnArgs& a, const StepTail<KIND>& t, int threads) {
-    return t.step.scan_wgs + merge_workgroups(a, threads) + a.B * t.step.copiers;
+inline int rest_of(AttnArgs& a, StepTail<KIND>& t, int threads) {
+    const AttnWaiting w = plan_waiting(merge_workgroups(a, threads), a.B, a.Hkv, accept::kMostCopiers, a.cus);
+    a.merge_wgs = w.merging;
+    t.step.heads = w.heads;
+    t.step.copiers = copiers_of(a.Hkv, w.heads);
+    return t.step.scan_wgs + a.merge_wgs + a.B * t.step.copiers;
 }
 
 // The attention's workgroups are row 0 of the grid, the others the rows behind it: told apart without waiting for an argument
@@ -68,7 +75,7 @@ __device__ __forceinline__ void rest_of_launch(unsigned char* smem) {
     if constexpr (KIND != kNoStep) {
         const StepTail<KIND>& t = args.tail<KIND>();
         typedef typename std::conditional<E == parts::kF32, float, typename std::conditional<E == parts::kH16, f16_t, bf16_t>::type>::type T;
-        const int merging = a.tag != 0 ? (parts::tasks(a) + THREADS / 64 - 1) / (THREADS / 64) : 0;
+        const int merging = a.merge_wgs;
         accept::Shared& sh = *(accept::Shared*)smem;
         const bool scan = wg < t.step.scan_wgs, copy = !scan && wg - t.step.scan_wgs >= merging;
         if (scan || copy) {
@@ -83,7 +90,13 @@ __device__ __forceinline__ void rest_of_launch(unsigned char* smem) {
         }
         wg -= t.step.scan_wgs;
     }
-    parts::take<D, E, 8>(a, wg * (THREADS / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+    const int turn = a.merge_wgs * (THREADS / 64), all = parts::tasks(a);
+    int task = wg * (THREADS / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (task >= turn) return;                                // (the grid's last row is not full)
+    parts::take<D, E, 8>(a, task);
+    // (Further turns have code of their own, units of few parts: as turns of one loop they cost the first 0.2 us.)
+    if (__builtin_expect(turn < all, 0))
+        while ((task += turn) < all) parts::take<D, E, 4>(Arguments().attn(), task);
 }
 
 }  // namespace s4c

@@ -71,7 +71,9 @@ struct AttnArgs {
     int32_t tile_rows;  // query rows per workgroup
     int32_t tile_keys, tile_shift;   // keys per tile of the kernel that will run, and its log2
     int32_t part_keys;  // waves that share the columns of a row in a part (attn_parts.h)
+    int32_t cus;        // compute units of the device
     int32_t attn_wgs;   // set by the launcher: workgroups of the launch that attend
+    int32_t merge_wgs;  // set by the launcher: and that merge (plan_waiting)
     uint64_t tag;       // of this call's parts; 0: the next launch merges them
     long long wait_ticks;     // how long a merging workgroup waits for its parts (100 MHz wall clock)
     float scale_log2; // softmax scale * log2(e)

@@ -204,7 +204,8 @@ s4c_status tree_attn_prepare(const s4c_attn_shape* shape, const void* q, const v
     a.scale_log2 = (scale > 0.f ? scale : 1.0f / sqrtf((float)shape->D)) * kLog2e;
     a.block_table = block_table; a.max_blocks = max_blocks; a.page_shift = page_shift; a.num_pages = num_pages;
     a.part_keys = p.tile.part_keys;
-    a.attn_wgs = 0;
+    a.cus = device_cus();
+    a.attn_wgs = a.merge_wgs = 0;
     a.tag = 0;
     a.wait_ticks = 0;
     *plan = p;
@@ -672,7 +673,7 @@ namespace {
 size_t step_bytes(const s4c_attn_shape& s, int32_t V) {
     return s4c_accept_path_workspace_size(s.B, s.N, V) + (step_message_bytes(s.B, s.Hkv) + 255) / 256 * 256;
 }
-constexpr int kOneLaunchMostSequences = 32;
+constexpr int kOneLaunchMostSequences = 32;           // (plan_waiting)
 size_t one_launch_bytes(const s4c_attn_shape& s) {
     return s.B > kOneLaunchMostSequences ? 0 : (size_t)s.B * device_cus() * 2 * sizeof(word::Pair);      // at most two workgroups a CU
 }
@@ -680,7 +681,7 @@ size_t one_launch_bytes(const s4c_attn_shape& s) {
 // A step in one launch: where the attention leaves places for the collectors and for enough scanning workgroups that the scan
 // is not the longer half.
 bool plan_one_launch(const s4c_step& p, const AttnPlan& plan, const AttnArgs& attn, AcceptArgs& accept) {
-    if (p.logits_dtype != p.shape.dtype || attn.split == 0 || attn.B > kOneLaunchMostSequences) return false;
+    if (p.logits_dtype != p.shape.dtype || attn.split == 0 || attn.B > kOneLaunchMostSequences || attn.B * 8 > attn.cus) return false;
     if (p.accept_workspace_bytes < step_bytes(p.shape, p.V) + (size_t)attn.B * attn_workgroups(attn) * sizeof(word::Pair)) return false;
     const int places = device_cus() * plan.tile.per_cu - attn_workgroups(attn) - attn.B;
     const int wgs = places / attn.B < accept.plan.wgs ? places / attn.B : accept.plan.wgs;

@@ -534,13 +534,13 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
 int pick_wr(int M) { return M <= 128 ? 4 : 8; }
 
 template <int WR, int NS, int WPE, bool PAGED, bool F16, int D, StepKind STEP>
-hipError_t launch(AttnArgs a, const StepTail<STEP>& tail, hipStream_t st) {
+hipError_t launch(AttnArgs a, StepTail<STEP> tail, hipStream_t st) {
     constexpr int kLds = lds_bytes_for(NS, D);
     static std::atomic<uint64_t> lds_set{0};
     const hipError_t ea = ensure_dynamic_lds((const void*)tree_attn_mfma_kernel<WR, NS, WPE, PAGED, F16, D, STEP>, kLds, lds_set);
     if (ea != hipSuccess) return ea;
     a.attn_wgs = attn_workgroups(a);
-    const dim3 grid = launch_grid(a, rest_workgroups(a, tail, WR * 64)), block(WR * 64);
+    const dim3 grid = launch_grid(a, rest_of(a, tail, WR * 64)), block(WR * 64);
     hipLaunchKernelGGL((tree_attn_mfma_kernel<WR, NS, WPE, PAGED, F16, D, STEP>), grid, block, kLds, st, a, tail);
     return hipGetLastError();
 }

@@ -571,12 +571,12 @@ void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP> tail) {
 }
 
 template <class C, bool PAGED, StepKind STEP>
-hipError_t launch(AttnArgs a, const StepTail<STEP>& tail, hipStream_t st) {
+hipError_t launch(AttnArgs a, StepTail<STEP> tail, hipStream_t st) {
     static std::atomic<uint64_t> lds_set{0};
     const hipError_t ea = ensure_dynamic_lds((const void*)tree_attn_smallm_kernel<C, PAGED, STEP>, C::kLdsBytes, lds_set);
     if (ea != hipSuccess) return ea;
     a.attn_wgs = attn_workgroups(a);
-    const dim3 grid = launch_grid(a, rest_workgroups(a, tail, C::kThreads)), block(C::kThreads);
+    const dim3 grid = launch_grid(a, rest_of(a, tail, C::kThreads)), block(C::kThreads);
     hipLaunchKernelGGL((tree_attn_smallm_kernel<C, PAGED, STEP>), grid, block, C::kLdsBytes, st, a, tail);
     return hipGetLastError();
 }

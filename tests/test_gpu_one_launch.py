@@ -1,0 +1,105 @@
+"""A step in one launch, and divided attention merged in its own: against the oracle and the separate calls, eagerly and from a captured
+graph, where merging waves take several turns, sequences have fewer copiers, and the waits run out."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import s4c_oracle as O
+from paper_2506_14158_amd import synth
+from paper_2506_14158_amd.verify import TreeVerifier
+from tests.util import attn_errors, to_device
+
+pytestmark = pytest.mark.gpu
+C = synth.CONFIGS
+TIMEOUT = 4
+TOL = {"f32": (1e-5, 1e-5), "bf16": (1e-2, 2e-2), "f16": (2e-3, 4e-3)}      # the storage type's rounding of P and of the output, as in the parity tests
+
+CASES = [
+    synth.scaled(C[3], name="several-turns", B=4, Hq=40, Hkv=40, P=1100, V=4000, index=0),               # 1280 merging tasks
+    synth.scaled(C[3], name="32-sequences", B=32, Hq=5, Hkv=5, P=300, N=20, levels=5, V=2000, ragged=True, index=0),     # two copiers each
+    synth.scaled(C[2], name="odd-f16", B=3, Hq=7, Hkv=7, P=777, N=33, levels=5, V=5003, dtype="f16", ragged=True, index=0),
+    synth.scaled(C[1], name="f32-d64", B=2, Hq=3, Hkv=3, P=900, N=17, V=3001, index=0),
+    synth.scaled(C[5], name="many-rows", B=1, Hq=32, Hkv=4, P=2000, N=60, levels=6, V=9001, index=0),
+    synth.scaled(C[4], name="80-rows-d64", B=2, Hq=10, Hkv=5, D=64, P=1500, N=40, levels=6, V=6000, index=0),
+]
+
+
+def _same(a, b):
+    return all(torch.equal(x.contiguous().view(torch.uint8), y.contiguous().view(torch.uint8)) for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("cfg", CASES, ids=lambda c: c.name)
+def test_eager_and_replayed_steps(cfg):
+    par = synth.make_parent(cfg)
+    at, ac = synth.make_attn_inputs(cfg), synth.make_accept_inputs(cfg, par)
+    d = to_device(cfg, par, at, ac)
+    mode = 0 if cfg.mode == "greedy" else 1
+    tv = TreeVerifier(cfg.B, cfg.N, cfg.Hq, cfg.Hkv, cfg.D, cfg.S_cap, cfg.V, d["q"].dtype, cfg.levels, cfg.P)
+    k, v, n = d["k_cache"].clone(), d["v_cache"].clone(), d["cache_len"].clone()
+    rest = (d["logits"], d["tokens"], mode, d["p_draft"], d["uniforms"], cfg.temperature)
+    step = lambda: tv.step(d["q"], d["k_tree"], d["v_tree"], k, v, n, d["parent"], *rest)
+    seen = lambda: [t.clone() for t in (tv.out, tv.path, tv.accept_len, tv.accepted_tokens, tv.bonus_token, tv.dst_index, tv.attn_status,
+                                        tv.accept_status, tv.compact_status, k, v, n)]
+
+    def reset():
+        for dst, src in ((k, "k_cache"), (v, "v_cache"), (n, "cache_len")):
+            dst.copy_(d[src])
+        tv.out.fill_(7.0)
+
+    reset()
+    step()
+    torch.cuda.synchronize()
+    first = seen()
+    ref, _ = O.tree_attn(at.q, at.k_tree, at.v_tree, at.k_cache, at.v_cache, at.cache_len, par)
+    amax, rel = attn_errors(tv.out, ref)
+    assert amax <= TOL[cfg.dtype][0] and rel <= TOL[cfg.dtype][1], (amax, rel)
+    r = O.accept_path(ac.logits, par, ac.tokens, cfg.mode, cfg.levels, ac.p_draft, ac.uniforms, cfg.temperature)
+    assert np.array_equal(tv.path.cpu().numpy(), r["path"]) and np.array_equal(tv.accept_len.cpu().numpy(), r["accept_len"])
+    kc, vc, cl = at.k_cache.copy(), at.v_cache.copy(), at.cache_len.copy()
+    O.kv_compact(at.k_tree, at.v_tree, kc, vc, cl, r["path"], r["accept_len"])
+    assert np.array_equal(n.cpu().numpy(), cl)
+    assert np.array_equal(k.cpu().contiguous().view(torch.uint8).numpy(), kc.view(np.uint8))
+    assert np.array_equal(v.cpu().contiguous().view(torch.uint8).numpy(), vc.view(np.uint8))
+    g, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(g, stream=side):
+            step()
+    for call in (g.replay, g.replay, step, g.replay):
+        reset()
+        torch.cuda.synchronize()
+        call()
+        torch.cuda.synchronize()
+        assert _same(seen(), first)
+
+
+@pytest.mark.parametrize("cfg", [CASES[0], CASES[4]], ids=lambda c: c.name)
+def test_merging_waves_that_give_up_flag_the_sequence(cfg, monkeypatch):
+    """A waiting time of zero: a merging wave that does not find all parts at its first look flags the sequence and leaves zero rows; sequences
+    that are not flagged are right.  With the usual wait the same buffers and the same graph's words give the right rows again."""
+    par = synth.make_parent(cfg)
+    at = synth.make_attn_inputs(cfg)
+    d = to_device(cfg, par, at, synth.make_accept_inputs(cfg, par))
+    tv = TreeVerifier(cfg.B, cfg.N, cfg.Hq, cfg.Hkv, cfg.D, cfg.S_cap, cfg.V, d["q"].dtype, cfg.levels, cfg.P)
+    call = lambda: tv.tree_attn(d["q"], d["k_tree"], d["v_tree"], d["k_cache"], d["v_cache"], d["cache_len"], d["parent"])
+    call()
+    torch.cuda.synchronize()
+    want = tv.out.clone()
+    g, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    monkeypatch.setenv("S4C_MERGE_WAIT_US", "0")
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(g, stream=side):
+            call()
+    for again in (call, g.replay, g.replay):
+        tv.out.fill_(7.0)
+        torch.cuda.synchronize()
+        again()
+        torch.cuda.synchronize()
+        flags = tv.attn_status.cpu().numpy()
+        assert set(flags.tolist()) <= {0, TIMEOUT}
+        for b in range(cfg.B):
+            right = (tv.out[b] == want[b])
+            assert bool(right.all()) if flags[b] == 0 else bool((right | (tv.out[b] == 0)).all())
+    monkeypatch.delenv("S4C_MERGE_WAIT_US")
+    call()
+    torch.cuda.synchronize()
+    assert int(tv.attn_status.abs().sum()) == 0 and torch.equal(tv.out, want)
