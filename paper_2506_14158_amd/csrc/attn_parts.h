@@ -90,11 +90,15 @@ __device__ __forceinline__ void store_out(void* out, size_t at, f32x4 v) {
 
 // ---- A wave hands over its columns of a row block: KEYS such waves have equal shares of the D / 8 slabs, this one is number
 // `key`.  `slab(q)` is its slab q: columns 8 (key slabs + q) + 4 (lane / 32) .. + 3 of row 32 block + lane % 32.  m, l: the row's.
-template <int D, int KEYS, class Slab>
+// LATE: the places are found here rather than kept while tiles are multiplied, for a kernel that has no registers left (it kept them, and the
+// tag, in scratch: 8 layers of 4 x 64/8 heads, 20 nodes 166 us against 162.5, a step of 32/8 heads, 4000 keys 27.1 against 26.4; in the kernel for few rows,
+// which has room, it costs 0.15 us a launch).
+template <int D, int KEYS, bool LATE = false, class Slab>
 __device__ __forceinline__ void put(const AttnArgs& a, int team, int block, int key, float m, float l, long long started, Slab slab) {
     constexpr int kSlabs = D / 8 / KEYS;
     typedef Region<D> R;
-    const int lane = threadIdx.x & 63;
+    int lane = threadIdx.x & 63;
+    if constexpr (LATE) asm volatile("" : "+v"(lane));
     if (32 * block >= a.M) return;
     const __amdgpu_buffer_rsrc_t r = resource(R::of(a, team), R::bytes(a.M));
     auto store = [&](auto policy) __attribute__((always_inline)) {

@@ -60,7 +60,7 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
 
     static_assert(sizeof(accept::Shared) <= NS * kStageB, "the ring is also what the other workgroups of a step have");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    if (blockIdx.y > 0) {
+    if (__builtin_expect(blockIdx.y > 0, 0)) {              // (the attention's code first: a far jump at its start costs a fetch)
         rest_of_launch<kD, F16 ? parts::kH16 : parts::kB16, NT, STEP>(smem);
         return;
     }
@@ -508,13 +508,13 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
             }
         }
     } else if (a.split > 0) {
-        parts::put<kD, 1>(a, team, mt * WR + wave, 0, m_run, l_tot, started, [&](int q) __attribute__((always_inline)) {
+        parts::put<kD, 1, true>(Arguments().attn(), team, mt * WR + wave, 0, m_run, l_tot, started, [&](int q) __attribute__((always_inline)) {
             return f32x4{o[q >> 2][4 * (q & 3)], o[q >> 2][4 * (q & 3) + 1], o[q >> 2][4 * (q & 3) + 2], o[q >> 2][4 * (q & 3) + 3]};
         });
     } else {
         if (rvalid) {
             const size_t prow = work::part_row(a, team, work::part_slot(cw)) + rq;
-            float* orow = a.ws_o + prow * kD + 4 * g32;
+            float* orow = Arguments().attn().ws_o + prow * kD + 4 * g32;       // (not kept in scratch while tiles are multiplied)
 #pragma unroll
             for (int db = 0; db < kDB; ++db)
 #pragma unroll

@@ -89,7 +89,7 @@ void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP> tail) {
     constexpr int kLPR = kRowB / 16;                          // lanes (16-byte chunks) per row in a direct-to-LDS load
     constexpr int kRPI = 64 / kLPR;                           // rows per load instruction
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    if (blockIdx.y > 0) {
+    if (__builtin_expect(blockIdx.y > 0, 0)) {              // (the attention's code first: a far jump at its start costs a fetch)
         rest_of_launch<kD, C::kElem, kThreads, STEP>(smem);
         return;
     }
