@@ -25,7 +25,7 @@
 //     ancestors; 128-bit masks built from parent[] in LDS) run a masked copy of the body.  Rows
 //     past the end of a ragged tile are clamped to its last valid row (in bounds, finite).
 //   * The keys are divided between teams of workgroups (attn_division.h); parts of a divided unit are written
-//     unnormalised for the merge kernel.
+//     unnormalised (attn_parts.h, attn_merge.h).
 #pragma once
 #include "attn_step.h"
 

@@ -103,3 +103,32 @@ def test_merging_waves_that_give_up_flag_the_sequence(cfg, monkeypatch):
     call()
     torch.cuda.synchronize()
     assert int(tv.attn_status.abs().sum()) == 0 and torch.equal(tv.out, want)
+
+
+def test_steps_on_two_streams():
+    """Two steps that overlap, each with its own buffers: what each gives by itself."""
+    runs = []
+    for cfg in (CASES[0], CASES[4]):
+        par = synth.make_parent(cfg)
+        d = to_device(cfg, par, synth.make_attn_inputs(cfg), synth.make_accept_inputs(cfg, par))
+        tv = TreeVerifier(cfg.B, cfg.N, cfg.Hq, cfg.Hkv, cfg.D, cfg.S_cap, cfg.V, d["q"].dtype, cfg.levels, cfg.P)
+        k, v, n = d["k_cache"].clone(), d["v_cache"].clone(), d["cache_len"].clone()
+
+        def step(d=d, tv=tv, k=k, v=v, n=n, cfg=cfg):
+            n.copy_(d["cache_len"])
+            tv.step(d["q"], d["k_tree"], d["v_tree"], k, v, n, d["parent"], d["logits"], d["tokens"], 0 if cfg.mode == "greedy" else 1,
+                    d["p_draft"], d["uniforms"], cfg.temperature)
+
+        seen = lambda tv=tv, k=k, v=v, n=n: [t.clone() for t in (tv.out, tv.path, tv.accept_len, tv.attn_status, tv.accept_status,
+                                                                 tv.compact_status, k, v, n)]
+        step()
+        torch.cuda.synchronize()
+        runs.append((step, seen, seen(), torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    for _ in range(20):
+        for step, _, _, stream in runs:
+            with torch.cuda.stream(stream):
+                step()
+    torch.cuda.synchronize()
+    for _, seen, alone, _ in runs:
+        assert _same(seen(), alone)
