@@ -513,10 +513,11 @@ void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP> tail) {
 #pragma unroll
             for (int g = 0; g < kKG; ++g) l_tot = fmaf(mml[((g * kRBW + rb) * 32 + (lane & 31)) * 2 + 1], weight(g), l_tot);
             w_own = weight(kg);
+            if (kg < kOwners)                                                 // (the others send what is left as it is: who adds it up weights it)
 #pragma unroll
-            for (int db = 0; db < kOwn; ++db)
+                for (int db = 0; db < kOwn; ++db)
 #pragma unroll
-                for (int j = 0; j < 16; ++j) o[db][j] *= w_own;
+                    for (int j = 0; j < 16; ++j) o[db][j] *= w_own;
 #pragma unroll
             for (int db = kFirst; db < kDB; ++db)
 #pragma unroll

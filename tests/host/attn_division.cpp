@@ -4,7 +4,7 @@
 //   a unit that one team covered alone is not merged, and a unit that is merged was written by no team alone;
 //   every part that the merge reads was written by this call, and it reads every part of its unit.
 // Usage: attn_division split|balanced LAUNCHES; prints the first wrong launch and their number, exit status 1 if any.
-//        attn_division plan B Hkv N M max_cache_len ROWS KEYS PER_CU WIDE CUS; prints the plan's teams and split
+//        attn_division plan B Hkv N M max_cache_len ROWS KEYS PER_CU WIDE CUS; prints the plan's teams, split and parts
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -113,7 +113,7 @@ int main(int argc, char** argv) {
         int n[10];
         for (int i = 0; i < 10; ++i) n[i] = atoi(argv[2 + i]);
         const AttnDivision d = plan_division(n[0], n[1], n[2], n[3], n[4], AttnTile{n[5], n[6], n[7], n[8] != 0}, n[9]);
-        printf("%d %d\n", d.teams, d.split);
+        printf("%d %d %d\n", d.teams, d.split, d.parts);
         return 0;
     }
     const bool split = argc > 1 && !strcmp(argv[1], "split");
@@ -125,7 +125,7 @@ int main(int argc, char** argv) {
         return (int)std::exp(x);
     };
     // rows, keys and workgroups per CU of the kernels' configurations
-    const AttnTile tiles[] = {{128, 64, 1, true}, {128, 64, 2, false}, {256, 64, 1, true}, {256, 64, 1, false}, {32, 32, 1, true}, {32, 32, 2, false},
+    const AttnTile tiles[] = {{128, 64, 1, true}, {128, 64, 2, false}, {256, 64, 1, true}, {256, 64, 1, false}, {32, 32, 1, true}, {32, 32, 1, false}, {32, 32, 2, false},
                               {64, 32, 1, false}, {64, 32, 2, true}, {64, 32, 2, false}};
     int played = 0, bad = 0, divided = 0;
     while (played < launches) {
@@ -133,7 +133,7 @@ int main(int argc, char** argv) {
         a.B = log_pick(1, 80);
         a.Hkv = log_pick(1, 40);
         a.N = rng() % 4 ? pick(1, 128) : pick(1, 20);
-        const AttnTile t = tiles[rng() % 9];
+        const AttnTile t = tiles[rng() % 10];
         const int G = t.rows <= 64 && rng() % 2 ? 1 : log_pick(1, 16);
         a.M = a.N * G;
         a.max_cache_len = rng() % 8 ? log_pick(1, 40000) : 0;

@@ -4,6 +4,7 @@ import subprocess
 
 import pytest
 
+from paper_2506_14158_amd import binding as B
 from tests.test_gpu_division import CASES, plan_inputs
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -30,9 +31,12 @@ def test_merge_reads_what_the_call_wrote(player, kind):
 @pytest.mark.parametrize("case", CASES, ids=lambda c: c.name)
 def test_gpu_cases_are_divided_as_they_say(player, case):
     r = subprocess.run([player, "plan"] + [str(x) for x in plan_inputs(case)], capture_output=True, text=True, check=True)
-    teams, split = (int(x) for x in r.stdout.split())
+    teams, split, parts = (int(x) for x in r.stdout.split())
     units = case.B * case.Hkv
     assert split > 1 if case.kind == "split" else split == 0 and teams > units // 2, r.stdout
+    # and the library's own plan is this one (rows, keys and workgroups per CU are the kernel's)
+    shape = B.AttnShape(case.B, case.Hkv * case.G, case.Hkv, case.D, case.N, case.max_len + case.N, {"f32": B.S4C_F32, "bf16": B.S4C_BF16, "f16": B.S4C_F16}[case.dtype])
+    assert B.s4c_tree_attn_num_splits(shape, case.max_len) == parts
 
 
 # (B, Hkv, N, query rows, max_cache_len), the tile of 16-bit data of head size 128 (rows, keys, workgroups per CU): sequences so
@@ -53,7 +57,7 @@ WHOLE = [
 @pytest.mark.parametrize("sizes, tile", WHOLE, ids=lambda x: "-".join(map(str, x)))
 def test_short_sequences_are_not_divided(player, sizes, tile):
     r = subprocess.run([player, "plan"] + [str(x) for x in sizes + tile + (1, 256)], capture_output=True, text=True, check=True)
-    teams, split = (int(x) for x in r.stdout.split())
+    teams, split, _ = (int(x) for x in r.stdout.split())
     assert split == 1 and teams == sizes[0] * sizes[1], r.stdout
 
 

@@ -46,10 +46,16 @@ CASES = [
     Case("shares-rows256-mixed", "balanced", 13, 8, 4, 128, 47, "bf16", 5003, (5, 900, 0, 64, 5004, 129)),
     Case("shares-rows64", "balanced", 3, 32, 1, 128, 37, "bf16", 24000, (64, 33, 1)),
     Case("shares-rows64-mixed", "balanced", 3, 32, 1, 128, 37, "f16", 24000, (700, 0, 40)),
-    Case("shares-rows32", "balanced", 5, 18, 1, 64, 20, "bf16", 3000, (32, 0, 1, 500, -1)),
+    Case("rows32-d64", "split", 5, 18, 1, 64, 20, "bf16", 3000, (32, 0, 1, 500, -1)),
+    Case("shares-rows32", "balanced", 13, 16, 1, 64, 20, "bf16", 3000, (32, 0, 1, 500, -1)),
     Case("shares-f32", "balanced", 3, 30, 2, 64, 40, "f32", 3000, (2, 50, 333)),
+    # long shares of few rows: the key groups of a workgroup see different maxima
+    Case("shares-rows32-long", "balanced", 13, 16, 2, 64, 1, "f16", 3000, (3000, 2901)),
+    Case("shares-rows32-long-bf16", "balanced", 13, 16, 1, 64, 32, "bf16", 3000, (2777, 3000, 1500)),
+    Case("shares-rows32-long-f32", "balanced", 7, 20, 2, 64, 13, "f32", 2500, (2500, 2431)),
     Case("shares-rows32-deep", "balanced", 33, 8, 1, 128, 20, "bf16", 7960, (500, 0, 33, 7961, 64)),   # four key groups
-    Case("shares-70-sequences", "balanced", 70, 2, 1, 64, 20, "bf16", 3000, (1, 0, 64, 100, 31)),
+    Case("70-sequences", "split", 70, 2, 1, 64, 20, "bf16", 3000, (1, 0, 64, 100, 31)),
+    Case("shares-70-sequences", "balanced", 70, 3, 1, 64, 20, "bf16", 3000, (1, 0, 64, 100, 31)),
 ]
 
 
@@ -61,7 +67,7 @@ def plan_inputs(c):
     if c.dtype != "f32" and M > 64:
         tile = (128, 64, 2 if c.D == 64 else 1) if M <= 128 else (256, 64, 1)
     elif M <= 32 and (c.D == 64 or (wide and c.max_len >= 4096 and c.B * c.Hkv * c.max_len >= 7168 * 256)):
-        tile = (32, 32, 1)
+        tile = (32, 32, 2 if c.D == 64 and c.dtype != "f32" else 1)
     else:
         tile = (64, 32, 1 if c.dtype == "f32" and c.D == 128 else 2)
     return (c.B, c.Hkv, c.N, M, c.max_len) + tile + (int(wide), 256)
