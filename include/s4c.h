@@ -58,9 +58,7 @@ typedef enum { S4C_GREEDY = 0, S4C_STOCHASTIC = 1 } s4c_accept_mode;
 #define S4C_SEQ_BAD_LEN  2     /* cache_len out of range / accepted rows do not fit S_cap */
 #define S4C_SEQ_TIMEOUT  4     /* s4c_accept_path, s4c_accept_resample: the workgroups of a sequence could not
                                   hand their partial results to each other within the waiting limit (a GPU
-                                  that stopped scheduling them); accept_len = 0, path = [0], bonus = -1.
-                                  s4c_tree_attn and s4c_tree_attn_paged: the same between workgroups that attend and
-                                  that merge; rows whose parts did not come are zero */
+                                  that stopped scheduling them); accept_len = 0, path = [0], bonus = -1 */
 
 typedef struct {
     int32_t B;       /* sequences */
@@ -91,9 +89,8 @@ size_t s4c_tree_attn_workspace_size(const s4c_attn_shape* shape, int32_t max_cac
  *                   gets an all-zero output.
  *   workspace       >= s4c_tree_attn_workspace_size(shape, max_cache_len) bytes, 256-byte
  *                   aligned; contents need not be initialised; may be NULL if that size is 0.
- * Workgroups that merge the parts of divided sequences wait for them in the same launch: 2 s, or S4C_MERGE_WAIT_US
- * microseconds (environment, an integer >= 0, read at every call), then the sequence is flagged S4C_SEQ_TIMEOUT.  A call by
- * itself always completes, and so do two that overlap in time.  Calls that may overlap must not share a workspace.
+ * Any number of calls may overlap in time, each with a workspace of its own (workgroups only wait for such of their
+ * sequence as are running already).
  * Results are deterministic: how the keys are divided between workgroups, and the order in which parts are merged,
  * follow from the shape, max_cache_len and cache_len[]. */
 s4c_status s4c_tree_attn(const s4c_attn_shape* shape, const void* q, const void* k_tree,

@@ -1,5 +1,6 @@
 // The acceptance kernels: accept_roles.h in launches of their own.
 #include "accept_roles.h"
+#include "attn_parts.h"
 
 namespace s4c {
 
@@ -26,8 +27,8 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd<T>) void step_kernel(AttnAr
         if (attn.split > 0) {
             constexpr parts::Elem E = sizeof(T) == 4 ? parts::kF32 : std::is_same<T, f16_t>::value ? parts::kH16 : parts::kB16;
             const int task = wg * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-            if (attn.D == 64) parts::take<64, E, 3>(attn, task);
-            else parts::take<128, E, 3>(attn, task);
+            if (attn.D == 64) parts::take_task<64, E, 3>(attn, task);
+            else parts::take_task<128, E, 3>(attn, task);
             return;
         }
         const int unit = wg / x.merge_chunks, chunk = wg - unit * x.merge_chunks;

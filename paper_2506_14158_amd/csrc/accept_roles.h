@@ -40,10 +40,41 @@
 // rows lie in pages of their own): 13b, batch 4: 12.5 + 5.6 + 10.4 us in three launches.
 #pragma once
 #include "attn_merge.h"
-#include "attn_parts.h"
 #include "row_chunk.h"
 
 namespace s4c {
+
+// ---- words under a tag, one writer and one reader each, a mark of the reader's beside every word
+namespace word {
+struct Pair { uint64_t word, mark; };
+__device__ __forceinline__ uint64_t load(const uint64_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void store(uint64_t* p, uint64_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// A reader that gives up leaves its mark and then looks once more; the writer publishes and then looks for a mark: at least one of
+// the two sees the other, and no word of this call stays behind for a replay to find.  Readers start after
+// the writer (`started`, 100 MHz wall clock) and wait for `ticks`, so there can only be marks after half that time.
+__device__ __forceinline__ void publish(Pair* p, uint64_t tag, long long started, long long ticks) {
+    store(&p->word, tag);
+    if ((long long)wall_clock64() - started >= ticks / 2) {
+        __threadfence();
+        if (load(&p->mark) == tag) {
+            store(&p->word, ~tag);
+            store(&p->mark, ~tag);
+        }
+    }
+}
+__device__ __forceinline__ bool here(const Pair* p, uint64_t tag) { return load(&p->word) == tag; }
+__device__ __forceinline__ void taken(Pair* p, uint64_t tag) { store(&p->word, ~tag); }
+// The reader has waited long enough: whether the word is here after all.  If not, the writer takes it back.
+__device__ __forceinline__ bool give_up(Pair* p, uint64_t tag) {
+    store(&p->mark, tag);
+    __threadfence();
+    const bool came = here(p, tag);
+    if (came) store(&p->mark, ~tag);
+    return came;
+}
+}  // namespace word
+
+
 namespace accept {
 
 using namespace rowchunk;
@@ -160,7 +191,7 @@ struct StepArgs {
     int32_t attn_wgs;
     uint64_t tag;               // of these
     long long copy_ticks;       // how long a copier waits for its message (100 MHz wall clock)
-    int32_t merge_wgs, merge_chunks, merge_passes;           // balanced shares: attn_merge.h; equal runs: attn_parts.h, a wave each
+    int32_t merge_wgs, merge_chunks, merge_passes;           // behind the attention.  balanced shares: attn_merge.h; equal runs: attn_parts.h, a wave each
     int32_t scan_wgs;
     int32_t copiers, heads;     // workgroups per sequence that append rows, KV heads of each
 };

@@ -10,8 +10,8 @@
 //             the teams take equal consecutive shares (sizes differ by one tile).  A share may end inside a unit.  Equal
 //             shares are what keeps every CU busy to the end: 104 units on 256 CUs leave 48 of them idle at two runs per
 //             unit, and with ragged lengths the rest wait for the longest sequence.
-// A part of a unit that several teams share goes to the workspace unnormalised; attn_merge_kernel combines a unit's
-// parts in order.
+// A part of a unit that several teams share goes to the workspace unnormalised, and a unit's parts are combined in order: equal
+// runs by attn_parts.h, balanced shares by attn_merge.h.
 // The shares are a function of the shape and of cache_len, so results are deterministic for given inputs.
 //
 // `A` is AttnArgs, or what a host program has with the same members; `L` tells the sequences' lengths, L::Order their
@@ -101,31 +101,33 @@ inline AttnDivision plan_division(int B, int Hkv, int N, int M, int max_cache_le
     return p;
 }
 
-// Workgroups of an attention launch that wait for others of it: merging ones, and in a step's only launch a collector for each
-// sequence and its copiers.  Every XCD starts a launch's workgroups in order, but which of two streams it serves first is its own
+// Where a team of a launch of equal runs leaves its part: a region with room for 2 M rows of D floats, of which the slabs (8 columns of a
+// row block of 32; a lane's 16 bytes are 4 columns of a row) need M.  In the other half lie the rows' (maximum in log2 units, sum) for every
+// wave that wrote columns of its own, 4 of them at most, and behind them a word for each tile of the unit's rows (attn_meet.h).
+template <int D>
+struct PartRegion {
+    static S4C_WORK uint32_t bytes(int M) { return 8u * M * D; }
+    static S4C_WORK uint32_t slab(int M, int block, int s, int lane) {
+        const int rows = M - 32 * block < 32 ? M - 32 * block : 32;
+        return 4u * (32 * block * D + ((2 * s + (lane >> 5)) * rows + (lane & 31)) * 4);
+    }
+    static S4C_WORK uint32_t stats(int M, int block, int key, int lane) { return 4u * M * D + 8u * (key * M + 32 * block + (lane & 31)); }
+    static S4C_WORK uint32_t word(int M, int mt) { return 4u * M * D + 4 * 8u * M + 8u * mt; }
+};
+
+// Workgroups of a step's only launch that wait for others of it: a collector for each
+// sequence, and its copiers.  Every XCD starts a launch's workgroups in order, but which of two streams it serves first is its own
 // affair: with one XCD full of waiting workgroups of one call and another full of the other's, neither call's attention would
 // be started, until the waits run out.  So a launch keeps to four fifths of an XCD's CUs with all of its waiting
 // workgroups together: whatever an XCD serves first, a call's waiting workgroups and the collectors (at most one sequence
-// in eight CUs) of another leave a CU of it to those that are waited for.
-// Merging waves beyond that take several turns, and a sequence has fewer copiers, each with more heads.
-struct AttnWaiting { int merging, heads; };            // workgroups that merge; KV heads of a copier
+// in eight CUs) of another leave a CU of it to those that are waited for.  Returns the KV heads of a copier.
 inline int copiers_of(int Hkv, int heads) { return (Hkv + heads - 1) / heads; }
-// merging: workgroups that would merge in one turn; sequences: of a step's only launch (0: none), at most an eighth of the CUs;
-// most_copiers: of a sequence
-inline AttnWaiting plan_waiting(int merging, int sequences, int Hkv, int most_copiers, int cus) {
+// sequences: at most an eighth of the CUs; most: copiers of a sequence
+inline int heads_of_copier(int sequences, int Hkv, int most, int cus) {
     const int all = cus / 8 * 4 / 5 * 8;
-    AttnWaiting w = {merging, 1};
-    int taken = 0;
-    if (sequences > 0) {
-        int copiers = all / 3 / sequences;
-        copiers = copiers < 1 ? 1 : copiers > most_copiers ? most_copiers : copiers;
-        w.heads = (Hkv + copiers - 1) / copiers;
-        taken = sequences * (1 + copiers_of(Hkv, w.heads));
-    }
-    const int rest = all - taken > 1 ? all - taken : 1;
-    const int turns = (merging + rest - 1) / rest;
-    if (turns > 1) w.merging = (merging + turns - 1) / turns;
-    return w;
+    int copiers = all / 3 / sequences;
+    copiers = copiers < 1 ? 1 : copiers > most ? most : copiers;
+    return (Hkv + copiers - 1) / copiers;
 }
 
 namespace work {
@@ -213,20 +215,18 @@ S4C_WORK Walk walk_next(const A& a, const L& lens, const Walk w) {
 // empty prefix, a flagged sequence) is one part and empty ones.
 template <class A>
 S4C_WORK bool walk_is_whole(const A& a, const Walk& w) { return a.split <= 1 && w.tile == 0 && w.tile_end == w.tiles; }
-// Workspace slot of a part: a team leaves at most one part that ends a unit or lies inside it (slot 0) and one
+// Workspace slot of a part in a balanced launch: a team leaves at most one part that ends a unit or lies inside it (slot 0) and one
 // that begins a unit (slot 1).
 S4C_WORK int part_slot(const Walk& w) { return w.tile == 0 ? 1 : 0; }
 template <class A>
 S4C_WORK size_t part_row(const A& a, int team, int slot) { return ((size_t)team * 2 + slot) * a.M; }
 
-// A team without tiles in a split launch leaves empty parts (sum 0), so that the merge kernel need not know how many
-// teams had some.
+// A team without tiles in a split launch leaves empty parts (sum 0), so that who merges need not know how many teams had
+// some.
 template <class A>
 S4C_WORK bool leaves_empty(const A& a, int team) { return a.split > 1 && team < a.teams; }
-template <class A>
-S4C_WORK int empty_slot(const A& a, int team) { return team % a.split == 0 ? 1 : 0; }
 
-// Tells the merge kernel which teams share a unit (balanced launches): the team that begins it and the team that ends it.
+// Tells the merge which teams share a unit (balanced launches): the team that begins it and the team that ends it.
 template <class A>
 S4C_WORK void note_parts(const A& a, int team, const Walk& w) {
     const size_t unit = (size_t)w.b * a.Hkv + w.kvh;
@@ -234,13 +234,12 @@ S4C_WORK void note_parts(const A& a, int team, const Walk& w) {
     if (w.tile_end == w.tiles) a.ws_parts[2 * unit + 1] = team;
 }
 
-// The teams whose parts make up a unit: slot 1 of the first one, slot 0 of the others; one team alone has written the
-// unit's output itself.  Split: the unit's teams, whether they had tiles or not; balanced: as the teams noted.
+// The teams whose parts make up a unit of a balanced launch, as they noted: slot 1 of the first one, slot 0 of the others; one team
+// alone has written the unit's output itself.
 struct Parts {
     int first, last;
     template <class A>
-    S4C_WORK Parts(const A& a, int unit)
-        : first(a.split > 0 ? unit * a.split : a.ws_parts[2 * unit]), last(a.split > 0 ? first + a.split - 1 : a.ws_parts[2 * unit + 1]) {}
+    S4C_WORK Parts(const A& a, int unit) : first(a.ws_parts[2 * unit]), last(a.ws_parts[2 * unit + 1]) {}
     S4C_WORK int slot(int team) const { return team == first ? 1 : 0; }
 };
 

@@ -73,9 +73,7 @@ struct AttnArgs {
     int32_t part_keys;  // waves that share the columns of a row in a part (attn_parts.h)
     int32_t cus;        // compute units of the device
     int32_t attn_wgs;   // set by the launcher: workgroups of the launch that attend
-    int32_t merge_wgs;  // set by the launcher: and that merge (plan_waiting)
-    uint64_t tag;       // of this call's parts; 0: the next launch merges them
-    long long wait_ticks;     // how long a merging workgroup waits for its parts (100 MHz wall clock)
+    uint64_t tag;       // equal runs: the call's, under which its workgroups agree on the merge (attn_meet.h); 0: the next launch merges
     float scale_log2; // softmax scale * log2(e)
     // paged cache (block_table != null): k_cache / v_cache are pools [num_pages][Hkv][page][D],
     // row j of sequence b is row j & (page-1) of page block_table[b][j >> page_shift]

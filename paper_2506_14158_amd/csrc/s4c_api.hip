@@ -65,13 +65,19 @@ uint32_t next_nonce() {
     }
 }
 
-// A different 64-bit number for every attention call of the process, under which its parts are published.  They lie where other
-// calls keep numbers of any kind, so all 64 bits are mixed: what is there is not taken for this call's.
+// A different number for every attention call of the process, under which its workgroups' words count (attn_meet.h).  They lie where
+// other calls keep numbers of any kind, so all bits are mixed: what is there is not taken for this call's.  Never 0.
 uint64_t next_tag() {
     static std::atomic<uint64_t> counter{0};
-    uint64_t x = (counter.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9E3779B97F4A7C15ull;
-    x ^= x >> 30; x *= 0xBF58476D1CE4E5B9ull; x ^= x >> 27; x *= 0x94D049BB133111EBull; x ^= x >> 31;
-    return x;
+    for (;;) {
+        uint64_t x = counter.fetch_add(1, std::memory_order_relaxed) + 1;
+        constexpr int half = 64 - __builtin_popcountll(meet::kStateBits);
+        // a bijection of the words of that many bits: odd factors, and shifts to the right
+        const uint64_t mask = (1ull << half) - 1;
+        x = x * 0x9E3779B97F4A7C15ull & mask;
+        x ^= x >> 30; x = x * 0xBF58476D1CE4E5B9ull & mask; x ^= x >> 27; x = x * 0x94D049BB133111EBull & mask; x ^= x >> 31;
+        if (x != 0) return x << (64 - half);
+    }
 }
 
 // A waiting time in microseconds, up to a minute, replaced by an environment variable (read at every call).
@@ -205,29 +211,17 @@ s4c_status tree_attn_prepare(const s4c_attn_shape* shape, const void* q, const v
     a.block_table = block_table; a.max_blocks = max_blocks; a.page_shift = page_shift; a.num_pages = num_pages;
     a.part_keys = p.tile.part_keys;
     a.cus = device_cus();
-    a.attn_wgs = a.merge_wgs = 0;
-    a.tag = 0;
-    a.wait_ticks = 0;
+    a.attn_wgs = 0;
+    a.tag = a.split > 1 ? next_tag() : 0;
     *plan = p;
     return S4C_OK;
-}
-
-// Equal runs are merged by the attention launch itself.
-void merge_in_launch(AttnArgs& a) {
-    if (a.split > 1) {
-        a.tag = next_tag();
-        // S4C_MERGE_WAIT_US (environment, >= 0): how long a merging workgroup waits for its parts before it flags the sequence;
-        // a diagnostic knob as S4C_ACCEPT_WAIT_US.
-        a.wait_ticks = wait_us("S4C_MERGE_WAIT_US", 2000000) * 100;
-    }
 }
 
 hipError_t launch_tree_attn(const AttnPlan& p, const AttnArgs& a, int dtype, const StepTail<kGreedyStep>* step, hipStream_t st) {
     return p.large ? launch_tree_attn_large(a, dtype, step, st) : launch_tree_attn_small(a, dtype, step, st);
 }
 // attention and its merge
-hipError_t launch_attn_and_merge(const AttnPlan& p, AttnArgs a, int dtype, hipStream_t st) {
-    merge_in_launch(a);
+hipError_t launch_attn_and_merge(const AttnPlan& p, const AttnArgs& a, int dtype, hipStream_t st) {
     const hipError_t e = launch_tree_attn(p, a, dtype, nullptr, st);
     return e == hipSuccess && a.split == 0 ? launch_attn_merge(a, dtype, st) : e;       // the parts of balanced shares
 }
@@ -731,7 +725,6 @@ s4c_status s4c_verify_step(const s4c_step* p, void* hip_stream) {
     const long long copy_ticks = wait_us("S4C_COPY_WAIT_US", accept.wait_ticks / 100 + 2000000) * 100;
     hipError_t e;
     if (plan_one_launch(*p, plan, attn, accept)) {
-        merge_in_launch(attn);
         StepTail<kGreedyStep> tail;
         tail.accept = accept;
         tail.step = accept::make_step(accept, compact, messages, copy_ticks);
@@ -740,6 +733,7 @@ s4c_status s4c_verify_step(const s4c_step* p, void* hip_stream) {
         tail.step.tag = next_tag();
         e = launch_tree_attn(plan, attn, p->shape.dtype, &tail, st);
     } else if (p->logits_dtype == p->shape.dtype) {
+        attn.tag = 0;
         e = launch_tree_attn(plan, attn, p->shape.dtype, nullptr, st);
         if (e == hipSuccess) e = launch_step(attn, accept, compact, messages, copy_ticks, st);
     } else {

@@ -39,7 +39,7 @@ constexpr int kBN = 64;                     // keys per tile
 constexpr float kLazyLog2 = 8.0f;           // full tiles rescale only when a row maximum grew by more than 2^8
 constexpr int lds_bytes_for(int ns, int d) { return ns * 2 * kBN * d * 2 + kMaxNodes * 16 + kMaxNodes * 4; }
 
-template <int WR, int NS, int WPE, bool PAGED, bool F16, int kD, StepKind STEP>
+template <int WR, int NS, int WPE, bool PAGED, bool F16, int kD, StepKind STEP, parts::Merge MERGE>
 __global__ __launch_bounds__(WR * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
     constexpr int NT = WR * 64;
@@ -60,10 +60,12 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
 
     static_assert(sizeof(accept::Shared) <= NS * kStageB, "the ring is also what the other workgroups of a step have");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    if (__builtin_expect(blockIdx.y > 0, 0)) {              // (the attention's code first: a far jump at its start costs a fetch)
-        rest_of_launch<kD, F16 ? parts::kH16 : parts::kB16, NT, STEP>(smem);
-        return;
-    }
+    constexpr parts::Elem kElem = F16 ? parts::kH16 : parts::kB16;
+    if constexpr (STEP != kNoStep)
+        if (__builtin_expect(blockIdx.y > 0, 0)) {          // (the attention's code first: a far jump at its start costs a fetch)
+            rest_of_launch<kElem, STEP>(smem);
+            return;
+        }
     uint32_t* anc = (uint32_t*)(smem + NS * kStageB);        // [kMaxNodes][4]
     int32_t* spar = (int32_t*)(anc + kMaxNodes * 4);         // [kMaxNodes]
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem;
@@ -122,14 +124,18 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
             if (gg >= G) { gg -= G; ++nd; }
         }
     }
+    if constexpr (MERGE == parts::kHere)
+        if (wave == 0) parts::begin<kD>(a, team, mt);
     work::Walk cw = work::walk_first(a, lens, team);      // what is multiplied
-    const long long started = STEP != kNoStep || a.tag != 0 ? (long long)wall_clock64() : 0;
+    const long long started = STEP != kNoStep ? (long long)wall_clock64() : 0;
     if (cw.b < 0) {
         if constexpr (STEP != kNoStep) {
             __syncthreads();
             lens_read(tail, a, lens, started);
         }
-        if (work::leaves_empty(a, team)) parts::put_empty<kD, 1>(a, team, mt * WR + wave, 0, started);
+        if constexpr (MERGE != parts::kShares)
+            if (work::leaves_empty(a, team))
+                parts::finish<kD, kElem, MERGE, WR, WR>(a, team, mt, smem, [&]() __attribute__((always_inline)) { parts::put_empty<kD, 1, MERGE>(a, team, mt * WR + wave, 0); });
         return;
     }
     work::Walk pw = cw;                                   // what is loaded
@@ -433,6 +439,17 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
                     for (int db = 0; db < kDB; ++db)
                         o[db] = mma32<F16>(vf[st & 1][db], pb[part][st], o[db]);
             }
+            // A fragment's reads, one ahead of the product that takes it: left to itself the compiler reads as many as it has registers for, and
+            // the products wait for the LDS in bursts (16 x 64/8 heads, 32768 keys + 128 nodes 1997 us, 1980 so).
+            if constexpr (kParts == 1 && kDB == 4) {
+                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);      // LDS reads
+#pragma unroll
+                for (int i = 1; i < 4 * kDB; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+                }
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            }
         }
     };
 
@@ -481,7 +498,7 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
         if (nw.b != b && tid < N) parent = a.parent[(size_t)nw.b * N + tid];
         load_q(nw.b, nw.kvh);
     }
-    if (a.split == 0 && mt == 0 && tid == 0) work::note_parts(a, team, cw);
+    if (MERGE == parts::kShares && a.split == 0 && mt == 0 && tid == 0) work::note_parts(a, team, cw);
     // ---- write this lane's row: d = 32 db + 8 (j/4) + 4 g32 + (j%4)
     const int flagged = (work::tree_is_bad(a, spar) ? S4C_SEQ_BAD_TREE : 0) | (len_bad ? S4C_SEQ_BAD_LEN : 0);
     if (a.status && tid == 0 && cw.tile == 0 && kvh == 0 && mt == 0) a.status[b] = flagged;
@@ -492,6 +509,14 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
         for (int db = 0; db < kDB; ++db)
 #pragma unroll
             for (int j = 0; j < 16; ++j) o[db][j] = 0.f;
+    }
+    if constexpr (MERGE != parts::kShares) {
+        parts::finish<kD, kElem, MERGE, WR, WR>(Arguments().attn(), team, mt, smem, [&]() __attribute__((always_inline)) {
+            parts::put<kD, 1, MERGE, true>(Arguments().attn(), team, mt * WR + wave, 0, m_run, l_tot, [&](int q) __attribute__((always_inline)) {
+                return f32x4{o[q >> 2][4 * (q & 3)], o[q >> 2][4 * (q & 3) + 1], o[q >> 2][4 * (q & 3) + 2], o[q >> 2][4 * (q & 3) + 3]};
+            });
+        });
+        return;
     }
     if (work::walk_is_whole(a, cw)) {
         if (rvalid) {
@@ -507,10 +532,6 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
                 *(uint2*)(orow + 32 * db + 8 * jq) = pk;
             }
         }
-    } else if (a.split > 0) {
-        parts::put<kD, 1, true>(Arguments().attn(), team, mt * WR + wave, 0, m_run, l_tot, started, [&](int q) __attribute__((always_inline)) {
-            return f32x4{o[q >> 2][4 * (q & 3)], o[q >> 2][4 * (q & 3) + 1], o[q >> 2][4 * (q & 3) + 2], o[q >> 2][4 * (q & 3) + 3]};
-        });
     } else {
         if (rvalid) {
             const size_t prow = work::part_row(a, team, work::part_slot(cw)) + rq;
@@ -533,22 +554,29 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
 
 int pick_wr(int M) { return M <= 128 ? 4 : 8; }
 
-template <int WR, int NS, int WPE, bool PAGED, bool F16, int D, StepKind STEP>
+template <int WR, int NS, int WPE, bool PAGED, bool F16, int D, StepKind STEP, parts::Merge MERGE>
 hipError_t launch(AttnArgs a, StepTail<STEP> tail, hipStream_t st) {
     constexpr int kLds = lds_bytes_for(NS, D);
     static std::atomic<uint64_t> lds_set{0};
-    const hipError_t ea = ensure_dynamic_lds((const void*)tree_attn_mfma_kernel<WR, NS, WPE, PAGED, F16, D, STEP>, kLds, lds_set);
+    const hipError_t ea = ensure_dynamic_lds((const void*)tree_attn_mfma_kernel<WR, NS, WPE, PAGED, F16, D, STEP, MERGE>, kLds, lds_set);
     if (ea != hipSuccess) return ea;
     a.attn_wgs = attn_workgroups(a);
-    const dim3 grid = launch_grid(a, rest_of(a, tail, WR * 64)), block(WR * 64);
-    hipLaunchKernelGGL((tree_attn_mfma_kernel<WR, NS, WPE, PAGED, F16, D, STEP>), grid, block, kLds, st, a, tail);
+    const dim3 grid = launch_grid(a, rest_of(a, tail)), block(WR * 64);
+    hipLaunchKernelGGL((tree_attn_mfma_kernel<WR, NS, WPE, PAGED, F16, D, STEP, MERGE>), grid, block, kLds, st, a, tail);
     return hipGetLastError();
 }
 
 // four waves (up to 128 rows): one workgroup per CU and wave per SIMD; eight: two waves per SIMD
+template <bool PAGED, bool F16, int D, StepKind STEP, parts::Merge MERGE>
+hipError_t launch_rows(const AttnArgs& a, const StepTail<STEP>& tail, hipStream_t st) {
+    return pick_wr(a.M) == 4 ? launch<4, 4, 1, PAGED, F16, D, STEP, MERGE>(a, tail, st) : launch<8, 4, 2, PAGED, F16, D, STEP, MERGE>(a, tail, st);
+}
 template <bool PAGED, bool F16, int D, StepKind STEP>
 hipError_t launch_rows(const AttnArgs& a, const StepTail<STEP>& tail, hipStream_t st) {
-    return pick_wr(a.M) == 4 ? launch<4, 4, 1, PAGED, F16, D>(a, tail, st) : launch<8, 4, 2, PAGED, F16, D>(a, tail, st);
+    if (a.split <= 1) return launch_rows<PAGED, F16, D, STEP, parts::kShares>(a, tail, st);
+    if constexpr (!PAGED && STEP == kNoStep)
+        if (a.tag == 0) return launch_rows<PAGED, F16, D, STEP, parts::kNext>(a, tail, st);
+    return launch_rows<PAGED, F16, D, STEP, parts::kHere>(a, tail, st);
 }
 template <bool F16, int D>
 hipError_t launch_as(const AttnArgs& a, const StepTail<kGreedyStep>* step, hipStream_t st) {

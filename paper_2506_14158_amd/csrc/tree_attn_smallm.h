@@ -76,7 +76,7 @@ struct Cfg {
     }
 };
 
-template <class C, bool PAGED, StepKind STEP>
+template <class C, bool PAGED, StepKind STEP, parts::Merge MERGE>
 __global__ __launch_bounds__(C::kThreads) __attribute__((amdgpu_waves_per_eu(C::kPerCu * C::kWaves / 4, 2)))
 void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP> tail) {
     constexpr int kD = C::kD, kKG = C::kKG, kRBW = C::kRBW, kNR = C::kNR, kRowB = C::kRowB;
@@ -89,10 +89,11 @@ void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP> tail) {
     constexpr int kLPR = kRowB / 16;                          // lanes (16-byte chunks) per row in a direct-to-LDS load
     constexpr int kRPI = 64 / kLPR;                           // rows per load instruction
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    if (__builtin_expect(blockIdx.y > 0, 0)) {              // (the attention's code first: a far jump at its start costs a fetch)
-        rest_of_launch<kD, C::kElem, kThreads, STEP>(smem);
-        return;
-    }
+    if constexpr (STEP != kNoStep)
+        if (__builtin_expect(blockIdx.y > 0, 0)) {          // (the attention's code first: a far jump at its start costs a fetch)
+            rest_of_launch<C::kElem, STEP>(smem);
+            return;
+        }
     uint32_t* anc = (uint32_t*)(smem + C::kRingB);            // [kMaxNodes][4]
     int32_t* spar = (int32_t*)(anc + kMaxNodes * 4);          // [kMaxNodes]
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem;
@@ -159,14 +160,20 @@ void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP> tail) {
             if (g >= G) { g -= G; ++nd; }
         }
     }
+    if constexpr (MERGE == parts::kHere)
+        if (wave == 0) parts::begin<kD>(a, team, mt);
     work::Walk cw = work::walk_first(a, lens, team);      // what is multiplied
-    const long long started = STEP != kNoStep || a.tag != 0 ? (long long)wall_clock64() : 0;
+    const long long started = STEP != kNoStep ? (long long)wall_clock64() : 0;
     if (cw.b < 0) {
         if constexpr (STEP != kNoStep) {
             __syncthreads();
             lens_read(tail, a, lens, started);
         }
-        if (work::leaves_empty(a, team) && kg < kOwners) parts::put_empty<kD, kOwners>(a, team, mt * kRBW + rb, kg, started);
+        if constexpr (MERGE != parts::kShares)
+            if (work::leaves_empty(a, team))
+                parts::finish<kD, C::kElem, MERGE, C::kWaves, kRBW>(a, team, mt, smem, [&]() __attribute__((always_inline)) {
+                    if (kg < kOwners) parts::put_empty<kD, kOwners, MERGE>(a, team, mt * kRBW + rb, kg);
+                });
         return;
     }
     work::Walk pw = cw;                                   // what is loaded
@@ -542,44 +549,53 @@ void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP> tail) {
                         }
                 }
         };
-        if (a.split > 0) meet(std::integral_constant<bool, true>{});
+        if (MERGE != parts::kShares || a.split > 0) meet(std::integral_constant<bool, true>{});
         else meet(std::integral_constant<bool, false>{});
-        if (a.split == 0 && mt == 0 && tid == 0) work::note_parts(a, team, cw);
+        if (MERGE == parts::kShares && a.split == 0 && mt == 0 && tid == 0) work::note_parts(a, team, cw);
         // ---- the row's columns: d = 32 column_block(db) + 8 (j/4) + 4 g32 + (j%4)
         auto piece = [&](int q) __attribute__((always_inline)) {
             return f32x4{o[q >> 2][4 * (q & 3)], o[q >> 2][4 * (q & 3) + 1], o[q >> 2][4 * (q & 3) + 2], o[q >> 2][4 * (q & 3) + 3]};
         };
-        if (kg < kOwners) {
-            if (work::walk_is_whole(a, cw)) {
-                const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
-                const size_t o0 = (((size_t)b * N + node) * a.Hq + kvh * G + gh) * kD + 32 * kOwn * kg + 4 * g32;
-                if (rvalid)
+        if constexpr (MERGE != parts::kShares) {
+            parts::finish<kD, C::kElem, MERGE, C::kWaves, kRBW>(a, team, mt, smem, [&]() __attribute__((always_inline)) {
+                if (kg < kOwners) parts::put<kD, kOwners, MERGE>(a, team, mt * kRBW + rb, kg, m_max, l_tot, piece);
+            });
+            return;
+        }
+        if (work::walk_is_whole(a, cw)) {
+            const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
+            const size_t o0 = (((size_t)b * a.N + node) * a.Hq + kvh * G + gh) * kD + 32 * kOwn * kg + 4 * g32;
+            if (rvalid && kg < kOwners)
 #pragma unroll
-                    for (int q = 0; q < 4 * kOwn; ++q) parts::store_out<C::kElem>(a.out, o0 + 8 * q, piece(q) * inv);
-            } else if (a.split > 0) {
-                parts::put<kD, kOwners>(a, team, mt * kRBW + rb, kg, m_max, l_tot, started, piece);
-            } else if (rvalid) {
-                const size_t prow = work::part_row(a, team, work::part_slot(cw)) + rq;
-                float* orow = a.ws_o + prow * kD + 32 * kOwn * kg + 4 * g32;
+                for (int q = 0; q < 4 * kOwn; ++q) parts::store_out<C::kElem>(a.out, o0 + 8 * q, piece(q) * inv);
+        } else if (rvalid && kg < kOwners) {
+            const size_t prow = work::part_row(a, team, work::part_slot(cw)) + rq;
+            float* orow = a.ws_o + prow * kD + 32 * kOwn * kg + 4 * g32;
 #pragma unroll
-                for (int q = 0; q < 4 * kOwn; ++q) *(f32x4*)(orow + 8 * q) = piece(q);
-                if (kg == 0 && g32 == 0) *(float2*)(a.ws_ml + prow * 2) = make_float2(m_max, l_tot);
-            }
+            for (int q = 0; q < 4 * kOwn; ++q) *(f32x4*)(orow + 8 * q) = piece(q);
+            if (kg == 0 && g32 == 0) *(float2*)(a.ws_ml + prow * 2) = make_float2(m_max, l_tot);
         }
         if (a.split > 0) return;
         cw = nw;
     }
 }
 
-template <class C, bool PAGED, StepKind STEP>
+template <class C, bool PAGED, StepKind STEP, parts::Merge MERGE>
 hipError_t launch(AttnArgs a, StepTail<STEP> tail, hipStream_t st) {
     static std::atomic<uint64_t> lds_set{0};
-    const hipError_t ea = ensure_dynamic_lds((const void*)tree_attn_smallm_kernel<C, PAGED, STEP>, C::kLdsBytes, lds_set);
+    const hipError_t ea = ensure_dynamic_lds((const void*)tree_attn_smallm_kernel<C, PAGED, STEP, MERGE>, C::kLdsBytes, lds_set);
     if (ea != hipSuccess) return ea;
     a.attn_wgs = attn_workgroups(a);
-    const dim3 grid = launch_grid(a, rest_of(a, tail, C::kThreads)), block(C::kThreads);
-    hipLaunchKernelGGL((tree_attn_smallm_kernel<C, PAGED, STEP>), grid, block, C::kLdsBytes, st, a, tail);
+    const dim3 grid = launch_grid(a, rest_of(a, tail)), block(C::kThreads);
+    hipLaunchKernelGGL((tree_attn_smallm_kernel<C, PAGED, STEP, MERGE>), grid, block, C::kLdsBytes, st, a, tail);
     return hipGetLastError();
+}
+template <class C, bool PAGED, StepKind STEP>
+hipError_t launch(const AttnArgs& a, const StepTail<STEP>& tail, hipStream_t st) {
+    if (a.split <= 1) return launch<C, PAGED, STEP, parts::kShares>(a, tail, st);
+    if constexpr (!PAGED && STEP == kNoStep)
+        if (a.tag == 0) return launch<C, PAGED, STEP, parts::kNext>(a, tail, st);
+    return launch<C, PAGED, STEP, parts::kHere>(a, tail, st);
 }
 
 // The configuration for an element type, head size and rows per workgroup (attn_tile_small), handed to `use` as a type.

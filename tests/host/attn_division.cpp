@@ -2,7 +2,8 @@
 // lengths, and checks what the kernels and the merge rely on:
 //   every key tile of every unit is walked exactly once, and no workspace slot is written twice;
 //   a unit that one team covered alone is not merged, and a unit that is merged was written by no team alone;
-//   every part that the merge reads was written by this call, and it reads every part of its unit.
+//   every part that the merge reads was written by this call, and it reads every part of its unit (equal runs: a region for
+//   every team; balanced shares: slots, which teams note).
 // Usage: attn_division split|balanced LAUNCHES; prints the first wrong launch and their number, exit status 1 if any.
 //        attn_division plan B Hkv N M max_cache_len ROWS KEYS PER_CU WIDE CUS; prints the plan's teams, split and parts
 #include <cmath>
@@ -48,6 +49,7 @@ struct Order {
 
 const char* wrong(const Args& a, const AttnDivision& d, const Lens& lens) {
     const int units = a.B * a.Hkv, kNobody = -1, kEmpty = -2;
+    if (a.split > 32) return "more runs than a wave has bits and words for";
     std::vector<std::vector<int>> walked(units);
     for (int u = 0; u < units; ++u) walked[u].assign(lens.tiles(a, u / a.Hkv), 0);
     std::vector<int> whole(units, 0), slots((size_t)a.teams * 2, kNobody), parts_of(units, 0);
@@ -57,11 +59,7 @@ const char* wrong(const Args& a, const AttnDivision& d, const Lens& lens) {
         const int team = work::team_id(a, wg & 7, wg >> 3);
         if (team < a.teams && seen[team]++) return "a team number is used twice";
         work::Walk w = work::walk_first(a, lens, team);
-        if (w.b < 0 && work::leaves_empty(a, team)) {
-            int& s = slots[work::part_row(a, team, work::empty_slot(a, team)) / a.M];
-            if (s != kNobody) return "a workspace slot is written twice";
-            s = kEmpty;
-        }
+        if (w.b < 0 && work::leaves_empty(a, team)) slots[team] = kEmpty;
         while (w.b >= 0) {
             const int u = w.b * a.Hkv + w.kvh;
             if (w.b >= a.B || w.kvh >= a.Hkv || w.tile < 0 || w.tile >= w.tile_end || w.tile_end > (int)walked[u].size())
@@ -71,7 +69,7 @@ const char* wrong(const Args& a, const AttnDivision& d, const Lens& lens) {
             if (work::walk_is_whole(a, w)) {
                 ++whole[u];
             } else {
-                int& s = slots[work::part_row(a, team, work::part_slot(w)) / a.M];
+                int& s = slots[a.split > 0 ? (size_t)team : work::part_row(a, team, work::part_slot(w)) / a.M];
                 if (s != kNobody) return "a workspace slot is written twice";
                 s = u;
                 ++parts_of[u];
@@ -86,6 +84,16 @@ const char* wrong(const Args& a, const AttnDivision& d, const Lens& lens) {
             if (n != 1) return "a tile is not walked once";
         if (d.split == 1) {                                  // no merge is launched
             if (whole[u] != 1) return "nobody writes a unit's output";
+            continue;
+        }
+        if (a.split > 0) {                                   // every team of the unit leaves a part, and all are merged
+            int read = 0;
+            for (int k = 0; k < a.split; ++k) {
+                const int s = slots[u * a.split + k];
+                if (s != u && s != kEmpty) return "the merge reads a part that this call did not write for the unit";
+                read += s == u;
+            }
+            if (whole[u] || read != parts_of[u]) return "the merge misses a part";
             continue;
         }
         const work::Parts p(a, u);

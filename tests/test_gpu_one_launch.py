@@ -1,5 +1,5 @@
 """A step in one launch, and divided attention merged in its own: against the oracle and the separate calls, eagerly and from a captured
-graph, where merging waves take several turns, sequences have fewer copiers, and the waits run out."""
+graph, where a merge takes several turns, sequences have fewer copiers, and several calls overlap."""
 import numpy as np
 import pytest
 import torch
@@ -11,7 +11,6 @@ from tests.util import attn_errors, to_device
 
 pytestmark = pytest.mark.gpu
 C = synth.CONFIGS
-TIMEOUT = 4
 TOL = {"f32": (1e-5, 1e-5), "bf16": (1e-2, 2e-2), "f16": (2e-3, 4e-3)}      # the storage type's rounding of P and of the output, as in the parity tests
 
 CASES = [
@@ -22,6 +21,15 @@ CASES = [
     synth.scaled(C[5], name="many-rows", B=1, Hq=32, Hkv=4, P=2000, N=60, levels=6, V=9001, index=0),
     synth.scaled(C[4], name="80-rows-d64", B=2, Hq=10, Hkv=5, D=64, P=1500, N=40, levels=6, V=6000, index=0),
 ]
+
+
+def _in_one_launch(tv, run):
+    """Whether `run` left marks where a step of one launch has its attention workgroups tell that they have read the lengths."""
+    words = tv.accept_ws[-tv.B * torch.cuda.get_device_properties(0).multi_processor_count * 2 * 16:]
+    words.fill_(0x5A)
+    run()
+    torch.cuda.synchronize()
+    return bool((words != 0x5A).any())
 
 
 def _same(a, b):
@@ -47,8 +55,8 @@ def test_eager_and_replayed_steps(cfg):
         tv.out.fill_(7.0)
 
     reset()
-    step()
-    torch.cuda.synchronize()
+    assert _in_one_launch(tv, step)
+    assert (tv.num_splits > 1) == (cfg.name != "32-sequences")
     first = seen()
     ref, _ = O.tree_attn(at.q, at.k_tree, at.v_tree, at.k_cache, at.v_cache, at.cache_len, par)
     amax, rel = attn_errors(tv.out, ref)
@@ -72,37 +80,68 @@ def test_eager_and_replayed_steps(cfg):
         assert _same(seen(), first)
 
 
-@pytest.mark.parametrize("cfg", [CASES[0], CASES[4]], ids=lambda c: c.name)
-def test_merging_waves_that_give_up_flag_the_sequence(cfg, monkeypatch):
-    """A waiting time of zero: a merging wave that does not find all parts at its first look flags the sequence and leaves zero rows; sequences
-    that are not flagged are right.  With the usual wait the same buffers and the same graph's words give the right rows again."""
+@pytest.mark.parametrize("cfg", [CASES[0], CASES[3], CASES[4]], ids=lambda c: c.name)
+def test_replayed_attention_reads_the_inputs_of_the_replay(cfg):
+    """A part of the replay before has the same tag: new queries between the replays, every result as an eager call gives it."""
     par = synth.make_parent(cfg)
-    at = synth.make_attn_inputs(cfg)
-    d = to_device(cfg, par, at, synth.make_accept_inputs(cfg, par))
+    d = to_device(cfg, par, synth.make_attn_inputs(cfg), synth.make_accept_inputs(cfg, par))
     tv = TreeVerifier(cfg.B, cfg.N, cfg.Hq, cfg.Hkv, cfg.D, cfg.S_cap, cfg.V, d["q"].dtype, cfg.levels, cfg.P)
-    call = lambda: tv.tree_attn(d["q"], d["k_tree"], d["v_tree"], d["k_cache"], d["v_cache"], d["cache_len"], d["parent"])
+    assert tv.num_splits > 1
+    q = d["q"].clone()
+    call = lambda: tv.tree_attn(q, d["k_tree"], d["v_tree"], d["k_cache"], d["v_cache"], d["cache_len"], d["parent"])
     call()
     torch.cuda.synchronize()
-    want = tv.out.clone()
     g, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
-    monkeypatch.setenv("S4C_MERGE_WAIT_US", "0")
     with torch.cuda.stream(side):
         with torch.cuda.graph(g, stream=side):
             call()
-    for again in (call, g.replay, g.replay):
+    for i in range(6):
+        q.copy_(torch.roll(d["q"], i + 1, 0 if cfg.B > 1 else 1) * (1.0 if i % 2 else -1.0))
+        call()
+        torch.cuda.synchronize()
+        want = tv.out.clone()
         tv.out.fill_(7.0)
+        tv.attn_status.fill_(7)
         torch.cuda.synchronize()
-        again()
+        g.replay()
         torch.cuda.synchronize()
-        flags = tv.attn_status.cpu().numpy()
-        assert set(flags.tolist()) <= {0, TIMEOUT}
-        for b in range(cfg.B):
-            right = (tv.out[b] == want[b])
-            assert bool(right.all()) if flags[b] == 0 else bool((right | (tv.out[b] == 0)).all())
-    monkeypatch.delenv("S4C_MERGE_WAIT_US")
-    call()
+        assert int(tv.attn_status.abs().sum()) == 0 and torch.equal(tv.out, want)
+
+
+def test_divided_attention_on_four_streams():
+    """Four calls at a time, each with its own buffers, whose workgroups fill the chip several times over: some start when others of their
+    unit are through.  What each gives by itself, eagerly and replayed."""
+    cases = [synth.scaled(C[4], name="a", B=8, Hq=32, Hkv=8, P=2000, V=500, index=0), synth.scaled(C[3], name="b", B=4, Hq=40, Hkv=40, P=1100, V=500, index=0),
+             synth.scaled(C[4], name="c", B=13, Hq=32, Hkv=8, N=18, levels=6, P=1500, V=500, index=0),
+             synth.scaled(C[1], name="d", B=2, Hq=3, Hkv=3, P=900, N=17, V=500, index=0)]
+    runs = []
+    for cfg in cases:
+        par = synth.make_parent(cfg)
+        d = to_device(cfg, par, synth.make_attn_inputs(cfg), synth.make_accept_inputs(cfg, par))
+        tv = TreeVerifier(cfg.B, cfg.N, cfg.Hq, cfg.Hkv, cfg.D, cfg.S_cap, cfg.V, d["q"].dtype, cfg.levels, cfg.P)
+        assert tv.num_splits > 1
+
+        def call(d=d, tv=tv):
+            tv.tree_attn(d["q"], d["k_tree"], d["v_tree"], d["k_cache"], d["v_cache"], d["cache_len"], d["parent"])
+
+        call()
+        torch.cuda.synchronize()
+        stream, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        with torch.cuda.stream(stream):
+            with torch.cuda.graph(g, stream=stream):
+                call()
+        runs.append((call, g.replay, tv, tv.out.clone(), stream))
     torch.cuda.synchronize()
-    assert int(tv.attn_status.abs().sum()) == 0 and torch.equal(tv.out, want)
+    for i in range(30):
+        for call, replay, _, _, stream in runs:
+            with torch.cuda.stream(stream):
+                call() if i % 2 else replay()
+        if i % 10 == 9:
+            torch.cuda.synchronize()
+            for _, _, tv, alone, _ in runs:
+                assert int(tv.attn_status.abs().sum()) == 0 and torch.equal(tv.out, alone)
+                tv.out.fill_(7.0)
+            torch.cuda.synchronize()
 
 
 def test_steps_on_two_streams():

@@ -9,7 +9,7 @@ from paper_2506_14158_amd import build
 
 
 def resources(source):
-    """{kernel: {"VGPRs": .., "ScratchSize": .., "VGPRs Spill": .., "Occupancy": waves per SIMD}}"""
+    """{kernel: {"VGPRs": .., "SGPRs Spill": .., "ScratchSize": .., "VGPRs Spill": .., "Occupancy": waves per SIMD}}"""
     r = subprocess.run([build.HIPCC] + build.FLAGS + ["-Rpass-analysis=kernel-resource-usage", "--offload-device-only", "-c",
                         os.path.join(build.CSRC, source), "-o", os.devnull], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-4000:]
@@ -20,7 +20,7 @@ def resources(source):
             name = m.group(1)
             out[name] = {}
             continue
-        m = re.search(r"(VGPRs Spill|VGPRs|ScratchSize|Occupancy)(?: \[[^\]]*\])?: (\d+)", line)
+        m = re.search(r"(SGPRs Spill|VGPRs Spill|VGPRs|ScratchSize|Occupancy)(?: \[[^\]]*\])?: (\d+)", line)
         if m and name:
             out[name][m.group(1)] = int(m.group(2))
     return out
@@ -42,3 +42,15 @@ def test_sequential_acceptance_keeps_its_rows_in_registers(resample, kernel, blo
     for name, r in got.items():
         assert r["VGPRs Spill"] == 0 and r["ScratchSize"] == 0, (name, r)
         assert r["Occupancy"] >= (4 if blocks <= 2 else 2), (name, r)
+
+
+def test_attention_that_merges_nothing_keeps_nothing_for_it():
+    """Many-row kernels: no scratch memory in any of them; those of launches without equal runs (parts::kShares, 0) and without the rest of a
+    step (kNoStep, 0) spill next to no scalar registers (none contiguous; 5 paged, for the page table)."""
+    got = {k: v for k, v in resources("tree_attn_mfma_f16.hip").items() if "tree_attn_mfma_kernel" in k}
+    lean = {k: v for k, v in got.items() if "StepKindE0ELNS_5parts5MergeE0E" in k}
+    assert len(lean) == 8, sorted(got)                       # rows, head sizes, paged or not
+    for name, r in got.items():
+        assert r["VGPRs Spill"] == 0 and r["ScratchSize"] == 0, (name, r)
+    for name, r in lean.items():
+        assert r["SGPRs Spill"] <= (8 if "Lb1ELb1E" in name else 2), (name, r)
