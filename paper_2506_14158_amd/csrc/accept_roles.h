@@ -29,8 +29,8 @@
 // collector overwrites what it consumed with the complement of the nonce, so a captured graph can
 // replay the call, nonce and all.  The collector's wait is bounded by wall-clock time; when it runs
 // out (which needs a GPU that stops scheduling the sequence's other workgroups) the sequence is
-// flagged S4C_SEQ_TIMEOUT and gets the empty result.  Workgroups are dispatched in grid order, so
-// by the time a collector starts every other workgroup of its sequence has been given a compute unit.
+// flagged S4C_SEQ_TIMEOUT and gets the empty result.  Workgroups are dispatched in grid order within each
+// eighth of the chip, so a collector seldom starts before the workgroups that it waits for; it may, where other streams hold places.
 //
 // step_kernel: the acceptance scan with its collectors, then the workgroups of the attention merge (it only needs the
 // attention kernel to have ended; the other chain is the longer one), then workgroups that append the accepted path's K/V rows to the cache: a few per
@@ -41,39 +41,24 @@
 #pragma once
 #include "attn_merge.h"
 #include "row_chunk.h"
+#include "told.h"
 
 namespace s4c {
 
-// ---- words under a tag, one writer and one reader each, a mark of the reader's beside every word
-namespace word {
+namespace told {
+// a word and its mark in device memory
 struct Pair { uint64_t word, mark; };
-__device__ __forceinline__ uint64_t load(const uint64_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ void store(uint64_t* p, uint64_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-// A reader that gives up leaves its mark and then looks once more; the writer publishes and then looks for a mark: at least one of
-// the two sees the other, and no word of this call stays behind for a replay to find.  Readers start after
-// the writer (`started`, 100 MHz wall clock) and wait for `ticks`, so there can only be marks after half that time.
-__device__ __forceinline__ void publish(Pair* p, uint64_t tag, long long started, long long ticks) {
-    store(&p->word, tag);
-    if ((long long)wall_clock64() - started >= ticks / 2) {
-        __threadfence();
-        if (load(&p->mark) == tag) {
-            store(&p->word, ~tag);
-            store(&p->mark, ~tag);
-        }
-    }
-}
-__device__ __forceinline__ bool here(const Pair* p, uint64_t tag) { return load(&p->word) == tag; }
-__device__ __forceinline__ void taken(Pair* p, uint64_t tag) { store(&p->word, ~tag); }
-// The reader has waited long enough: whether the word is here after all.  If not, the writer takes it back.
-__device__ __forceinline__ bool give_up(Pair* p, uint64_t tag) {
-    store(&p->mark, tag);
-    __threadfence();
-    const bool came = here(p, tag);
-    if (came) store(&p->mark, ~tag);
-    return came;
-}
-}  // namespace word
-
+struct At {
+    Pair* p;
+    static __device__ __forceinline__ uint64_t load(const uint64_t* at) { return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    static __device__ __forceinline__ void store(uint64_t* at, uint64_t v) { __hip_atomic_store(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ uint64_t word() const { return load(&p->word); }
+    __device__ __forceinline__ uint64_t mark() const { return load(&p->mark); }
+    __device__ __forceinline__ void set_word(uint64_t v) const { store(&p->word, v); }
+    __device__ __forceinline__ void set_mark(uint64_t v) const { store(&p->mark, v); }
+    __device__ __forceinline__ void settle() const { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+};
+}  // namespace told
 
 namespace accept {
 
@@ -187,7 +172,7 @@ enum Part { kAlone, kBehindAttention, kBesideAttention };     // acceptance by i
 struct StepArgs {
     CompactArgs compact;
     rec_t* messages;            // [B][copiers][kMessageWords]
-    word::Pair* lens;           // in the launch of the attention: [B][attn_wgs], told by every attention workgroup when it has read cache_len
+    told::Pair* lens;           // in the launch of the attention: [B][attn_wgs], told by every attention workgroup when it has read cache_len
     int32_t attn_wgs;
     uint64_t tag;               // of these
     long long copy_ticks;       // how long a copier waits for its message (100 MHz wall clock)
@@ -202,12 +187,7 @@ constexpr int kMostCopiers = 8;
 // The collector's half of the compaction, as s4c_kv_compact: checks that the rows fit, writes dst_index and status,
 // advances cache_len, and tells the sequence's copiers, each in a message of its own (it clears the message when
 // it has read it, so that a captured graph can replay the call).  Path of L + 1 nodes in `node`; all threads.
-//
-// A copier waits longer than the collector does before it gives up (copy_ticks; it starts after the collector), so it
-// is only ever alone if the collector was held up on its way here.  A collector that comes here after half that time
-// looks whether a copier has left: then rows are missing, so the sequence is flagged and its length stays.  Copier: tell that it has given
-// up, then look once more; collector: publish, then look: at least one of the two sees the other.
-__device__ __forceinline__ void announce_path(const StepArgs& x, const AcceptArgs& a, Shared& sh, int b, int base, bool unread, long long started) {
+__device__ __forceinline__ void announce_path(const StepArgs& x, const AcceptArgs& a, Shared& sh, int b, int base, bool unread) {
     const CompactArgs& c = x.compact;
     const int i = threadIdx.x;
     const int L = sh.len;
@@ -217,27 +197,35 @@ __device__ __forceinline__ void announce_path(const StepArgs& x, const AcceptArg
         const int32_t word = i == 0 ? (bad ? -1 : base) : i == 1 ? L : i - 2 <= L ? sh.node[i - 2] : -1;
         for (int w = 0; w < x.copiers; ++w) publish(first + w * kMessageWords + i, a.nonce, (uint32_t)word);
     }
-    int gone = 0;
-    if (any_of(sh, (long long)wall_clock64() - started >= x.copy_ticks / 2)) {
-        __threadfence();
-        __syncthreads();
-        __threadfence();
-        for (int w = 0; w < x.copiers; ++w)
-            if ((uint32_t)(__hip_atomic_load(first + w * kMessageWords + kMessage, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32) == a.nonce) {
-                gone = 1;
-                if (i < kMessage) publish(first + w * kMessageWords + i, ~a.nonce, 0u);
-            }
-        gone = any_of(sh, gone);                           // (every thread has looked before a mark is cleared)
-        if (gone && i < x.copiers) {
-            rec_t* mark = first + i * kMessageWords + kMessage;
-            if ((uint32_t)(__hip_atomic_load(mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32) == a.nonce) publish(mark, ~a.nonce, 0u);
-        }
+    if (c.dst_index)
+        for (int k = i; k < c.max_path; k += kThreads) c.dst_index[(size_t)b * c.max_path + k] = (!bad && k <= L) ? base + k : -1;
+    if (i == 0) {
+        if (c.status) c.status[b] = unread ? S4C_SEQ_TIMEOUT : bad ? S4C_SEQ_BAD_LEN : 0;
+        if (!bad) c.cache_len[b] = base + L + 1;
+    }
+}
+// The end of a collector: whether a copier has left before it was told (told.h, a message for a word).  Then rows are missing, so the sequence is
+// flagged and its length is what it was; nothing of the message or of the mark stays behind.  (A copier waits longer than a
+// collector does before it gives up, but a collector may begin later.)
+__device__ __forceinline__ void look_for_leavers(const StepArgs& x, const AcceptArgs& a, Shared& sh, int b, int base) {
+    const CompactArgs& c = x.compact;
+    const int i = threadIdx.x;
+    rec_t* const first = x.messages + (size_t)b * x.copiers * kMessageWords;
+    auto left = [&](const rec_t* mark) { return (uint32_t)(__hip_atomic_load(mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32) == a.nonce; };
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();                                       // every thread's words can be seen
+    if (!any_of(sh, i < x.copiers && left(first + i * kMessageWords + kMessage))) return;
+    for (int w = 0; w < x.copiers; ++w) {
+        rec_t* const m = first + w * kMessageWords;
+        const bool gone = left(m + kMessage);
+        __syncthreads();                                   // every thread has looked before the mark is cleared
+        if (gone && i <= kMessage) publish(m + i, ~a.nonce, 0u);
     }
     if (c.dst_index)
-        for (int k = i; k < c.max_path; k += kThreads) c.dst_index[(size_t)b * c.max_path + k] = (!bad && !gone && k <= L) ? base + k : -1;
+        for (int k = i; k < c.max_path; k += kThreads) c.dst_index[(size_t)b * c.max_path + k] = -1;
     if (i == 0) {
-        if (c.status) c.status[b] = (unread ? S4C_SEQ_TIMEOUT : bad ? S4C_SEQ_BAD_LEN : 0) | (gone ? S4C_SEQ_TIMEOUT : 0);
-        if (!bad && !gone) c.cache_len[b] = base + L + 1;
+        if (c.status) c.status[b] |= S4C_SEQ_TIMEOUT;
+        c.cache_len[b] = base;
     }
 }
 
@@ -280,7 +268,7 @@ __device__ __forceinline__ void copy_rows(const StepArgs& x, const AcceptArgs& a
         __threadfence();
         __syncthreads();
         __threadfence();
-        if (any_of(sh, tid < kMessage && !look())) return;       // the collector flags the sequence (announce_path)
+        if (any_of(sh, tid < kMessage && !look())) return;       // the collector flags the sequence (look_for_leavers)
         if (tid == 0) publish(m + kMessage, ~a.nonce, 0u);
     }
     if (tid < kMessage) publish(m + tid, ~a.nonce, 0u);
@@ -313,15 +301,14 @@ __device__ __forceinline__ void copy_rows(const StepArgs& x, const AcceptArgs& a
 // it in time.  This thread's share of them.
 __device__ __forceinline__ bool lens_unread(const StepArgs& x, int b, long long started) {
     bool unread = false;
-    word::Pair* const p = x.lens + (size_t)b * x.attn_wgs;
     for (int w = threadIdx.x; w < x.attn_wgs; w += kThreads) {
-        bool here = word::here(p + w, x.tag);
+        told::At p{x.lens + (size_t)b * x.attn_wgs + w};
+        bool here = told::take(p, x.tag);
         while (!here) {
-            if ((long long)wall_clock64() - started >= x.copy_ticks / 2) { here = word::give_up(p + w, x.tag); break; }
+            if ((long long)wall_clock64() - started >= x.copy_ticks / 2) { here = told::give_up(p, x.tag); break; }
             __builtin_amdgcn_s_sleep(4);
-            here = word::here(p + w, x.tag);
+            here = told::take(p, x.tag);
         }
-        if (here) word::taken(p + w, x.tag);
         unread = unread || !here;
     }
     return unread;
@@ -432,9 +419,10 @@ __device__ __forceinline__ void path_step(const AcceptArgs& a, const StepArgs& x
         }
         if constexpr (PART != kAlone) {
             __syncthreads();
-            announce_path(x, a, sh, b, base, unread, started);
+            announce_path(x, a, sh, b, base, unread);
         }
         spend();
+        if constexpr (PART != kAlone) look_for_leavers(x, a, sh, b, base);
         return;
     }
     // ---- local test of node i against its parent's row
@@ -471,13 +459,14 @@ __device__ __forceinline__ void path_step(const AcceptArgs& a, const StepArgs& x
     }
     if constexpr (PART != kAlone) {
         __syncthreads();
-        announce_path(x, a, sh, b, base, unread, started);
+        announce_path(x, a, sh, b, base, unread);
     }
     for (int k = i; k < a.max_path; k += kThreads) {
         if (k > L) pth[k] = -1;
         if (k >= L) atk[k] = -1;
     }
     spend();
+    if constexpr (PART != kAlone) look_for_leavers(x, a, sh, b, base);
 }
 
 // one workgroup of the scan: run j of sequence b.  AHEAD chunks are in flight behind the one that is reduced.

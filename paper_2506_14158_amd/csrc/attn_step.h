@@ -38,12 +38,34 @@ struct Arguments {
     }
 };
 
-// the first wave, once all waves of the workgroup have the lengths
+// What an attention workgroup says to the collectors, the first wave's lanes to one sequence's each: that all its waves have the lengths ...
 template <StepKind KIND>
-__device__ __forceinline__ void lens_read(const StepTail<KIND>& t, const AttnArgs& a, const work::Lens& lens, long long started) {
+__device__ __forceinline__ void lens_read(const StepTail<KIND>& t, const AttnArgs& a, const work::Lens& lens) {
     asm volatile("" ::"v"(lens.mine));
-    const int lane = threadIdx.x;
-    if (lane < a.B) word::publish(t.step.lens + (size_t)lane * a.attn_wgs + blockIdx.x, t.step.tag, started, t.step.copy_ticks);
+    told::At p{t.step.lens + (size_t)threadIdx.x * a.attn_wgs + blockIdx.x};
+    if (threadIdx.x < (unsigned)a.B) told::tell(p, t.step.tag);
+}
+// ... and its look for one that has given up, before its output and behind it.
+template <StepKind KIND>
+__device__ __forceinline__ uint64_t lens_look_back() {
+    uint64_t mark = 0;
+    if constexpr (KIND != kNoStep) {
+        const Arguments args;
+        const AttnArgs& a = args.attn();
+        told::At p{args.tail<KIND>().step.lens + (size_t)threadIdx.x * a.attn_wgs + blockIdx.x};
+        if (threadIdx.x < (unsigned)a.B) mark = told::look_back(p);
+    }
+    return mark;
+}
+template <StepKind KIND>
+__device__ __forceinline__ void lens_end(uint64_t mark) {
+    if constexpr (KIND != kNoStep) {
+        const Arguments args;
+        const AttnArgs& a = args.attn();
+        const StepTail<KIND>& t = args.tail<KIND>();
+        told::At p{t.step.lens + (size_t)threadIdx.x * a.attn_wgs + blockIdx.x};
+        if (threadIdx.x < (unsigned)a.B) told::end(p, t.step.tag, mark);
+    }
 }
 
 // workgroups of a launch: the attention's, whole rounds over the XCDs, and the others

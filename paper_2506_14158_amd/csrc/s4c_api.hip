@@ -669,14 +669,14 @@ size_t step_bytes(const s4c_attn_shape& s, int32_t V) {
 }
 constexpr int kOneLaunchMostSequences = 32;           // (plan_waiting)
 size_t one_launch_bytes(const s4c_attn_shape& s) {
-    return s.B > kOneLaunchMostSequences ? 0 : (size_t)s.B * device_cus() * 2 * sizeof(word::Pair);      // at most two workgroups a CU
+    return s.B > kOneLaunchMostSequences ? 0 : (size_t)s.B * device_cus() * 2 * sizeof(told::Pair);      // at most two workgroups a CU
 }
 
 // A step in one launch: where the attention leaves places for the collectors and for enough scanning workgroups that the scan
 // is not the longer half.
 bool plan_one_launch(const s4c_step& p, const AttnPlan& plan, const AttnArgs& attn, AcceptArgs& accept) {
     if (p.logits_dtype != p.shape.dtype || attn.split == 0 || attn.B > kOneLaunchMostSequences || attn.B * 8 > attn.cus) return false;
-    if (p.accept_workspace_bytes < step_bytes(p.shape, p.V) + (size_t)attn.B * attn_workgroups(attn) * sizeof(word::Pair)) return false;
+    if (p.accept_workspace_bytes < step_bytes(p.shape, p.V) + (size_t)attn.B * attn_workgroups(attn) * sizeof(told::Pair)) return false;
     const int places = device_cus() * plan.tile.per_cu - attn_workgroups(attn) - attn.B;
     const int wgs = places / attn.B < accept.plan.wgs ? places / attn.B : accept.plan.wgs;
     if (wgs < 1) return false;
@@ -728,7 +728,7 @@ s4c_status s4c_verify_step(const s4c_step* p, void* hip_stream) {
         StepTail<kGreedyStep> tail;
         tail.accept = accept;
         tail.step = accept::make_step(accept, compact, messages, copy_ticks);
-        tail.step.lens = (word::Pair*)((char*)p->accept_workspace + step_bytes(p->shape, V));
+        tail.step.lens = (told::Pair*)((char*)p->accept_workspace + step_bytes(p->shape, V));
         tail.step.attn_wgs = attn_workgroups(attn);
         tail.step.tag = next_tag();
         e = launch_tree_attn(plan, attn, p->shape.dtype, &tail, st);

@@ -127,15 +127,15 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
     if constexpr (MERGE == parts::kHere)
         if (wave == 0) parts::begin<kD>(a, team, mt);
     work::Walk cw = work::walk_first(a, lens, team);      // what is multiplied
-    const long long started = STEP != kNoStep ? (long long)wall_clock64() : 0;
     if (cw.b < 0) {
         if constexpr (STEP != kNoStep) {
             __syncthreads();
-            lens_read(tail, a, lens, started);
+            lens_read(tail, a, lens);
         }
         if constexpr (MERGE != parts::kShares)
             if (work::leaves_empty(a, team))
                 parts::finish<kD, kElem, MERGE, WR, WR>(a, team, mt, smem, [&]() __attribute__((always_inline)) { parts::put_empty<kD, 1, MERGE>(a, team, mt * WR + wave, 0); });
+        lens_end<STEP>(lens_look_back<STEP>());
         return;
     }
     work::Walk pw = cw;                                   // what is loaded
@@ -253,7 +253,7 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
 #pragma unroll
     for (int t = 0; t < kKT; ++t) asm volatile("" : "+v"(qf[t]));          // in registers before the barrier
     __syncthreads();                                      // Q and parent[] are here, their stages free
-    if constexpr (STEP != kNoStep) lens_read(tail, a, lens, started);
+    if constexpr (STEP != kNoStep) lens_read(tail, a, lens);
     while (issued < NS - 1 && issued < n_share) issue_next();
 
     int parent = -1, b_known = cw.b;
@@ -510,12 +510,14 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
 #pragma unroll
             for (int j = 0; j < 16; ++j) o[db][j] = 0.f;
     }
+    const uint64_t left = lens_look_back<STEP>();
     if constexpr (MERGE != parts::kShares) {
         parts::finish<kD, kElem, MERGE, WR, WR>(Arguments().attn(), team, mt, smem, [&]() __attribute__((always_inline)) {
             parts::put<kD, 1, MERGE, true>(Arguments().attn(), team, mt * WR + wave, 0, m_run, l_tot, [&](int q) __attribute__((always_inline)) {
                 return f32x4{o[q >> 2][4 * (q & 3)], o[q >> 2][4 * (q & 3) + 1], o[q >> 2][4 * (q & 3) + 2], o[q >> 2][4 * (q & 3) + 3]};
             });
         });
+        lens_end<STEP>(left);
         return;
     }
     if (work::walk_is_whole(a, cw)) {
@@ -548,6 +550,7 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
             }
         }
     }
+    lens_end<STEP>(left);
     cw = nw;
     }
 }

@@ -163,17 +163,17 @@ void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP> tail) {
     if constexpr (MERGE == parts::kHere)
         if (wave == 0) parts::begin<kD>(a, team, mt);
     work::Walk cw = work::walk_first(a, lens, team);      // what is multiplied
-    const long long started = STEP != kNoStep ? (long long)wall_clock64() : 0;
     if (cw.b < 0) {
         if constexpr (STEP != kNoStep) {
             __syncthreads();
-            lens_read(tail, a, lens, started);
+            lens_read(tail, a, lens);
         }
         if constexpr (MERGE != parts::kShares)
             if (work::leaves_empty(a, team))
                 parts::finish<kD, C::kElem, MERGE, C::kWaves, kRBW>(a, team, mt, smem, [&]() __attribute__((always_inline)) {
                     if (kg < kOwners) parts::put_empty<kD, kOwners, MERGE>(a, team, mt * kRBW + rb, kg);
                 });
+        lens_end<STEP>(lens_look_back<STEP>());
         return;
     }
     work::Walk pw = cw;                                   // what is loaded
@@ -272,7 +272,7 @@ void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP> tail) {
         if (pw.b >= 0) issue_round();
     if constexpr (STEP != kNoStep) {
         __syncthreads();
-        lens_read(tail, a, lens, started);
+        lens_read(tail, a, lens);
     }
     if (issued == kNR - 1) wait_vmcnt<2 * kCH * (kNR - 1)>(); else wait_vmcnt<0>();
 
@@ -556,10 +556,12 @@ void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP> tail) {
         auto piece = [&](int q) __attribute__((always_inline)) {
             return f32x4{o[q >> 2][4 * (q & 3)], o[q >> 2][4 * (q & 3) + 1], o[q >> 2][4 * (q & 3) + 2], o[q >> 2][4 * (q & 3) + 3]};
         };
+        const uint64_t left = lens_look_back<STEP>();
         if constexpr (MERGE != parts::kShares) {
             parts::finish<kD, C::kElem, MERGE, C::kWaves, kRBW>(a, team, mt, smem, [&]() __attribute__((always_inline)) {
                 if (kg < kOwners) parts::put<kD, kOwners, MERGE>(a, team, mt * kRBW + rb, kg, m_max, l_tot, piece);
             });
+            lens_end<STEP>(left);
             return;
         }
         if (work::walk_is_whole(a, cw)) {
@@ -575,6 +577,7 @@ void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP> tail) {
             for (int q = 0; q < 4 * kOwn; ++q) *(f32x4*)(orow + 8 * q) = piece(q);
             if (kg == 0 && g32 == 0) *(float2*)(a.ws_ml + prow * 2) = make_float2(m_max, l_tot);
         }
+        lens_end<STEP>(left);
         if (a.split > 0) return;
         cw = nw;
     }

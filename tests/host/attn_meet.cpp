@@ -67,10 +67,7 @@ struct View {
         p->pause();
     }
     void settle() {
-        while (!p->written.empty()) {
-            land(*p, rng() % p->written.size());
-            p->pause();
-        }
+        while (!p->written.empty()) p->pause();
     }
     void look() {
         states.assign(launch->n, 0);

@@ -1,9 +1,7 @@
-"""How the workgroups of a divided unit agree on its merge (csrc/attn_meet.h), and where their parts lie (csrc/attn_division.h), played on
-the host: no GPU."""
+"""How workgroups of a launch hand things to each other, played on the host: those of a divided unit (csrc/attn_meet.h; where their parts lie:
+csrc/attn_division.h), and writers and readers that may give up (csrc/told.h).  No GPU."""
 import os
 import subprocess
-
-import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -24,4 +22,10 @@ def test_every_launch_ends_and_merges_its_own_parts_once(tmp_path):
 def test_parts_do_not_overlap(tmp_path):
     """Slabs, words and statistics of a team: inside its region, no byte in two of them; every column of every row once."""
     r = run(tmp_path, "attn_region")
+    assert r.returncode == 0, r.stdout
+
+
+def test_what_was_told_is_heard_or_taken_back(tmp_path):
+    """Readers that are gone before the writer begins, and the other way round, replays under one tag."""
+    r = run(tmp_path, "told", "60000")
     assert r.returncode == 0, r.stdout
