@@ -306,7 +306,9 @@ s4c_status s4c_draft_linear(int32_t T, int32_t H, int32_t Hout, int32_t dtype, c
  * acceptance and the compaction share one launch, which is also the attention's where that leaves room on the chip.  S4C_SEQ_TIMEOUT may also appear in
  * compact_status, if a workgroup that copies a sequence's rows did not hear of its path within the collector's waiting
  * time (s4c_accept_path) plus 2 s, or within S4C_COPY_WAIT_US microseconds (environment, an integer >= 0, read at
- * every call): that sequence's rows are not (all) appended, its cache_len stays and its dst_index is -1.
+ * every call), or if the attention in the same launch did not come to read the lengths in half that time: that sequence's rows are not (all) appended, its cache_len stays and its dst_index is -1.
+ * As many as four steps of up to 32 sequences may overlap in time without holding each other up, each with workspaces of its own.  (Of more, or
+ * larger ones, or beside large calls of s4c_accept_resample, some may wait until their limits run out.)
  *   attn_workspace    as s4c_tree_attn (s4c_tree_attn_workspace_size)
  *   accept_workspace  >= s4c_verify_step_workspace_size(&shape, V) bytes, 256-byte aligned, otherwise as
  *                     s4c_accept_path's */

@@ -667,7 +667,7 @@ namespace {
 size_t step_bytes(const s4c_attn_shape& s, int32_t V) {
     return s4c_accept_path_workspace_size(s.B, s.N, V) + (step_message_bytes(s.B, s.Hkv) + 255) / 256 * 256;
 }
-constexpr int kOneLaunchMostSequences = 32;           // (plan_waiting)
+constexpr int kOneLaunchMostSequences = 32;           // (heads_of_copier)
 size_t one_launch_bytes(const s4c_attn_shape& s) {
     return s.B > kOneLaunchMostSequences ? 0 : (size_t)s.B * device_cus() * 2 * sizeof(told::Pair);      // at most two workgroups a CU
 }

@@ -144,10 +144,10 @@ def test_divided_attention_on_four_streams():
             torch.cuda.synchronize()
 
 
-def test_steps_on_two_streams():
-    """Two steps that overlap, each with its own buffers: what each gives by itself."""
+def test_steps_on_four_streams():
+    """Four steps that overlap, each with its own buffers: what each gives by itself."""
     runs = []
-    for cfg in (CASES[0], CASES[4]):
+    for cfg in (CASES[0], CASES[4], CASES[1], CASES[2]):
         par = synth.make_parent(cfg)
         d = to_device(cfg, par, synth.make_attn_inputs(cfg), synth.make_accept_inputs(cfg, par))
         tv = TreeVerifier(cfg.B, cfg.N, cfg.Hq, cfg.Hkv, cfg.D, cfg.S_cap, cfg.V, d["q"].dtype, cfg.levels, cfg.P)
