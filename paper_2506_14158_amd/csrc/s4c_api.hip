@@ -2,6 +2,7 @@
 #include "attn_step.h"
 #include "common.h"
 #include "resample_plan.h"
+#include "step_plan.h"
 
 #include <math.h>
 #include <stdlib.h>
@@ -672,8 +673,7 @@ size_t one_launch_bytes(const s4c_attn_shape& s) {
     return s.B > kOneLaunchMostSequences ? 0 : (size_t)s.B * device_cus() * 2 * sizeof(told::Pair);      // at most two workgroups a CU
 }
 
-// A step in one launch: where the attention leaves places for the collectors and for enough scanning workgroups that the scan
-// is not the longer half.
+// A step in one launch: where the attention leaves places for the collectors and for enough scanning workgroups (step_plan.h).
 bool plan_one_launch(const s4c_step& p, const AttnPlan& plan, const AttnArgs& attn, AcceptArgs& accept) {
     if (p.logits_dtype != p.shape.dtype || attn.split == 0 || attn.B > kOneLaunchMostSequences || attn.B * 8 > attn.cus) return false;
     if (p.accept_workspace_bytes < step_bytes(p.shape, p.V) + (size_t)attn.B * attn_workgroups(attn) * sizeof(told::Pair)) return false;
@@ -682,7 +682,9 @@ bool plan_one_launch(const s4c_step& p, const AttnPlan& plan, const AttnArgs& at
     if (wgs < 1) return false;
     const long long chunks = ((long long)attn.N * accept.chunks + wgs - 1) / wgs;
     const long long tiles = ((attn.max_cache_len + attn.tile_keys - 1) / attn.tile_keys + (attn.N + attn.tile_keys - 1) / attn.tile_keys + attn.split - 1) / attn.split;
-    if (chunks > 4 + tiles) return false;
+    const StepScan scan = {chunks, accept.chunks, tiles, (long long)attn.B * attn.N * p.V * (p.logits_dtype == S4C_F32 ? 4 : 2), p.logits_dtype == S4C_F32,
+                           p.mode == S4C_GREEDY, plan.large, plan.tile.per_cu};
+    if (!one_launch_pays(scan)) return false;
     accept.plan.wgs = wgs;
     return true;
 }

@@ -1,5 +1,5 @@
 """A step in one launch, and divided attention merged in its own: against the oracle and the separate calls, eagerly and from a captured
-graph, where a merge takes several turns, sequences have fewer copiers, and several calls overlap."""
+graph, where the attention leaves few places, sequences have fewer copiers, and several calls overlap."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +14,7 @@ C = synth.CONFIGS
 TOL = {"f32": (1e-5, 1e-5), "bf16": (1e-2, 2e-2), "f16": (2e-3, 4e-3)}      # the storage type's rounding of P and of the output, as in the parity tests
 
 CASES = [
-    synth.scaled(C[3], name="several-turns", B=4, Hq=40, Hkv=40, P=1100, V=4000, index=0),               # 1280 merging tasks
+    synth.scaled(C[3], name="most-places", B=4, Hq=40, Hkv=40, P=2000, V=4000, index=0),                 # 480 workgroups attend
     synth.scaled(C[3], name="32-sequences", B=32, Hq=5, Hkv=5, P=300, N=20, levels=5, V=2000, ragged=True, index=0),     # two copiers each
     synth.scaled(C[2], name="odd-f16", B=3, Hq=7, Hkv=7, P=777, N=33, levels=5, V=5003, dtype="f16", ragged=True, index=0),
     synth.scaled(C[1], name="f32-d64", B=2, Hq=3, Hkv=3, P=900, N=17, V=3001, index=0),
@@ -78,6 +78,23 @@ def test_eager_and_replayed_steps(cfg):
         call()
         torch.cuda.synchronize()
         assert _same(seen(), first)
+
+
+def test_a_step_whose_scan_would_outlast_the_attention_takes_two_launches():
+    """Many short rows for the few workgroups that fit beside the attention (tests/test_step_plan.py)."""
+    cfg = synth.scaled(C[4], name="short-rows", B=6, Hq=32, Hkv=32, N=69, levels=6, P=134, V=4127, index=0)
+    par = synth.make_parent(cfg)
+    d = to_device(cfg, par, synth.make_attn_inputs(cfg), synth.make_accept_inputs(cfg, par))
+    tv = TreeVerifier(cfg.B, cfg.N, cfg.Hq, cfg.Hkv, cfg.D, cfg.S_cap, cfg.V, d["q"].dtype, cfg.levels, cfg.P)
+    k, v, n = d["k_cache"].clone(), d["v_cache"].clone(), d["cache_len"].clone()
+    assert not _in_one_launch(tv, lambda: tv.step(d["q"], d["k_tree"], d["v_tree"], k, v, n, d["parent"], d["logits"], d["tokens"], 0))
+    seen = [t.clone() for t in (tv.out, tv.path, tv.accept_len, tv.bonus_token, k, v, n)]
+    k, v, n = d["k_cache"].clone(), d["v_cache"].clone(), d["cache_len"].clone()
+    tv.tree_attn(d["q"], d["k_tree"], d["v_tree"], k, v, n, d["parent"])
+    tv.accept_path(d["logits"], d["parent"], d["tokens"], 0)
+    tv.kv_compact(d["k_tree"], d["v_tree"], k, v, n)
+    torch.cuda.synchronize()
+    assert _same(seen, [tv.out, tv.path, tv.accept_len, tv.bonus_token, k, v, n])
 
 
 @pytest.mark.parametrize("cfg", [CASES[0], CASES[3], CASES[4]], ids=lambda c: c.name)
