@@ -80,6 +80,45 @@ def test_eager_and_replayed_steps(cfg):
         assert _same(seen(), first)
 
 
+def test_waits_that_run_out_leave_nothing_behind(monkeypatch):
+    """A waiting time of zero: collectors that find a length unread, and copiers without a message, flag their sequence and leave its length; so
+    does every replay of the call, and the paths are right all the same.  With the usual wait the same workspaces serve again."""
+    cfg = synth.scaled(C[4], name="no-wait", B=3, Hq=16, Hkv=8, P=500, N=24, levels=5, V=150_007, index=0)
+    par = synth.make_parent(cfg)
+    d = to_device(cfg, par, synth.make_attn_inputs(cfg), synth.make_accept_inputs(cfg, par))
+    tv = TreeVerifier(cfg.B, cfg.N, cfg.Hq, cfg.Hkv, cfg.D, cfg.S_cap, cfg.V, d["q"].dtype, cfg.levels, cfg.P)
+    k, v, n = d["k_cache"].clone(), d["v_cache"].clone(), d["cache_len"].clone()
+    step = lambda: tv.step(d["q"], d["k_tree"], d["v_tree"], k, v, n, d["parent"], d["logits"], d["tokens"], 0)
+    seen = lambda: [t.clone() for t in (tv.out, tv.path, tv.accept_len, tv.bonus_token)]
+
+    def reset(shorter=0):
+        for dst, src in ((k, "k_cache"), (v, "v_cache"), (n, "cache_len")):
+            dst.copy_(d[src])
+        n.sub_(shorter)
+        torch.cuda.synchronize()
+
+    reset()
+    assert _in_one_launch(tv, step)
+    want, after = seen(), [t.clone() for t in (k, v, n, tv.dst_index, tv.compact_status)]
+    monkeypatch.setenv("S4C_COPY_WAIT_US", "0")
+    g, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(g, stream=side):
+            step()
+    monkeypatch.delenv("S4C_COPY_WAIT_US")
+    for i in range(6):
+        reset(shorter=7 * (i % 2))
+        g.replay()
+        torch.cuda.synchronize()
+        assert tv.compact_status.tolist() == [4] * cfg.B and bool((tv.dst_index == -1).all())      # S4C_SEQ_TIMEOUT
+        assert torch.equal(n, d["cache_len"] - 7 * (i % 2))
+        assert _same(seen()[1:], want[1:]) and (i % 2 == 1 or torch.equal(tv.out, want[0]))
+    reset()
+    step()
+    torch.cuda.synchronize()
+    assert _same(seen(), want) and _same([k, v, n, tv.dst_index, tv.compact_status], after)
+
+
 def test_a_step_whose_scan_would_outlast_the_attention_takes_two_launches():
     """Many short rows for the few workgroups that fit beside the attention (tests/test_step_plan.py)."""
     cfg = synth.scaled(C[4], name="short-rows", B=6, Hq=32, Hkv=32, N=69, levels=6, P=134, V=4127, index=0)
