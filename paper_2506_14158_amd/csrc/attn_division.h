@@ -162,21 +162,26 @@ struct Walk {
     int left;              // tiles of the share after this segment
 };
 
+// ... of a launch of equal runs, or of whole units (split = 1): the only segment of team's share
 template <class A, class L>
-S4C_WORK Walk walk_first(const A& a, const L& lens, int team) {
+S4C_WORK Walk walk_run(const A& a, const L& lens, int team) {
     Walk w = {-1, 0, 0, 0, 0, 0};
     if (team >= a.teams) return w;
-    if (a.split > 0) {
-        const int unit = team / a.split, k = team - unit * a.split;
-        w.b = unit / a.Hkv;
-        w.kvh = unit - w.b * a.Hkv;
-        w.tiles = lens.tiles(a, w.b);
-        const int run = (w.tiles + a.split - 1) / a.split;
-        w.tile = k * run;
-        w.tile_end = w.tiles < w.tile + run ? w.tiles : w.tile + run;
-        if (w.tile >= w.tile_end) w.b = -1;         // (an empty run: see leaves_empty)
-        return w;
-    }
+    const int unit = team / a.split, k = team - unit * a.split;
+    w.b = unit / a.Hkv;
+    w.kvh = unit - w.b * a.Hkv;
+    w.tiles = lens.tiles(a, w.b);
+    const int run = (w.tiles + a.split - 1) / a.split;
+    w.tile = k * run;
+    w.tile_end = w.tiles < w.tile + run ? w.tiles : w.tile + run;
+    if (w.tile >= w.tile_end) w.b = -1;         // (an empty run: see leaves_empty)
+    return w;
+}
+// ... of a balanced launch: the first segment
+template <class A, class L>
+S4C_WORK Walk walk_share(const A& a, const L& lens, int team) {
+    Walk w = {-1, 0, 0, 0, 0, 0};
+    if (team >= a.teams) return w;
     const typename L::Order order(a, lens);
     // Fewer tiles than teams (short sequences under a large max_cache_len): as many teams as tiles, so that every team
     // between the one that begins a unit and the one that ends it has a part of it.

@@ -22,12 +22,12 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kCoherent = 16;                // cache policy of the buffer instructions: sc1, device scope
 constexpr int kTake = 4;                     // slabs of a merging wave (32 columns)
-// What a kernel does with units of several parts.  kShares: it has none, or the parts of balanced shares (attn_merge.h).  Equal runs: kHere
-// merges them in this launch; kNext leaves them to the next one, where that has other work to do meanwhile (the acceptance of a step behind the
+// What the workgroups of a kernel walk, and what becomes of units in parts.  kWhole: a unit each.  kShares: balanced shares, their parts for attn_merge.h.
+// Equal runs: kHere merges them in this launch; kNext leaves them to the next one, where that has other work to do meanwhile (the acceptance of a step behind the
 // attention: 8 x 32/8 heads, 8192 keys 115.1 us merged here, 113.8 there).
-// (In one kernel for all three, undivided launches kept the values of the other two: 29 scalar registers spilled
+// (In one kernel for all of them, whole units kept the values of the others: 29 scalar registers spilled
 // instead of none, 27 layers of 3 x 4 heads, 73 nodes 461.5 us against 459.0.)
-enum Merge { kShares, kHere, kNext };
+enum Merge { kWhole, kShares, kHere, kNext };
 
 template <int D>
 struct Region : PartRegion<D> {

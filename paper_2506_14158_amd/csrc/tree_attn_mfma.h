@@ -126,13 +126,15 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
     }
     if constexpr (MERGE == parts::kHere)
         if (wave == 0) parts::begin<kD>(a, team, mt);
-    work::Walk cw = work::walk_first(a, lens, team);      // what is multiplied
+    constexpr bool kOne = MERGE != parts::kShares;        // a share is one segment
+    work::Walk cw;                                        // what is multiplied
+    if constexpr (kOne) cw = work::walk_run(a, lens, team); else cw = work::walk_share(a, lens, team);
     if (cw.b < 0) {
         if constexpr (STEP != kNoStep) {
             __syncthreads();
             lens_read(tail, a, lens);
         }
-        if constexpr (MERGE != parts::kShares)
+        if constexpr (MERGE == parts::kHere || MERGE == parts::kNext)
             if (work::leaves_empty(a, team))
                 parts::finish<kD, kElem, MERGE, WR, WR>(a, team, mt, smem, [&]() __attribute__((always_inline)) { parts::put_empty<kD, 1, MERGE>(a, team, mt * WR + wave, 0); });
         lens_end<STEP>(lens_look_back<STEP>());
@@ -181,8 +183,8 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
     };
     auto end_tile = [&]() __attribute__((always_inline)) {
         if (pw.tile == pw.tile_end) {
-            pw = work::walk_next(a, lens, pw);
-            if (pw.b >= 0) begin_segment();
+            if constexpr (kOne) pw.b = -1; else pw = work::walk_next(a, lens, pw);
+            if (!kOne && pw.b >= 0) begin_segment();
         }
     };
     auto issue_next = [&]() __attribute__((always_inline)) {
@@ -493,12 +495,15 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
         if (wave_on) tile_body(std::integral_constant<int, kTree>{}, t - u_pref);
     }
 
-    const work::Walk nw = work::walk_next(a, lens, cw);
-    if (nw.b >= 0) {
-        if (nw.b != b && tid < N) parent = a.parent[(size_t)nw.b * N + tid];
-        load_q(nw.b, nw.kvh);
+    work::Walk nw = cw;
+    if constexpr (!kOne) {
+        nw = work::walk_next(a, lens, cw);
+        if (nw.b >= 0) {
+            if (nw.b != b && tid < N) parent = a.parent[(size_t)nw.b * N + tid];
+            load_q(nw.b, nw.kvh);
+        }
+        if (mt == 0 && tid == 0) work::note_parts(a, team, cw);
     }
-    if (MERGE == parts::kShares && a.split == 0 && mt == 0 && tid == 0) work::note_parts(a, team, cw);
     // ---- write this lane's row: d = 32 db + 8 (j/4) + 4 g32 + (j%4)
     const int flagged = (work::tree_is_bad(a, spar) ? S4C_SEQ_BAD_TREE : 0) | (len_bad ? S4C_SEQ_BAD_LEN : 0);
     if (a.status && tid == 0 && cw.tile == 0 && kvh == 0 && mt == 0) a.status[b] = flagged;
@@ -511,7 +516,7 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
             for (int j = 0; j < 16; ++j) o[db][j] = 0.f;
     }
     const uint64_t left = lens_look_back<STEP>();
-    if constexpr (MERGE != parts::kShares) {
+    if constexpr (MERGE == parts::kHere || MERGE == parts::kNext) {
         parts::finish<kD, kElem, MERGE, WR, WR>(Arguments().attn(), team, mt, smem, [&]() __attribute__((always_inline)) {
             parts::put<kD, 1, MERGE, true>(Arguments().attn(), team, mt * WR + wave, 0, m_run, l_tot, [&](int q) __attribute__((always_inline)) {
                 return f32x4{o[q >> 2][4 * (q & 3)], o[q >> 2][4 * (q & 3) + 1], o[q >> 2][4 * (q & 3) + 2], o[q >> 2][4 * (q & 3) + 3]};
@@ -520,7 +525,7 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
         lens_end<STEP>(left);
         return;
     }
-    if (work::walk_is_whole(a, cw)) {
+    if (MERGE == parts::kWhole || work::walk_is_whole(a, cw)) {
         if (rvalid) {
         const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
         bf16_t* orow = (bf16_t*)a.out + (((size_t)b * N + node) * a.Hq + kvh * G + g) * kD + 4 * g32;
@@ -551,6 +556,7 @@ void tree_attn_mfma_kernel(AttnArgs a, StepTail<STEP> tail) {
         }
     }
     lens_end<STEP>(left);
+    if constexpr (kOne) return;
     cw = nw;
     }
 }
@@ -576,7 +582,9 @@ hipError_t launch_rows(const AttnArgs& a, const StepTail<STEP>& tail, hipStream_
 }
 template <bool PAGED, bool F16, int D, StepKind STEP>
 hipError_t launch_rows(const AttnArgs& a, const StepTail<STEP>& tail, hipStream_t st) {
-    if (a.split <= 1) return launch_rows<PAGED, F16, D, STEP, parts::kShares>(a, tail, st);
+    if (a.split == 1) return launch_rows<PAGED, F16, D, STEP, parts::kWhole>(a, tail, st);
+    if constexpr (STEP == kNoStep)
+        if (a.split == 0) return launch_rows<PAGED, F16, D, STEP, parts::kShares>(a, tail, st);
     if constexpr (!PAGED && STEP == kNoStep)
         if (a.tag == 0) return launch_rows<PAGED, F16, D, STEP, parts::kNext>(a, tail, st);
     return launch_rows<PAGED, F16, D, STEP, parts::kHere>(a, tail, st);

@@ -162,13 +162,15 @@ void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP> tail) {
     }
     if constexpr (MERGE == parts::kHere)
         if (wave == 0) parts::begin<kD>(a, team, mt);
-    work::Walk cw = work::walk_first(a, lens, team);      // what is multiplied
+    constexpr bool kOne = MERGE != parts::kShares;            // a share is one segment
+    work::Walk cw;                                        // what is multiplied
+    if constexpr (kOne) cw = work::walk_run(a, lens, team); else cw = work::walk_share(a, lens, team);
     if (cw.b < 0) {
         if constexpr (STEP != kNoStep) {
             __syncthreads();
             lens_read(tail, a, lens);
         }
-        if constexpr (MERGE != parts::kShares)
+        if constexpr (MERGE == parts::kHere || MERGE == parts::kNext)
             if (work::leaves_empty(a, team))
                 parts::finish<kD, C::kElem, MERGE, C::kWaves, kRBW>(a, team, mt, smem, [&]() __attribute__((always_inline)) {
                     if (kg < kOwners) parts::put_empty<kD, kOwners, MERGE>(a, team, mt * kRBW + rb, kg);
@@ -219,8 +221,8 @@ void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP> tail) {
     };
     auto end_round = [&]() __attribute__((always_inline)) {
         if (pw.tile >= pw.tile_end) {
-            pw = work::walk_next(a, lens, pw);
-            if (pw.b >= 0) begin_segment();
+            if constexpr (kOne) pw.b = -1; else pw = work::walk_next(a, lens, pw);
+            if (!kOne && pw.b >= 0) begin_segment();
         }
     };
     auto issue_round = [&]() __attribute__((always_inline)) {
@@ -464,10 +466,13 @@ void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP> tail) {
             tile(std::integral_constant<bool, true>{}, visible);
         }
 
-        const work::Walk nw = work::walk_next(a, lens, cw);
-        if (nw.b >= 0) {
-            if (nw.b != b && tid < N) parent = a.parent[(size_t)nw.b * N + tid];
-            load_q(nw.b, nw.kvh);
+        work::Walk nw = cw;
+        if constexpr (!kOne) {
+            nw = work::walk_next(a, lens, cw);
+            if (nw.b >= 0) {
+                if (nw.b != b && tid < N) parent = a.parent[(size_t)nw.b * N + tid];
+                load_q(nw.b, nw.kvh);
+            }
         }
         const int flagged = (work::tree_is_bad(a, spar) ? S4C_SEQ_BAD_TREE : 0) | (len_bad ? S4C_SEQ_BAD_LEN : 0);
         if (a.status && tid == 0 && cw.tile == 0 && kvh == 0 && mt == 0) a.status[b] = flagged;
@@ -549,22 +554,21 @@ void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP> tail) {
                         }
                 }
         };
-        if (MERGE != parts::kShares || a.split > 0) meet(std::integral_constant<bool, true>{});
-        else meet(std::integral_constant<bool, false>{});
-        if (MERGE == parts::kShares && a.split == 0 && mt == 0 && tid == 0) work::note_parts(a, team, cw);
+        meet(std::integral_constant<bool, kOne>{});
+        if (!kOne && mt == 0 && tid == 0) work::note_parts(a, team, cw);
         // ---- the row's columns: d = 32 column_block(db) + 8 (j/4) + 4 g32 + (j%4)
         auto piece = [&](int q) __attribute__((always_inline)) {
             return f32x4{o[q >> 2][4 * (q & 3)], o[q >> 2][4 * (q & 3) + 1], o[q >> 2][4 * (q & 3) + 2], o[q >> 2][4 * (q & 3) + 3]};
         };
         const uint64_t left = lens_look_back<STEP>();
-        if constexpr (MERGE != parts::kShares) {
+        if constexpr (MERGE == parts::kHere || MERGE == parts::kNext) {
             parts::finish<kD, C::kElem, MERGE, C::kWaves, kRBW>(a, team, mt, smem, [&]() __attribute__((always_inline)) {
                 if (kg < kOwners) parts::put<kD, kOwners, MERGE>(a, team, mt * kRBW + rb, kg, m_max, l_tot, piece);
             });
             lens_end<STEP>(left);
             return;
         }
-        if (work::walk_is_whole(a, cw)) {
+        if (MERGE == parts::kWhole || work::walk_is_whole(a, cw)) {
             const float inv = (l_tot > 0.f) ? 1.f / l_tot : 0.f;
             const size_t o0 = (((size_t)b * a.N + node) * a.Hq + kvh * G + gh) * kD + 32 * kOwn * kg + 4 * g32;
             if (rvalid && kg < kOwners)
@@ -578,7 +582,7 @@ void tree_attn_smallm_kernel(AttnArgs a, StepTail<STEP> tail) {
             if (kg == 0 && g32 == 0) *(float2*)(a.ws_ml + prow * 2) = make_float2(m_max, l_tot);
         }
         lens_end<STEP>(left);
-        if (a.split > 0) return;
+        if constexpr (kOne) return;
         cw = nw;
     }
 }
@@ -595,7 +599,9 @@ hipError_t launch(AttnArgs a, StepTail<STEP> tail, hipStream_t st) {
 }
 template <class C, bool PAGED, StepKind STEP>
 hipError_t launch(const AttnArgs& a, const StepTail<STEP>& tail, hipStream_t st) {
-    if (a.split <= 1) return launch<C, PAGED, STEP, parts::kShares>(a, tail, st);
+    if (a.split == 1) return launch<C, PAGED, STEP, parts::kWhole>(a, tail, st);
+    if constexpr (STEP == kNoStep)
+        if (a.split == 0) return launch<C, PAGED, STEP, parts::kShares>(a, tail, st);
     if constexpr (!PAGED && STEP == kNoStep)
         if (a.tag == 0) return launch<C, PAGED, STEP, parts::kNext>(a, tail, st);
     return launch<C, PAGED, STEP, parts::kHere>(a, tail, st);

@@ -58,7 +58,7 @@ const char* wrong(const Args& a, const AttnDivision& d, const Lens& lens) {
     for (int wg = 0; wg < (a.teams + 7) / 8 * 8; ++wg) {
         const int team = work::team_id(a, wg & 7, wg >> 3);
         if (team < a.teams && seen[team]++) return "a team number is used twice";
-        work::Walk w = work::walk_first(a, lens, team);
+        work::Walk w = a.split > 0 ? work::walk_run(a, lens, team) : work::walk_share(a, lens, team);
         if (w.b < 0 && work::leaves_empty(a, team)) slots[team] = kEmpty;
         while (w.b >= 0) {
             const int u = w.b * a.Hkv + w.kvh;

@@ -45,12 +45,13 @@ def test_sequential_acceptance_keeps_its_rows_in_registers(resample, kernel, blo
 
 
 def test_attention_that_merges_nothing_keeps_nothing_for_it():
-    """Many-row kernels: no scratch memory in any of them; those of launches without equal runs (parts::kShares, 0) and without the rest of a
-    step (kNoStep, 0) spill next to no scalar registers (none contiguous; 5 paged, for the page table)."""
+    """Many-row kernels: no scratch memory in any of them; those without the rest of a step (kNoStep, 0) spill no scalar registers where
+    they walk one unit (parts::kWhole, 0), next to none where they walk shares (kShares, 1; a few paged, for the page table)."""
     got = {k: v for k, v in resources("tree_attn_mfma_f16.hip").items() if "tree_attn_mfma_kernel" in k}
-    lean = {k: v for k, v in got.items() if "StepKindE0ELNS_5parts5MergeE0E" in k}
-    assert len(lean) == 8, sorted(got)                       # rows, head sizes, paged or not
     for name, r in got.items():
         assert r["VGPRs Spill"] == 0 and r["ScratchSize"] == 0, (name, r)
-    for name, r in lean.items():
-        assert r["SGPRs Spill"] <= (8 if "Lb1ELb1E" in name else 2), (name, r)
+    for merge, paged, most in ((0, False, 0), (0, True, 0), (1, False, 2), (1, True, 8)):
+        lean = {k: v for k, v in got.items() if "StepKindE0ELNS_5parts5MergeE%dE" % merge in k and ("Lb1ELb1E" in k) == paged}
+        assert len(lean) == 4, sorted(got)                   # rows, head sizes
+        for name, r in lean.items():
+            assert r["SGPRs Spill"] <= most, (name, r)
