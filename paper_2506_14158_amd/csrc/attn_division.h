@@ -34,6 +34,8 @@ namespace s4c {
 // data of head size 128; part_keys: waves that share the columns of a row when it writes.
 struct AttnTile { int rows, keys, per_cu; bool wide; int part_keys = 1; };
 
+constexpr int kMostRuns = 24;              // of a unit; up to 32 (attn_parts.h)
+
 struct AttnDivision {
     int teams, split, mtiles;
     int parts;                 // most parts a unit is divided into when no sequence is shorter than max_cache_len
@@ -51,13 +53,13 @@ inline AttnDivision plan_division(int B, int Hkv, int N, int M, int max_cache_le
     // shorter than kMinKeys keys, below which a part's fixed costs (prologue, partial results, its share of the merge)
     // outweigh what the extra workgroups stream, but never fewer than units for that: whole units have no parts, and several
     // short ones in a row are a chain (512 units of 20 keys + 20 nodes: 28.0 us on 192 teams, 8.6 on 512).  At most
-    // kMaxParts runs per unit.
-    const long long kMinKeys = 256, kMaxParts = 24, per_xcd = slots / 8;
+    // kMostRuns per unit.
+    const long long kMinKeys = 256, per_xcd = slots / 8;
     long long teams = per_xcd >= p.mtiles ? per_xcd / p.mtiles * 8 : 8;
     long long most = units * tiles * t.keys / kMinKeys;
     if (most < units) most = units;
     if (teams > most) teams = most;
-    if (teams > units * kMaxParts) teams = units * kMaxParts;
+    if (teams > units * kMostRuns) teams = units * kMostRuns;
     // A share that ends inside a unit has a second segment to start and finish, which costs as much as kSwitchKeys keys:
     // whole numbers of runs per unit where the longer runs cost less than that, and where no unit would get a second.
     //
@@ -79,7 +81,8 @@ inline AttnDivision plan_division(int B, int Hkv, int N, int M, int max_cache_le
     const long long rounds = (units + teams - 1) / teams, idle = tiles * t.keys * (rounds * teams - units) / (rounds * teams);
     const long long rows = M < t.rows ? M : t.rows;
     long long split = 0;
-    if (units * tiles > 0x3FFFFFFFll) split = 1;                             // beyond the kernels' 32-bit tile numbers
+    // beyond the kernels' 32-bit tile numbers, or offsets in the parts of a unit (8 M 128 bytes each: PartRegion)
+    if (units * tiles > 0x3FFFFFFFll || M > (int)(0xFFFFFFFFu / (8u * 128u * kMostRuns))) split = 1;
     else if (teams >= units) {
         const long long q = teams / units;
         if ((tiles + q - 1) / q * t.keys <= units * tiles * t.keys / teams + kSwitchKeys) split = q;

@@ -21,7 +21,6 @@ enum Elem { kB16 = 0, kH16 = 1, kF32 = 2 };  // bf16, fp16, fp32
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kCoherent = 16;                // cache policy of the buffer instructions: sc1, device scope
-constexpr int kTake = 4;                     // slabs of a merging wave (32 columns)
 // What the workgroups of a kernel walk, and what becomes of units in parts.  kWhole: a unit each.  kShares: balanced shares, their parts for attn_merge.h.
 // Equal runs: kHere merges them in this launch; kNext leaves them to the next one, where that has other work to do meanwhile (the acceptance of a step behind the
 // attention: 8 x 32/8 heads, 8192 keys 115.1 us merged here, 113.8 there).
@@ -74,35 +73,37 @@ __device__ __forceinline__ void put_empty(const AttnArgs& a, int team, int block
     put<D, KEYS, MERGE>(a, team, block, key, -INFINITY, 0.f, [](int) { return f32x4{0.f, 0.f, 0.f, 0.f}; });
 }
 
-// ---- A wave merges 32 columns of a row block of one unit, its parts in the order of the runs => deterministic.
-// BATCH parts are in flight together (18 registers each).
-template <int D, Elem E, Merge MERGE, int BATCH>
-__device__ __forceinline__ void take(const AttnArgs& a, int unit, int block, int quarter) {
+// ---- A wave merges SLABS slabs of a row block of one unit from number `slab` on, its parts in the order of the runs => deterministic.
+// BATCH parts are in flight together (4 SLABS + 2 registers each).
+template <int D, Elem E, Merge MERGE, int SLABS, int BATCH>
+__device__ __forceinline__ void take(const AttnArgs& a, int unit, int block, int slab) {
     typedef Region<D> R;
     constexpr int kPolicy = MERGE == kHere ? kCoherent : 0;
     const int lane = threadIdx.x & 63, n = a.split;
-    const int key = quarter * a.part_keys / (D / 32);
+    const int key = slab * a.part_keys / (D / 8);
     const int b = unit / a.Hkv, kvh = unit - b * a.Hkv;
     const int r = 32 * block + (lane & 31);
     if (r >= a.M) return;
-    f32x4 o[kTake];
+    f32x4 o[SLABS];
     float m = -INFINITY, l = 0.f;
 #pragma unroll
-    for (int q = 0; q < kTake; ++q) o[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto from = [&](int p) __attribute__((always_inline)) { return resource(R::of(a, unit * n + p), R::bytes(a.M)); };
-    f32x4 v[BATCH][kTake];
+    for (int q = 0; q < SLABS; ++q) o[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // (one resource for all parts: one for each took more scalar registers than there are)
+    const uint32_t bytes = R::bytes(a.M);
+    const __amdgpu_buffer_rsrc_t all = resource(R::of(a, unit * n), bytes * n);
+    f32x4 v[BATCH][SLABS];
     u32x2 st[BATCH];
     auto fetch = [&](int p0, bool slabs) __attribute__((always_inline)) {
 #pragma unroll
         for (int p = 0; p < BATCH; ++p) {
             st[p] = u32x2{0, 0};
             if (p0 + p < n) {
-                st[p] = __builtin_amdgcn_raw_buffer_load_b64(from(p0 + p), R::stats(a.M, block, key, lane), 0, kPolicy);
+                st[p] = __builtin_amdgcn_raw_buffer_load_b64(all, R::stats(a.M, block, key, lane), (p0 + p) * bytes, kPolicy);
                 if (slabs) {
 #pragma unroll
-                    for (int q = 0; q < kTake; ++q)
-                        v[p][q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                            from(p0 + p), R::slab(a.M, block, quarter * kTake + q, lane), 0, kPolicy));
+                    for (int q = 0; q < SLABS; ++q)
+                        v[p][q] = __builtin_bit_cast(
+                            f32x4, __builtin_amdgcn_raw_buffer_load_b128(all, R::slab(a.M, block, slab + q, lane), (p0 + p) * bytes, kPolicy));
                 }
             }
         }
@@ -126,7 +127,7 @@ __device__ __forceinline__ void take(const AttnArgs& a, int unit, int block, int
                 const float w = pl > 0.f ? fast_exp2(__uint_as_float(st[p][0]) - m) : 0.f;       // 0: the part saw nothing visible
                 l = fmaf(pl, w, l);
 #pragma unroll
-                for (int q = 0; q < kTake; ++q)
+                for (int q = 0; q < SLABS; ++q)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) o[q][e] = fmaf(v[p][q][e], w, o[q][e]);
             }
@@ -135,18 +136,18 @@ __device__ __forceinline__ void take(const AttnArgs& a, int unit, int block, int
     }
     const float inv = l > 0.f ? 1.f / l : 0.f;
     const int node = r / a.G, g = r - node * a.G;
-    const size_t o0 = (((size_t)b * a.N + node) * a.Hq + kvh * a.G + g) * D + 32 * quarter + 4 * (lane >> 5);
+    const size_t o0 = (((size_t)b * a.N + node) * a.Hq + kvh * a.G + g) * D + 8 * slab + 4 * (lane >> 5);
 #pragma unroll
-    for (int q = 0; q < kTake; ++q) store_out<E>(a.out, o0 + 8 * q, o[q] * inv);
+    for (int q = 0; q < SLABS; ++q) store_out<E>(a.out, o0 + 8 * q, o[q] * inv);
 }
 
-// The merging waves of the next launch.
+// The merging waves of the next launch, 32 columns each.
 __host__ __device__ inline int tasks(const AttnArgs& a) { return a.split > 1 ? a.B * a.Hkv * ((a.M + 31) / 32) * (a.D / 32) : 0; }
 template <int D, Elem E, int BATCH>
 __device__ __forceinline__ void take_task(const AttnArgs& a, int task) {
     if (task >= tasks(a)) return;
     const int blocks = (a.M + 31) / 32, at = task / (D / 32);
-    take<D, E, kNext, BATCH>(a, at / blocks, at % blocks, task % (D / 32));
+    take<D, E, kNext, 4, BATCH>(a, at / blocks, at % blocks, task % (D / 32) * 4);
 }
 
 // ---- The workgroups of a unit's runs (for one tile of its rows) meet, seen from a wave of one of them (attn_meet.h).
@@ -215,8 +216,16 @@ __device__ __forceinline__ void finish(const AttnArgs& a, int team, int mt, unsi
     const int unit = team / a.split, me = team - unit * a.split;      // (me < 32)
     const int rank = __builtin_popcount(lo & ((1u << me) - 1u)), stay = __builtin_popcount(lo) + __builtin_popcount(hi);
     const int blocks = min(BLOCKS, (a.M + 31) / 32 - mt * BLOCKS);
-    // (over the workgroups first: 16 parts of 108 rows, merged by the waves of four of the 16 CUs, took 0.6 us longer a launch)
-    for (int t = wave * stay + rank; t < blocks * (D / 32); t += stay * WAVES) take<D, E, kHere, 8>(a, unit, mt * BLOCKS + t / (D / 32), t % (D / 32));
+    // Over the workgroups first: 16 parts of 108 rows, merged by the waves of four of the 16 CUs, took 0.6 us longer a launch.  32 columns a wave of
+    // up to eight parts, all in flight together; of more, 8 columns, all of them in flight too.  (Batches of eight parts one after the other: a
+    // step of 32/8 heads, 4000 keys, 16 parts 22.8 us and 21.0; 21 parts of 56 rows of size 64 32.5 and 30.4.)
+    auto share = [&](auto slabs, auto batch) __attribute__((always_inline)) {
+        constexpr int kSlabs = decltype(slabs)::value, kTasks = D / 8 / kSlabs;
+        for (int t = wave * stay + rank; t < blocks * kTasks; t += stay * WAVES)
+            take<D, E, kHere, kSlabs, decltype(batch)::value>(a, unit, mt * BLOCKS + t / kTasks, t % kTasks * kSlabs);
+    };
+    if (a.split <= 8) share(std::integral_constant<int, 4>{}, std::integral_constant<int, 8>{});
+    else share(std::integral_constant<int, 1>{}, std::integral_constant<int, kMostRuns>{});
     if (wave == 0) meet::end(w);
 }
 
