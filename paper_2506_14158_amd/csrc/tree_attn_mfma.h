@@ -575,10 +575,11 @@ hipError_t launch(AttnArgs a, StepTail<STEP> tail, hipStream_t st) {
     return hipGetLastError();
 }
 
-// four waves (up to 128 rows): one workgroup per CU and wave per SIMD; eight: two waves per SIMD
+// four waves (up to 128 rows): one workgroup per CU and wave per SIMD, or two of head size 64 (attn_tile_large), which 256 registers a thread allow (with 262
+// there was one: 24 parts of 76 rows, 21000 keys 67.5 us and 53.0; 12 parts of 71 rows, 12000 keys 55.5 and 42.9); eight: two waves per SIMD
 template <bool PAGED, bool F16, int D, StepKind STEP, parts::Merge MERGE>
 hipError_t launch_rows(const AttnArgs& a, const StepTail<STEP>& tail, hipStream_t st) {
-    return pick_wr(a.M) == 4 ? launch<4, 4, 1, PAGED, F16, D, STEP, MERGE>(a, tail, st) : launch<8, 4, 2, PAGED, F16, D, STEP, MERGE>(a, tail, st);
+    return pick_wr(a.M) == 4 ? launch<4, 4, D == 64 ? 2 : 1, PAGED, F16, D, STEP, MERGE>(a, tail, st) : launch<8, 4, 2, PAGED, F16, D, STEP, MERGE>(a, tail, st);
 }
 template <bool PAGED, bool F16, int D, StepKind STEP>
 hipError_t launch_rows(const AttnArgs& a, const StepTail<STEP>& tail, hipStream_t st) {

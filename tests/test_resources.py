@@ -50,6 +50,8 @@ def test_attention_that_merges_nothing_keeps_nothing_for_it():
     got = {k: v for k, v in resources("tree_attn_mfma_f16.hip").items() if "tree_attn_mfma_kernel" in k}
     for name, r in got.items():
         assert r["VGPRs Spill"] == 0 and r["ScratchSize"] == 0, (name, r)
+        # as many waves on a SIMD as the launches count on: two of four-wave workgroups of head size 64, or of eight waves
+        assert r["Occupancy"] >= (1 if "kernelILi4E" in name and "ELi128E" in name else 2), (name, r)
     for merge, paged, most in ((0, False, 0), (0, True, 0), (1, False, 2), (1, True, 8)):
         lean = {k: v for k, v in got.items() if "StepKindE0ELNS_5parts5MergeE%dE" % merge in k and ("Lb1ELb1E" in k) == paged}
         assert len(lean) == 4, sorted(got)                   # rows, head sizes
