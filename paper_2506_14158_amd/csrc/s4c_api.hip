@@ -683,7 +683,7 @@ bool plan_one_launch(const s4c_step& p, const AttnPlan& plan, const AttnArgs& at
     const long long chunks = ((long long)attn.N * accept.chunks + wgs - 1) / wgs;
     const long long tiles = ((attn.max_cache_len + attn.tile_keys - 1) / attn.tile_keys + (attn.N + attn.tile_keys - 1) / attn.tile_keys + attn.split - 1) / attn.split;
     const StepScan scan = {chunks, accept.chunks, tiles, (long long)attn.B * attn.N * p.V * (p.logits_dtype == S4C_F32 ? 4 : 2), p.logits_dtype == S4C_F32,
-                           p.mode == S4C_GREEDY, plan.large, plan.tile.per_cu};
+                           p.mode == S4C_GREEDY, plan.large, attn.D};
     if (!one_launch_pays(scan)) return false;
     accept.plan.wgs = wgs;
     return true;

@@ -1,5 +1,5 @@
 // Prints what csrc/step_plan.h says of steps, a line each: 1 one launch, 0 two.
-// Usage: step_plan CHUNKS ROW_CHUNKS TILES LOGITS_BYTES FP32 GREEDY LARGE PER_CU [...]
+// Usage: step_plan CHUNKS ROW_CHUNKS TILES LOGITS_BYTES FP32 GREEDY LARGE HEAD [...]
 #include <cstdio>
 #include <cstdlib>
 
