@@ -80,7 +80,7 @@ def _timed_ms(torch, fn, reps=10):
     return e0.elapsed_time(e1) / reps
 
 
-ATTN_SOURCES = ("tree_attn_mfma.h", "tree_attn_smallm.h", "attn_parts.h", "attn_step.h", "attn_merge.hip", "attn_merge.h", "attn_work.h", "attn_division.h",
+ATTN_SOURCES = ("tree_attn_mfma.h", "tree_attn_smallm.h", "attn_parts.h", "attn_meet.h", "attn_step.h", "told.h", "attn_merge.hip", "attn_merge.h", "attn_work.h", "attn_division.h",
                 "mfma_common.h")
 
 

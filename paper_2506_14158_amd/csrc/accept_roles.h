@@ -4,8 +4,8 @@
 // Scan (the HBM-bound part).  The rows to scan of a sequence -- every row in greedy mode (the bonus token may come from
 // any), the rows of nodes that have children in stochastic mode -- are laid end to end and cut into equal runs of
 // 8192-logit chunks, one for each of the sequence's scanning workgroups.  For batches of no more sequences than the chip
-// holds workgroups (scan_plan) the scanning workgroups are resident at once, so none of them waits for a second turn; what
-// else the launch holds comes behind them in grid order.  (Fixed segments of up to 8 chunks made config 5 2612 workgroups on
+// holds workgroups (scan_plan) the scanning workgroups are resident at once on a free chip, so none of them waits for a second turn; what
+// else the launch holds comes behind them in the grid.  (Fixed segments of up to 8 chunks made config 5 2612 workgroups on
 // 1280 places, the third turn almost empty.)  Measured, whole calls back to back on one input, against fixed segments: 345 MB of bf16
 // logits 72.3 -> 70.5 us, 131 MB 29.0 -> 28.0, 9 MB 11.9 -> 9.1, 4 MB 10.8 -> 6.7; 51 MB in rows of odd length 71.7 -> 18.7.
 // About 6 us of that are the launch, the first loads and the collector's look.  With inputs that the last-level cache does not
@@ -19,8 +19,8 @@
 //   2^kLazyLog2 (any reference serves, as long as reference and sum go together).
 //
 // Path step.  A run publishes its statistics of each row it touches as two 8-byte records (call nonce in the upper
-// half) with device-coherent stores.  The sequence's collector, a workgroup of its own behind the scanning ones in grid
-// order, loads everything else the path step needs and then polls the records of the sequence until every one
+// half) with device-coherent stores.  The sequence's collector, a workgroup of its own behind the scanning ones in the
+// grid, loads everything else the path step needs and then polls the records of the sequence until every one
 // carries this call's nonce, combines them per row, applies the per-node test against the parent's row, ANDs along each
 // node's ancestor chain and writes the deepest accepted node's path (lowest index among equals).  No second launch,
 // no read-modify-write atomics (they serialise per address and take microseconds across the chip's separate L2s), no

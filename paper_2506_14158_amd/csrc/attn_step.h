@@ -4,8 +4,8 @@
 // the attention's where those leave places on the chip free, instead of behind them: attention, scan, collectors, copiers,
 // in this order.  The appended rows lie behind every key that the attention
 // reads; the lengths, which all its workgroups read, are advanced when all of them have said that they have.
-// Two launches and one, a whole step, us: fp32, 4 heads, 128 keys + 15 nodes 20.9 and 13.0; 32 heads, 1024 keys + 60 nodes, V 32000
-// 22.3 and 15.3; 3 x 8 heads of size 64, 2049 keys 28.1 and 21.2; 4 x 40 heads, 4096 keys 84.3 and 75.3.
+// Two launches and one, a whole step, us: fp32, 4 heads, 128 keys + 15 nodes 19.6 and 12.4; 32 heads, 1024 keys + 60 nodes, V 32000
+// 19.7 and 15.6; 3 x 8 heads of size 64, 2049 keys 25.7 and 21.3; 4 x 40 heads, 4096 keys 81.1 and 73.9.  (Which of the two a step takes: step_plan.h.)
 #pragma once
 #include "accept_roles.h"
 #include "attn_parts.h"
