@@ -11,7 +11,7 @@
 //   a key tile takes 0.5 to 0.8 us of the kernel for few rows (1 to 2.3 in fp32) and 1.1 to 2 us of the one for many;
 //   behind the attention a step takes 6 us, and 0.16 us a megabyte of logits that are scanned, longer than the attention alone;
 //     an attention workgroup takes 6 us more than its tiles in the kernel for many rows, 2.5 in fp32.
-// The estimates below lean towards two launches: 1150 of the steps go in one, none slower so, and of the others one was the faster way for 105 by
+// The estimates below lean towards two launches: 1150 of the steps go in one, none slower so, and of the others one was the faster way for 104 by
 // more than 3 %.  One and two launches, us, left to two: 28.4 and 28.1 (9 x 4 x 4 heads of size 64, 92 nodes, 381 keys, V 3661), 26.0 and 24.8 (2 x 8 x 4 heads, 29
 // nodes, 3777 keys, V 32000); sent in one: 85.7 and 88.5 (fp32, 2 x 8 x 8 heads, 19 nodes, 4831 keys, V 32000), 38.0 and 39.0 (fp32, 2 x 8 heads of size 64, 81
 // nodes, 4722 keys).  Far from the line: one 189, two 87 (27 x 16 heads, 55 nodes, 1654
